@@ -94,10 +94,11 @@ typedef struct {
                             * pass from the thresholds found then, a margin lower, instead of
                             * sampling the data first.  Results do not depend on it: a layer
                             * whose data moved past the margin is collected again. */
-    int32_t  dp_groups;    /* solver: 0 = decide per solve from its size; 1 = always one sequential
-                            * sweep; 2, 4, 8 = sweep the layers in that many groups side by side and
-                            * join the groups' tables (results are the same in every case,
-                            * Algorithm 1's tie-breaks included) */
+    int32_t  dp_groups;    /* solver: 0, 1 = one sequential sweep, over the cells and candidates an
+                            * assignment of the smallest size can use; 2, 4, 8 = sweep the whole table
+                            * with the layers in that many groups side by side and join the groups'
+                            * tables (results are the same in every case, Algorithm 1's tie-breaks
+                            * included) */
     int32_t  strict_budget; /* solver: 0 = Algorithm 1's constraint on the discretised errors, sum of
                             * bins <= n_bins, under which the real errors may exceed e_max by up to
                             * L steps (see lgreco_solve); 1 = only assignments whose bins sum to at
@@ -197,11 +198,11 @@ int lgreco_solve_weighted(lgreco_handle_t* h, const double* errors, const int64_
                           int64_t* total_cost, double* total_error, void* stream);
 
 /* lgreco_emax + lgreco_solve for callers that cannot allocate device memory: code under HIP graph
- * capture, tight serving loops, harnesses that forbid hipMalloc.  No handle: every intermediate
- * table (candidate lists, the arg-min table PD) lives in one array in the library's device image,
- * LGRECO_STATIC_MAX_PD_BYTES + 82432 bytes (4.08 MiB) per GPU the library runs on, held until the
+ * capture, tight serving loops, harnesses that forbid hipMalloc.  No handle: what does not stay
+ * in the kernel (the arg-min table PD where it is too large for that) lives in one array in the library's device
+ * image, LGRECO_STATIC_MAX_PD_BYTES + 256 bytes per GPU the library runs on, held until the
  * process ends.  The call allocates nothing, copies nothing to or from the host and does not wait:
- * its three kernels are queued on `stream` and the outputs are complete in stream order.
+ * its two kernels are queued on `stream` and the outputs are complete in stream order.
  *   d_errors      device [L x P] fp64, row-major, 16-byte aligned (e.g. the table a profile left)
  *   d_sizes       device [L x P] int64 bytes, 16-byte aligned; every size in [0, 2^30) and the sum
  *                 over layers of each layer's largest size below 2^30 (else d_result[0] = 3)
@@ -233,8 +234,9 @@ int lgreco_solve_static(const double* d_errors, const int64_t* d_sizes, int32_t 
  *   e_max         host out (required)
  *   choice        host out [L]
  * Returns LGRECO_EINFEASIBLE with the minimum-error choice as lgreco_solve does.  Problems the
- * device-side step does not take (more than 1024 layers, more than 16 candidates, more than 4096
- * table entries, total size of 2^30 bytes or more) go through the three calls internally. */
+ * device-side step does not take (more than 1024 layers, more than 16384 table entries, more than
+ * 4096 candidates left when those that cannot be used are dropped, total size of 2^30 bytes or
+ * more, layer groups asked for) go through the three calls internally. */
 int lgreco_profile_solve(lgreco_handle_t* h, const float* d_grads, const float* d_ef,
                          const lgreco_layer_t* layers, int32_t L, const lgreco_cand_t* cands,
                          int32_t P, const float* d_q0, int32_t default_cand, int32_t n_bins,
@@ -370,7 +372,7 @@ int lgreco_set_ef_zero_on_entry(lgreco_handle_t* h, int32_t on);
  * on waiting until the block was whole).  Diagnostics only. */
 int64_t lgreco_late_handovers(const lgreco_handle_t* h);
 
-/* How the last successful solve on this handle swept its table: 0 sequentially, G > 0 in G layer
+/* How the last successful solve on this handle swept its table: 0 in one piece, G > 0 in G layer
  * groups, 1000 + G in G groups where ties between ways of sharing the error bins among the groups
  * had to be resolved by Algorithm 1's tie-breaks, -G sequentially after that resolution gave up.
  * Diagnostics only. */

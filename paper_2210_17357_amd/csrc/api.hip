@@ -62,16 +62,19 @@ struct lgreco_handle {
     int32_t* h_count = nullptr;
     int32_t* h_choice = nullptr;
     int64_t* h_result = nullptr;
-    // lgreco_profile_solve: error and size tables in device memory for the device-side entry build
-    // (the sizes with a pinned staging copy, uploaded when they change), what the build reports back
-    // (pinned: sweep_layer | fixed_choice) and the swept-layer count / status it hands the sweep
+    // error and size tables in device memory for the one-kernel solve behind a profile (the sizes with a
+    // pinned staging copy, uploaded when they change; the kernel forwards the errors to h_errors), and
+    // the sizes of a table the caller holds, pinned, as the kernel reads them
     int64_t* h_sizes = nullptr;
     int64_t* d_sizes = nullptr;
     size_t sizes_count = 0;            // entries of h_sizes / d_sizes in use
-    double* d_errors_dev = nullptr;    // error table in device memory (the build forwards it to h_errors)
-    int32_t* h_build = nullptr;
-    int32_t* d_build_host = nullptr;
-    int32_t* d_nsweep = nullptr;
+    double* d_errors_dev = nullptr;
+    int64_t* h_table_sizes = nullptr;
+    int64_t* d_table_sizes = nullptr;
+    // candidates of every layer in order of size, lowest index first among equals, for either table
+    uint8_t* h_order = nullptr;        // pinned, read by the kernel
+    uint8_t* d_order_host = nullptr;   // the same as the kernel addresses it
+    uint8_t* d_order = nullptr;        // uploaded with d_sizes
     int64_t dp_seq = 0;                  // sequence number of the last solver launch
     int64_t last_solve_groups = 0;       // how the last solve swept its table (the kernel's report)
     // layer groups of the solver (see DpGroups): tree nodes, group ranges
@@ -80,10 +83,8 @@ struct lgreco_handle {
     uint32_t* d_dp_nodes = nullptr;
     int32_t* d_dp_range = nullptr;
     // lgreco_profile_solve_compress: what the solver kernel needs to write the compression's layer
-    // records itself - device copies of the build's report and, per (layer, candidate), the integer
-    // parameter a choice stands for plus the family per candidate (pinned staging copy, uploaded
-    // when it changes)
-    int32_t* d_build_dev = nullptr;      // [2 x max_layers] sweep_layer | fixed_choice
+    // records itself - per (layer, candidate) the integer parameter a choice stands for plus the family
+    // per candidate (pinned staging copy, uploaded when it changes)
     int32_t* h_apply = nullptr;          // pinned [max_layers x max_cands | max_cands | max_cands] iparam | family | Top-K slot
     int32_t* d_apply = nullptr;
     size_t apply_count = 0;              // int32 entries of h_apply / d_apply in use
@@ -118,6 +119,39 @@ DpGroups dp_groups(const lgreco_handle* h) {
     g.range = h->d_dp_range;
     g.flag = h->d_dp_range + 2 * kMaxDpGroups;
     return g;
+}
+
+// Whether a table of this shape goes to the one-kernel solve (solve.hip): layer groups asked for by the
+// configuration take the grouped kernels instead.
+bool one_kernel_solve(const lgreco_handle* h, int L, int P) {
+    return h->cfg.dp_groups <= 1 && L <= kSolveMaxLayers && (int64_t)L * P <= kSolveMaxLP;
+}
+
+// Candidates of every layer in order of size, the lowest index first among equals (insertion: the lists
+// are runs in order, one per family).
+void size_order(const int64_t* sizes, int L, int P, uint8_t* order) {
+    for (int l = 0; l < L; ++l) {
+        const int64_t* const z = sizes + (size_t)l * P;
+        uint8_t* const o = order + (size_t)l * P;
+        for (int c = 0; c < P; ++c) {
+            int k = c;
+            for (; k > 0 && z[o[k - 1]] > z[c]; --k) o[k] = o[k - 1];
+            o[k] = (uint8_t)c;
+        }
+    }
+}
+
+SolveParams solve_params(lgreco_handle* h, int L, int P, int n_bins) {
+    SolveParams p{};
+    p.L = L;
+    p.P = P;
+    p.D = n_bins;
+    p.e_limit = h->cfg.strict_budget ? n_bins - L : n_bins;      // all L layers round down
+    p.choice = h->d_choice;
+    p.result = h->d_result;
+    p.seq = ++h->dp_seq;
+    p.pd = h->d_pd;
+    return p;
 }
 
 // lgreco_profile_solve_compress: the compression's first kernel queued behind the solver.
@@ -328,35 +362,23 @@ void begin_call(lgreco_handle* h, hipStream_t s, int kind) {
 // word; until then the host keeps polling.  Whatever does not arrive within the limit (a solve
 // that long, a launch that failed) ends in an ordinary stream synchronisation, which also brings
 // up any error, and a block that still does not add up then is reported, never used.
-// What the list-building kernel (an earlier launch of the same call) left in host memory - the
-// error table and its report of fixed and swept layers - has check words of its own (slots 11,
-// 12) and is held against them in the same way.
-//   n_choice: swept layers whose assignment follows the block; < 0: lists built on the device,
-//   the count is in slot 5 and the error table (L x P) and the report are checked as well
-int wait_for_solver(lgreco_handle* h, int64_t seq, hipStream_t s, int n_choice, int L = 0, int P = 0) {
+//   n_choice: entries of the assignment behind the block
+//   LP: entries of the error table the kernel forwarded to h_errors (0: none), which has a check word
+//   of its own (slot 11)
+int wait_for_solver(lgreco_handle* h, int64_t seq, hipStream_t s, int n_choice, int LP = 0) {
     volatile const int64_t* const r = h->h_result;
     volatile const int32_t* const ch = h->h_choice;
     auto complete = [&]() -> bool {
         if (r[7] != seq || r[4] != seq || r[15] != seq) return false;
-        const int n = n_choice >= 0 ? n_choice : (int)r[5];
-        if (n < 0 || n > h->max_layers) return false;
-        if (n_choice < 0) {
+        if (LP > 0) {
             volatile const uint64_t* const eb = reinterpret_cast<volatile const uint64_t*>(h->h_errors);
             uint64_t ce = 0;
-            for (int i = 0; i < L * P; ++i) ce += eb[i] * (uint64_t)(i + 1);
+            for (int i = 0; i < LP; ++i) ce += eb[i] * (uint64_t)(i + 1);
             if (ce != (uint64_t)r[11]) return false;
-            if (r[0] == 0) {                     // the report is read for a solved table only
-                volatile const int32_t* const sweep_layer = h->h_build;
-                volatile const int32_t* const fixed_choice = h->h_build + L;
-                uint64_t cb = 0;
-                for (int l = 0; l < L; ++l) cb += (uint64_t)(uint32_t)(fixed_choice[l] + 2) * (uint64_t)(l + 1);
-                for (int i = 0; i < n; ++i) cb += 65537ull * (uint64_t)(sweep_layer[i] + 1) * (uint64_t)(i + 1);
-                if (cb != (uint64_t)r[12]) return false;
-            }
         }
         if (r[0] != 0) return true;                          // nothing was traced back
         uint64_t sum = 0;
-        for (int i = 0; i < n; ++i) sum += (uint64_t)(uint32_t)(ch[i] + 1) * (uint64_t)(i + 1);
+        for (int i = 0; i < n_choice; ++i) sum += (uint64_t)(uint32_t)(ch[i] + 1) * (uint64_t)(i + 1);
         return sum == (uint64_t)r[10];
     };
     const auto t0 = std::chrono::steady_clock::now();
@@ -496,10 +518,11 @@ int lgreco_create(lgreco_handle_t** out, const lgreco_config_t* cfg, int64_t max
     HIPCHK_C(hipHostMalloc(&h->h_sizes, sizeof(int64_t) * (size_t)max_layers * max_cands + 16, hipHostMallocDefault));
     HIPCHK_C(hipMalloc(&h->d_sizes, sizeof(int64_t) * (size_t)max_layers * max_cands + 16));
     HIPCHK_C(hipMalloc(&h->d_errors_dev, sizeof(double) * (size_t)max_layers * max_cands + 16));
-    HIPCHK_C(hipHostMalloc(&h->h_build, sizeof(int32_t) * 2 * (size_t)max_layers, hipHostMallocCoherent));
-    HIPCHK_C(hipHostGetDevicePointer(reinterpret_cast<void**>(&h->d_build_host), h->h_build, 0));
-    HIPCHK_C(hipMalloc(&h->d_nsweep, sizeof(int32_t) * 2));
-    HIPCHK_C(hipMalloc(&h->d_build_dev, sizeof(int32_t) * 2 * (size_t)max_layers));
+    HIPCHK_C(hipHostMalloc(&h->h_table_sizes, sizeof(int64_t) * (size_t)max_layers * max_cands + 16, hipHostMallocCoherent));
+    HIPCHK_C(hipHostGetDevicePointer(reinterpret_cast<void**>(&h->d_table_sizes), h->h_table_sizes, 0));
+    HIPCHK_C(hipHostMalloc(&h->h_order, (size_t)max_layers * max_cands + 16, hipHostMallocCoherent));
+    HIPCHK_C(hipHostGetDevicePointer(reinterpret_cast<void**>(&h->d_order_host), h->h_order, 0));
+    HIPCHK_C(hipMalloc(&h->d_order, (size_t)max_layers * max_cands + 16));
     HIPCHK_C(hipHostMalloc(&h->h_apply, sizeof(int32_t) * ((size_t)max_layers * max_cands + 2 * max_cands), hipHostMallocDefault));
     HIPCHK_C(hipMalloc(&h->d_apply, sizeof(int32_t) * ((size_t)max_layers * max_cands + 2 * max_cands)));
     HIPCHK_C(hipHostMalloc(&h->h_bins, sizeof(int32_t) * lp, hipHostMallocDefault));
@@ -534,9 +557,9 @@ int lgreco_destroy(lgreco_handle_t* h) {
     (void)hipHostFree(h->h_sizes);
     (void)hipFree(h->d_sizes);
     (void)hipFree(h->d_errors_dev);
-    (void)hipHostFree(h->h_build);
-    (void)hipFree(h->d_nsweep);
-    (void)hipFree(h->d_build_dev);
+    (void)hipHostFree(h->h_table_sizes);
+    (void)hipHostFree(h->h_order);
+    (void)hipFree(h->d_order);
     (void)hipHostFree(h->h_apply);
     (void)hipFree(h->d_apply);
     (void)hipHostFree(h->h_bins);
@@ -837,6 +860,70 @@ int lgreco_solve(lgreco_handle_t* h, const double* errors, const int64_t* sizes,
     if (L > h->max_layers || P > h->max_cands) return LGRECO_ENOSPACE;
     hipStream_t s = (hipStream_t)stream;
     begin_call(h, s, LGRECO_CALL_SOLVE);
+    auto infeasible = [&]() {
+        for (int l = 0; l < L; ++l) {           // report each layer's minimum-error candidate
+            int best = 0;
+            for (int c = 1; c < P; ++c)
+                if (errors[(size_t)l * P + c] < errors[(size_t)l * P + best]) best = c;
+            choice[l] = best;
+        }
+        return LGRECO_EINFEASIBLE;
+    };
+    auto totals = [&]() {
+        double terr = 0.0;
+        int64_t tsize = 0;
+        for (int l = 0; l < L; ++l) {
+            terr += errors[(size_t)l * P + choice[l]];
+            tsize += sizes[(size_t)l * P + choice[l]];
+        }
+        if (total_size) *total_size = tsize;
+        if (total_error) *total_error = terr;
+        return LGRECO_OK;
+    };
+    // One kernel takes the table as it is, read from pinned memory, wherever 32-bit costs hold it and
+    // no layer groups are asked for.
+    if (one_kernel_solve(h, L, P)) {
+        int64_t all = 0;
+        for (int l = 0; l < L; ++l) {
+            int64_t big = 0;
+            for (int c = 0; c < P; ++c) {
+                const size_t i = (size_t)l * P + c;
+                if (sizes[i] < 0 || sizes[i] >= ((int64_t)1 << 45) || !(errors[i] == errors[i])) return LGRECO_EINVAL;
+                big = std::max(big, sizes[i]);
+            }
+            all += big;
+        }
+        if (all < ((int64_t)1 << 30)) {
+            std::memcpy(h->h_errors, errors, sizeof(double) * (size_t)L * P);
+            std::memcpy(h->h_table_sizes, sizes, sizeof(int64_t) * (size_t)L * P);
+            size_order(sizes, L, P, h->h_order);
+            SolveParams sp = solve_params(h, L, P, n_bins);
+            sp.order = h->d_order_host;
+            sp.errors = h->d_errors;
+            sp.sizes = h->d_table_sizes;
+            sp.have_e_max = 1;
+            sp.e_max = e_max;
+            {
+                Section sec(h->tm, "dp_solve", true);
+                HIPCHK(launch_solve(sp, s, &sec));
+            }
+            harvest_others(h);
+            const int wst = wait_for_solver(h, h->dp_seq, s, L);
+            if (wst != LGRECO_OK) return wst;
+            const int64_t status = h->h_result[0];
+            if (status == 1) return infeasible();
+            if (status == 0) {
+                h->last_solve_groups = 0;
+                if (h->tm->active) record_dp_sub(h);
+                std::memcpy(choice, h->h_choice, sizeof(int32_t) * (size_t)L);
+                return totals();
+            }
+            if (status != 4) {
+                h->hip_error = "dp back-trace inconsistent";
+                return LGRECO_EHIP;
+            }
+        }
+    }
     const double D = (double)n_bins;
     int64_t worst = 0;                  // sum over layers of the largest usable size
     int max_bin = 0;
@@ -904,15 +991,6 @@ int lgreco_solve(lgreco_handle_t* h, const double* errors, const int64_t* sizes,
             ++n_sweep;
         }
     }
-    auto infeasible = [&]() {
-        for (int l = 0; l < L; ++l) {           // report each layer's minimum-error candidate
-            int best = 0;
-            for (int c = 1; c < P; ++c)
-                if (errors[(size_t)l * P + c] < errors[(size_t)l * P + best]) best = c;
-            choice[l] = best;
-        }
-        return LGRECO_EINFEASIBLE;
-    };
     if (dead_layer) return infeasible();
     if (h->cfg.strict_budget && n_bins - L < 0) return infeasible();      // more layers than bins: nothing is certain to fit
     if (n_sweep > 0) {
@@ -924,8 +1002,8 @@ int lgreco_solve(lgreco_handle_t* h, const double* errors, const int64_t* sizes,
         // the kernel itself fetches the input block from the pinned staging memory
         const size_t in_bytes = h->dp_entries_off + sizeof(DpEntry) * (size_t)n_sweep * max_count;
         DpParams dp{h->d_entries, h->d_count, h->d_pd, h->d_choice, h->d_result, n_sweep, n_bins, 0, 0, 0, max_count,
-                    h->d_dp_in_host, reinterpret_cast<uint4*>(h->d_dp_in), (int32_t)((in_bytes + 15) / 16), nullptr,
-                    ++h->dp_seq, DpApply{}, dp_groups(h)};
+                    h->d_dp_in_host, reinterpret_cast<uint4*>(h->d_dp_in), (int32_t)((in_bytes + 15) / 16),
+                    ++h->dp_seq, dp_groups(h)};
         if (h->cfg.strict_budget) dp.e_limit = n_bins - L;        // all L layers round down, the fixed ones too
         {
             Section sec(h->tm, "dp_solve", true);
@@ -945,15 +1023,7 @@ int lgreco_solve(lgreco_handle_t* h, const double* errors, const int64_t* sizes,
         }
         for (int i = 0; i < n_sweep; ++i) choice[h->h_bins[i]] = h->h_choice[i];
     }
-    double terr = 0.0;
-    int64_t tsize = 0;
-    for (int l = 0; l < L; ++l) {
-        terr += errors[(size_t)l * P + choice[l]];
-        tsize += sizes[(size_t)l * P + choice[l]];
-    }
-    if (total_size) *total_size = tsize;
-    if (total_error) *total_error = terr;
-    return LGRECO_OK;
+    return totals();
 }
 
 // lgreco_profile_solve; with `ec`, also the compression's first kernel (see EarlyCompress).
@@ -981,12 +1051,12 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
         if (total_error) *total_error = terr;
         return (int)LGRECO_OK;
     };
-    // the device-side build reads the error table from device memory and passes it on to the host
-    const bool on_device = L <= kBuildThreads && P <= kBuildMaxP && L * P <= kBuildMaxLP;
+    // the solver kernel reads the error table from device memory and passes it on to the host
+    const bool on_device = one_kernel_solve(h, L, P);
     int st = profile_enqueue(h, d_grads, d_ef, layers, L, cands, P, d_q0, sizes,
                              on_device ? h->d_errors_dev : h->d_errors, s, (ec && ec->x_in_e) ? ec->d_ef : nullptr);
     if (st != LGRECO_OK) return st;
-    // The device-side build takes 32-bit costs only; anything it does not take goes the three
+    // The one-kernel solve takes 32-bit costs only; anything it does not take goes the three
     // calls' route (same results, one more host round trip).
     int64_t worst = 0;
     for (int l = 0; l < L; ++l) {
@@ -1016,14 +1086,16 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
         std::memcpy(h->h_sizes, sizes, sizeof(int64_t) * (size_t)L * P);
         h->sizes_count = (size_t)L * P;
         HIPCHK(hipMemcpyAsync(h->d_sizes, h->h_sizes, sizeof(int64_t) * (size_t)L * P, hipMemcpyHostToDevice, s));
+        size_order(sizes, L, P, h->h_order);
+        HIPCHK(hipMemcpyAsync(h->d_order, h->h_order, (size_t)L * P, hipMemcpyHostToDevice, s));
         HIPCHK(hipStreamSynchronize(s));      // h_sizes may be rewritten by the next call
     }
-    DpBuildParams bp{h->d_errors_dev, h->d_sizes, h->d_errors, L, P, n_bins, default_cand, P, h->d_entries,
-                     h->d_count, h->d_build_host, h->d_build_host + L, h->d_build_dev, h->d_build_dev + L,
-                     h->d_nsweep, h->d_result};
-    DpParams dp{h->d_entries, h->d_count, h->d_pd, h->d_choice, h->d_result, L, n_bins, 0, 0, 0, P,
-                nullptr, nullptr, 0, h->d_nsweep, ++h->dp_seq, DpApply{}, dp_groups(h)};
-    if (h->cfg.strict_budget) dp.e_limit = n_bins - L;
+    SolveParams sp = solve_params(h, L, P, n_bins);
+    sp.order = h->d_order;
+    sp.errors = h->d_errors_dev;
+    sp.sizes = h->d_sizes;
+    sp.errors_host = h->d_errors;
+    sp.default_cand = default_cand;
     if (ec) {
         // what every (layer, candidate) means to the compression kernels, as lgreco_compress works
         // it out for a choice: the solver kernel picks the chosen column
@@ -1046,13 +1118,12 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
             HIPCHK(hipMemcpyAsync(h->d_apply, h->h_apply, sizeof(int32_t) * n_apply, hipMemcpyHostToDevice, s));
             HIPCHK(hipStreamSynchronize(s));      // h_apply may be rewritten by the next call
         }
-        dp.apply = DpApply{h->d_layers, h->d_build_dev, h->d_build_dev + L, h->d_sizes, h->d_apply,
-                           h->d_apply + (size_t)L * P, h->d_apply + (size_t)L * P + P, L, P, ec->capacity};
+        sp.apply = SolveApply{h->d_layers, h->d_apply, h->d_apply + (size_t)L * P, h->d_apply + (size_t)L * P + P,
+                              ec->capacity};
     }
     {
         Section sec(h->tm, "dp_solve", true);
-        HIPCHK(launch_dp_build(bp, s, &sec));
-        HIPCHK(launch_dp(dp, true, n_bins, s, &sec, false));
+        HIPCHK(launch_solve(sp, s, &sec));
     }
     if (ec) {
         // The quantization kernel of the compression, queued behind the solver: it reads the layer
@@ -1111,13 +1182,13 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
     }
     harvest_others(h);
     {
-        // error table, build report and solver output are in pinned memory
-        const int wst = wait_for_solver(h, h->dp_seq, s, -1, L, P);
+        // error table and solver output are in pinned memory
+        const int wst = wait_for_solver(h, h->dp_seq, s, L, L * P);
         if (wst != LGRECO_OK) return wst;
     }
     std::memcpy(errors, h->h_errors, sizeof(double) * (size_t)L * P);
     const int64_t status = h->h_result[0];
-    h->last_solve_groups = status == 0 ? h->h_result[9] : 0;
+    h->last_solve_groups = 0;
     if (ec) ec->applied = h->h_result[8] == 1;
     {
         const uint64_t bits = (uint64_t)h->h_result[6];
@@ -1135,20 +1206,22 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
         }
         return LGRECO_EINFEASIBLE;
     }
+    if (status == 4) {                                      // more entries than the kernel holds
+        HIPCHK(hipStreamSynchronize(s));
+        st = lgreco_solve(h, errors, sizes, L, P, *e_max, n_bins, choice, total_size, total_error, stream);
+        if (st == LGRECO_EINFEASIBLE && h->cfg.strict_budget) return strict_default(errors, sizes);
+        return st;
+    }
     if (status != 0) {
         h->hip_error = "dp back-trace inconsistent";
         return LGRECO_EHIP;
     }
-    const int n_sweep = (int)h->h_result[5];
-    const int32_t* const sweep_layer = h->h_build;
-    const int32_t* const fixed_choice = h->h_build + L;
-    for (int l = 0; l < L; ++l) choice[l] = fixed_choice[l];
-    for (int i = 0; i < n_sweep; ++i) choice[sweep_layer[i]] = h->h_choice[i];
+    std::memcpy(choice, h->h_choice, sizeof(int32_t) * (size_t)L);
     double terr = 0.0;
     int64_t tsize = 0;
     for (int l = 0; l < L; ++l) {
         if (choice[l] < 0 || choice[l] >= P) {
-            h->hip_error = "device-side entry build left a layer without a choice";
+            h->hip_error = "the solver left a layer without a choice";
             return LGRECO_EHIP;
         }
         terr += errors[(size_t)l * P + choice[l]];

@@ -1,4 +1,6 @@
-// Layer x error-bin dynamic program of Algorithm 1 and its back-trace, one workgroup.
+// Layer x error-bin dynamic program of Algorithm 1 over the whole table, and its back-trace, from entry
+// lists the host built: 64-bit costs, tables with more entries than the one-kernel solve (solve.hip) holds
+// in LDS, and layer groups where the configuration asks for them.
 //
 // DP[l][e] = min over candidates c with bin(l,c) <= e of DP[l-1][e - bin(l,c)] + size(l,c),
 // starting from a virtual row DP[0] = (0, inf, inf, ...).  Layers are sequential; the bins of a
@@ -167,11 +169,7 @@ __global__ __launch_bounds__(kDpThreads) void dp_group_kernel(DpParams p) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int G = p.groups.G, g = blockIdx.x;
     constexpr T kInf = DpInf<T>::v;
-    int L = p.L;
-    if (p.L_dev) {
-        if (p.L_dev[1] != 0) return;                  // nothing to solve: the last kernel reports
-        L = p.L_dev[0];
-    }
+    const int L = p.L;
     // group boundaries from the exclusive prefix of the entry counts (L <= kDpThreads)
     const int c = tid < L ? p.count[tid] : 0;
     int inc = c;
@@ -214,11 +212,9 @@ __global__ __launch_bounds__(kDpThreads) void dp_group_kernel(DpParams p) {
 // children sit in LDS; a wavefront takes whole cells (interleaved over the grid: a cell costs
 // e + 1 terms), its lanes the terms of a cell.
 constexpr int kConvThreads = 1024;
-__global__ __launch_bounds__(kConvThreads) void dp_conv_kernel(DpGroups gr, int first_node, int D,
-                                                                const int32_t* __restrict__ L_dev) {
+__global__ __launch_bounds__(kConvThreads) void dp_conv_kernel(DpGroups gr, int first_node, int D) {
     extern __shared__ uint32_t conv_smem[];
     constexpr uint32_t kInf = DpInf<uint32_t>::v;
-    if (L_dev && L_dev[1] != 0) return;
     const int node = first_node + blockIdx.y;
     const uint32_t* __restrict__ X = gr.nodes + (size_t)(2 * node + 1) * gr.stride;
     const uint32_t* __restrict__ Y = gr.nodes + (size_t)(2 * node + 2) * gr.stride;
@@ -323,81 +319,17 @@ __device__ __forceinline__ int dp_walk(const uint8_t* __restrict__ pd, const int
 
 // What a solve ends with, once s_val[0] / s_idx[0] hold the minimum of the last row and its cell,
 // s_idx[1] the cell the walk ended in and s_pick the picked entry of every swept layer: the
-// compression's layer records (see DpApply), the assignment and the result block.  `staging`:
-// 16 KB of LDS free by now.  Every thread calls; the threads past the first wavefront return
-// before the hand-over.
-template <typename T, int kDpThreads>
+// assignment and the result block.  Every thread calls; the threads past the first wavefront
+// return before the hand-over.
+template <typename T>
 __device__ __forceinline__ void dp_finish(const DpParams& p, const int L, const bool lds_bins, const uint8_t* const s_pick,
-                                          unsigned char* const staging, const int64_t* const s_val,
-                                          const int32_t* const s_idx, const int32_t pre_fixed, const int32_t pre_sweep,
-                                          const uint64_t t_begin, const uint64_t t_sweep, const int64_t how) {
+                                          const int64_t* const s_val, const int32_t* const s_idx, const uint64_t t_begin,
+                                          const uint64_t t_sweep, const int64_t how) {
     constexpr T kInf = DpInf<T>::v;
     const int tid = threadIdx.x, lane = tid & 63;
     const int bstride = p.max_count;
     const bool feasible = s_val[0] < (int64_t)kInf;
     const bool traced = feasible && lds_bins && s_idx[1] == 0;
-    int64_t applied = 0;                 // the layer records were written (workgroup-uniform)
-    if (p.apply.layers) {
-        // The compression's layer records from the assignment, one thread per layer: candidate per
-        // layer first (fixed layers from the build's report, swept ones from the back-trace), then
-        // the payload offsets, a running sum of the chosen sizes rounded up to 16 bytes.
-        const DpApply& A = p.apply;
-        static_assert(kDpThreads >= kBuildThreads, "one thread per layer");
-        uint8_t* const s_chosen = staging;                                                         // [threads]
-        int64_t* const s_wtot = reinterpret_cast<int64_t*>(staging) + kDpThreads / 8;              // [waves]
-        int32_t* const s_bad = reinterpret_cast<int32_t*>(s_wtot + kDpThreads / 64);
-        const int wave = tid >> 6;
-        bool ok = traced && A.L <= kDpThreads;          // workgroup-uniform
-        int c = 0;
-        int32_t fam = 0, ipar = 0, tslot = -1;
-        int64_t off = 0;
-        if (ok) {
-            const int32_t swept_cand = tid < L ? p.entries[(size_t)tid * bstride + s_pick[tid]].cand : 0;
-            s_chosen[tid] = tid < A.L ? (uint8_t)pre_fixed : (uint8_t)0;
-            if (tid == 0) *s_bad = 0;
-            __syncthreads();
-            if (tid < L) s_chosen[pre_sweep] = (uint8_t)swept_cand;
-            __syncthreads();
-            c = s_chosen[tid];
-            const bool mine = tid < A.L;
-            const bool bad = mine && c >= A.P;           // a layer neither fixed nor swept
-            const int cc = bad ? 0 : c;
-            // the three table reads of the chosen column go out together
-            const int64_t raw = mine ? A.sizes[(size_t)tid * A.P + cc] : 0;
-            fam = mine ? A.family[cc] : 0;
-            tslot = mine ? A.topk_slot[cc] : -1;
-            ipar = mine ? A.iparam[(size_t)tid * A.P + cc] : 0;
-            const int64_t sz = (mine && !bad) ? (raw + 15) / 16 * 16 : 0;
-            int64_t inc = sz;
-            for (int o = 1; o < 64; o <<= 1) {
-                const int64_t n = __shfl_up(inc, o, 64);
-                if (lane >= o) inc += n;
-            }
-            if (lane == 63) s_wtot[wave] = inc;
-            if (bad) *s_bad = 1;
-            __syncthreads();
-            int64_t base = 0, total = 0;
-            for (int w = 0; w < kDpThreads / 64; ++w) {
-                if (w < wave) base += s_wtot[w];
-                total += s_wtot[w];
-            }
-            off = base + inc - sz;
-            ok = *s_bad == 0 && total <= A.capacity;
-        }
-        if (tid < A.L) {
-            if (ok) {
-                A.layers[tid].payload = off;
-                A.layers[tid].family = fam;
-                A.layers[tid].iparam = ipar;
-                A.layers[tid].slot = tslot;
-            } else {
-                A.layers[tid].family = -1;
-            }
-        }
-        if (A.L > kDpThreads)
-            for (int l = kDpThreads + tid; l < A.L; l += kDpThreads) A.layers[l].family = -1;
-        applied = ok ? 1 : 0;
-    }
     // The result block lies in the host's pinned memory and the host may be polling it: the first
     // wavefront alone writes it (the other writer of host memory, the back-trace without LDS
     // tables, is its thread 0).  What the host relies on does not depend on the order in which
@@ -442,35 +374,18 @@ __device__ __forceinline__ void dp_finish(const DpParams& p, const int L, const 
         // back-trace (high half)
         case 3: v = (int64_t)((ticks_sweep & 0xFFFFFFFFull) | (ticks_trace << 32)); break;
         case 4: v = p.seq; break;
-        case 8: v = applied; break;
+        case 8: v = 0; break;                     // no layer records
         // how the table was swept: 0 sequentially, G in G groups, 1000 + G in G groups with
         // ambiguous splits resolved by comparing traced sequences, -G sequentially after the
         // grouped route gave up
         case 9: v = how; break;
         case 10: v = (int64_t)check; break;
         case 15: v = p.seq; break;
-        default: mine = false;                    // 5, 6: the list-building kernel's; 7: below
+        default: mine = false;                    // 7: below
     }
     if (mine) p.result[lane] = v;
     __threadfence_system();
     if (tid == 0) p.result[7] = p.seq;
-}
-
-// The build kernel found nothing to solve (a NaN, a layer without usable candidate): only the
-// hand-over is left.  Every thread calls.
-template <int kDpThreads>
-__device__ __forceinline__ void dp_hand_over_unsolved(const DpParams& p) {
-    const int tid = threadIdx.x;
-    if (p.apply.layers)
-        for (int l = tid; l < p.apply.L; l += kDpThreads) p.apply.layers[l].family = -1;
-    if (tid < 64) {
-        // slots as in dp_finish; the status in slot 0 is the list-building kernel's
-        const int lane = tid;
-        if (lane == 4 || lane == 15) p.result[lane] = p.seq;
-        if (lane == 8 || lane == 10) p.result[lane] = 0;
-        __threadfence_system();
-        if (tid == 0) p.result[7] = p.seq;
-    }
 }
 
 // ---- the sequential solve: one workgroup sweeps every layer, traces back and finishes
@@ -497,23 +412,7 @@ __global__ __launch_bounds__(kDpThreads) void dp_kernel(DpParams p) {
     uint16_t* const s_bins = reinterpret_cast<uint16_t*>(row + KMAX * kDpThreads);
     const int bstride = p.max_count;
     uint8_t* const s_pick = reinterpret_cast<uint8_t*>(s_bins + (size_t)p.L * bstride);   // p.L: capacity
-    // Entry lists built on the device (dp_build_kernel): the number of swept layers and the status
-    // it found come from memory; anything but "ok" there ends the solve.
-    int L = p.L;
-    if (p.L_dev) {
-        if (p.L_dev[1] != 0) {
-            dp_hand_over_unsolved<kDpThreads>(p);
-            return;
-        }
-        L = p.L_dev[0];
-    }
-    // for the apply step at the end (see DpApply): the build's report for this thread's layer,
-    // fetched now so that the tail does not wait for it
-    int32_t pre_fixed = 0, pre_sweep = 0;
-    if (p.apply.layers) {
-        if (tid < p.apply.L) pre_fixed = p.apply.fixed_choice[tid];
-        if (tid < L) pre_sweep = p.apply.sweep_layer[tid];
-    }
+    const int L = p.L;
     const uint64_t t_begin = wall_clock64();
     if (p.host_in) {
         // fetch the input block from the host's pinned memory: one 16-byte word per thread and
@@ -553,8 +452,7 @@ __global__ __launch_bounds__(kDpThreads) void dp_kernel(DpParams p) {
         if (tid == 0) s_idx[1] = e;
     }
     __syncthreads();
-    dp_finish<T, kDpThreads>(p, L, lds_bins, s_pick, reinterpret_cast<unsigned char*>(s_entries), s_val, s_idx, pre_fixed,
-                             pre_sweep, t_begin, t_sweep, G > 1 ? -(int64_t)G : 0);
+    dp_finish<T>(p, L, lds_bins, s_pick, s_val, s_idx, t_begin, t_sweep, G > 1 ? -(int64_t)G : 0);
 }
 
 // ---- tracing a grouped solve (see dp_group_kernel / dp_conv_kernel): one workgroup
@@ -590,19 +488,7 @@ __global__ __launch_bounds__(kDpThreads) void dp_trace_kernel(DpParams p) {
     const int G = p.groups.G;
     const DpGroups& gr = p.groups;
     if (tid == 0) gr.flag[0] = 0;
-    int L = p.L;
-    if (p.L_dev) {
-        if (p.L_dev[1] != 0) {
-            dp_hand_over_unsolved<kDpThreads>(p);
-            return;
-        }
-        L = p.L_dev[0];
-    }
-    int32_t pre_fixed = 0, pre_sweep = 0;
-    if (p.apply.layers) {
-        if (tid < p.apply.L) pre_fixed = p.apply.fixed_choice[tid];
-        if (tid < L) pre_sweep = p.apply.sweep_layer[tid];
-    }
+    const int L = p.L;
     const uint64_t t_begin = wall_clock64();
     // the bin of every entry, for the walks
     for (int i = tid; i < L * bstride; i += kDpThreads) s_bins[i] = (uint16_t)p.entries[i].bin;
@@ -826,210 +712,7 @@ __global__ __launch_bounds__(kDpThreads) void dp_trace_kernel(DpParams p) {
     uint64_t t_sweep = 0;
     if (tid == 0) t_sweep = wall_clock64();
     __syncthreads();
-    dp_finish<T, kDpThreads>(p, L, true, s_pick, s_stage, s_val, s_idx, pre_fixed, pre_sweep, t_begin, t_sweep,
-                             resolved ? 1000 + G : G);
-}
-
-// ------------------------------------------------------------------ entry lists on the device
-// What lgreco_solve does on the host between the error table and the sweep, for a solve that
-// follows the profile on the same stream without a host round trip: E_max (the default
-// candidate's errors summed in layer order), bins = floor(err * D / E_max) in fp64, equal bins
-// merged (smallest size, lowest index among equals), entries beaten in both bin and size dropped,
-// layers with a single entry of bin 0 fixed, the others compacted into the sweep's tables.  One
-// workgroup.  Binning, then merging and pruning in one pass, run with one thread per (layer,
-// candidate), each comparing itself with the layer's other candidates in LDS; then one thread per layer counts
-// what is left, the swept layers are numbered in layer order and their entries written in
-// candidate order, as on the host.
-__global__ __launch_bounds__(kBuildThreads) void dp_build_kernel(DpBuildParams p) {
-    // tables from device memory into LDS; the error table is passed on to the host's pinned copy
-    // on the way (posted writes; reading the tables from there instead took 30 us)
-    __shared__ __align__(16) double s_err[kBuildMaxLP];
-    __shared__ __align__(16) int64_t s_size[kBuildMaxLP];
-    __shared__ int32_t s_bin[kBuildMaxLP], s_sz32[kBuildMaxLP];   // sizes below 2^30 on this path
-    __shared__ uint8_t s_kept[kBuildMaxLP];
-    __shared__ double s_emax;
-    __shared__ int32_t s_wave[kBuildThreads / 64];
-    __shared__ int32_t s_flags[2];          // [0] a layer without usable candidate, [1] invalid input
-    // check words over what this kernel writes into the host's memory (the host holds what it reads
-    // there against them): [0] the error table, sum of bit pattern * (index + 1); [1] the report,
-    // sum of (fixed choice + 2) * (layer + 1) plus 65537 * sum of (swept layer + 1) * (slot + 1)
-    __shared__ unsigned long long s_chk[2];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int L = p.L, P = p.P, LP = L * P;
-    const double D = (double)p.D;
-    if (tid < 2) {
-        s_flags[tid] = 0;
-        s_chk[tid] = 0;
-    }
-    {
-        // whole 16-byte words, then the odd last entry on its own: a caller's table ends at LP entries
-        const int n16 = LP / 2;
-        const uint4* const ge = reinterpret_cast<const uint4*>(p.errors);
-        const uint4* const gs = reinterpret_cast<const uint4*>(p.sizes);
-        uint4* const he = reinterpret_cast<uint4*>(p.errors_host);
-        for (int i = tid; i < n16; i += kBuildThreads) {
-            const uint4 e = ge[i];
-            reinterpret_cast<uint4*>(s_err)[i] = e;
-            if (he) he[i] = e;
-            reinterpret_cast<uint4*>(s_size)[i] = gs[i];
-        }
-        if ((LP & 1) && tid == 0) {
-            const double e = p.errors[LP - 1];
-            s_err[LP - 1] = e;
-            if (p.errors_host) p.errors_host[LP - 1] = e;
-            s_size[LP - 1] = p.sizes[LP - 1];
-        }
-    }
-    __syncthreads();
-    if (p.errors_host) {
-        unsigned long long c = 0;
-        for (int i = tid; i < LP; i += kBuildThreads)
-            c += __builtin_bit_cast(unsigned long long, s_err[i]) * (unsigned long long)(i + 1);
-        for (int o = 1; o < 64; o <<= 1) c += (unsigned long long)__shfl_xor((long long)c, o, 64);
-        if (lane == 0) atomicAdd(&s_chk[0], c);
-    }
-    // This path sweeps with 32-bit costs.  A caller whose size table the host has not seen asks for
-    // the check here: sizes must be non-negative and every layer's largest, summed, below 2^30.
-    if (p.check_sizes) {
-        int64_t lmax = 0;
-        if (tid < L)
-            for (int c = 0; c < P; ++c) {
-                const int64_t sz = s_size[tid * P + c];
-                if (sz < 0 || sz >= ((int64_t)1 << 30)) s_flags[1] = 1;
-                lmax = sz > lmax ? sz : lmax;
-            }
-        for (int o = 1; o < 64; o <<= 1) lmax += __shfl_xor(lmax, o, 64);
-        __shared__ int64_t s_lmax[kBuildThreads / 64];
-        if (lane == 0) s_lmax[wave] = lmax;
-        __syncthreads();
-        if (tid == 0) {
-            int64_t worst = 0;
-            for (int w = 0; w < kBuildThreads / 64; ++w) worst += s_lmax[w];
-            if (worst >= ((int64_t)1 << 30)) s_flags[1] = 1;
-        }
-    }
-    // E_max: errors[l][default] summed for l = 0 .. L-1 in that order (bit-identical to the host
-    // loop): one thread, the LDS reads issued in batches ahead of the dependent adds
-    if (tid == 0) {
-        double sum = 0.0;
-        int l = 0;
-        for (; l + 32 <= L; l += 32) {
-            double v[32];
-#pragma unroll
-            for (int u = 0; u < 32; ++u) v[u] = s_err[(l + u) * P + p.default_cand];
-#pragma unroll
-            for (int u = 0; u < 32; ++u) sum += v[u];
-        }
-        for (; l < L; ++l) sum += s_err[l * P + p.default_cand];
-        s_emax = sum;
-    }
-    __syncthreads();
-    const double e_max = s_emax;
-    if (!(e_max == e_max) && tid == 0) s_flags[1] = 1;
-    // bins, one (layer, candidate) per thread and pass
-    for (int i = tid; i < LP; i += kBuildThreads) {
-        double e = s_err[i];
-        if (!(e == e)) s_flags[1] = 1;
-        if (e < 0.0) e = 0.0;
-        int32_t b;
-        if (e_max > 0.0) {
-            const double q = floor((e * D) / e_max);
-            b = (q <= D) ? (int32_t)q : -1;
-        } else {
-            b = (e <= 0.0) ? 0 : -1;
-        }
-        s_bin[i] = (e == e) ? b : -1;
-        s_sz32[i] = (int32_t)s_size[i];
-    }
-    __syncthreads();
-    // What stays of a layer's list: a candidate goes when another usable one has the same bin and
-    // a smaller size (or the same size and a lower index: one representative per bin), or a smaller
-    // bin and a size that is not larger.  (The host states the second rule for representatives
-    // only; a usable candidate that beats this one has a representative that does, too.)
-    for (int i = tid; i < LP; i += kBuildThreads) {
-        const int l = i / P, c = i - l * P;
-        const int32_t b = s_bin[i];
-        const int32_t sz = s_sz32[i];
-        bool k = b >= 0;
-        // all of the layer's candidates are read before the first comparison (fixed trip count;
-        // reads past the layer's last candidate are clamped and not used)
-        int32_t bo[kBuildMaxP], so[kBuildMaxP];
-#pragma unroll
-        for (int o = 0; o < kBuildMaxP; ++o) {
-            const int j = min(l * P + o, LP - 1);
-            bo[o] = s_bin[j];
-            so[o] = s_sz32[j];
-        }
-#pragma unroll
-        for (int o = 0; o < kBuildMaxP; ++o) {
-            const bool same = bo[o] == b && (so[o] < sz || (so[o] == sz && o < c));
-            const bool lower = bo[o] >= 0 && bo[o] < b && so[o] <= sz;
-            if (o < P && o != c && (same || lower)) k = false;
-        }
-        s_kept[i] = k ? 1 : 0;
-    }
-    __syncthreads();
-    // one thread per layer: what is left of its list
-    const bool active = tid < L;
-    int cnt = 0, first_bin = -1, first_cand = -1;
-    if (active) {
-        for (int c = P - 1; c >= 0; --c)
-            if (s_kept[tid * P + c]) { ++cnt; first_bin = s_bin[tid * P + c]; first_cand = c; }
-    }
-    const bool dead = active && cnt == 0;
-    const bool fixed = active && cnt == 1 && first_bin == 0;
-    const bool swept = active && !dead && !fixed;
-    if (dead) s_flags[0] = 1;
-    // position among the swept layers, in layer order
-    const unsigned long long m = __ballot(swept);
-    const int before = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-    if (lane == 0) s_wave[wave] = (int)__popcll(m);
-    __syncthreads();
-    int base = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < kBuildThreads / 64; ++w) {
-        if (w < wave) base += s_wave[w];
-        total += s_wave[w];
-    }
-    const int slot = base + before;
-    {
-        unsigned long long c = 0;
-        if (active) c = (unsigned long long)(uint32_t)((fixed ? first_cand : -1) + 2) * (unsigned long long)(tid + 1);
-        if (swept) c += 65537ull * (unsigned long long)(tid + 1) * (unsigned long long)(slot + 1);
-        for (int o = 1; o < 64; o <<= 1) c += (unsigned long long)__shfl_xor((long long)c, o, 64);
-        if (lane == 0) atomicAdd(&s_chk[1], c);
-    }
-    if (active) {
-        p.fixed_choice[tid] = fixed ? first_cand : -1;
-        p.fixed_choice_dev[tid] = fixed ? first_cand : -1;
-    }
-    if (swept) {
-        p.count[slot] = cnt;
-        p.sweep_layer[slot] = tid;
-        p.sweep_layer_dev[slot] = tid;
-        DpEntry* const en = p.entries + (size_t)slot * p.stride;
-        int r = 0;
-        for (int c = 0; c < P; ++c)
-            if (s_kept[tid * P + c]) en[r++] = DpEntry{s_bin[tid * P + c], c, s_size[tid * P + c]};
-    }
-    __syncthreads();                           // the check words are complete
-    if (tid == 0) {
-        const int status = s_flags[1] ? 3 : (s_flags[0] ? 1 : 0);  // 3: invalid input, 1: infeasible
-        p.n_sweep[0] = total;
-        p.n_sweep[1] = status;
-        p.result[0] = status;
-        p.result[5] = total;
-        p.result[6] = (int64_t)__builtin_bit_cast(uint64_t, e_max);
-        p.result[11] = (int64_t)s_chk[0];
-        p.result[12] = (int64_t)s_chk[1];
-    }
-}
-
-hipError_t launch_dp_build(const DpBuildParams& p, hipStream_t s, Section* sec) {
-    if (p.L < 1 || p.L > kBuildThreads || p.P < 1 || p.P > kBuildMaxP || p.L * p.P > kBuildMaxLP)
-        return hipErrorInvalidValue;
-    launch_timed(sec, true, false, dp_build_kernel, dim3(1), dim3(kBuildThreads), 0, s, p);
-    return hipGetLastError();
+    dp_finish<T>(p, L, true, s_pick, s_val, s_idx, t_begin, t_sweep, resolved ? 1000 + G : G);
 }
 
 constexpr size_t kDpLdsBudget = 140 * 1024;     // dynamic LDS; ~17 KB more is static (160 KB per CU)
@@ -1112,7 +795,7 @@ static hipError_t launch_dp_t(DpParams p, int max_bin, hipStream_t s, Section* s
             // two cells per wavefront or more, and no more workgroups than fit the chip at once
             const int per_node = std::max(1, std::min(256 / nodes, (p.D + 1 + 31) / 32));
             hipLaunchKernelGGL(dp_conv_kernel, dim3(per_node, nodes), dim3(kConvThreads), conv_lds, s, p.groups,
-                               nodes - 1, (int)p.D, p.L_dev);
+                               nodes - 1, (int)p.D);
         }
         {
             static bool configured = false;

@@ -133,23 +133,6 @@ struct DpEntry {            // one usable candidate of a layer (equal bins merge
     int32_t cand;
     int64_t size;
 };
-// Optional last step of the solver kernel: turn the assignment into the per-layer records the
-// compression kernels read (family, parameter, payload offset), so that a compression kernel
-// queued right behind the solver needs nothing from the host.  The tables hold, per (layer,
-// candidate), what the host would compute for that choice.  If the solve fails, the layout does
-// not fit `capacity`, or the back-trace ran without its LDS tables, every record gets family -1
-// (no compression kernel touches such a layer) and result[8] stays 0; otherwise result[8] = 1.
-struct DpApply {
-    DevLayer* layers;             // null: off
-    const int32_t* sweep_layer;   // [swept] device copy of the build's report
-    const int32_t* fixed_choice;  // [L]
-    const int64_t* sizes;         // [L x P] bytes
-    const int32_t* iparam;        // [L x P] bits / k / rank
-    const int32_t* family;        // [P]
-    const int32_t* topk_slot;     // [P] position of a Top-K candidate in the profile's selection records, else -1
-    int32_t L, P;
-    int64_t capacity;             // bytes the payload buffer holds
-};
 // Layer groups swept side by side (dp_group_kernel) and joined pairwise (dp_conv_kernel): a
 // complete binary tree in heap order, node 0 the whole table, leaves G-1 .. 2G-2 the groups in
 // layer order, the left child of a node holding the lower layers.
@@ -177,47 +160,59 @@ struct DpParams {
     const uint4* host_in;
     uint4* dev_in;
     int32_t in_vec;
-    // Not null: the entry lists were built on the device; [0] is the number of swept layers (L above
-    // is then only the capacity the LDS tables are sized for), [1] the status the build found
-    // (not 0: nothing to solve).
-    const int32_t* L_dev;
     // Written to result[7] as the kernel's last store (after a system-scope fence): the host
     // may poll the pinned result block for it instead of waiting for the stream.
     int64_t seq;
-    DpApply apply;
     DpGroups groups;
     // The traced-back assignment starts from the best cell among 0 .. min(D, e_limit) of the last
     // row (the strict budget looks at fewer cells than the table has; negative: none, no
     // assignment fits).
     int32_t e_limit = 0x7FFFFFFF;
 };
-// Entry lists built on the device from the error table (see dp_build_kernel).
-constexpr int kBuildThreads = 1024;   // layers per solve on this path
-constexpr int kBuildMaxP = 16;        // candidates per layer on this path
-constexpr int kBuildMaxLP = 4096;     // table entries (layers x candidates) on this path: 64 KB of LDS
-struct DpBuildParams {
-    const double* errors;     // [L x P] device memory
-    const int64_t* sizes;     // [L x P] device memory
-    double* errors_host;      // [L x P] the host's pinned copy of the error table, written here (may be null)
-    int32_t L, P, D, default_cand;
-    int32_t stride;           // row stride of `entries` (>= P)
-    DpEntry* entries;         // out: swept layers, compacted
-    int32_t* count;           // out [swept]
-    int32_t* sweep_layer;     // out [swept] original index of every swept layer
-    int32_t* fixed_choice;    // out [L] candidate of a layer fixed here, -1 otherwise
-    int32_t* sweep_layer_dev; // the same two in device memory, for the solver's apply step
-    int32_t* fixed_choice_dev;
-    int32_t* n_sweep;         // out, device memory, read by the sweep: [0] swept layers, [1] status
-    int64_t* result;          // out: [0] status (0 ok, 1 infeasible, 3 invalid input), [5] swept layers,
-                              //      [6] bit pattern of E_max
-    int32_t check_sizes;      // 1: also reject (status 3) sizes this path's 32-bit costs cannot hold
-};
-hipError_t launch_dp_build(const DpBuildParams& p, hipStream_t s, Section* sec);
 // narrow: 32-bit costs (sum of the layers' largest sizes < 2^30)
 // max_bin: largest bin in entries
 // sec (may be null): the section's last kernel, and its first one too when `first_in_section`
 hipError_t launch_dp(const DpParams& p, bool narrow, int max_bin, hipStream_t s, Section* sec,
                      bool first_in_section);
+
+// ---- solve.hip: the whole solve from the error table as one kernel
+constexpr int kSolveMaxLayers = 1024;
+constexpr int kSolveMaxLP = 16384;      // table entries (layers x candidates)
+constexpr int kSolveMaxEntries = 4096;  // entries left after dropping unusable and beaten candidates (more: status 4)
+// Optional last step: the per-layer records the compression kernels read (family, parameter, payload
+// offset), so that a compression queued right behind the solver needs nothing from the host.  The
+// tables hold, per (layer, candidate), what the host would compute for that choice.  If the solve
+// fails or the layout does not fit `capacity`, every record gets family -1 (no compression kernel
+// touches such a layer) and result[8] stays 0; otherwise result[8] = 1.
+struct SolveApply {
+    DevLayer* layers;             // null: off
+    const int32_t* iparam;        // [L x P] bits / k / rank
+    const int32_t* family;        // [P]
+    const int32_t* topk_slot;     // [P] position of a Top-K candidate in the profile's selection records, else -1
+    int64_t capacity;             // bytes the payload buffer holds
+};
+struct SolveParams {
+    const double* errors;         // [L x P], device memory or the host's pinned memory as the device addresses it
+    const int64_t* sizes;         // [L x P]; the layers' largest sizes sum to less than 2^30
+    const uint8_t* order;         // [L x P] per layer its candidates in order of size, lowest index first among equals
+                                  // (null: sorted by the kernel, at most 4096 table entries)
+    double* errors_host;          // [L x P] the host's pinned copy of the error table, written here (may be null)
+    int32_t L, P, D;
+    int32_t default_cand;         // E_max = sum of this candidate's errors ...
+    int32_t have_e_max;           // ... unless the caller gives it
+    double e_max;
+    int32_t e_limit;              // the bins of an accepted assignment sum to at most min(D, e_limit)
+    int32_t check_sizes;          // 1: reject (status 3) sizes this path's 32-bit costs cannot hold
+    int32_t* choice;              // out [L] candidate per layer, -1 when not solved
+    int64_t* result;              // out [16]: [0] status (0 ok, 1 infeasible, 2 inconsistent, 3 invalid input, 4 table too
+                                  //      large for this kernel), [1] size and [2] bins of the layers that were not fixed at
+                                  //      bin 0, [3] ticks, [5] L, [6] bit pattern of E_max, [8] records written, [9] 0,
+                                  //      [10] / [11] check words over choice / error table, [4], [15] and, last, [7] seq
+    int64_t seq;
+    uint8_t* pd;                  // device memory, L x (D + 1) bytes: arg-min table where LDS does not hold it
+    SolveApply apply;
+};
+hipError_t launch_solve(const SolveParams& p, hipStream_t s, Section* sec);
 
 // ---- topk.hip
 struct TopkScratch {

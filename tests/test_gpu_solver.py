@@ -216,3 +216,36 @@ def test_strict_budget_keeps_the_real_errors_within_e_max(groups):
     assert over > 10 and infeasible > 0, (over, infeasible)
     plain.close()
     strict.close()
+
+
+@pytest.mark.parametrize("L,P,D,kind", [
+    (40, 6, 250, "fall"), (40, 6, 900, "fall"), (60, 6, 4090, "fall"), (60, 6, 4100, "fall"),       # row widths: 256, 512, 1024, 4096
+    (5, 4, 16384, "free"), (3, 2, 16384, "fall"), (70, 16, 2000, "free"), (70, 17, 2000, "free"),    # whole rows; 16 / 64 candidates
+    (20, 64, 3000, "fall"), (20, 65, 3000, "free"), (24, 128, 9000, "fall"),                        # a wavefront per list, two lists' halves
+    (1024, 8, 3000, "free"), (1000, 16, 9000, "fall"),                                              # most layers; more entries than LDS takes
+    (300, 7, 2000, "same"), (64, 13, 1000, "ties"), (200, 5, 4000, "one")])
+def test_reduced_sweep_on_its_edges(L, P, D, kind):
+    """The one-kernel solve sweeps only cells and candidates an optimal assignment can use; widths,
+    list lengths and table sizes at which its steps change, with and without structure and ties."""
+    rng = np.random.default_rng(7 * L + P + D)
+    h = _handle(L, P)
+    for trial in range(3):
+        base = 10.0 ** rng.uniform(-5, -1, (L, 1))
+        if kind == "same":                               # identical layers: any two may swap
+            errors = np.tile(np.sort(rng.random((1, P)), axis=1)[:, ::-1], (L, 1))
+            sizes = np.tile(np.sort(rng.integers(1, 1000, (1, P)), axis=1), (L, 1)).astype(np.int64)
+        elif kind == "ties":
+            errors = rng.integers(0, 12, (L, P)).astype(np.float64) * 0.25
+            sizes = rng.integers(0, 5, (L, P)).astype(np.int64)
+        else:
+            errors = base * (rng.random((L, P)) if kind == "free" else np.sort(rng.random((L, P)), axis=1)[:, ::-1])
+            sizes = rng.integers(1, 1 << 17, (L, P)).astype(np.int64)
+            if kind == "fall":
+                sizes = np.sort(sizes, axis=1)
+            if kind == "one":                            # one layer holds nearly all of the error and the size
+                errors[0] *= 1e4
+                sizes[0] *= 1000
+        e_max = solver.e_max_uniform(errors, P // 2)
+        for share in (1.0, 0.35, 0.02):
+            _compare(h, errors, sizes, e_max * share, D)
+    h.close()
