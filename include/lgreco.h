@@ -89,11 +89,10 @@ typedef struct {
                             * computation", "Power Iteration Steps"): 1..16; every step is P = XQ, Phat = orth(P),
                             * Q = X^T Phat, with Q feeding the next step */
     int32_t  r_max;        /* columns of the warm-start Q per layer; this build: <= 64 */
-    int32_t  reuse_thresholds; /* TOPK: 1 = a call with the same layer table and the same k as the
-                            * previous call of its kind (profile / compress) starts its single
-                            * pass from the thresholds found then, a margin lower, instead of
-                            * sampling the data first.  Results do not depend on it: a layer
-                            * whose data moved past the margin is collected again. */
+    int32_t  reuse_thresholds; /* TOPK: accepted, no effect.  (A call used to start its single pass from
+                            * the previous call's thresholds instead of sampling the data first;
+                            * the sample of every call now costs less than one step whose gradient
+                            * differs from the last one's in size did.) */
     int32_t  dp_groups;    /* solver: 0, 1 = one sequential sweep, over the cells and candidates an
                             * assignment of the smallest size can use; 2, 4, 8 = sweep the whole table
                             * with the layers in that many groups side by side and join the groups'

@@ -535,7 +535,6 @@ int lgreco_create(lgreco_handle_t** out, const lgreco_config_t* cfg, int64_t max
     HIPCHK_C(hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming));
     {
         hipError_t e = topk_scratch_create(&h->topk, max_elems, max_layers, h->max_tiles);
-        h->topk.reuse_thresholds = cfg->reuse_thresholds != 0;
         if (e != hipSuccess) { hip_fail(h, e, "topk_scratch_create"); return fail(LGRECO_EHIP); }
         e = lowrank_scratch_create(&h->lowrank, max_elems, max_layers, cfg->r_max, cfg->power_iters);
         if (e != hipSuccess) { hip_fail(h, e, "lowrank_scratch_create"); return fail(LGRECO_EHIP); }
@@ -795,7 +794,7 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
         qp.seed_hi = (uint32_t)(h->cfg.seed >> 32);
         if (ntk) {
             qp.hist = h->topk.d_hist;
-            qp.lo = h->topk.lo_src;
+            qp.lo = h->topk.d_lo;
             qp.cand = h->topk.d_cand;
             qp.cand_base = h->topk.d_cand_base;
             qp.tinfo = h->topk.d_tinfo;
@@ -818,7 +817,7 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
     if (ntk) {
         // (the per-layer sums of the quantization errors ride on the scan's launch)
         const QuantReduce qr{h->d_partials, d_err, P, qp.col, qp.nq};
-        HIPCHK(topk_select(&h->topk, g_after, e_after, nullptr, h->d_layers, h->d_tiles, L, n_tiles, ntk, true,
+        HIPCHK(topk_select(&h->topk, g_after, e_after, nullptr, h->d_layers, h->d_tiles, L, n_tiles, ntk,
                            ntk_all <= (int)kMaxTopk, h->tm, s, qp.nq ? &qr : nullptr));
     } else if (qp.nq) {
         Section sec(h->tm, "reduce_partials");
@@ -828,7 +827,7 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
     for (int first = kMaxTopk; first < ntk_all; first += kMaxTopk) {
         const int cnt = load_group(first);
         HIPCHK(topk_regroup(&h->topk, L, ks.data(), 0, s));
-        HIPCHK(topk_select(&h->topk, g_after, e_after, nullptr, h->d_layers, h->d_tiles, L, n_tiles, cnt, false,
+        HIPCHK(topk_select(&h->topk, g_after, e_after, nullptr, h->d_layers, h->d_tiles, L, n_tiles, cnt,
                            first + (int)kMaxTopk >= ntk_all, h->tm, s, nullptr));
         HIPCHK(topk_finalize(&h->topk, h->d_layers, h->d_tiles, L, cnt, tk_col, d_err, P, h->tm, s));
     }

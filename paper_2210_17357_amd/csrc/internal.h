@@ -216,7 +216,7 @@ hipError_t launch_solve(const SolveParams& p, hipStream_t s, Section* sec);
 
 // ---- topk.hip
 struct TopkScratch {
-    uint32_t* d_hist = nullptr;       // [2 x max_layers x kHistBins] exact coarse histogram, then the sample's
+    uint32_t* d_hist = nullptr;       // [max_layers x kHistBins] exact coarse histogram
     void* d_tl = nullptr;             // per-layer selection records
     uint32_t* d_cnt_known = nullptr;  // [max_layers x 512] sub-bin counts of topk_compress_known
     uint32_t* d_cand = nullptr;       // bit patterns of the candidates, tile i at its own first element
@@ -233,12 +233,7 @@ struct TopkScratch {
     const float* rc_g = nullptr;
     const float* rc_e = nullptr;
     float* rc_ef_out = nullptr;
-    uint32_t* d_hint[2] = {nullptr, nullptr};   // per kind of call: bound derived from the last thresholds
-    bool hint_valid[2] = {false, false};
-    bool reuse_thresholds = false;
-    const uint32_t* lo_src = nullptr; // bound the main pass of this call collects with: d_lo or a d_hint
     bool hist_clean = false;          // the exact histogram is all zero (the last scan of a call clears it)
-    int cur_slot = 0;
     int64_t* d_cand_base = nullptr;   // [max_layers] first candidate slot of every layer
     void* d_tilecnt = nullptr;        // per tile (above, equal) counts (compress)
     void* d_tilebase = nullptr;       // per tile exclusive prefix of those counts
@@ -270,8 +265,7 @@ struct TopkScratch {
 };
 hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers, int max_tiles);
 void topk_scratch_destroy(TopkScratch* t);
-// upload k per (layer, candidate), clear the histograms, sample the data and predict every
-// layer's collection bound
+// upload k per (layer, candidate), sample the data and predict every layer's collection bound
 hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevLayer* d_layers,
                       const DevLayer* h_layers, const Tile* d_tiles, int L, int n_tiles, int tile_elems,
                       const uint32_t* ks, int ntk, int slot, Timing* tm, hipStream_t s);
@@ -293,8 +287,8 @@ struct QuantReduce {
     int ncols;
 };
 hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers,
-                       const Tile* d_tiles, int L, int n_tiles, int ntk, bool first_group, bool last_group,
-                       Timing* tm, hipStream_t s, const QuantReduce* quant);
+                       const Tile* d_tiles, int L, int n_tiles, int ntk, bool last_group, Timing* tm, hipStream_t s,
+                       const QuantReduce* quant);
 // refinement on the candidates: exact thresholds; writes the dropped energy to errors (if not null)
 hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d_tiles, int L, int ntk,
                          const int* col, double* d_errors, int stride, Timing* tm, hipStream_t s);

@@ -3,9 +3,9 @@
 //
 // Magnitudes are compared as the fp32 bit pattern with the sign cleared (31 bits); the "coarse
 // key" of an element is the top 12 bits (exponent + 4 mantissa bits).  Per call:
-//   1. sample: coarse histogram of 1/16 of the data (one 512-element chunk out of 16).  From it a
-//      cautious lower bound `lo` of the coarse key of the k-th largest magnitude is predicted for
-//      every layer (the largest k asked for, with a wide margin).
+//   1. sample: coarse histogram of up to 16384 elements of every layer.  From it a cautious lower
+//      bound `lo` of the coarse key of the k-th largest magnitude is predicted for every layer (the
+//      largest k asked for, with a margin).
 //   2. main pass, ONE read of the data (fused into the quantization profile kernel when both
 //      families are profiled): exact coarse histogram of every element (LDS per tile, integer
 //      atomics to global); elements with key >= lo ("candidates", 10-20 % of the data) are
@@ -52,13 +52,13 @@ struct TopkLayer {
     TopkList lists[kMaxTopk];
     TopkSel sel[kMaxTopk];
 };
-constexpr int kRefTiles = 16;       // largest tiles per refinement / sample workgroup (fewer elements never: with
+constexpr int kRefTiles = 16;       // largest tiles per refinement workgroup (fewer elements never: with
                                     // smaller tiles a workgroup takes proportionally more of them)
 constexpr int kRefThreads = 1024;
 constexpr int kRefSlots = 512;      // refinement workgroups the chip runs at a time (256 CUs x 2)
 constexpr int kBinsA = 1024, kBinsB = 512;
-constexpr int kSampleEvery = 16;    // one 512-element chunk out of 16 is sampled
-constexpr uint32_t kHintMargin = 2; // coarse bins (4.4 % in magnitude each) between a remembered threshold and the bound derived from it
+constexpr int kSampleSegs = 512, kSampleSeg = 32;     // sample of a layer: segments, consecutive elements in each
+constexpr int kSampleThreads = 1024;
 
 // ------------------------------------------------------------------------ block helpers
 // Suffix sums of a histogram in LDS over the block's first 256 threads: thread t owns the bins
@@ -161,109 +161,79 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
         p[i] = v;
 }
 
-struct RefWork {                     // one workgroup of the sample / refinement kernels: tiles [t0, t1) of a layer
+struct RefWork {                     // one workgroup of the refinement kernels: tiles [t0, t1) of a layer
     int32_t layer, t0, t1, pad;
 };
 
-// Coarse histogram of a sample: every kSampleEvery-th 512-element chunk of every tile (chunk 0
-// included, so short tiles are sampled whole or by their first chunk).  One workgroup takes a run
-// of tiles of one layer; a wavefront takes whole sampled chunks.
-__global__ __launch_bounds__(kThreads) void topk_sample_kernel(const float* __restrict__ g,
-                                                                const float* __restrict__ e,
-                                                                const DevLayer* __restrict__ layers,
-                                                                const Tile* __restrict__ tiles,
-                                                                const RefWork* __restrict__ work,
-                                                                int per_tile, uint32_t* __restrict__ shist) {
-    __shared__ uint32_t s_hist[kHistBins];
-    const RefWork w = work[blockIdx.x];
-    const DevLayer L = layers[w.layer];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int b = threadIdx.x; b < kHistBins; b += kThreads) s_hist[b] = 0;
-    __syncthreads();
-    const int kPerTile = per_tile;                               // sampled chunks of a full tile
-    constexpr int kWaves = kThreads / 64, kBatch = 4;            // chunks a wavefront has in flight
-    const int npairs = (w.t1 - w.t0) * kPerTile;
-    for (int pr0 = wave * kBatch; pr0 < npairs; pr0 += kWaves * kBatch) {
-        float4 a[kBatch][2];
-        bool vec[kBatch];
-#pragma unroll
-        for (int q = 0; q < kBatch; ++q) {
-            const int pr = pr0 + q;
-            vec[q] = false;
-            if (pr >= npairs) continue;
-            const Tile t = tiles[w.t0 + pr / kPerTile];
-            const int first = (pr % kPerTile) * kSampleEvery * kChunk;
-            if (first >= t.count) continue;
-            const float* gp = g + L.offset + t.pos + first;
-            const float* ep = e ? e + L.offset + t.pos + first : nullptr;
-            if (t.fast) {
-                vec[q] = true;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    a[q][h] = reinterpret_cast<const float4*>(gp)[h * 64 + lane];
-                    if (ep) {
-                        const float4 b = reinterpret_cast<const float4*>(ep)[h * 64 + lane];
-                        a[q][h].x += b.x; a[q][h].y += b.y; a[q][h].z += b.z; a[q][h].w += b.w;
-                    }
-                }
-            } else {
-                const int n = min(kChunk, t.count - first);
-                for (int i = lane; i < n; i += 64) {
-                    const float x = ep ? gp[i] + ep[i] : gp[i];
-                    atomicAdd(&s_hist[mag_bits(x) >> kHistShift], 1u);
-                }
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < kBatch; ++q) {
-            if (!vec[q]) continue;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                atomicAdd(&s_hist[mag_bits(a[q][h].x) >> kHistShift], 1u);
-                atomicAdd(&s_hist[mag_bits(a[q][h].y) >> kHistShift], 1u);
-                atomicAdd(&s_hist[mag_bits(a[q][h].z) >> kHistShift], 1u);
-                atomicAdd(&s_hist[mag_bits(a[q][h].w) >> kHistShift], 1u);
-            }
-        }
-    }
-    __syncthreads();
-    uint32_t* gh = shist + (size_t)w.layer * kHistBins;
-    for (int b = threadIdx.x; b < kHistBins; b += kThreads) {
-        const uint32_t c = s_hist[b];
-        if (c) atomicAdd(&gh[b], c);
-    }
-}
-
-// One workgroup per layer: predicted lower bound of the lowest threshold bin.
-__global__ __launch_bounds__(256) void topk_predict_kernel(const uint32_t* __restrict__ shist,
-                                                           const uint32_t* __restrict__ ks, int ntk,
-                                                           const DevLayer* __restrict__ layers,
-                                                           uint32_t* __restrict__ lo) {
+// Lower bound of every layer's lowest threshold bin, one workgroup per layer: coarse histogram of a
+// sample in LDS, and the bin that holds somewhat more of it than the largest k asks for.  The sample
+// is 512 segments of 32 consecutive elements (one 128-byte line each), spread evenly over the layer with a
+// scrambled offset inside each stride, so that no row length of a matrix lines up with it; a layer
+// of at most 16384 elements is taken whole and its bound is exact.  Every thread issues its 16 loads
+// (32 with error feedback) before it uses the first: the kernel is a memory round trip, 64 KB per
+// layer, and two searches of the histogram.  (A sample of 1/16 of the data in three kernels took 33 us
+// on a 26 M-element model, remembering the last call's thresholds instead nothing, but a step
+// whose gradient is larger or smaller than the one before then collects everything again, or up to
+// half of the elements.)
+__global__ __launch_bounds__(kSampleThreads) void topk_bound_kernel(const float* __restrict__ g,
+                                                                    const float* __restrict__ e,
+                                                                    const uint32_t* __restrict__ ks, int ntk,
+                                                                    const DevLayer* __restrict__ layers,
+                                                                    uint32_t* __restrict__ lo) {
     __shared__ uint32_t s_hist[kHistBins];
     __shared__ uint32_t s_scan[256];
     __shared__ uint32_t s_res[2];
-    const int l = blockIdx.x;
-    if (ks[(size_t)l * kMaxTopk] == 0) {
-        if (threadIdx.x == 0) lo[l] = 0xFFFFFFFFu;
-        return;
-    }
-    for (int b = threadIdx.x; b < kHistBins; b += 256) s_hist[b] = shist[(size_t)l * kHistBins + b];
-    __syncthreads();
+    constexpr int kPer = kSampleSegs * kSampleSeg / kSampleThreads;
+    const int l = blockIdx.x, tid = threadIdx.x;
     uint32_t kmax = 0;
     for (int j = 0; j < ntk; ++j) kmax = max(kmax, ks[(size_t)l * kMaxTopk + j]);
-    // sample size = total of the histogram (left in s_scan[0] by a scan for "everything")
-    block_kth_from_top(s_hist, kHistBins, 0xFFFFFFFFu, s_scan, s_res);
-    const double ns = (double)s_scan[0];
-    __syncthreads();
-    const double n = (double)layers[l].numel;
-    const double t = (double)kmax * ns / n;                 // expected sample entries above the threshold
-    const double want = 1.5 * t + 6.0 * sqrt(t) + 16.0;     // wide margin: the sample only has to be roughly right
-    if (want >= ns) {
-        if (threadIdx.x == 0) lo[l] = 0u;
+    if (kmax == 0) {
+        if (tid == 0) lo[l] = 0xFFFFFFFFu;
         return;
     }
-    block_kth_from_top(s_hist, kHistBins, (uint32_t)want, s_scan, s_res);
-    if (threadIdx.x == 0) lo[l] = s_res[0];
+    const DevLayer L = layers[l];
+    const uint32_t n = (uint32_t)L.numel;
+    const bool whole = n <= (uint32_t)(kSampleSegs * kSampleSeg);
+    const uint32_t stride = n / kSampleSegs;             // at least kSampleSeg unless whole
+    float x[kPer], y[kPer];
+    uint32_t at[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        if (whole) {
+            at[q] = (uint32_t)(q * kSampleThreads + tid);
+        } else {
+            const uint32_t seg = (uint32_t)(q * (kSampleThreads / kSampleSeg) + tid / kSampleSeg);
+            const uint32_t room = stride - kSampleSeg + 1u;
+            at[q] = seg * stride + __umulhi(seg * 2654435761u, room) + (uint32_t)(tid % kSampleSeg);
+        }
+    }
+    const float* const gl = g + L.offset;
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) x[q] = gl[min(at[q], n - 1u)];
+    if (e) {
+        const float* const el = e + L.offset;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) y[q] = el[min(at[q], n - 1u)];
+    }
+    for (int b = tid; b < kHistBins; b += kSampleThreads) s_hist[b] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q)
+        if (at[q] < n) atomicAdd(&s_hist[mag_bits(e ? x[q] + y[q] : x[q]) >> kHistShift], 1u);
+    __syncthreads();
+    uint32_t want = kmax;
+    if (!whole) {
+        const float ns = (float)(kSampleSegs * kSampleSeg);
+        const float t = (float)kmax * (ns / (float)n);   // expected sample entries above the threshold
+        const float w = 1.2f * t + 5.0f * sqrtf(t) + 16.0f;      // a margin: the sample only has to be roughly right
+        if (w >= ns) {
+            if (tid == 0) lo[l] = 0u;
+            return;
+        }
+        want = (uint32_t)w;
+    }
+    block_kth_from_top(s_hist, kHistBins, want, s_scan, s_res);
+    if (tid == 0) lo[l] = s_res[0];
 }
 
 struct CollectParams {
@@ -620,8 +590,7 @@ struct ScanReduce {
 __global__ __launch_bounds__(256) void topk_scan_kernel(uint32_t* __restrict__ hist,
                                                         const uint32_t* __restrict__ ks, int ntk,
                                                         const int64_t* __restrict__ cand_base,
-                                                        const uint32_t* lo_in, uint32_t* lo_out,
-                                                        TopkLayer* __restrict__ tl, uint32_t* hint, int clear,
+                                                        uint32_t* lo, TopkLayer* __restrict__ tl, int clear,
                                                         int n_layers, ScanReduce red) {
     __shared__ __align__(16) unsigned char s_raw[sizeof(uint32_t) * kHistBins];   // 16 KB: the histogram, or the reduction's tree
     static_assert(sizeof(s_raw) >= sizeof(double) * kMaxQuant * 256, "shared by both jobs");
@@ -639,8 +608,6 @@ __global__ __launch_bounds__(256) void topk_scan_kernel(uint32_t* __restrict__ h
         if (threadIdx.x == 0) {
             T.nlists = 0; T.min_tbin = 0; T.recollect = 0;
             for (int j = 0; j < kMaxTopk; ++j) T.sel[j].k = 0;
-            lo_out[l] = lo_in[l];
-            if (hint) hint[l] = 0xFFFFFFFFu;
         }
         if (clear)
             for (int b = threadIdx.x; b < kHistBins; b += 256) hist[(size_t)l * kHistBins + b] = 0u;
@@ -684,14 +651,10 @@ __global__ __launch_bounds__(256) void topk_scan_kernel(uint32_t* __restrict__ h
         sT.min_tbin = mn;
         sT.cand_base = cand_base[l];
         // every element at or above the lowest threshold bin must be among the candidates
-        // (lo_in may be the same array as hint: it is read before hint is written)
-        const uint32_t used = lo_in[l];
+        const uint32_t used = lo[l];
         sT.recollect = used > mn ? 1u : 0u;
         sT.pad = 0;
-        lo_out[l] = sT.recollect ? mn : used;
-        // collection bound for the next call of this kind: kHintMargin coarse bins (4.4 % in magnitude each)
-        // under the lowest threshold found now
-        if (hint) hint[l] = mn > kHintMargin ? mn - kHintMargin : 0u;
+        if (sT.recollect) lo[l] = mn;
     }
     __syncthreads();
     static_assert(sizeof(TopkLayer) % 4 == 0, "copied as 32-bit words");
@@ -1396,10 +1359,10 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
     t->max_elems = max_elems;
     t->max_layers = max_layers;
     t->max_tiles = max_tiles;
-    TK_CHECK(hipMalloc(&t->d_hist, sizeof(uint32_t) * 2 * (size_t)max_layers * kHistBins));   // exact + sample
+    TK_CHECK(hipMalloc(&t->d_hist, sizeof(uint32_t) * (size_t)max_layers * kHistBins));
     // Between calls the exact histogram is all zero: cleared here once, and by the last scan of every
     // call for the layers that call counted.  hist_clean is false only after a call that failed midway.
-    TK_CHECK(hipMemset(t->d_hist, 0, sizeof(uint32_t) * 2 * (size_t)max_layers * kHistBins));
+    TK_CHECK(hipMemset(t->d_hist, 0, sizeof(uint32_t) * (size_t)max_layers * kHistBins));
     t->hist_clean = true;
     TK_CHECK(hipMalloc(&t->d_tl, sizeof(TopkLayer) * (size_t)max_layers));
     // counts of the known-threshold compression: all zero between calls (the pick kernel clears what it reads)
@@ -1411,7 +1374,6 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
     TK_CHECK(hipMalloc(&t->d_kept_idx, sizeof(uint32_t) * (size_t)max_elems));
     TK_CHECK(hipMalloc(&t->d_tinfo_kept, sizeof(TopkTileInfo) * (size_t)max_tiles));
     TK_CHECK(hipMalloc(&t->d_lo, sizeof(uint32_t) * (size_t)max_layers));
-    for (int i = 0; i < 2; ++i) TK_CHECK(hipMalloc(&t->d_hint[i], sizeof(uint32_t) * (size_t)max_layers));
     TK_CHECK(hipMalloc(&t->d_tilecnt, sizeof(uint2) * (size_t)max_tiles * (kThreads / 64)));
     TK_CHECK(hipMalloc(&t->d_tilebase, sizeof(uint2) * (size_t)max_tiles * (kThreads / 64)));
     TK_CHECK(hipMalloc(&t->d_tinfo, sizeof(TopkTileInfo) * (size_t)max_tiles));
@@ -1453,7 +1415,6 @@ void topk_scratch_destroy(TopkScratch* t) {
     (void)hipFree(t->d_kept_idx);
     (void)hipFree(t->d_tinfo_kept);
     (void)hipFree(t->d_lo);
-    for (int i = 0; i < 2; ++i) (void)hipFree(t->d_hint[i]);
     (void)hipFree(t->d_tilecnt);
     (void)hipFree(t->d_tilebase);
     (void)hipFree(t->d_tinfo);
@@ -1481,7 +1442,7 @@ static hipError_t ctl_writable(TopkScratch* t) {
 
 // One upload of the control block up to the last work item, skipped when this slot's device copy
 // already holds the same bytes.
-static hipError_t upload_ctl(TopkScratch* t, int slot, hipStream_t s, bool* changed = nullptr) {
+static hipError_t upload_ctl(TopkScratch* t, int slot, hipStream_t s) {
     uint8_t* const d = t->d_ctl[slot];
     t->d_k = reinterpret_cast<uint32_t*>(d + t->ctl_off[0]);
     t->d_cand_base = reinterpret_cast<int64_t*>(d + t->ctl_off[1]);
@@ -1497,7 +1458,6 @@ static hipError_t upload_ctl(TopkScratch* t, int slot, hipStream_t s, bool* chan
         std::memcpy(t->h_ctl_last[slot], t->h_ctl, used);
         t->ctl_last_bytes[slot] = used;
     }
-    if (changed) *changed = differs;
     return hipSuccess;
 }
 
@@ -1510,13 +1470,14 @@ hipError_t topk_regroup(TopkScratch* t, int L, const uint32_t* ks, int slot, hip
     return upload_ctl(t, slot, s);
 }
 
-// Upload the requested k per (layer, candidate) (0 = layer inactive), clear both histograms, take
-// the sample and predict the collection bound of every layer.
+// Upload the requested k per (layer, candidate) (0 = layer inactive) and predict the collection bound
+// of every layer from a sample.
 hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevLayer* d_layers,
                       const DevLayer* h_layers, const Tile* d_tiles, int L, int n_tiles, int tile_elems,
                       const uint32_t* ks, int ntk, int slot, Timing* tm, hipStream_t s) {
     (void)n_tiles;
-    // Tiles per work item of the sample / refinement kernels: 2^19 elements, fewer when that would
+    (void)d_tiles;
+    // Tiles per work item of the refinement kernels: 2^19 elements, fewer when that would
     // leave part of the chip without a work item (two 1024-thread workgroups per CU, kRefSlots in
     // all): a work item's time is proportional to its candidates, and a small problem's chain is as
     // long as its largest item.
@@ -1555,40 +1516,18 @@ hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevL
     t->n_work = nw;
     t->max_items = max_items;
     t->cand_has_idx = false;
-    bool changed = true;
-    TK_CHECK(upload_ctl(t, slot, s, &changed));
-    t->cur_slot = slot;
+    TK_CHECK(upload_ctl(t, slot, s));
     Section sec(tm, "topk_sample");
-    // the sample's histogram has its own half of the buffer, whatever L is: a call never leaves
-    // counts where a later call with more layers expects a cleared exact histogram
-    uint32_t* const shist = t->d_hist + (size_t)t->max_layers * kHistBins;
-    auto fill = [&](uint32_t* dst, size_t n) {
+    // (the previous call's last scan left the exact histogram cleared)
+    if (!t->hist_clean) {
+        const size_t n = (size_t)t->max_layers * kHistBins;
         hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)std::min<size_t>((n + 255) / 256, 2048)), dim3(256), 0, s,
-                           dst, n, 0u);
-        return hipGetLastError();
-    };
-    if (t->reuse_thresholds && t->hint_valid[slot] && !changed) {
-        // Same layers and the same k as the previous call of this kind: start from the thresholds
-        // it found, a margin lower, instead of sampling.  The scan still checks the bound against
-        // the exact histogram and collects a layer again if the data moved past the margin.  The
-        // previous call's last scan left the histogram cleared, so no kernel runs before the main pass.
-        t->lo_src = t->d_hint[slot];
-        if (!t->hist_clean) TK_CHECK(fill(t->d_hist, (size_t)t->max_layers * kHistBins));
-        t->hist_clean = false;
-        return hipSuccess;
-    }
-    t->lo_src = t->d_lo;
-    t->hint_valid[slot] = false;
-    if (!t->hist_clean) TK_CHECK(fill(t->d_hist, (size_t)t->max_layers * kHistBins));
-    t->hist_clean = false;
-    TK_CHECK(fill(shist, (size_t)L * kHistBins));
-    if (nw > 0) {
-        hipLaunchKernelGGL(topk_sample_kernel, dim3(nw), dim3(kThreads), 0, s, g, e, d_layers, d_tiles,
-                           (const RefWork*)t->d_work, std::max(1, tile_elems / kChunk / kSampleEvery), shist);
+                           t->d_hist, n, 0u);
         TK_CHECK(hipGetLastError());
     }
-    hipLaunchKernelGGL(topk_predict_kernel, dim3(L), dim3(256), 0, s, (const uint32_t*)shist,
-                       (const uint32_t*)t->d_k, ntk, d_layers, t->d_lo);
+    t->hist_clean = false;
+    hipLaunchKernelGGL(topk_bound_kernel, dim3(L), dim3(kSampleThreads), 0, s, g, e, (const uint32_t*)t->d_k, ntk, d_layers,
+                       t->d_lo);
     return hipGetLastError();
 }
 
@@ -1601,7 +1540,7 @@ static CollectParams collect_params(TopkScratch* t, const float* g, const float*
     p.tiles = d_tiles;
     p.ks = t->d_k;
     p.tl = (const TopkLayer*)t->d_tl;
-    p.lo = t->lo_src;
+    p.lo = t->d_lo;
     p.hist = t->d_hist;
     p.cand = t->d_cand;
     p.cand_idx = t->d_cand_idx;
@@ -1631,12 +1570,10 @@ hipError_t topk_collect(TopkScratch* t, const float* g, const float* e, float* e
 
 // exact threshold bins; layers whose predicted bound was too high are collected again
 hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers,
-                       const Tile* d_tiles, int L, int n_tiles, int ntk, bool first_group, bool last_group,
-                       Timing* tm, hipStream_t s, const QuantReduce* quant) {
+                       const Tile* d_tiles, int L, int n_tiles, int ntk, bool last_group, Timing* tm,
+                       hipStream_t s, const QuantReduce* quant) {
     {
         Section sec(tm, "topk_scan");
-        // the first group of a call holds the lowest thresholds: it leaves the bound for the next call
-        uint32_t* const hint = (first_group && t->reuse_thresholds) ? t->d_hint[t->cur_slot] : nullptr;
         ScanReduce red{};
         if (quant) {
             red.partials = quant->partials;
@@ -1647,13 +1584,10 @@ hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef
             for (int i = 0; i < red.cols.n; ++i) red.cols.col[i] = quant->cols[i];
         }
         hipLaunchKernelGGL(topk_scan_kernel, dim3(quant ? 2 * L : L), dim3(256), 0, s, t->d_hist,
-                           (const uint32_t*)t->d_k, ntk, (const int64_t*)t->d_cand_base,
-                           first_group ? t->lo_src : (const uint32_t*)t->d_lo, t->d_lo, (TopkLayer*)t->d_tl, hint,
+                           (const uint32_t*)t->d_k, ntk, (const int64_t*)t->d_cand_base, t->d_lo, (TopkLayer*)t->d_tl,
                            last_group ? 1 : 0, L, red);
         TK_CHECK(hipGetLastError());
-        if (hint) t->hint_valid[t->cur_slot] = true;
         if (last_group) t->hist_clean = true;
-        t->lo_src = t->d_lo;                     // a second collection uses the bound the scan wrote
     }
     // Layers whose predicted bound was too high (flagged by the scan; none in the usual call) are
     // collected a second time with the exact bound, by the first refinement kernel's workgroups,
@@ -1742,7 +1676,7 @@ hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLaye
         Section sec(tm, "topk_collect", true);
         TK_CHECK(topk_collect(t, g, e_in, e, d_layers, d_tiles, n_tiles, s, &sec));
     }
-    TK_CHECK(topk_select(t, g, e_in, e, d_layers, d_tiles, L, n_tiles, 1, true, true, tm, s, nullptr));
+    TK_CHECK(topk_select(t, g, e_in, e, d_layers, d_tiles, L, n_tiles, 1, true, tm, s, nullptr));
     TK_CHECK(topk_finalize(t, d_layers, d_tiles, L, 1, nullptr, nullptr, 0, tm, s));
     {
         Section sec(tm, "topk_count");

@@ -331,3 +331,23 @@ def test_compress_calls_queued_back_to_back():
             assert np.array_equal(pay[offsets[l]:offsets[l] + 4 * k].view(np.uint32), vals.view(np.uint32)), l
             assert np.array_equal(new_ef[off:off + n].view(np.uint32), e_ref.view(np.uint32)), l
     h.close()
+
+
+@pytest.mark.parametrize("n", [16384, 16385, 300000, (1 << 20) + 3])
+def test_bound_predicted_too_high_or_too_low(n):
+    """Layers laid out against the sample (512 segments of 32 elements at scrambled places; a layer of
+    at most 16384 elements is taken whole): all large entries where it looks (the predicted
+    collection bound lies above the thresholds and the layer is collected again), or none of them
+    (nearly everything is a candidate).  Profile and compression against the oracle."""
+    rng = np.random.default_rng(n)
+    seg = np.arange(512, dtype=np.uint64)
+    stride = max(n // 512, 32)
+    first = seg * stride + (((seg * 2654435761) % (1 << 32)) * (stride - 31) >> np.uint64(32))
+    seen = (first[:, None] + np.arange(32, dtype=np.uint64)).reshape(-1).astype(np.int64)
+    sampled = np.zeros(n, bool)
+    sampled[seen[seen < n]] = True
+    big = rng.laplace(0, 1.0, n).astype(np.float32)
+    small = rng.laplace(0, 1e-3, n).astype(np.float32)
+    a = np.where(sampled, big, small).astype(np.float32)
+    b = np.where(sampled, small, big).astype(np.float32)
+    _check(_flat_batch([a, b]), (0.001, 0.01, 0.1, 0.5))
