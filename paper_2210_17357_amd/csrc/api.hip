@@ -534,7 +534,7 @@ int lgreco_create(lgreco_handle_t** out, const lgreco_config_t* cfg, int64_t max
     HIPCHK_C(hipEventCreateWithFlags(&h->ev_fork, hipEventDisableTiming));
     HIPCHK_C(hipEventCreateWithFlags(&h->ev_join, hipEventDisableTiming));
     {
-        hipError_t e = topk_scratch_create(&h->topk, max_elems, max_layers, h->max_tiles);
+        hipError_t e = topk_scratch_create(&h->topk, max_elems, max_layers, h->max_tiles, max_cands);
         if (e != hipSuccess) { hip_fail(h, e, "topk_scratch_create"); return fail(LGRECO_EHIP); }
         e = lowrank_scratch_create(&h->lowrank, max_elems, max_layers, cfg->r_max, cfg->power_iters);
         if (e != hipSuccess) { hip_fail(h, e, "lowrank_scratch_create"); return fail(LGRECO_EHIP); }
@@ -720,9 +720,7 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
     } phase{h->tm, -1};
 
     QuantParams qp{};
-    // Top-K candidates, largest density first: one pass resolves kMaxTopk of them, the rest follow
-    // in further groups on the same collected candidates (the first group has the lowest
-    // thresholds, so its collection bound serves all)
+    // Top-K candidates, largest density first (its threshold is the lowest: the collection bound)
     std::vector<std::pair<double, int>> tk_all;
     int lr_col[LGRECO_MAX_CANDS], lr_rank[LGRECO_MAX_CANDS], nlr = 0;
     for (int c = 0; c < P; ++c) {
@@ -761,26 +759,28 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
     std::stable_sort(tk_all.begin(), tk_all.end(),
                      [](const std::pair<double, int>& a, const std::pair<double, int>& b) { return a.first > b.first; });
     const int ntk_all = (int)tk_all.size();
-    const int ntk = std::min(ntk_all, (int)kMaxTopk);          // size of the first group
+    // up to kMaxTopk of them have a column each in the kernels' k table; more than that go through
+    // the tables of TopkRange, and the k table holds the largest alone
+    const bool many = ntk_all > (int)kMaxTopk;
+    const int ntk = many ? 1 : ntk_all;
     h->last_ntk = ntk_all;
-    for (int j = 0; j < ntk; ++j) h->last_tk_col[j] = tk_all[j].second;
     int tk_col[kMaxTopk];
     std::vector<uint32_t> ks((size_t)L * kMaxTopk, 0u);
-    auto load_group = [&](int first) {                          // fills ks / tk_col, returns the group's size
-        const int cnt = std::min((int)kMaxTopk, ntk_all - first);
-        std::fill(ks.begin(), ks.end(), 0u);
-        for (int j = 0; j < cnt; ++j) {
-            tk_col[j] = tk_all[first + j].second;
-            for (int l = 0; l < L; ++l)
-                ks[(size_t)l * kMaxTopk + j] = (uint32_t)topk_k(layers[l].numel, tk_all[first + j].first);
-        }
-        return cnt;
-    };
-    if (ntk) {
-        load_group(0);
-        HIPCHK(topk_begin(&h->topk, d_grads, d_ef, h->d_layers, h->hl.data(), h->d_tiles, L, n_tiles,
-                          h->tile_elems, ks.data(), ntk, 0, h->tm, s));
+    for (int j = 0; j < ntk; ++j) {
+        h->last_tk_col[j] = tk_col[j] = tk_all[j].second;
+        for (int l = 0; l < L; ++l) ks[(size_t)l * kMaxTopk + j] = (uint32_t)topk_k(layers[l].numel, tk_all[j].first);
     }
+    TopkRange range;
+    if (many) {
+        range.ks.resize((size_t)L * ntk_all);
+        for (int j = 0; j < ntk_all; ++j) range.cols.push_back(tk_all[j].second);
+        for (int l = 0; l < L; ++l)
+            for (int j = 0; j < ntk_all; ++j)
+                range.ks[(size_t)l * ntk_all + j] = (uint32_t)topk_k(layers[l].numel, tk_all[j].first);
+    }
+    if (ntk)
+        HIPCHK(topk_begin(&h->topk, d_grads, d_ef, h->d_layers, h->hl.data(), h->d_tiles, L, n_tiles,
+                          h->tile_elems, ks.data(), ntk, 0, h->tm, s, many ? &range : nullptr));
     if (qp.nq) {
         qp.g = d_grads;
         qp.e = d_ef;
@@ -817,20 +817,12 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
     if (ntk) {
         // (the per-layer sums of the quantization errors ride on the scan's launch)
         const QuantReduce qr{h->d_partials, d_err, P, qp.col, qp.nq};
-        HIPCHK(topk_select(&h->topk, g_after, e_after, nullptr, h->d_layers, h->d_tiles, L, n_tiles, ntk,
-                           ntk_all <= (int)kMaxTopk, h->tm, s, qp.nq ? &qr : nullptr));
+        HIPCHK(topk_select(&h->topk, g_after, e_after, nullptr, h->d_layers, L, ntk, h->tm, s, qp.nq ? &qr : nullptr));
     } else if (qp.nq) {
         Section sec(h->tm, "reduce_partials");
         HIPCHK(launch_reduce_partials(h->d_partials, P, qp.col, qp.nq, h->d_layers, L, d_err, s));
     }
     if (ntk) HIPCHK(topk_finalize(&h->topk, h->d_layers, h->d_tiles, L, ntk, tk_col, d_err, P, h->tm, s));
-    for (int first = kMaxTopk; first < ntk_all; first += kMaxTopk) {
-        const int cnt = load_group(first);
-        HIPCHK(topk_regroup(&h->topk, L, ks.data(), 0, s));
-        HIPCHK(topk_select(&h->topk, g_after, e_after, nullptr, h->d_layers, h->d_tiles, L, n_tiles, cnt,
-                           first + (int)kMaxTopk >= ntk_all, h->tm, s, nullptr));
-        HIPCHK(topk_finalize(&h->topk, h->d_layers, h->d_tiles, L, cnt, tk_col, d_err, P, h->tm, s));
-    }
     if (nlr) {
         HIPCHK(lowrank_profile(&h->lowrank, d_grads, d_ef, h->d_layers, h->hl.data(), L, d_q0, h->cfg.r_max,
                                lr_rank, lr_col, nlr, d_err, P, h->tm, s));

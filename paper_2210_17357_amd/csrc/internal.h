@@ -251,7 +251,15 @@ struct TopkScratch {
     bool ctl_pending = false;         // an upload was queued since h_ctl was last known to be free
     uint8_t* h_ctl_last[2] = {nullptr, nullptr};    // what each d_ctl holds
     size_t ctl_bytes = 0, ctl_last_bytes[2] = {0, 0};
-    size_t ctl_off[4] = {0, 0, 0, 0}; // byte offsets of k, cand_base, work_range, work
+    size_t ctl_off[5] = {};           // byte offsets of k, cand_base, work_range, work, many
+    // more than kMaxTopk densities in one profile
+    uint32_t* h_many = nullptr;       // (in the control block) column of every density, then k per (layer, density)
+    uint32_t* d_many_in = nullptr;
+    int nk_many = 0;                  // densities of the current call, 0: at most kMaxTopk
+    void* d_many = nullptr;           // per-layer records
+    unsigned long long* d_cell_many = nullptr;   // per (work item, list): partial histogram, and
+    double* d_below_many = nullptr;              // the energy below the list's bin
+    size_t many_lists = 0;            // (work item, list) pairs the two hold
     void* d_work = nullptr;           // refinement work table and per-layer ranges
     void* d_work_range = nullptr;
     void* h_work = nullptr;
@@ -263,14 +271,17 @@ struct TopkScratch {
     int64_t max_elems = 0;
     int max_layers = 0, max_tiles = 0;
 };
-hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers, int max_tiles);
+hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers, int max_tiles, int max_cands);
 void topk_scratch_destroy(TopkScratch* t);
+// More than kMaxTopk densities: their columns and k per (layer, density), the largest density first.
+struct TopkRange {
+    std::vector<int32_t> cols;
+    std::vector<uint32_t> ks;         // [L x cols.size()]
+};
 // upload k per (layer, candidate), sample the data and predict every layer's collection bound
 hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevLayer* d_layers,
                       const DevLayer* h_layers, const Tile* d_tiles, int L, int n_tiles, int tile_elems,
-                      const uint32_t* ks, int ntk, int slot, Timing* tm, hipStream_t s);
-// replace the requested k by another group (each k no larger than the first group's largest)
-hipError_t topk_regroup(TopkScratch* t, int L, const uint32_t* ks, int slot, hipStream_t s);
+                      const uint32_t* ks, int ntk, int slot, Timing* tm, hipStream_t s, const TopkRange* range);
 // main pass (exact coarse histogram + candidate collection) when no quantization candidate shares
 // the read; otherwise the quantization profile kernel does the same work
 hipError_t topk_collect(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers,
@@ -286,9 +297,8 @@ struct QuantReduce {
     const int* cols;
     int ncols;
 };
-hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers,
-                       const Tile* d_tiles, int L, int n_tiles, int ntk, bool last_group, Timing* tm, hipStream_t s,
-                       const QuantReduce* quant);
+hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers, int L,
+                       int ntk, Timing* tm, hipStream_t s, const QuantReduce* quant);
 // refinement on the candidates: exact thresholds; writes the dropped energy to errors (if not null)
 hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d_tiles, int L, int ntk,
                          const int* col, double* d_errors, int stride, Timing* tm, hipStream_t s);

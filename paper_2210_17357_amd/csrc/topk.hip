@@ -52,6 +52,18 @@ struct TopkLayer {
     TopkList lists[kMaxTopk];
     TopkSel sel[kMaxTopk];
 };
+// The same for a profile of more than kMaxTopk densities.  The requested k do not increase with j, so
+// the densities whose threshold lies in one coarse bin are consecutive: list i holds the densities
+// [first[i], first[i + 1]).
+struct TopkMany {
+    uint32_t nlists, recollect;
+    uint32_t bin[LGRECO_MAX_CANDS];      // threshold bin of every list, ascending
+    uint32_t first[LGRECO_MAX_CANDS + 1];
+    uint32_t need[LGRECO_MAX_CANDS];     // per density: entries to take from its threshold bin
+};
+constexpr int kManyChunk = 8;       // lists one refinement workgroup works on at a time
+constexpr int kManySplit = 4;       // refinement workgroups that share a work item's lists
+constexpr int kManySlots = 32;      // workgroups that share a layer's lists in the pick
 constexpr int kRefTiles = 16;       // largest tiles per refinement workgroup (fewer elements never: with
                                     // smaller tiles a workgroup takes proportionally more of them)
 constexpr int kRefThreads = 1024;
@@ -590,7 +602,7 @@ struct ScanReduce {
 __global__ __launch_bounds__(256) void topk_scan_kernel(uint32_t* __restrict__ hist,
                                                         const uint32_t* __restrict__ ks, int ntk,
                                                         const int64_t* __restrict__ cand_base,
-                                                        uint32_t* lo, TopkLayer* __restrict__ tl, int clear,
+                                                        uint32_t* lo, TopkLayer* __restrict__ tl,
                                                         int n_layers, ScanReduce red) {
     __shared__ __align__(16) unsigned char s_raw[sizeof(uint32_t) * kHistBins];   // 16 KB: the histogram, or the reduction's tree
     static_assert(sizeof(s_raw) >= sizeof(double) * kMaxQuant * 256, "shared by both jobs");
@@ -609,13 +621,12 @@ __global__ __launch_bounds__(256) void topk_scan_kernel(uint32_t* __restrict__ h
             T.nlists = 0; T.min_tbin = 0; T.recollect = 0;
             for (int j = 0; j < kMaxTopk; ++j) T.sel[j].k = 0;
         }
-        if (clear)
-            for (int b = threadIdx.x; b < kHistBins; b += 256) hist[(size_t)l * kHistBins + b] = 0u;
+        for (int b = threadIdx.x; b < kHistBins; b += 256) hist[(size_t)l * kHistBins + b] = 0u;
         return;
     }
     for (int b = threadIdx.x; b < kHistBins; b += 256) {
         s_hist[b] = hist[(size_t)l * kHistBins + b];
-        if (clear) hist[(size_t)l * kHistBins + b] = 0u;     // the next call's main pass starts from zero
+        hist[(size_t)l * kHistBins + b] = 0u;                // the next call's main pass starts from zero
     }
     __syncthreads();
     // one suffix scan of the histogram serves every requested k
@@ -662,6 +673,73 @@ __global__ __launch_bounds__(256) void topk_scan_kernel(uint32_t* __restrict__ h
         reinterpret_cast<uint32_t*>(&T)[w] = reinterpret_cast<const uint32_t*>(&sT)[w];
 }
 
+// The bin that holds the entry of rank `need` from the top, and the entries in higher bins, by one
+// thread alone (after block_suffix; need <= scan[0]).
+__device__ __forceinline__ void thread_find(const uint32_t* hist, int nbins, uint32_t need, const uint32_t* scan,
+                                            uint32_t* bin, uint32_t* above) {
+    const int per = (nbins + 255) / 256;
+    int t = 0;                                            // largest t with scan[t] >= need
+    for (int step = 128; step; step >>= 1)
+        if (t + step < 256 && scan[t + step] >= need) t += step;
+    uint32_t running = t + 1 < 256 ? scan[t + 1] : 0u;
+    int b = min((t + 1) * per, nbins) - 1;
+    for (; b > t * per && running + hist[b] < need; --b) running += hist[b];
+    *bin = (uint32_t)b;
+    *above = running;
+}
+
+// The scan for more than kMaxTopk densities: a thread per density finds its bin.
+__global__ __launch_bounds__(256) void topk_scan_many_kernel(uint32_t* __restrict__ hist,
+                                                             const uint32_t* __restrict__ ks, int nk, uint32_t* lo,
+                                                             TopkMany* __restrict__ many, int n_layers,
+                                                             ScanReduce red) {
+    static_assert(LGRECO_MAX_CANDS <= 128, "a thread per density, two wavefronts");
+    __shared__ __align__(16) unsigned char s_raw[sizeof(uint32_t) * kHistBins];
+    if ((int)blockIdx.x >= n_layers) {
+        reduce_partials_block(red.partials, red.stride, red.cols, red.layers, red.errors, (int)blockIdx.x - n_layers,
+                              reinterpret_cast<double(*)[256]>(s_raw));
+        return;
+    }
+    uint32_t* const s_hist = reinterpret_cast<uint32_t*>(s_raw);
+    __shared__ uint32_t s_scan[256], s_bin[LGRECO_MAX_CANDS], s_heads[2];
+    const int l = blockIdx.x, tid = threadIdx.x;
+    TopkMany& T = many[l];
+    uint4* const h4 = reinterpret_cast<uint4*>(hist + (size_t)l * kHistBins);
+    for (int b = tid; b < kHistBins / 4; b += 256) {
+        reinterpret_cast<uint4*>(s_hist)[b] = h4[b];
+        h4[b] = make_uint4(0u, 0u, 0u, 0u);               // the next call's main pass starts from zero
+    }
+    const uint32_t k = tid < nk ? ks[(size_t)l * nk + tid] : 0u;
+    __syncthreads();
+    block_suffix(s_hist, kHistBins, s_scan);
+    uint32_t bin = 0, above = 0;
+    if (tid < nk) {
+        thread_find(s_hist, kHistBins, k, s_scan, &bin, &above);
+        s_bin[tid] = bin;
+    }
+    __syncthreads();
+    const bool head = tid < nk && (tid == 0 || s_bin[tid - 1] != bin);
+    const unsigned long long m = __ballot(head);
+    if (tid == 0) s_heads[0] = (uint32_t)__popcll(m);
+    if (tid == 64) s_heads[1] = (uint32_t)__popcll(m);
+    __syncthreads();
+    if (tid < nk) T.need[tid] = k - above;
+    if (head) {
+        const uint32_t i = (tid < 64 ? 0u : s_heads[0]) + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+        T.bin[i] = bin;
+        T.first[i] = (uint32_t)tid;
+    }
+    if (tid == 0) {
+        const uint32_t nl = s_heads[0] + s_heads[1];
+        T.nlists = nl;
+        T.first[nl] = (uint32_t)nk;
+        // every element at or above the lowest threshold bin must be among the candidates
+        const bool again = lo[l] > bin;
+        T.recollect = again ? 1u : 0u;
+        if (again) lo[l] = bin;
+    }
+}
+
 struct RefineParams {
     TopkLayer* tl;
     const DevLayer* layers;
@@ -680,6 +758,14 @@ struct RefineParams {
     int32_t stride;
     int32_t ntk;
     int32_t col[kMaxTopk];
+    // more than kMaxTopk densities: the layers' records, and per (work item, list), nk lists in a
+    // row, the partial histogram and the energy below the list's bin
+    const TopkMany* many;
+    const int64_t* cand_base;
+    const int32_t* cols;              // [nk] column of every density
+    unsigned long long* cell_many;
+    double* below_many;
+    int32_t nk;
     // the second collection of a layer whose predicted bound was too high (flagged by the scan):
     // every workgroup of the first refinement kernel makes it for its own tiles before it looks at
     // their candidates (rc.ef_out not null: the compression's form, which also writes x)
@@ -705,14 +791,14 @@ __device__ __forceinline__ void collect_again(const CollectParams& rc, int t0, i
 // time, 8 loads in flight per lane; f(pattern) is called for every candidate, in a fixed order
 // per thread.
 template <typename F>
-__device__ __forceinline__ void for_each_candidate(const RefineParams& p, const TopkLayer& T, int t0, int t1, F f) {
+__device__ __forceinline__ void for_each_candidate(const RefineParams& p, int64_t cand_base, int t0, int t1, F f) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     constexpr int kSub = kThreads / 64;
     const int npairs = (t1 - t0) * kSub;
     for (int pr = wave; pr < npairs; pr += kRefThreads / 64) {
         const int t = t0 + pr / kSub, sub = pr % kSub;
         const uint32_t n = p.tinfo[t].cnt[sub];
-        const uint32_t* __restrict__ items = p.cand + T.cand_base + p.tiles[t].pos + p.tinfo[t].start[sub];
+        const uint32_t* __restrict__ items = p.cand + cand_base + p.tiles[t].pos + p.tinfo[t].start[sub];
         uint32_t i0 = 0;
         for (; i0 + 64 * 8 <= n; i0 += 64 * 8) {          // full batches: no range checks
             uint32_t pat[8];
@@ -832,7 +918,7 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_a_kernel(RefinePar
     float below[kMaxTopk];
 #pragma unroll
     for (int j = 0; j < kMaxTopk; ++j) below[j] = 0.0f;
-    for_each_candidate(p, T, w.t0, w.t1, [&](uint32_t pat) {
+    for_each_candidate(p, T.cand_base, w.t0, w.t1, [&](uint32_t pat) {
         const uint32_t key = pat >> kHistShift;
         const uint32_t hit = s_tab[key];
         if constexpr (ENERGY) below_chain<NTK>(below, tb, key, __uint_as_float(pat));
@@ -866,6 +952,21 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_a_kernel(RefinePar
     }
 }
 
+// A thread's share (of 256) of a layer's energy below the collection bound, in index order with four loads in flight.
+__device__ __forceinline__ double base_energy(const RefineParams& p, int l) {
+    const DevLayer& L = p.layers[l];
+    const int end = L.tile_end;
+    double part = 0.0;
+    for (int tt = L.tile_begin + (int)(threadIdx.x & 255); tt < end; tt += 4 * 256) {
+        double v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = tt + q * 256 < end ? p.base_part[tt + q * 256] : 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) part += v[q];
+    }
+    return part;
+}
+
 // One workgroup per (layer, requested k): sub-bin of level A holding the k-th magnitude.
 // ENERGY (profile): the dropped energy is written here.  Everything outside the boundary sub-bin is
 // summed exactly (integer energies).  Inside it the dropped entries are the `drop` smallest of
@@ -880,6 +981,50 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_a_kernel(RefinePar
 // smallest.  The deviation from the exact dropped energy is therefore at most 1e-5 relative from
 // this step (plus 1.2e-7 from the truncated integer energies and the fp32 sums below the bound).
 constexpr double kInsideTolerance = 1e-5;
+// The midpoint for the sub-bin `prefix` (pattern >> 9) with `cnt` entries of summed integer energy `sum`, `need_a`
+// of them kept, in *inside; false if it is not good enough.
+__device__ __forceinline__ bool dropped_inside(uint32_t prefix, uint32_t cnt, uint32_t need_a, unsigned long long sum_e,
+                                               int sh, double outside, double* inside) {
+    const uint32_t edge = prefix << 9;
+    const double e_lo = (double)(packed_cell(edge) >> kPackCountBits);
+    const double e_hi = (double)(packed_cell(edge | 0x1FFu) >> kPackCountBits);
+    const double sum = (double)sum_e;
+    const double drop = (double)(cnt - need_a), keep = (double)need_a;
+    const double lower = fmax(drop * e_lo, sum - keep * e_hi);
+    const double upper = drop * (sum / (double)cnt);
+    *inside = 0.5 * (lower + upper);
+    const double half = 0.5 * (upper - lower);
+    return !(ldexp(half, sh) > kInsideTolerance * (outside + ldexp(*inside, sh)));
+}
+
+// Shift from integer energy units of a coarse bin to x^2.
+__device__ __forceinline__ int energy_shift(uint32_t tbin) {
+    const uint32_t ex = tbin >> (23 - kHistShift);
+    return 2 * ((int)(ex ? ex : 1u) - 150) + kPackEnergyShift;
+}
+
+// The rare exact route: histogram of the last 9 bits of a layer's candidates inside the sub-bin
+// `prefix`.  s_hist holds kBinsB cells; the whole workgroup calls.
+template <int NT>
+__device__ void count_sub_bin(const RefineParams& p, int l, int64_t cand_base, uint32_t prefix, uint32_t* s_hist) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int b = tid; b < kBinsB; b += NT) s_hist[b] = 0;
+    __syncthreads();
+    const DevLayer L = p.layers[l];
+    constexpr int kSub = kThreads / 64;
+    const int npairs = (L.tile_end - L.tile_begin) * kSub;
+    for (int pr = wave; pr < npairs; pr += NT / 64) {
+        const int tt = L.tile_begin + pr / kSub, sub = pr % kSub;
+        const uint32_t n = p.tinfo[tt].cnt[sub];
+        const uint32_t* __restrict__ items = p.cand + cand_base + p.tiles[tt].pos + p.tinfo[tt].start[sub];
+        for (uint32_t i = lane; i < n; i += 64) {
+            const uint32_t pat = items[i];
+            if ((pat >> 9) == prefix) atomicAdd(&s_hist[pat & (kBinsB - 1)], 1u);
+        }
+    }
+    __syncthreads();
+}
+
 template <bool ENERGY, int kPickThreads>
 __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams p) {
     __shared__ uint32_t s_hist[kBinsA];
@@ -909,15 +1054,7 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
     // are summed in a fixed order (per thread, then a fixed tree)
     double part = 0.0;
     if (ENERGY && tid < 256) {
-        const DevLayer L = p.layers[l];
-        // four loads in flight per round trip; summed in index order all the same
-        for (int tt = L.tile_begin + tid; tt < L.tile_end; tt += 4 * 256) {
-            double v[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = tt + q * 256 < L.tile_end ? p.base_part[tt + q * 256] : 0.0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) part += v[q];
-        }
+        part = base_energy(p, l);
         for (int wg = wr.x + tid; wg < wr.y; wg += 256) part += p.below_part[(size_t)wg * kMaxTopk + j];
     }
     __syncthreads();
@@ -967,8 +1104,7 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
         }
         __syncthreads();
     }
-    const uint32_t ex = S.tbin >> (23 - kHistShift);
-    const int sh = 2 * ((int)(ex ? ex : 1u) - 150) + kPackEnergyShift;    // integer energy units -> x^2
+    const int sh = energy_shift(S.tbin);
     if (tid == 0) {
         const uint32_t need_a = S.need - s_res[1];
         T.sel[j].bin_a = bin_a;
@@ -977,19 +1113,8 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
             const uint32_t cnt = s_hist[bin_a];
             const double outside = ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3])) + ldexp((double)s_e, sh);
             double inside = 0.0;      // dropped part of the sub-bin, in integer-energy units
-            bool exact = false;
-            if (cnt > need_a) {
-                const uint32_t edge = (S.tbin << kHistShift) | (bin_a << 9);
-                const double e_lo = (double)(packed_cell(edge) >> kPackCountBits);
-                const double e_hi = (double)(packed_cell(edge | 0x1FFu) >> kPackCountBits);
-                const double sum = (double)s_en[bin_a];
-                const double drop = (double)(cnt - need_a), keep = (double)need_a;
-                const double lower = fmax(drop * e_lo, sum - keep * e_hi);
-                const double upper = drop * (sum / (double)cnt);
-                inside = 0.5 * (lower + upper);
-                const double half = 0.5 * (upper - lower);
-                exact = ldexp(half, sh) > kInsideTolerance * (outside + ldexp(inside, sh));
-            }
+            const bool exact = cnt > need_a && !dropped_inside((S.tbin << 10) | bin_a, cnt, need_a, s_en[bin_a], sh,
+                                                               outside, &inside);
             if (exact) {
                 s_outside = outside;
                 s_exact[1] = (S.tbin << 10) | bin_a;
@@ -1003,26 +1128,8 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
     if (!ENERGY) return;
     __syncthreads();
     if (!s_exact[0]) return;                                  // workgroup-uniform
-    // ---- the rare exact route: last 9 bits of the candidates inside the sub-bin
     const uint32_t prefix = s_exact[1], need_a = s_exact[2];
-    for (int b = tid; b < kBinsB; b += kPickThreads) s_hist[b] = 0;      // kBinsB <= kBinsA
-    __syncthreads();
-    {
-        const DevLayer L = p.layers[l];
-        const int lane = tid & 63, wave = tid >> 6;
-        constexpr int kSub = kThreads / 64;
-        const int npairs = (L.tile_end - L.tile_begin) * kSub;
-        for (int pr = wave; pr < npairs; pr += kPickThreads / 64) {
-            const int tt = L.tile_begin + pr / kSub, sub = pr % kSub;
-            const uint32_t n = p.tinfo[tt].cnt[sub];
-            const uint32_t* __restrict__ items = p.cand + T.cand_base + p.tiles[tt].pos + p.tinfo[tt].start[sub];
-            for (uint32_t i = lane; i < n; i += 64) {
-                const uint32_t pat = items[i];
-                if ((pat >> 9) == prefix) atomicAdd(&s_hist[pat & (kBinsB - 1)], 1u);
-            }
-        }
-    }
-    __syncthreads();
+    count_sub_bin<kPickThreads>(p, l, T.cand_base, prefix, s_hist);
     block_kth_from_top(s_hist, kBinsB, need_a, s_scan, s_res);
     const uint32_t thr_b = s_res[0], keep_at_thr = need_a - s_res[1];
     // dropped inside the sub-bin: every pattern below the threshold pattern, and the entries equal
@@ -1045,6 +1152,172 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
     }
 }
 
+// ---- more than kMaxTopk densities
+// All of them are resolved at once on the candidates collected once.  What is shared between densities is worked
+// out once per list (distinct threshold bin; 100 densities between 0.1 % and 10 % have about 25), and the lists
+// are dealt to workgroups in chunks of 8, as many as keep two workgroups on a compute unit.  In groups of 8
+// densities, each with its own upload, scan, refinement and pick, the 100 densities of a 26 M-element
+// model took 13 times 80 us, nearly all of it the latency of short kernels.
+
+// Layers whose predicted bound was too high are collected again (flagged by the scan; usually none).
+__global__ __launch_bounds__(kRefThreads) void topk_recollect_many_kernel(RefineParams p) {
+    const RefWork w = p.work[blockIdx.x];
+    if (p.many[w.layer].recollect) collect_again<false>(p.rc, w.t0, w.t1);
+}
+
+// As topk_refine_a_kernel with energies, for the chunks blockIdx.y, blockIdx.y + kManySplit, ... of the layer's lists.
+__global__ __launch_bounds__(kRefThreads, 8) void topk_refine_many_kernel(RefineParams p) {
+    extern __shared__ unsigned char refine_smem[];
+    __shared__ double s_red[kRefThreads / 64][kManyChunk];
+    const RefWork w = p.work[blockIdx.x];
+    const TopkMany& T = p.many[w.layer];
+    const int64_t cand_base = p.cand_base[w.layer];
+    const int nlists = (int)T.nlists, tid = threadIdx.x;
+    unsigned long long* const s_cell = reinterpret_cast<unsigned long long*>(refine_smem);
+    uint8_t* const s_tab = refine_smem + (size_t)kManyChunk * kBinsA * 8;
+    for (int c0 = (int)blockIdx.y * kManyChunk; c0 < nlists; c0 += kManySplit * kManyChunk) {
+        const int n = min(kManyChunk, nlists - c0);
+        for (int i = tid; i < n * kBinsA; i += kRefThreads) s_cell[i] = 0;
+        uint32_t lb[kManyChunk];                        // ascending; past the end nothing lies above
+#pragma unroll
+        for (int j = 0; j < kManyChunk; ++j) lb[j] = __builtin_amdgcn_readfirstlane(j < n ? T.bin[c0 + j] : 0xFFFFFFFFu);
+        for (uint32_t key = tid; key < (uint32_t)kHistBins; key += kRefThreads) {
+            uint32_t hit = 0;
+#pragma unroll
+            for (int j = 0; j < kManyChunk; ++j) hit = key == lb[j] ? (uint32_t)(j + 1) : hit;
+            s_tab[key] = (uint8_t)hit;
+        }
+        __syncthreads();
+        float below[kManyChunk];
+#pragma unroll
+        for (int j = 0; j < kManyChunk; ++j) below[j] = 0.0f;
+        for_each_candidate(p, cand_base, w.t0, w.t1, [&](uint32_t pat) {
+            const uint32_t key = pat >> kHistShift;
+            const uint32_t hit = s_tab[key];
+            below_chain<kManyChunk>(below, lb, key, __uint_as_float(pat));
+            if (hit) atomicAdd(&s_cell[(hit - 1) * kBinsA + ((pat >> 9) & (kBinsA - 1))], packed_cell(pat));
+        });
+#pragma unroll
+        for (int j = 0; j < kManyChunk; ++j) {
+            const double s = wave_sum((double)below[j]);
+            if ((tid & 63) == 0) s_red[tid >> 6][j] = s;
+        }
+        __syncthreads();
+        const size_t out = (size_t)blockIdx.x * p.nk + c0;
+        if (tid < n) {
+            double s = 0.0;
+            for (int wv = 0; wv < kRefThreads / 64; ++wv) s += s_red[wv][tid];
+            p.below_many[out + tid] = s;
+        }
+        ulonglong2* const gc = reinterpret_cast<ulonglong2*>(p.cell_many + out * kBinsA);
+        for (int i = tid; i < n * kBinsA / 2; i += kRefThreads) gc[i] = reinterpret_cast<const ulonglong2*>(s_cell)[i];
+        __syncthreads();                                // the cells are cleared for the next chunk
+    }
+}
+
+// A workgroup takes the lists blockIdx.y, blockIdx.y + kManySlots, ... of a layer: the list's histogram over the
+// layer's work items, then a thread per density for what topk_pick_a_kernel's thread 0 does.
+__global__ __launch_bounds__(256) void topk_pick_many_kernel(RefineParams p) {
+    __shared__ uint32_t s_hist[kBinsA];
+    __shared__ unsigned long long s_en[kBinsA];
+    __shared__ uint32_t s_scan[256];
+    __shared__ unsigned long long s_pre[256];       // energy of the cells before thread t's four
+    __shared__ unsigned long long s_wave[4];
+    __shared__ double s_sum[4];
+    __shared__ uint32_t s_open;                     // one density that still has to be resolved exactly, plus 1
+    __shared__ uint32_t s_prefix;
+    const int l = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const TopkMany& T = p.many[l];
+    const int nlists = (int)T.nlists;
+    if ((int)blockIdx.y >= nlists) return;
+    const int2 wr = p.work_range[l];
+    const double base = base_energy(p, l);
+    for (int li = blockIdx.y; li < nlists; li += kManySlots) {
+        const uint32_t tbin = T.bin[li], first = T.first[li], count = T.first[li + 1] - first;
+        double part = base;
+        for (int wg = wr.x + tid; wg < wr.y; wg += 256) part += p.below_many[(size_t)wg * p.nk + li];
+        // cells 4 t .. 4 t + 3
+        uint32_t c[4] = {0, 0, 0, 0};
+        unsigned long long e[4] = {0, 0, 0, 0};
+#pragma unroll 8
+        for (int wg = wr.x; wg < wr.y; ++wg) {
+            const ulonglong2* const v2 = reinterpret_cast<const ulonglong2*>(p.cell_many + ((size_t)wg * p.nk + li) * kBinsA + 4 * tid);
+            const ulonglong2 v0 = v2[0], v1 = v2[1];
+            const unsigned long long v[4] = {v0.x, v0.y, v1.x, v1.y};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                c[q] += (uint32_t)(v[q] & ((1ull << kPackCountBits) - 1));
+                e[q] += v[q] >> kPackCountBits;
+            }
+        }
+        __syncthreads();                            // the previous list is done with the tables
+        unsigned long long mine = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            s_hist[4 * tid + q] = c[q];
+            s_en[4 * tid + q] = e[q];
+            mine += e[q];
+        }
+        unsigned long long inc = mine;
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned long long n = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += n;
+        }
+        if (lane == 63) s_wave[wave] = inc;
+        const double ws = wave_sum(part);
+        if (lane == 0) s_sum[wave] = ws;
+        if (tid == 0) s_open = 0;
+        __syncthreads();
+        for (int w = 0; w < wave; ++w) inc += s_wave[w];
+        s_pre[tid] = inc - mine;
+        block_suffix(s_hist, kBinsA, s_scan);
+        const double under = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+        const int sh = energy_shift(tbin);
+        bool open = false;
+        uint32_t prefix = 0, need_a = 0;
+        double outside = 0.0;
+        if ((uint32_t)tid < count) {
+            uint32_t bin_a, above;
+            thread_find(s_hist, kBinsA, T.need[first + tid], s_scan, &bin_a, &above);
+            need_a = T.need[first + tid] - above;
+            unsigned long long en = s_pre[bin_a >> 2];
+            for (uint32_t b = bin_a & ~3u; b < bin_a; ++b) en += s_en[b];
+            outside = under + ldexp((double)en, sh);
+            prefix = (tbin << 10) | bin_a;
+            const uint32_t cnt = s_hist[bin_a];
+            double inside = 0.0;
+            open = cnt > need_a && !dropped_inside(prefix, cnt, need_a, s_en[bin_a], sh, outside, &inside);
+            if (!open) p.errors[(size_t)l * p.stride + p.cols[first + tid]] = outside + ldexp(inside, sh);
+        }
+        // densities that need it are resolved exactly, those of one sub-bin together
+        for (;;) {
+            if (open) s_open = (uint32_t)tid + 1u;
+            __syncthreads();
+            const uint32_t who = s_open;
+            if (!who) break;                        // workgroup-uniform
+            if (who == (uint32_t)tid + 1u) s_prefix = prefix;
+            __syncthreads();
+            const uint32_t now = s_prefix;
+            count_sub_bin<256>(p, l, p.cand_base[l], now, s_hist);
+            block_suffix(s_hist, kBinsB, s_scan);
+            if (tid == 0) s_open = 0;
+            if (open && prefix == now) {
+                uint32_t thr_b, above;
+                thread_find(s_hist, kBinsB, need_a, s_scan, &thr_b, &above);
+                double inside = 0.0;
+                for (uint32_t b = 0; b <= thr_b; ++b) {
+                    const uint32_t n_drop = b < thr_b ? s_hist[b] : s_hist[b] - (need_a - above);
+                    const double v = (double)__uint_as_float((prefix << 9) | b);
+                    inside += (double)n_drop * (v * v);
+                }
+                p.errors[(size_t)l * p.stride + p.cols[first + tid]] = outside + inside;
+                open = false;
+            }
+            __syncthreads();
+        }
+    }
+}
+
 // Refinement level B (compress only): histogram of bits 8..0 of the candidates inside each k's
 // level-A sub-bin.
 __global__ __launch_bounds__(kRefThreads) void topk_refine_b_kernel(RefineParams p) {
@@ -1060,7 +1333,7 @@ __global__ __launch_bounds__(kRefThreads) void topk_refine_b_kernel(RefineParams
     for (int j = 0; j < kMaxTopk; ++j)
         prefix[j] = (j < ntk && T.sel[j].k) ? ((T.sel[j].tbin << 10) | T.sel[j].bin_a) : 0xFFFFFFFFu;
     __syncthreads();
-    for_each_candidate(p, T, w.t0, w.t1, [&](uint32_t pat) {
+    for_each_candidate(p, T.cand_base, w.t0, w.t1, [&](uint32_t pat) {
         const uint32_t pre = pat >> 9;
 #pragma unroll
         for (int j = 0; j < kMaxTopk; ++j)
@@ -1355,7 +1628,7 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__
         if (_e != hipSuccess) return _e;   \
     } while (0)
 
-hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers, int max_tiles) {
+hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers, int max_tiles, int max_cands) {
     t->max_elems = max_elems;
     t->max_layers = max_layers;
     t->max_tiles = max_tiles;
@@ -1384,11 +1657,14 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
     TK_CHECK(hipMalloc(&t->d_ref, sizeof(uint32_t) * t->ref_words));
     // control block layout (every part a multiple of 16 bytes)
     const size_t o_k = 0;
-    const size_t o_base = o_k + sizeof(uint32_t) * (size_t)max_layers * kMaxTopk;
+    const size_t o_many = o_k + sizeof(uint32_t) * (size_t)max_layers * kMaxTopk;
+    const size_t many_words = max_cands > kMaxTopk ? (size_t)max_layers * max_cands + max_cands : 0;    // columns, k
+    const size_t o_base = o_many + (sizeof(uint32_t) * many_words + 15) / 16 * 16;
     const size_t o_range = o_base + (sizeof(int64_t) * (size_t)max_layers + 15) / 16 * 16;
     const size_t o_work = o_range + (sizeof(int2) * (size_t)max_layers + 15) / 16 * 16;
     t->ctl_bytes = o_work + sizeof(RefWork) * (size_t)t->max_work;
     t->ctl_off[0] = o_k; t->ctl_off[1] = o_base; t->ctl_off[2] = o_range; t->ctl_off[3] = o_work;
+    t->ctl_off[4] = o_many;
     TK_CHECK(hipHostMalloc(&t->h_ctl, t->ctl_bytes, hipHostMallocDefault));
     TK_CHECK(hipEventCreateWithFlags(&t->ctl_copied, hipEventDisableTiming));
     std::memset(t->h_ctl, 0, t->ctl_bytes);
@@ -1399,6 +1675,7 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
         t->ctl_last_bytes[i] = 0;
     }
     t->h_k = reinterpret_cast<uint32_t*>(t->h_ctl + o_k);
+    t->h_many = reinterpret_cast<uint32_t*>(t->h_ctl + o_many);
     t->h_cand_base = reinterpret_cast<int64_t*>(t->h_ctl + o_base);
     t->h_work_range = t->h_ctl + o_range;
     t->h_work = t->h_ctl + o_work;
@@ -1421,6 +1698,9 @@ void topk_scratch_destroy(TopkScratch* t) {
     (void)hipFree(t->d_base_part);
     (void)hipFree(t->d_below_part);
     (void)hipFree(t->d_ref);
+    (void)hipFree(t->d_many);
+    (void)hipFree(t->d_cell_many);
+    (void)hipFree(t->d_below_many);
     for (int i = 0; i < 2; ++i) {
         (void)hipFree(t->d_ctl[i]);
         std::free(t->h_ctl_last[i]);
@@ -1448,6 +1728,7 @@ static hipError_t upload_ctl(TopkScratch* t, int slot, hipStream_t s) {
     t->d_cand_base = reinterpret_cast<int64_t*>(d + t->ctl_off[1]);
     t->d_work_range = d + t->ctl_off[2];
     t->d_work = d + t->ctl_off[3];
+    t->d_many_in = reinterpret_cast<uint32_t*>(d + t->ctl_off[4]);
     const size_t used = t->ctl_off[3] + sizeof(RefWork) * (size_t)std::max(t->n_work, 1);
     const bool differs = used != t->ctl_last_bytes[slot] || std::memcmp(t->h_ctl, t->h_ctl_last[slot], used) != 0;
     if (differs) {
@@ -1461,20 +1742,30 @@ static hipError_t upload_ctl(TopkScratch* t, int slot, hipStream_t s) {
     return hipSuccess;
 }
 
-// A further group of requested k for the data that was just collected (more candidates than one
-// pass resolves): only the k table changes.  The group must not ask for more entries than the
-// first one did, so every threshold lies at or above the collection bound.
-hipError_t topk_regroup(TopkScratch* t, int L, const uint32_t* ks, int slot, hipStream_t s) {
-    TK_CHECK(ctl_writable(t));
-    for (size_t i = 0; i < (size_t)L * kMaxTopk; ++i) t->h_k[i] = ks[i];
-    return upload_ctl(t, slot, s);
+// What only calls with more than kMaxTopk densities need, allocated by the first one and grown by
+// one that needs more: the layers' records and the work items' partial histograms (8 KB per item and density at
+// most, touched only for the lists there are).
+static hipError_t many_reserve(TopkScratch* t, int n_work, int nk) {
+    if (!t->d_many) TK_CHECK(hipMalloc(&t->d_many, sizeof(TopkMany) * (size_t)t->max_layers));
+    const size_t n = (size_t)std::max(n_work, 1) * nk;
+    if (n > t->many_lists) {
+        (void)hipFree(t->d_cell_many);
+        (void)hipFree(t->d_below_many);
+        t->d_cell_many = nullptr;
+        t->d_below_many = nullptr;
+        t->many_lists = 0;
+        TK_CHECK(hipMalloc(&t->d_cell_many, sizeof(unsigned long long) * kBinsA * n));
+        TK_CHECK(hipMalloc(&t->d_below_many, sizeof(double) * n));
+        t->many_lists = n;
+    }
+    return hipSuccess;
 }
 
 // Upload the requested k per (layer, candidate) (0 = layer inactive) and predict the collection bound
 // of every layer from a sample.
 hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevLayer* d_layers,
                       const DevLayer* h_layers, const Tile* d_tiles, int L, int n_tiles, int tile_elems,
-                      const uint32_t* ks, int ntk, int slot, Timing* tm, hipStream_t s) {
+                      const uint32_t* ks, int ntk, int slot, Timing* tm, hipStream_t s, const TopkRange* range) {
     (void)n_tiles;
     (void)d_tiles;
     // Tiles per work item of the refinement kernels: 2^19 elements, fewer when that would
@@ -1486,9 +1777,21 @@ hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevL
         int64_t active = 0;
         for (int l = 0; l < L; ++l)
             if (ks[(size_t)l * kMaxTopk]) active += h_layers[l].tile_end - h_layers[l].tile_begin;
-        group = (int)std::max<int64_t>(1, std::min<int64_t>(group, active / kRefSlots));
+        // (more than kMaxTopk densities: kManySplit workgroups share an item's lists)
+        group = (int)std::max<int64_t>(1, std::min<int64_t>(group, active * (range ? kManySplit : 1) / kRefSlots));
     }
     TK_CHECK(ctl_writable(t));
+    t->nk_many = 0;
+    if (range) {
+        const size_t nk = range->cols.size();
+        for (size_t j = 0; j < nk; ++j) t->h_many[j] = (uint32_t)range->cols[j];
+        std::memcpy(t->h_many + nk, range->ks.data(), sizeof(uint32_t) * range->ks.size());
+        for (int l = 0; l < L; ++l)
+            for (size_t j = 1; j < nk; ++j)
+                if (range->ks[l * nk + j] == 0 || range->ks[l * nk + j] > range->ks[l * nk + j - 1])
+                    return hipErrorInvalidValue;
+        t->nk_many = (int)nk;
+    }
     int64_t base = 0;
     RefWork* const work = (RefWork*)t->h_work;
     int2* const wrange = (int2*)t->h_work_range;
@@ -1516,6 +1819,7 @@ hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevL
     t->n_work = nw;
     t->max_items = max_items;
     t->cand_has_idx = false;
+    if (range) TK_CHECK(many_reserve(t, nw, t->nk_many));
     TK_CHECK(upload_ctl(t, slot, s));
     Section sec(tm, "topk_sample");
     // (the previous call's last scan left the exact histogram cleared)
@@ -1569,9 +1873,8 @@ hipError_t topk_collect(TopkScratch* t, const float* g, const float* e, float* e
 }
 
 // exact threshold bins; layers whose predicted bound was too high are collected again
-hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers,
-                       const Tile* d_tiles, int L, int n_tiles, int ntk, bool last_group, Timing* tm,
-                       hipStream_t s, const QuantReduce* quant) {
+hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers, int L,
+                       int ntk, Timing* tm, hipStream_t s, const QuantReduce* quant) {
     {
         Section sec(tm, "topk_scan");
         ScanReduce red{};
@@ -1583,11 +1886,15 @@ hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef
             red.cols.n = std::min(quant->ncols, (int)kMaxQuant);
             for (int i = 0; i < red.cols.n; ++i) red.cols.col[i] = quant->cols[i];
         }
-        hipLaunchKernelGGL(topk_scan_kernel, dim3(quant ? 2 * L : L), dim3(256), 0, s, t->d_hist,
-                           (const uint32_t*)t->d_k, ntk, (const int64_t*)t->d_cand_base, t->d_lo, (TopkLayer*)t->d_tl,
-                           last_group ? 1 : 0, L, red);
+        if (t->nk_many)
+            hipLaunchKernelGGL(topk_scan_many_kernel, dim3(quant ? 2 * L : L), dim3(256), 0, s, t->d_hist,
+                               (const uint32_t*)t->d_many_in + t->nk_many, t->nk_many, t->d_lo, (TopkMany*)t->d_many, L, red);
+        else
+            hipLaunchKernelGGL(topk_scan_kernel, dim3(quant ? 2 * L : L), dim3(256), 0, s, t->d_hist,
+                               (const uint32_t*)t->d_k, ntk, (const int64_t*)t->d_cand_base, t->d_lo, (TopkLayer*)t->d_tl,
+                               L, red);
         TK_CHECK(hipGetLastError());
-        if (last_group) t->hist_clean = true;
+        t->hist_clean = true;
     }
     // Layers whose predicted bound was too high (flagged by the scan; none in the usual call) are
     // collected a second time with the exact bound, by the first refinement kernel's workgroups,
@@ -1596,7 +1903,6 @@ hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef
     t->rc_g = ef_out ? ef_out : g;
     t->rc_e = ef_out ? nullptr : e;
     t->rc_ef_out = ef_out;
-    (void)n_tiles;
     return hipSuccess;
 }
 
@@ -1629,6 +1935,27 @@ hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d
     p.rc.ef_out = t->rc_ef_out;
     p.rc.record_idx = (!t->rc_ef_out && t->cand_has_idx) ? 1 : 0;
     Section sec(tm, "topk_refine");
+    if (t->nk_many) {
+        p.many = (const TopkMany*)t->d_many;
+        p.cand_base = t->d_cand_base;
+        p.nk = t->nk_many;
+        p.cols = (const int32_t*)t->d_many_in;
+        p.cell_many = t->d_cell_many;
+        p.below_many = t->d_below_many;
+        static bool configured_many = false;
+        const size_t lds = refine_a_lds(kManyChunk, true);
+        if (!configured_many) {
+            TK_CHECK(hipFuncSetAttribute((const void*)topk_refine_many_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         (int)lds));
+            configured_many = true;
+        }
+        hipLaunchKernelGGL(topk_recollect_many_kernel, dim3(t->n_work), dim3(kRefThreads), 0, s, p);
+        TK_CHECK(hipGetLastError());
+        hipLaunchKernelGGL(topk_refine_many_kernel, dim3(t->n_work, kManySplit), dim3(kRefThreads), lds, s, p);
+        TK_CHECK(hipGetLastError());
+        hipLaunchKernelGGL(topk_pick_many_kernel, dim3(L, kManySlots), dim3(256), 0, s, p);
+        return hipGetLastError();
+    }
     if (d_errors) {       // profile: level A gives the dropped energy, no exact threshold is needed
         const size_t lds = refine_a_lds(ntk, true);
         static bool configured[kMaxTopk + 1] = {};   // the dynamic LDS limit is raised once per variant
@@ -1671,12 +1998,12 @@ hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLaye
     for (int l = 0; l < L; ++l)
         if (h_layers[l].family == LGRECO_TOPK) ks[(size_t)l * kMaxTopk] = (uint32_t)h_layers[l].iparam;
     const float* const e_in = x_in_e ? nullptr : e;
-    TK_CHECK(topk_begin(t, g, e_in, d_layers, h_layers, d_tiles, L, n_tiles, tile_elems, ks.data(), 1, 1, tm, s));
+    TK_CHECK(topk_begin(t, g, e_in, d_layers, h_layers, d_tiles, L, n_tiles, tile_elems, ks.data(), 1, 1, tm, s, nullptr));
     {
         Section sec(tm, "topk_collect", true);
         TK_CHECK(topk_collect(t, g, e_in, e, d_layers, d_tiles, n_tiles, s, &sec));
     }
-    TK_CHECK(topk_select(t, g, e_in, e, d_layers, d_tiles, L, n_tiles, 1, true, tm, s, nullptr));
+    TK_CHECK(topk_select(t, g, e_in, e, d_layers, L, 1, tm, s, nullptr));
     TK_CHECK(topk_finalize(t, d_layers, d_tiles, L, 1, nullptr, nullptr, 0, tm, s));
     {
         Section sec(tm, "topk_count");

@@ -351,3 +351,26 @@ def test_bound_predicted_too_high_or_too_low(n):
     a = np.where(sampled, big, small).astype(np.float32)
     b = np.where(sampled, small, big).astype(np.float32)
     _check(_flat_batch([a, b]), (0.001, 0.01, 0.1, 0.5))
+
+
+@pytest.mark.parametrize("count", [9, 64, 65, 128])
+def test_more_densities_than_one_column_each(count):
+    """Past 8 densities the profile resolves them per distinct threshold bin, in chunks of 8: from one bin for
+    all (constant, zero) to one for each (values over 40 octaves), one entry to several work items,
+    duplicates of a density, ties that need the exact route for several densities of one sub-bin, and a layer
+    whose sample misses its large entries."""
+    rng = np.random.default_rng(count)
+    n = 300000
+    seg = np.arange(512, dtype=np.uint64)
+    first = seg * (n // 512) + (((seg * 2654435761) % (1 << 32)) * (n // 512 - 31) >> np.uint64(32))
+    seen = (first[:, None] + np.arange(32, dtype=np.uint64)).reshape(-1).astype(np.int64)
+    fooled = rng.laplace(0, 1e-3, n).astype(np.float32)
+    fooled[seen] = rng.laplace(0, 1.0, seen.size)
+    ties = rng.integers(-3, 4, 30000).astype(np.float32)
+    near = np.where(rng.random(50000) < 0.3, np.float32(1.0) + np.float32(2.0 ** -23) * rng.integers(0, 400, 50000),
+                    rng.laplace(0, 1e-2, 50000)).astype(np.float32)
+    wide = (2.0 ** rng.uniform(-20, 20, 20000)).astype(np.float32)
+    arrays = [fooled, ties, near, wide, np.full(9000, -0.75, np.float32), np.zeros(5000, np.float32),
+              rng.laplace(0, 1e-3, (1 << 20) + 77).astype(np.float32), np.float32([0.5]), np.float32([1, -2, 3])]
+    densities = np.linspace(0.002, 0.4, count - 1).tolist() + [0.002]
+    _check(_flat_batch(arrays), rng.permutation(densities))
