@@ -36,7 +36,7 @@ constexpr int kMaxLayersS = kSolveMaxLayers;
 constexpr int kMaxT = kSolveMaxEntries;
 constexpr uint32_t kUnusable = 0xFFFFu;      // bin of a candidate whose error exceeds the budget (bins are at most 16384)
 constexpr uint32_t kInfS = 1u << 30;
-constexpr int kRowCells = 4096;              // widest interval swept with two row buffers in LDS
+constexpr int kRowCells = 4096;              // past this many bins intervals are worked out in any case
 constexpr size_t kRegionBytes = (size_t)kSolveMaxLP * 6;      // LDS: the table's bins and sizes, later see Relax and Core
 
 // ---- wavefront scans and reductions on DPP (no LDS round trips)
@@ -144,6 +144,7 @@ struct alignas(16) Lds {
     uint32_t ub;
     int32_t flags;                           // 1: a layer without usable candidate, 2: invalid input, 4 and up: inconsistent
     uint32_t acc[4];
+    uint32_t facts[4];                       // of the core layers: furthest shift down and up, longest list, sum of their largest sizes
 };
 // what the region holds while the intervals are worked out ...
 struct Relax {
@@ -158,10 +159,10 @@ struct Relax {
 // ... and, in front of the rows, during the sweep: one record per core layer, and its survivors in
 // candidate order, in groups of four (filled up with entries that never win)
 struct Core {
-    int32_t step;                            // bytes from the first cell of the row before to this row's first cell
-    int32_t behind;                          // bytes of the row before
+    int32_t step;                            // cells from the first cell of the row before to this row's first cell
+    int32_t lo;                              // the row's first cell
     uint32_t shape;                          // cells of this row | survivors << 16
-    int32_t trace;                           // place of cell 0's arg-min byte
+    int32_t trace;                           // place of the row's first arg-min byte
 };
 
 // number of bits of s.keep set in front of position t
@@ -193,138 +194,205 @@ __device__ __forceinline__ double relaxed_value(const Lds& s, const Relax& r, in
 }
 
 // Sweep of the core layers.  Row j covers the cells [lo, hi] of core layer j (bins summed over the core
-// layers so far), with a cell of infinity on either side of it, which every shifted read outside the
-// row is sent to.  The first NT threads take KMAX cells each, NT apart; the other wavefronts only join
-// the barriers.  What bounds it is the number of instructions a wavefront issues per layer: about 50
-// and 7 per cell and entry, at 7 cycles each when it has a SIMD to itself and 4 each in turn when it
-// shares one, with two LDS round trips and a barrier beside them.  So rows of up to 1023 cells go to
-// 256 or 512 threads (512 x 2 cells took 0.4 us a layer, 256 x 4 0.58, 1024 x 1 0.66), addresses come ready
-// made from the records, no store is masked (cells behind the row take infinity, their arg-min
-// bytes are overwritten by the next row's or lie in the slack behind the last) and nothing but the row
-// is waited for: records are fetched two layers ahead, survivors one.  TWO: two row buffers and
-// one barrier per layer, else one buffer and two barriers.  Arg-mins (position among the survivors) go
-// to pd, one byte per cell, rows back to back.
+// layers so far).  The first NT threads take KMAX cells each, NT apart; the other wavefronts only join
+// the barriers.  What bounds it is the number of instructions issued per layer: 7 cycles each for a
+// wavefront that has a SIMD to itself, 4 each in turn for wavefronts that share one, with two LDS round
+// trips and a barrier beside them.  So:
+//   * a row lies between cells of infinity as wide as any entry's shift reaches, and an entry's address
+//     is worked out once for all cells of a thread (with every shifted read clamped into the row, a compare
+//     and two selects per entry and a byte stored per cell, 10000 cells took 4.2 us a layer; now 1.2);
+//   * PACK: the position among the survivors rides in the low `bits` bits of the costs (the caller has
+//     checked that they stay below 2^30), so a minimum of two entries is one instruction;
+//   * rows of up to 1024 cells go to 256 or 512 threads (512 x 2 cells: 0.26 us a layer of 4 entries; 256 x 4
+//     0.28, 1024 x 1 0.29), wider ones to all 1024, where 4 wavefronts share a SIMD;
+//   * nothing but the row is waited for: records and survivors are fetched ahead.
+// TWO: two row buffers and one barrier per layer, else one buffer and two barriers.
+// Arg-mins (position among the survivors): bytes, rows back to back; WORDS: a 32-bit word per layer and
+// thread, `bits` bits per cell.
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 __device__ __forceinline__ uint32_t lds_address(const uint32_t* p) { return (uint32_t)(size_t)(const lds_u32*)p; }
 __device__ __forceinline__ uint32_t lds_load(uint32_t byte) { return *(const lds_u32*)(size_t)byte; }
-__device__ __forceinline__ int clamp_i32(int v, int lo, int hi) {
-    int r;
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "s"(lo), "v"(hi));
-    return r;
+__device__ __forceinline__ uint32_t lds_byte(uint32_t byte) {
+    return *(const __attribute__((address_space(3))) uint8_t*)(size_t)byte;
 }
-template <int NT, int KMAX, bool TWO, bool LDS_PD>
-__device__ __forceinline__ const uint32_t* sweep(const Core* core, const uint2* ent, uint32_t* rows, const int n_core,
-                                                 uint8_t* const pd) {
-    const int tid = threadIdx.x, lane = tid & 63;
-    constexpr int kStride = NT * KMAX + 2;
-    constexpr int kGroup = KMAX == 1 ? 4 : KMAX <= 4 ? 2 : 1;      // entries whose reads are in flight together
-    if (tid >= NT) {                                     // (whole wavefronts)
+__device__ __forceinline__ void lds_store(uint32_t byte, uint32_t v) { *(lds_u32*)(size_t)byte = v; }
+__device__ __forceinline__ void lds_store_byte(uint32_t byte, uint32_t v) {
+    *(__attribute__((address_space(3))) uint8_t*)(size_t)byte = (uint8_t)v;
+}
+constexpr uint32_t kInfPacked = 1u << 30;
+struct Sweep {
+    const Core* core;
+    const uint2* ent;
+    uint32_t* buffer;                        // front cells of infinity, the row, infinity up to `cells` (twice)
+    uint8_t* pd;
+    int front, cells, n_core, bits;
+};
+template <int NT, int KMAX, bool TWO, bool PACK, bool WORDS, bool LDS_PD>
+__device__ __forceinline__ const uint32_t* sweep(const Sweep& p) {
+    static_assert(!WORDS || (PACK && !LDS_PD), "words go to device memory");
+    constexpr uint32_t kInf = PACK ? kInfPacked : kInfS;
+    const int tid = threadIdx.x, n_core = p.n_core, bits = p.bits;
+    const uint32_t places = (1u << bits) - 1u;
+    for (int i = tid; i < (TWO ? 2 : 1) * p.cells; i += kThreadsS)
+        p.buffer[i] = i == p.front ? 0u : kInf;          // the row in front of the first layer is the single cell 0
+    uint32_t* const row0 = p.buffer + p.front;
+    uint32_t* const row1 = TWO ? row0 + p.cells : row0;
+    if (NT < kThreadsS && tid >= NT) {                   // (whole wavefronts)
         __syncthreads();
         for (int j = 0; j < n_core; ++j) {
             if (!TWO) __syncthreads();
             __syncthreads();
         }
-        return rows + 1 + (TWO && (n_core & 1) ? kStride : 0);
+        return n_core & 1 ? row1 : row0;
     }
-    uint32_t* cur = rows + 1;
-    uint32_t* nxt = TWO ? cur + kStride : cur;
-    // the row in front of the first layer is the single cell 0
-    if (tid == 0) { cur[-1] = kInfS; cur[0] = 0; cur[1] = kInfS; nxt[-1] = kInfS; }
-    const Core* rec = core;
-    const Core* const rec_end = core + (n_core - 1);
-    auto fetch = [&]() __attribute__((always_inline)) {
-        const Core c = *rec;
-        rec = rec < rec_end ? rec + 1 : rec;
-        return c;
-    };
-    Core c1 = fetch(), c2 = fetch();
-    const uint2* mine = ent + lane;                      // (lanes behind the list read what follows it)
-    uint2 e1 = *mine;
-    uint8_t* out = pd + tid;
+    uint32_t cur = lds_address(row0) + 4u * (uint32_t)tid, nxt = lds_address(row1) + 4u * (uint32_t)tid;
+    const uint32_t* shape_at = &p.core[0].shape;
+    uint32_t shape1 = *shape_at;
+    const uint4* list = reinterpret_cast<const uint4*>(p.ent);       // two entries each
+    uint4 e1 = list[0], f1 = list[1];
+    uint8_t* out = p.pd + (WORDS ? 4 : 1) * tid;
+    uint32_t out_lds = LDS_PD ? lds_address(reinterpret_cast<const uint32_t*>(p.pd)) + (uint32_t)tid : 0u;
     __syncthreads();
     for (int j = 0; j < n_core; ++j) {
-        const Core c0 = c1;
-        const uint2 e0 = e1;
-        c1 = c2;
-        const uint32_t shape = (uint32_t)__builtin_amdgcn_readfirstlane((int)c0.shape);
+        const uint32_t shape = (uint32_t)__builtin_amdgcn_readfirstlane((int)shape1);
         const int nw = (int)(shape & 0xFFFFu), n = (int)(shape >> 16);
-        uint32_t nv[KMAX];
-        uint32_t na[KMAX];
+        const uint4 e0 = e1, f0 = f1;
+        uint32_t nv[KMAX], na[KMAX];
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) { nv[k] = kInf; na[k] = 255u; }
+        // two entries at a time (a list is filled up with entries that never win)
+        auto relax = [&](const uint4 e, int c) __attribute__((always_inline)) {
+            const uint32_t x[2] = {e.x, e.z}, z[2] = {e.y, e.w};
+            uint32_t t[2][KMAX];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t f = cur + x[u];
+#pragma unroll
+                for (int k = 0; k < KMAX; ++k) t[u][k] = lds_load(f + 4 * k * NT);
+            }
+#pragma unroll
+            for (int k = 0; k < KMAX; ++k) {
+                if (PACK) {
+                    nv[k] = min(nv[k], min(t[0][k] + z[0], t[1][k] + z[1]));
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const uint32_t v = t[u][k] + z[u];
+                        const bool lt = v < nv[k];
+                        nv[k] = lt ? v : nv[k];
+                        na[k] = lt ? (uint32_t)(c + u) : na[k];
+                    }
+                }
+            }
+        };
+        relax(e0, 0);
+        if (n > 2) relax(f0, 2);
+        for (int c = 4; c < n; c += 2) relax(list[c >> 1], c);
+        list += ((n + 3) & ~3) >> 1;
+        shape_at += sizeof(Core) / sizeof(uint32_t);     // (past the last record: the first entries)
+        shape1 = *shape_at;
+        e1 = list[0];
+        f1 = list[1];
+        if (!TWO) __syncthreads();
+        uint32_t word = 0;
+        // Cells behind the row (sums of bins above the interval) are not stopped from taking part: what they
+        // hold are totals of assignments all the same, and none of the smallest size has such a sum.
+#pragma unroll
+        for (int k = 0; k < KMAX; ++k) {
+            lds_store(nxt + 4 * k * NT, PACK ? nv[k] & ~places : nv[k]);
+            const uint32_t place = PACK ? nv[k] : na[k];  // (bytes: the reader takes the low bits)
+            if (WORDS) word |= (place & places) << (bits * k);
+            else if (LDS_PD) lds_store_byte(out_lds + k * NT, place);      // (behind the row: overwritten by the next one's, or slack)
+            else if (tid + k * NT < nw) out[k * NT] = (uint8_t)place;
+        }
+        if (WORDS) *reinterpret_cast<uint32_t*>(out) = word;
+        __syncthreads();
+        if (TWO) { const uint32_t x = cur; cur = nxt; nxt = x; }
+        out += WORDS ? 4 * NT : nw;
+        out_lds += (uint32_t)nw;
+    }
+    return n_core & 1 ? row1 : row0;
+}
+
+// The last resort where a row's margins do not fit LDS: every shifted read is clamped into the row, which
+// has a cell of infinity on either side.
+__device__ __forceinline__ int clamp_i32(int v, int lo, int hi) {
+    int r;
+    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "s"(lo), "v"(hi));
+    return r;
+}
+constexpr int kClampCells = 17;              // per thread: rows of up to 17407 cells
+__device__ __forceinline__ const uint32_t* sweep_clamped(const Sweep& p) {
+    constexpr int NT = kThreadsS, KMAX = kClampCells;
+    const int tid = threadIdx.x;
+    uint32_t* const cur = p.buffer + 1;
+    if (tid == 0) { cur[-1] = kInfS; cur[0] = 0; cur[1] = kInfS; }
+    const uint2* e = p.ent;
+    uint8_t* out = p.pd + tid;
+    __syncthreads();
+    for (int j = 0; j < p.n_core; ++j) {
+        const Core c0 = p.core[j];
+        const int nw = (int)(c0.shape & 0xFFFFu), n = __builtin_amdgcn_readfirstlane((int)(c0.shape >> 16));
+        const int before = __builtin_amdgcn_readfirstlane(j ? (int)(p.core[j - 1].shape & 0xFFFFu) : 1);
+        uint32_t nv[KMAX], na[KMAX];
 #pragma unroll
         for (int k = 0; k < KMAX; ++k) { nv[k] = kInfS; na[k] = 255u; }
         const uint32_t row_at = lds_address(cur);
-        const int from = (int)row_at + 4 * tid + c0.step, below = (int)row_at - 4, behind = (int)row_at + c0.behind;
-        auto relax = [&](const uint32_t (&x)[kGroup], const uint32_t (&z)[kGroup], int c) __attribute__((always_inline)) {
-            uint32_t t[kGroup][KMAX];
+        const int from = (int)row_at + 4 * tid, below = __builtin_amdgcn_readfirstlane((int)row_at - 4);
+        const int behind = (int)row_at + 4 * before;
+        for (int c = 0; c < n; ++c) {
+            const uint2 x = e[c];
+            const uint32_t z = x.y == kInfPacked ? kInfS : x.y >> p.bits;
+            const int f = from + (int)x.x;
 #pragma unroll
-            for (int u = 0; u < kGroup; ++u) {
-                const int f = from - (int)(x[u] & 0xFFFFFFu);
-#pragma unroll
-                for (int k = 0; k < KMAX; ++k) t[u][k] = lds_load((uint32_t)clamp_i32(f + 4 * k * NT, below, behind));
+            for (int k = 0; k < KMAX; ++k) {
+                const uint32_t v = lds_load((uint32_t)clamp_i32(f + 4 * k * NT, below, behind)) + z;
+                const bool lt = v < nv[k];
+                nv[k] = lt ? v : nv[k];
+                na[k] = lt ? (uint32_t)c : na[k];
             }
-#pragma unroll
-            for (int u = 0; u < kGroup; ++u)
-#pragma unroll
-                for (int k = 0; k < KMAX; ++k) {
-                    const uint32_t v = t[u][k] + z[u];
-                    const bool lt = v < nv[k];
-                    nv[k] = lt ? v : nv[k];
-                    na[k] = lt ? (uint32_t)(c + u) : na[k];
-                }
-        };
-        const int n4 = (n + 3) & ~3;
-        mine += n4;
-        for (int c = 0; c < min(n, 64); c += kGroup) {
-            uint32_t x[kGroup], z[kGroup];
-#pragma unroll
-            for (int u = 0; u < kGroup; ++u) {
-                x[u] = lane_u32(e0.x, c + u);
-                z[u] = lane_u32(e0.y, c + u);
-            }
-            relax(x, z, c);
         }
-        for (int c = 64; c < n; c += kGroup) {            // rare: more than 64 survivors
-            uint32_t x[kGroup], z[kGroup];
-#pragma unroll
-            for (int u = 0; u < kGroup; ++u) {
-                const uint2 e = mine[c + u - n4 - lane];
-                x[u] = (uint32_t)__builtin_amdgcn_readfirstlane((int)e.x);
-                z[u] = (uint32_t)__builtin_amdgcn_readfirstlane((int)e.y);
-            }
-            relax(x, z, c);
-        }
-        c2 = fetch();
-        e1 = *mine;
-        if (!TWO) __syncthreads();
+        e += (n + 3) & ~3;
+        __syncthreads();
 #pragma unroll
         for (int k = 0; k < KMAX; ++k) {
             const int t = tid + k * NT;
-            const uint32_t v = t < nw ? nv[k] : kInfS;
-            if (TWO || t <= nw) nxt[t] = v;
-            if (LDS_PD ? (TWO || t <= nw) : t < nw) out[k * NT] = (uint8_t)na[k];
+            if (t <= nw) cur[t] = t < nw ? nv[k] : kInfS;
+            if (t < nw) out[k * NT] = (uint8_t)na[k];
         }
         __syncthreads();
-        if (TWO) { uint32_t* const x = cur; cur = nxt; nxt = x; }
         out += nw;
     }
     return cur;
 }
 
-// The same with the shape chosen by the widest row: cells a thread, threads (a row keeps one cell free
-// for the infinity behind it).
-__device__ __forceinline__ int sweep_shape(int w_max) {
-    return w_max < 256 ? 0 : w_max < 512 ? 1 : w_max < 1024 ? 2 : w_max < kRowCells ? 3 : 4;
+// Threads and cells a thread for rows of up to w_max cells.
+struct SweepShape {
+    int threads, per;
+    bool two;
+};
+__device__ __forceinline__ SweepShape sweep_shape(int w_max) {
+    if (w_max <= 1024) return w_max <= 256 ? SweepShape{256, 1, true} : SweepShape{512, w_max <= 512 ? 1 : 2, true};
+    const int k = (w_max + kThreadsS - 1) / kThreadsS;
+    return SweepShape{kThreadsS, k <= 2 ? 2 : k <= 4 ? 4 : k <= 6 ? 6 : k <= 8 ? 8 : k <= 10 ? 10 : k <= 13 ? 13 : 17, false};
 }
-__device__ __forceinline__ int sweep_cells(int shape) { return shape == 4 ? 17 * kThreadsS : shape == 3 ? kRowCells : 256 << shape; }
-template <bool LDS_PD>
-__device__ __forceinline__ const uint32_t* sweep_shaped(int shape, const Core* core, const uint2* ent, uint32_t* rows,
-                                                        const int n_core, uint8_t* const pd) {
-    switch (shape) {
-        case 0: return sweep<256, 1, true, LDS_PD>(core, ent, rows, n_core, pd);
-        case 1: return sweep<512, 1, true, LDS_PD>(core, ent, rows, n_core, pd);
-        case 2: return sweep<512, 2, true, LDS_PD>(core, ent, rows, n_core, pd);
-        case 3: return sweep<1024, 4, true, LDS_PD>(core, ent, rows, n_core, pd);
-        default: return sweep<1024, 17, false, LDS_PD>(core, ent, rows, n_core, pd);
+template <bool PACK, bool WORDS, bool LDS_PD>
+__device__ __forceinline__ const uint32_t* sweep_shaped(SweepShape f, const Sweep& p) {
+    if constexpr (!WORDS) {
+        if (f.threads == 256) return sweep<256, 1, true, PACK, WORDS, LDS_PD>(p);
+        if (f.threads == 512) {
+            if (f.per == 1) return sweep<512, 1, true, PACK, WORDS, LDS_PD>(p);
+            return sweep<512, 2, true, PACK, WORDS, LDS_PD>(p);
+        }
+    }
+    switch (f.per) {
+        case 2: return sweep<1024, 2, false, PACK, WORDS, LDS_PD>(p);
+        case 4: return sweep<1024, 4, false, PACK, WORDS, LDS_PD>(p);
+        case 6: return sweep<1024, 6, false, PACK, WORDS, LDS_PD>(p);
+        case 8: return sweep<1024, 8, false, PACK, WORDS, LDS_PD>(p);
+        case 10: return sweep<1024, 10, false, PACK, WORDS, LDS_PD>(p);
+        case 13: return sweep<1024, 13, false, PACK, WORDS, LDS_PD>(p);
+        default: return sweep<1024, 17, false, PACK, WORDS, LDS_PD>(p);
     }
 }
 
@@ -351,7 +419,7 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
         s.best = ~0ull;
         s.ub = kInfS;
     }
-    if (tid < 4) s.acc[tid] = 0;
+    if (tid < 4) s.acc[tid] = s.facts[tid] = 0;
     bool bad = false;
     unsigned long long chk = 0;
     int64_t sz[NE];
@@ -923,29 +991,38 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
             const uint32_t cell0 = block_scan(w, s.tmp, &cells);
             const int n_core = (int)(both_c >> 20);
             {
-                const uint32_t wm = wave_max_u32(w);
-                if (lane == 0) atomicMax(&s.acc[3], wm);
+                const uint32_t wm = wave_max_u32(w), lm = wave_max_u32(core ? (uint32_t)left : 0u);
+                const uint32_t top = wave_total(core ? s.size[e1 - 1] : 0u);       // (a list's last entry is its largest)
+                if (lane == 0 && wm) {
+                    atomicMax(&s.acc[3], wm);
+                    atomicMax(&s.facts[2], lm);
+                    atomicAdd(&s.facts[3], top);
+                }
                 if (core && my_hi < my_lo) atomicOr(&s.flags, 8);
             }
             Core* const rec = reinterpret_cast<Core*>(region);
             uint2* const ent = reinterpret_cast<uint2*>(region + sizeof(Core) * (size_t)max(n_core, 1));
-            if (on) s.first[tid] = core ? (int32_t)ce : -1;
+            uint8_t* const ent_cand = reinterpret_cast<uint8_t*>(ent + ents + 64);
+            if (on) s.first[tid] = core ? (int32_t)(ce | (j << 16)) : -1;      // (under 2^13 survivors, padding included)
             if (core) {
                 s.lo[j] = tid;                            // core layer -> swept layer (every interval has been read)
                 s.hi[j] = (int32_t)ce;                    // ... and its first survivor
-                rec[j] = Core{my_lo, (int32_t)w, w | ((uint32_t)left << 16), (int32_t)cell0 - my_lo};
+                rec[j] = Core{0, my_lo, w | ((uint32_t)left << 16), (int32_t)cell0};
             }
             __syncthreads();
-            // (steps and widths refer to the row in front)
-            int step = 0, behind = 0;
+            // positions ride in the costs' low bits where they fit
+            int bits = 32 - __builtin_clz(max(s.facts[2], 2u) - 1);
+            if (((unsigned long long)s.facts[3] << bits) >= kInfPacked) bits = 0;
+            uint32_t down = 0, up = 0;                    // how far shifts reach
             if (tid < n_core) {
-                step = 4 * (rec[tid].step - (tid ? rec[tid - 1].step : 0));
-                behind = 4 * (tid ? rec[tid - 1].behind : 1);
                 const Core c = rec[tid];
-                for (int u = (int)(c.shape >> 16); u & 3; ++u) ent[s.hi[tid] + u] = make_uint2(0u, kInfS);
+                const int step = c.lo - (tid ? rec[tid - 1].lo : 0);
+                rec[tid].step = step;
+                // entries that never win fill the lists up
+                for (int u = (int)(c.shape >> 16); u & 3; ++u) ent[s.hi[tid] + u] = make_uint2(0u, kInfPacked);
                 if (tid == n_core - 1) {
-                    s.acc[0] = (uint32_t)c.step;                     // the last row's first cell and width
-                    s.acc[1] = (uint32_t)c.behind;
+                    s.acc[0] = (uint32_t)c.lo;            // the last row's first cell and width
+                    s.acc[1] = c.shape & 0xFFFFu;
                 }
             }
 #pragma unroll
@@ -962,22 +1039,48 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
                             for (int k = s.off[i]; k < s.off[i + 1]; ++k)
                                 rank += ((s.keep[k >> 6] >> (k & 63)) & 1) && s.cand[k] < cd ? 1u : 0u;
                         }
-                        // (four times the bin: a byte distance in the row; the candidate in the top byte)
-                        ent[s.first[i] + (int)rank] = make_uint2(((uint32_t)s.bin[t] << 2) | ((uint32_t)s.cand[t] << 24), s.size[t]);
+                        const int q0 = s.first[i] >> 16;
+                        const Core c = rec[q0];
+                        const int lo_front = q0 ? rec[q0 - 1].lo : 0;
+                        const int w_front = q0 ? (int)(rec[q0 - 1].shape & 0xFFFFu) : 1;
+                        // where a cell's row index comes from in the row in front, in bytes
+                        const int d = c.lo - lo_front - (int)s.bin[t], at = (s.first[i] & 0xFFFF) + (int)rank;
+                        uint2 x = make_uint2((uint32_t)(4 * d), (s.size[t] << bits) | (bits ? rank : 0u));
+                        if (d >= w_front || d <= -(int)(c.shape & 0xFFFFu)) {     // leads from no cell of the row in front into this one
+                            x = make_uint2(0u, kInfPacked);
+                        } else {
+                            down = max(down, (uint32_t)max(-d, 0));
+                            up = max(up, (uint32_t)max(d, 0));
+                        }
+                        ent[at] = x;
+                        ent_cand[at] = s.cand[t];
                     }
                 }
             }
-            __syncthreads();
-            if (tid < n_core) {
-                rec[tid].step = step;
-                rec[tid].behind = behind;
+            down = wave_max_u32(down);
+            up = wave_max_u32(up);
+            if (lane == 0 && (down | up)) {
+                atomicMax(&s.facts[0], down);
+                atomicMax(&s.facts[1], up);
             }
+            __syncthreads();
             const int w_max = (int)s.acc[3];
+            const SweepShape form = sweep_shape(w_max);
+            const int row_cells = form.threads * form.per;
             // rows behind the survivors (and the words a wavefront reads past the last list), then the
             // arg-min bytes where they fit
-            const int shape = sweep_shape(w_max), row_cells = sweep_cells(shape);
-            const size_t at_row = sizeof(Core) * (size_t)max(n_core, 1) + sizeof(uint2) * ((size_t)ents + 64);
-            const size_t row_bytes = sizeof(uint32_t) * (size_t)(shape == 4 ? row_cells + 2 : 2 * (row_cells + 2));
+            const size_t at_row = sizeof(Core) * (size_t)max(n_core, 1) + sizeof(uint2) * ((size_t)ents + 64) + ((size_t)ents + 15) / 16 * 16;
+            Sweep sw{rec, ent, reinterpret_cast<uint32_t*>(region + at_row), p.pd, (int)s.facts[0],
+                     (int)(s.facts[0] + s.facts[1]) + row_cells, n_core, 0};
+            size_t row_bytes = sizeof(uint32_t) * (size_t)sw.cells * (form.two ? 2 : 1);
+            const bool clamped = at_row + row_bytes > kRegionBytes;
+            if (clamped) row_bytes = sizeof(uint32_t) * (kClampCells * kThreadsS + 2);
+            const bool pd_lds = !clamped && at_row + row_bytes + cells + (size_t)row_cells <= kRegionBytes;
+            if (pd_lds) sw.pd = region + at_row + row_bytes;
+            sw.bits = bits;
+            // (lists long enough that the positions do not fit the costs or a word are swept with bytes)
+            const bool words = !clamped && !pd_lds && bits && s.facts[2] <= 64 && form.threads == kThreadsS && form.per * bits <= 32 &&
+                               ((size_t)p.pd & 3) == 0 && (size_t)n_core * 4 * kThreadsS <= (size_t)L * (size_t)(p.D + 1);
             if (s.flags & 4) {
                 status = 2;
             } else if ((s.flags & 8) || (int)shift_all > D) {        // a layer no bin sum can reach
@@ -985,23 +1088,26 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
             } else if (at_row + row_bytes > kRegionBytes) {
                 status = 4;
             } else {
-                const bool pd_lds = at_row + row_bytes + cells + (size_t)row_cells <= kRegionBytes;
-                uint32_t* const row = reinterpret_cast<uint32_t*>(region + at_row);
-                uint8_t* const pd_l = region + at_row + row_bytes;
-                const uint32_t* last = row;
+                const uint32_t* last = sw.buffer;
+                const int row_bits = clamped ? 0 : bits;
                 if (n_core == 0) {
-                    if (tid == 0) row[0] = 0;
+                    if (tid == 0) sw.buffer[0] = 0;
                     __syncthreads();
-                } else if (pd_lds) {
-                    last = sweep_shaped<true>(shape, rec, ent, row, n_core, pd_l);
+                } else if (clamped) {
+                    last = sweep_clamped(sw);
+                } else if (words) {
+                    last = sweep_shaped<true, true, false>(form, sw);
+                } else if (bits) {
+                    last = pd_lds ? sweep_shaped<true, false, true>(form, sw) : sweep_shaped<true, false, false>(form, sw);
                 } else {
-                    last = sweep_shaped<false>(shape, rec, ent, row, n_core, p.pd);
+                    last = pd_lds ? sweep_shaped<false, false, true>(form, sw) : sweep_shaped<false, false, false>(form, sw);
                 }
                 // smallest total, lowest cell among equals, inside the budget
                 const int base = n_core ? (int)s.acc[0] : 0, top = n_core ? base + (int)s.acc[1] - 1 : 0;
                 unsigned long long best = ~0ull;
                 for (int e = base + tid; e <= min(top, D - (int)shift_all); e += kThreadsS) {
-                    const unsigned long long x = ((unsigned long long)last[e - base] << 32) | (uint32_t)e;
+                    const uint32_t v = last[e - base];
+                    const unsigned long long x = ((unsigned long long)(v >= kInfS ? kInfS : v >> row_bits) << 32) | (uint32_t)e;
                     best = x < best ? x : best;
                 }
                 if ((tid & ~63) <= top - base) {
@@ -1021,27 +1127,53 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
                     // bins are fetched ahead of it.  A byte that cannot be is caught by the sums below
                     // (LDS reads stay in range by themselves; the walk in device memory is clamped).
                     if (wave == 0 && n_core > 0) {
-                        int e = (int)(uint32_t)b;
-                        Core c1 = rec[n_core - 1], c2 = rec[max(n_core - 2, 0)];
-                        int f2 = s.hi[max(n_core - 2, 0)];
-                        uint32_t b1 = ent[s.hi[n_core - 1] + lane].x;
-                        for (int q = n_core - 1; q >= 0; --q) {
-                            const Core c0 = c1;
-                            const uint32_t b0 = b1;
-                            int a = c0.trace + e;
-                            if (!pd_lds) a = min(max(a, 0), (int)cells - 1);
-                            const int kv = pd_lds ? pd_l[a] : p.pd[a];
-                            c1 = c2;
-                            b1 = ent[f2 + lane].x;
-                            c2 = rec[max(q - 2, 0)];
-                            f2 = s.hi[max(q - 2, 0)];
-                            const int kk = __builtin_amdgcn_readfirstlane(kv);
-                            s.pick[q] = (uint8_t)kk;     // (every lane the same byte)
-                            uint32_t down = lane_u32(b0, kk & 63);
-                            if (kk > 63) down = (uint32_t)__builtin_amdgcn_readfirstlane((int)ent[s.hi[q] + min(kk, 127)].x);
-                            e -= (int)((down & 0xFFFFFFu) >> 2);
+                        // (in places of the rows: the sum of bins less the row's first; in front of the first layer 0)
+                        int t = (int)(uint32_t)b - base;
+                        const uint32_t pd_at = lds_address(reinterpret_cast<const uint32_t*>(region)) + (uint32_t)(at_row + row_bytes);
+                        const uint32_t places = bits ? (1u << bits) - 1u : 255u;
+                        // 64 layers at a time, lane i holding what layer q0 + i needs
+                        for (int q0 = (n_core - 1) & ~63; q0 >= 0; q0 -= 64) {
+                            const int mine = min(q0 + lane, n_core - 1);
+                            const uint32_t trace = (uint32_t)rec[mine].trace, head = (uint32_t)s.hi[mine];
+                            uint32_t picked = 0;
+                            const int top = min(63, n_core - 1 - q0);
+                            uint32_t b1 = ent[(int)lane_u32(head, top) + lane].x;
+                            auto walk = [&](auto place) __attribute__((always_inline)) {
+#pragma unroll 4
+                                for (int i = top; i >= 0; --i) {
+                                    const uint32_t b0 = b1;
+                                    b1 = ent[(int)lane_u32(head, max(i - 1, 0)) + lane].x;
+                                    const uint32_t kk = place(i);
+                                    picked = lane == i ? kk : picked;
+                                    t += (int)lane_u32(b0, (int)(kk & 63u)) >> 2;
+                                }
+                            };
+                            if (s.facts[2] > 64) {        // longer lists than a wavefront holds
+                                for (int i = top; i >= 0; --i) {
+                                    const int a = min(max((int)lane_u32(trace, i) + t, 0), (int)cells - 1);
+                                    const uint32_t kk = (uint32_t)__builtin_amdgcn_readfirstlane((int)sw.pd[a]) & places;
+                                    picked = lane == i ? kk : picked;
+                                    t += __builtin_amdgcn_readfirstlane((int)ent[(int)lane_u32(head, i) + (int)min(kk, 127u)].x) >> 2;
+                                }
+                            } else if (pd_lds) {
+                                walk([&](int i) __attribute__((always_inline)) {
+                                    return (uint32_t)__builtin_amdgcn_readfirstlane((int)lds_byte(pd_at + lane_u32(trace, i) + (uint32_t)t)) & places;
+                                });
+                            } else if (words) {
+                                walk([&](int i) __attribute__((always_inline)) {
+                                    const int a = min(max(t, 0), row_cells - 1);
+                                    const uint32_t w = reinterpret_cast<const uint32_t*>(p.pd)[(q0 + i) * kThreadsS + (a & (kThreadsS - 1))];
+                                    return ((uint32_t)__builtin_amdgcn_readfirstlane((int)w) >> (bits * (a / kThreadsS))) & places;
+                                });
+                            } else {
+                                walk([&](int i) __attribute__((always_inline)) {
+                                    const int a = min(max((int)lane_u32(trace, i) + t, 0), (int)cells - 1);
+                                    return (uint32_t)__builtin_amdgcn_readfirstlane((int)p.pd[a]) & places;
+                                });
+                            }
+                            if (lane <= top) s.pick[q0 + lane] = (uint8_t)picked;
                         }
-                        if (lane == 0 && e != 0) atomicOr(&s.flags, 16);
+                        if (lane == 0 && t != 0) atomicOr(&s.flags, 16);
                     }
                     __syncthreads();
                     // the assignment, and what it adds up to
@@ -1052,10 +1184,11 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
                         s.chosen[s.layer[tid]] = s.cand[only];
                     }
                     if (tid < n_core) {
-                        const uint2 x = ent[s.hi[tid] + min((int)s.pick[tid], (int)(rec[tid].shape >> 16) - 1)];
-                        pb += (x.x & 0xFFFFFFu) >> 2;
-                        pz += x.y;
-                        s.chosen[s.layer[s.lo[tid]]] = (uint8_t)(x.x >> 24);
+                        const int at = s.hi[tid] + min((int)s.pick[tid], (int)(rec[tid].shape >> 16) - 1);
+                        const uint2 x = ent[at];
+                        pb += (uint32_t)(rec[tid].step - ((int)x.x >> 2));
+                        pz += x.y >> bits;
+                        s.chosen[s.layer[s.lo[tid]]] = ent_cand[at];
                     }
                     uint32_t tb, tz;
                     (void)block_scan(pb, s.tmp, &tb);

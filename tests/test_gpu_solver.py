@@ -219,7 +219,10 @@ def test_strict_budget_keeps_the_real_errors_within_e_max(groups):
 
 
 @pytest.mark.parametrize("L,P,D,kind", [
-    (40, 6, 250, "fall"), (40, 6, 900, "fall"), (60, 6, 4090, "fall"), (60, 6, 4100, "fall"),       # row widths: 256, 512, 1024, 4096
+    (40, 6, 255, "fall"), (40, 6, 256, "fall"), (60, 6, 4090, "fall"), (60, 6, 4100, "fall"),       # row widths
+    (30, 7, 511, "quant"), (30, 7, 512, "quant"), (30, 7, 1024, "quant"), (30, 7, 2047, "quant"), (30, 7, 4096, "quant"),
+    (30, 7, 6143, "quant"), (30, 7, 8192, "quant"), (30, 7, 10000, "quant"), (30, 7, 13311, "quant"), (30, 7, 16384, "quant"),
+    (24, 8, 800, "large"), (24, 8, 5000, "large"), (24, 8, 10000, "large"), (6, 100, 9000, "free"),  # costs too large to pack; long lists
     (5, 4, 16384, "free"), (3, 2, 16384, "fall"), (70, 16, 2000, "free"), (70, 17, 2000, "free"),    # whole rows; 16 / 64 candidates
     (20, 64, 3000, "fall"), (20, 65, 3000, "free"), (24, 128, 9000, "fall"),                        # a wavefront per list, two lists' halves
     (1024, 8, 3000, "free"), (1000, 16, 9000, "fall"),                                              # most layers; more entries than LDS takes
@@ -237,6 +240,11 @@ def test_reduced_sweep_on_its_edges(L, P, D, kind):
         elif kind == "ties":
             errors = rng.integers(0, 12, (L, P)).astype(np.float64) * 0.25
             sizes = rng.integers(0, 5, (L, P)).astype(np.int64)
+        elif kind in ("quant", "large"):                 # few layers with steep steps: the bounds leave most of the bins
+            n = 16 * rng.choice([1, 1, 1, 60, 90, 500], (L, 1)) * (2000 if kind == "large" else 1)
+            bits = np.arange(1, P + 1)[None]
+            errors = n * base * 4.0 ** -bits * rng.uniform(0.8, 1.0, (L, P))
+            sizes = (n * bits + 8).astype(np.int64)
         else:
             errors = base * (rng.random((L, P)) if kind == "free" else np.sort(rng.random((L, P)), axis=1)[:, ::-1])
             sizes = rng.integers(1, 1 << 17, (L, P)).astype(np.int64)
