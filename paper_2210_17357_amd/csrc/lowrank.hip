@@ -240,99 +240,104 @@ __global__ __launch_bounds__(256) void lr_gemm1_kernel(LrParams p) {
     if (tid == 0) p.xnorm_part[blockIdx.x] = s_red[0] + s_red[1] + s_red[2] + s_red[3];
 }
 
-// ------------------------------------------------------------------ P = sum of column-split partials
-__global__ __launch_bounds__(256) void lr_preduce_kernel(LrParams p) {
-    const LrTile tile = p.row_tiles[blockIdx.x];
-    const LrLayer L = p.layers[tile.layer];
-    if (L.psplits <= 1) return;
-    const int nrows = min(kLrBM, L.rows - tile.a0);
-    const float* __restrict__ part = p.ppart + L.ppart_off;
-    float* __restrict__ P = p.P + L.p_off;
-    for (int f = threadIdx.x; f < nrows * kLrCols / 4; f += 256) {
-        const int64_t idx = (int64_t)tile.a0 * kLrCols + (int64_t)f * 4;
-        float4 s = *reinterpret_cast<const float4*>(part + idx);
-        for (int sp = 1; sp < L.psplits; ++sp) {
-            const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)sp * L.rows * kLrCols + idx);
-            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-        }
-        *reinterpret_cast<float4*>(P + idx) = s;
-    }
-}
-
 // ------------------------------------------------------------------ partial Gram matrices
 // G = P^T P over a span of rows, accumulated in fp64 on v_mfma_f64_16x16x4f64.  Operand layout of
 // that instruction, lane l of 64:  A (16 x 4): A[i = l % 16][k = l / 16];  B (4 x 16):
 // B[k = l / 16][j = l % 16];  D (16 x 16): register v (0..3) holds D[4 v + l / 16][l % 16].
-// With A = P^T and B = P both operands of a 4-row step are the same four values per lane
-// (P[row0 + l / 16][16 b + l % 16], b = 0..3), so P goes from global memory straight into the
-// matrix pipe.  The four wavefronts take interleaved 16-row groups and add their results in LDS
-// in wavefront order.
+// With A = P^T and B = P both operands of a 4-row step are values P[row0 + l / 16][16 b + l % 16] of the
+// same lane.  The instruction takes a SIMD 64 cycles and bounds the kernel, so only the 10 blocks of 16 x 16 on
+// and above the diagonal are computed (nothing below it is ever read), dealt to the four wavefronts so
+// that none has more than three and each finishes its own: nothing is added up across wavefronts.
+// The span goes through LDS once; where P was computed in column splits their sum is formed on the way
+// in (split order) and written to P.  LDS word 16 (b ^ (row & 3)) + c of a row holds column 16 b + c: the four rows
+// of a step lie on different banks.  On 106 k rows of 66 layers: 45 us with a kernel of its own for the sum
+// and all 16 blocks, each wavefront a quarter of the rows.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+template <int... AB>
+struct GramBlocks {                          // row block, column block; ...
+    static constexpr int n = sizeof...(AB) / 2;
+    static constexpr int ab[sizeof...(AB)] = {AB...};
+    __device__ static constexpr int a(int i) { return ab[2 * i]; }
+    __device__ static constexpr int b(int i) { return ab[2 * i + 1]; }
+    __device__ static constexpr bool uses(int v) { return ((AB == v) || ...); }
+};
 
 __global__ __launch_bounds__(256) void lr_gram_kernel(LrParams p) {
-    __shared__ double Gs[kLrCols][kLrCols];
+    __shared__ float Ps[kLrGramSpan][kLrCols];
     const LrTile tile = p.gram_tiles[blockIdx.x];
     const LrLayer L = p.layers[tile.layer];
-    const float* __restrict__ P = p.P + L.p_off;
-    const int span_end = min(L.rows, tile.a0 + kLrGramSpan);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int row0 = tile.a0, nrows = min(kLrGramSpan, L.rows - row0);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    float* __restrict__ P = p.P + L.p_off + (int64_t)row0 * kLrCols;
+    constexpr int kPer = kLrGramSpan * kLrCols / 4 / 256;
+    const int filled = nrows * (kLrCols / 4);
+    float4 v[kPer];
+    if (L.psplits > 1) {
+        const float* __restrict__ part = p.ppart + L.ppart_off + (int64_t)row0 * kLrCols;
+        const int64_t stride = (int64_t)L.rows * kLrCols;
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int f = tid + 256 * q;
+            v[q] = f < filled ? *reinterpret_cast<const float4*>(part + 4 * f) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+        for (int sp = 1; sp < L.psplits; ++sp) {
+            const float* __restrict__ src = part + sp * stride;
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                const int f = tid + 256 * q;
+                const float4 w = f < filled ? *reinterpret_cast<const float4*>(src + 4 * f) : make_float4(0.f, 0.f, 0.f, 0.f);
+                v[q].x += w.x; v[q].y += w.y; v[q].z += w.z; v[q].w += w.w;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int f = tid + 256 * q;
+            if (f < filled) *reinterpret_cast<float4*>(P + 4 * f) = v[q];
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int f = tid + 256 * q;
+            v[q] = f < filled ? *reinterpret_cast<const float4*>(P + 4 * f) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int f = tid + 256 * q, r = f >> 4, b = (f >> 2) & 3;
+        *reinterpret_cast<float4*>(&Ps[r][16 * (b ^ (r & 3)) + 4 * (f & 3)]) = v[q];
+    }
+    __syncthreads();
     const int lr = lane >> 4, lc = lane & 15;
-    f64x4 acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
-    // the loads of the next 16-row group are in flight while the current one is multiplied
-    auto fetch = [&](int r0, float (&x)[4][4]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-            const int r = r0 + 4 * st + lr;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) x[st][b] = r < span_end ? P[(int64_t)r * kLrCols + 16 * b + lc] : 0.0f;
-        }
-    };
-    float x[4][4], xn[4][4];      // [4-row step][column block]
-    fetch(tile.a0 + 16 * wave, x);          // rows past the span's end read as zero
-    for (int r0 = tile.a0 + 16 * wave; r0 < span_end; r0 += 64) {
-        fetch(r0 + 64, xn);
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)x[st][i], (double)x[st][j], acc[i][j],
-                                                                     0, 0, 0);
-        }
-#pragma unroll
-        for (int st = 0; st < 4; ++st)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) x[st][b] = xn[st][b];
-    }
-    for (int w = 0; w < 4; ++w) {
-        if (wave == w) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        double* g = &Gs[16 * i + 4 * v + lr][16 * j + lc];
-                        *g = (w == 0) ? acc[i][j][v] : *g + acc[i][j][v];
-                    }
-        }
-        __syncthreads();
-    }
     double* __restrict__ out = p.gram_part + (size_t)blockIdx.x * kLrCols * kLrCols;
-    for (int f = tid; f < kLrCols * kLrCols; f += 256) out[f] = Gs[f >> 6][f & 63];
+    const int steps = (nrows + 3) / 4;
+    // N blocks (ai[n], bi[n]) of the matrix; the lane's row of a step is 4 st + lr, and lr is also its low bits
+    auto run = [&](auto pairs) __attribute__((always_inline)) {
+        constexpr int N = decltype(pairs)::n;
+        f64x4 acc[N];
+#pragma unroll
+        for (int n = 0; n < N; ++n) acc[n] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int st = 0; st < steps; ++st) {
+            const float* const row = Ps[4 * st + lr];
+            double x[4];
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                if (pairs.uses(b)) x[b] = (double)row[16 * (b ^ lr) + lc];
+#pragma unroll
+            for (int n = 0; n < N; ++n)
+                acc[n] = __builtin_amdgcn_mfma_f64_16x16x4f64(x[pairs.a(n)], x[pairs.b(n)], acc[n], 0, 0, 0);
+        }
+#pragma unroll
+        for (int n = 0; n < N; ++n)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) out[(16 * pairs.a(n) + 4 * u + lr) * kLrCols + 16 * pairs.b(n) + lc] = acc[n][u];
+    };
+    if (wave == 0) run(GramBlocks<0, 0, 0, 1, 1, 1>{});
+    else if (wave == 1) run(GramBlocks<2, 2, 2, 3, 3, 3>{});
+    else if (wave == 2) run(GramBlocks<0, 2, 0, 3>{});
+    else run(GramBlocks<1, 2, 1, 3>{});
 }
 
 // ------------------------------------------------------------------ Gram-Schmidt coefficients
-// One workgroup per layer.  The Gram matrix sits in registers: thread (wavefront w, lane j) holds
-// G[4 m + w][j], m = 0..15.  Elimination step i (Gram-Schmidt on the inner products): the
-// wavefront that owns row i scales it into row i of R and publishes it in LDS; after one barrier
-// every thread subtracts R[i][k] R[i][j] from its rows k > i.  Then T = R^-1 by back substitution
-// (one wavefront, lane j solves column j against R in LDS).
 __device__ __forceinline__ double lane_value(double v, int lane) {      // v of a given lane, as a scalar
     const uint64_t b = __builtin_bit_cast(uint64_t, v);
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
@@ -340,119 +345,168 @@ __device__ __forceinline__ double lane_value(double v, int lane) {      // v of 
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// G = sum of a layer's Gram partials in partial order, one matrix element per thread (16
-// workgroups per layer), left in the layer's first partial.  A layer of many rows has many
-// partials: summed here their loads run eight deep on 4096 threads instead of serially in the
-// one workgroup that eliminates.
+// G = sum of a layer's Gram partials, left in the layer's first partial: 64 workgroups per layer of many
+// rows, a row of the matrix each, its four wavefronts a quarter of the partials with eight loads in flight
+// (added per quarter in partial order, then the quarters in order).  A layer of up to kLrFewPartials partials is
+// summed by the kernel that eliminates.
+constexpr int kLrFewPartials = 4;
 __global__ __launch_bounds__(256) void lr_gram_reduce_kernel(LrParams p) {
-    const LrLayer L = p.layers[blockIdx.x / 16];
-    if (L.gram_end - L.gram_begin < 2) return;
-    const int f = (blockIdx.x % 16) * 256 + threadIdx.x;
-    double* const first = p.gram_part + (size_t)L.gram_begin * kLrCols * kLrCols + f;
+    __shared__ double s_q[4][kLrCols];
+    const LrLayer L = p.layers[blockIdx.y];
     const int n = L.gram_end - L.gram_begin;
+    if (n <= kLrFewPartials) return;
+    const int k = blockIdx.x, j = threadIdx.x & 63, w = threadIdx.x >> 6;
+    double* const first = p.gram_part + (size_t)L.gram_begin * kLrCols * kLrCols + k * kLrCols + j;
+    const int per = (n + 3) / 4, c1 = min(n, (w + 1) * per);
     double s = 0.0;
-    int c = 0;
-    for (; c + 8 <= n; c += 8) {
-        double v[8];
+    if ((k >> 4) <= (j >> 4)) {                          // on and above the diagonal blocks
+        int c = w * per;
+        for (; c + 8 <= c1; c += 8) {
+            double v[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = first[(size_t)(c + u) * kLrCols * kLrCols];
+            for (int u = 0; u < 8; ++u) v[u] = first[(size_t)(c + u) * kLrCols * kLrCols];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s += v[u];
+            for (int u = 0; u < 8; ++u) s += v[u];
+        }
+        for (; c < c1; ++c) s += first[(size_t)c * kLrCols * kLrCols];
     }
-    for (; c < n; ++c) s += first[(size_t)c * kLrCols * kLrCols];
-    *first = s;
+    s_q[w][j] = s;
+    __syncthreads();
+    if (w == 0) *first = ((s_q[0][j] + s_q[1][j]) + s_q[2][j]) + s_q[3][j];
 }
 
-__global__ __launch_bounds__(256) void lr_orth_kernel(LrParams p) {
-    __shared__ double R[kLrCols][kLrCols];
-    __shared__ double diag0[kLrCols];
+// One workgroup per layer, the matrix in registers: wavefront w, lane j hold x[m] = element (k = 8 m + w, j).
+// Gram-Schmidt on the inner products is the elimination G = U^T D U (U unit upper triangular): step i
+// subtracts G[i][k] / d_i times row i from every row k > i.  The same row operations turn the identity into
+// U^-T, whose column i starts at step i, just when column i of G is used up: it takes its place.  At
+// the end T = U^-1 D^-1/2, so that Phat = P T.  A step is a chain of an LDS round trip (the row is published
+// by its owner), a reciprocal and an update, then a barrier; square roots wait for the end, where all 64 are
+// taken at once.  (Cholesky with the square root and the division inside the chain, back substitution behind it: 42 us.)
+constexpr int kLrOrthThreads = 512;
+__global__ __launch_bounds__(kLrOrthThreads) void lr_orth_kernel(LrParams p) {
+    __shared__ double X[kLrCols][kLrCols + 1];           // row i as it is when step i uses it
+    __shared__ double diag0[kLrCols], scale[kLrCols];
+    constexpr int kWaves = kLrOrthThreads / 64, kRows = kLrCols / kWaves;
     const LrLayer L = p.layers[blockIdx.x];
-    const int tid = threadIdx.x, w = tid >> 6, j = tid & 63;
-    // G: the layer's Gram matrix (its partials already summed into the first)
-    double g[16];
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6), j = tid & 63;
+    double x[kRows];
     {
+        const int n = L.gram_end - L.gram_begin;
         const double* __restrict__ src = p.gram_part + (size_t)L.gram_begin * kLrCols * kLrCols + w * kLrCols + j;
 #pragma unroll
-        for (int m = 0; m < 16; ++m) g[m] = src[4 * m * kLrCols];
-    }
-#pragma unroll
-    for (int m = 0; m < 16; ++m)
-        if (4 * m + w == j) diag0[j] = g[m];      // squared norms before any projection
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kLrCols; ++i) {
-        if (w == (i & 3)) {
-            const double gi = g[i >> 2];                     // G[i][j], current
-            const double d = lane_value(gi, i);
-            const double d0 = diag0[i];
-            const bool ok = d > 0.0 && d >= 1e-10 * d0;
-            const double rii = ok ? sqrt(d) : 0.0;
-            const double inv = ok ? 1.0 / rii : 0.0;
-            R[i][j] = (j >= i) ? ((j == i) ? rii : gi * inv) : 0.0;
-        }
-        __syncthreads();
-        const double rj = R[i][j];
-#pragma unroll
-        for (int m = 0; m < 16; ++m)
-            if (4 * m + 3 > i) {                              // some row of this group lies below i
-                const int k = 4 * m + w;
-                if (k > i) g[m] = __builtin_fma(-R[i][k], rj, g[m]);
+        for (int m = 0; m < kRows; ++m) {
+            const int k = kWaves * m + w;
+            x[m] = 0.0;
+            if ((k >> 4) <= (j >> 4)) {
+                x[m] = src[kWaves * m * kLrCols];
+                if (n <= kLrFewPartials)
+                    for (int c = 1; c < n; ++c) x[m] += src[((size_t)c * kLrCols + kWaves * m) * kLrCols];
             }
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < kRows; ++m)
+        if (kWaves * m + w == j) diag0[j] = x[m];          // squared norms before any projection
+    if (w == 0) X[0][j] = x[0];
+    __syncthreads();
+#pragma unroll
+    for (int mb = 0; mb < kRows; ++mb) {
+        for (int wi = 0; wi < kWaves; ++wi) {
+            const int i = kWaves * mb + wi;
+            const double row = X[i][j], d = X[i][i], d0 = diag0[i];
+            const bool ok = d > 0.0 && d >= 1e-10 * d0;
+            // 1 / d: the hardware's approximation and two Newton steps
+            double inv = __builtin_amdgcn_rcp(d);
+            inv = __builtin_fma(__builtin_fma(-d, inv, 1.0), inv, inv);
+            inv = __builtin_fma(__builtin_fma(-d, inv, 1.0), inv, inv);
+            if (!ok) inv = 0.0;                              // a column in the span of those before it becomes zero
+            const bool here = j == i;
+            const double rj = (here ? 1.0 : row) * inv;
+#pragma unroll
+            for (int m = mb; m < kRows; ++m) {
+                if (m == mb && w <= wi) continue;            // rows up to i are done (uniform)
+                const double f = lane_value(row, kWaves * m + w);
+                x[m] = __builtin_fma(-f, rj, here ? 0.0 : x[m]);
+                // the next row goes out as soon as it is ready
+                if (m <= mb + 1 && kWaves * m + w == i + 1) X[i + 1][j] = x[m];
+            }
+            __syncthreads();
+        }
+    }
+    if (w == 0) {
+        const double d = X[j][j];
+        scale[j] = (d > 0.0 && d >= 1e-10 * diag0[j]) ? 1.0 / sqrt(d) : 0.0;
     }
     __syncthreads();
-    if (w != 0) return;
-    // T = R^-1, column j; columns that were zeroed stay zero
-    double t[kLrCols];
-#pragma unroll
-    for (int i = kLrCols - 1; i >= 0; --i) {
-        double s = (i == j) ? 1.0 : 0.0;
-#pragma unroll
-        for (int k = i + 1; k < kLrCols; ++k) s = __builtin_fma(-R[i][k], t[k], s);
-        const double rii = R[i][i];
-        t[i] = (i <= j && rii != 0.0) ? s / rii : 0.0;
-    }
     double* __restrict__ T = p.T + (size_t)blockIdx.x * kLrCols * kLrCols;
+    const double sj = scale[j];
 #pragma unroll
-    for (int i = 0; i < kLrCols; ++i) T[i * kLrCols + j] = t[i];
+    for (int m = 0; m < kRows; ++m) {
+        const int r = kWaves * m + w;
+        T[r * kLrCols + j] = r < j ? X[j][r] * sj : (r == j ? sj : 0.0);
+    }
 }
 
 // ------------------------------------------------------------------ Phat = P T
-// fp64 MFMA: a wavefront takes 16 rows of P at a time (A[i][k] = P[row0 + i][k], 16 loads per
-// lane, all issued before the first MFMA and before any store, so the update is in place) against
-// T in LDS; T is upper triangular, so column block b needs only k < 16 (b + 1).
+// fp64 MFMA: a wavefront takes 64 rows of P, 16 per row operand, all of their loads issued before anything
+// else (and before any store, so the update is in place), against T in LDS.  The contraction index of
+// step (q, u) is 16 q + 4 (lane / 16) + u, so that a lane's four values of a q are one 128-bit load of its row.
+// T is upper triangular: column block b needs only q <= b.  What bounds it is the matrix pipe (40 steps of 64
+// cycles per 16 rows); every value of T fetched from LDS serves four of them.  (One 16-row group at a time
+// with 16 scattered 4-byte loads each took 35 us on 106 k rows.)
 __global__ __launch_bounds__(256) void lr_apply_kernel(LrParams p) {
-    __shared__ double Tl[kLrCols][kLrCols + 2];     // padded: the four k rows of a step on different banks
+    __shared__ double Tl[kLrCols][kLrCols + 4];     // padded: rows four apart half the banks apart
     const LrTile tile = p.gram_tiles[blockIdx.x];          // one workgroup per span of kLrGramSpan rows
     const LrLayer L = p.layers[tile.layer];
     float* __restrict__ P = p.P + L.p_off;
     const double* __restrict__ T = p.T + (size_t)tile.layer * kLrCols * kLrCols;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int lr = lane >> 4, lc = lane & 15;
-    for (int f = tid; f < kLrCols * kLrCols; f += 256) Tl[f >> 6][f & 63] = T[f];
+    static_assert(kLrGramSpan == 4 * 64, "a wavefront takes 64 rows");
+    const int row0 = tile.a0 + 64 * wave;
+    double2 t[kLrCols * kLrCols / 2 / 256];
+#pragma unroll
+    for (int q = 0; q < kLrCols * kLrCols / 2 / 256; ++q) t[q] = reinterpret_cast<const double2*>(T)[tid + 256 * q];
+    float4 a[4][4];                                        // [16-row group][q]
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const int row = row0 + 16 * g + lc;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            a[g][q] = row < L.rows ? *reinterpret_cast<const float4*>(P + (int64_t)row * kLrCols + 16 * q + 4 * lr)
+                                   : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+#pragma unroll
+    for (int q = 0; q < kLrCols * kLrCols / 2 / 256; ++q) {
+        const int f = tid + 256 * q;
+        *reinterpret_cast<double2*>(&Tl[f >> 5][2 * (f & 31)]) = t[q];
+    }
     float* pay = p.payload ? reinterpret_cast<float*>(p.payload + L.payload) : nullptr;
     __syncthreads();
-    for (int blk = wave; blk < kLrGramSpan / 16; blk += 4) {
-        const int row0 = tile.a0 + 16 * blk;
-        if (row0 >= L.rows) break;
-        const int arow = row0 + lc;
-        float a[16];
+    if (row0 >= L.rows) return;                            // (behind the only barrier)
 #pragma unroll
-        for (int s = 0; s < 16; ++s) a[s] = arow < L.rows ? P[(int64_t)arow * kLrCols + 4 * s + lr] : 0.0f;
+    for (int b = 0; b < 4; ++b) {
         f64x4 acc[4];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int g = 0; g < 4; ++g) acc[g] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-            for (int s = 0; s < 4 * (b + 1); ++s)
-                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[s], Tl[4 * s + lr][16 * b + lc], acc[b], 0, 0, 0);
-        }
+        for (int q = 0; q <= b; ++q)
 #pragma unroll
-        for (int b = 0; b < 4; ++b)
+            for (int u = 0; u < 4; ++u) {
+                const double tv = Tl[16 * q + 4 * lr + u][16 * b + lc];
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const float av = u == 0 ? a[g][q].x : u == 1 ? a[g][q].y : u == 2 ? a[g][q].z : a[g][q].w;
+                    acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av, tv, acc[g], 0, 0, 0);
+                }
+            }
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int row = row0 + 4 * v + lr, col = 16 * b + lc;
+                const int row = row0 + 16 * g + 4 * v + lr, col = 16 * b + lc;
                 if (row < L.rows) {
-                    const float val = (float)acc[b][v];
+                    const float val = (float)acc[g][v];
                     P[(int64_t)row * kLrCols + col] = val;
                     if (pay && col < L.rank) pay[(int64_t)row * L.rank + col] = val;
                 }
@@ -886,7 +940,7 @@ struct LrHost {
     std::vector<LrLayer> layers;
     std::vector<LrTile> row_tiles, p_tiles, ef_tiles, col_tiles, gram_tiles, q_chunks;
     std::vector<int64_t> sig;       // signature of the layer table the tables were built for
-    int64_t p_elems = 0, q_elems = 0, part_elems = 0, ppart_elems = 0;
+    bool many_partials = false;     // some layer has more Gram partials than the elimination sums itself
     // device copies
     LrLayer* d_layers = nullptr;
     LrTile* d_tiles = nullptr;      // the four tile tables back to back
@@ -966,6 +1020,7 @@ static hipError_t lr_prepare(LowrankScratch* t, int slot, const DevLayer* hl, in
     H->col_tiles.clear();
     H->gram_tiles.clear();
     H->q_chunks.clear();
+    H->many_partials = false;
     int64_t p_off = 0, q_off = 0, part_off = 0, ppart_off = 0;
     for (int l = 0; l < L; ++l) {
         if (rank[l] <= 0) continue;
@@ -1007,6 +1062,7 @@ static hipError_t lr_prepare(LowrankScratch* t, int slot, const DevLayer* hl, in
         a.gram_begin = (int)H->gram_tiles.size();
         for (int r0 = 0; r0 < a.rows; r0 += kLrGramSpan) H->gram_tiles.push_back(LrTile{li, r0, 0, 0});
         a.gram_end = (int)H->gram_tiles.size();
+        H->many_partials = H->many_partials || a.gram_end - a.gram_begin > kLrFewPartials;
         a.qc_begin = (int)H->q_chunks.size();
         {
             // rows per chunk: fewer when many split-K partials have to be summed per row
@@ -1019,10 +1075,6 @@ static hipError_t lr_prepare(LowrankScratch* t, int slot, const DevLayer* hl, in
         part_off += (int64_t)a.splits * a.cols * kLrCols;
         H->layers.push_back(a);
     }
-    H->p_elems = p_off;
-    H->q_elems = q_off;
-    H->part_elems = part_off;
-    H->ppart_elems = ppart_off;
     const size_t nl = H->layers.size();
     const size_t nt = H->row_tiles.size() + H->p_tiles.size() + H->ef_tiles.size() + H->col_tiles.size() +
                       H->gram_tiles.size() + H->q_chunks.size();
@@ -1078,26 +1130,21 @@ static hipError_t lr_factorize(LrHost* H, LrParams p, int iters, Timing* tm, hip
     p.q_from_scratch = it > 0 ? 1 : 0;
     {
         Section sec(tm, "lowrank_gemm_p", true);
-        const bool reduce = H->ppart_elems > 0;        // split-K partials: a second kernel ends the section
         if (p.e)
-            launch_timed(&sec, true, !reduce, lr_gemm1_kernel<true>, dim3((unsigned)H->p_tiles.size()), dim3(256), 0, s, p);
+            launch_timed(&sec, true, true, lr_gemm1_kernel<true>, dim3((unsigned)H->p_tiles.size()), dim3(256), 0, s, p);
         else
-            launch_timed(&sec, true, !reduce, lr_gemm1_kernel<false>, dim3((unsigned)H->p_tiles.size()), dim3(256), 0, s, p);
+            launch_timed(&sec, true, true, lr_gemm1_kernel<false>, dim3((unsigned)H->p_tiles.size()), dim3(256), 0, s, p);
         LR_CHECK(hipGetLastError());
-        if (reduce) {
-            launch_timed(&sec, false, true, lr_preduce_kernel, dim3((unsigned)H->row_tiles.size()), dim3(256), 0, s, p);
-            LR_CHECK(hipGetLastError());
-        }
     }
     {
         Section sec(tm, "lowrank_orth");
         hipLaunchKernelGGL(lr_gram_kernel, dim3((unsigned)H->gram_tiles.size()), dim3(256), 0, s, p);
         LR_CHECK(hipGetLastError());
-        if (H->gram_tiles.size() > H->layers.size()) {      // some layer has more than one partial
-            hipLaunchKernelGGL(lr_gram_reduce_kernel, dim3((unsigned)H->layers.size() * 16), dim3(256), 0, s, p);
+        if (H->many_partials) {
+            hipLaunchKernelGGL(lr_gram_reduce_kernel, dim3(kLrCols, (unsigned)H->layers.size()), dim3(256), 0, s, p);
             LR_CHECK(hipGetLastError());
         }
-        hipLaunchKernelGGL(lr_orth_kernel, dim3((unsigned)H->layers.size()), dim3(256), 0, s, p);
+        hipLaunchKernelGGL(lr_orth_kernel, dim3((unsigned)H->layers.size()), dim3(kLrOrthThreads), 0, s, p);
         LR_CHECK(hipGetLastError());
         hipLaunchKernelGGL(lr_apply_kernel, dim3((unsigned)H->gram_tiles.size()), dim3(256), 0, s, p);
         LR_CHECK(hipGetLastError());
