@@ -324,15 +324,16 @@ struct LowrankScratch {
 hipError_t lowrank_scratch_create(LowrankScratch* t, int64_t max_elems, int max_layers, int r_max,
                                   int power_iters);
 void lowrank_scratch_destroy(LowrankScratch* t);
+// x (may be null): room for the layers' elements; a compression that follows on the same data reads g + e there
 hipError_t lowrank_profile(LowrankScratch* t, const float* g, const float* e, const DevLayer* d_layers,
                            const DevLayer* h_layers, int L, const float* q0, int r_max, const int* rank,
-                           const int* col, int nlr, double* d_errors, int stride, Timing* tm, hipStream_t s);
+                           const int* col, int nlr, double* d_errors, int stride, float* x, Timing* tm, hipStream_t s);
 hipError_t lowrank_compress(LowrankScratch* t, const float* g, float* e, const DevLayer* d_layers,
                             const DevLayer* h_layers, int L, float* q, int r_max, uint8_t* payload, Timing* tm,
                             hipStream_t s);
 // low-rank layers of a compression queued right behind a profile of the same data (see topk_compress_known)
 hipError_t lowrank_compress_known(LowrankScratch* t, const float* g, float* e, const DevLayer* d_layers, float* q,
-                                  int r_max, uint8_t* payload, Timing* tm, hipStream_t s,
+                                  int r_max, uint8_t* payload, const float* x, Timing* tm, hipStream_t s,
                                   bool e_is_zero = false);   // e_is_zero: e holds zeros on entry (the caller's promise) and is not read
 // receiver side: out (+)= Phat Q^T from the payload
 hipError_t lowrank_decompress(LowrankScratch* t, const DevLayer* h_layers, int L, int r_max, const uint8_t* payload,

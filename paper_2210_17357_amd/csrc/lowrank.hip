@@ -35,6 +35,7 @@ constexpr int kLrEfSpan = 512;    // columns reconstructed per workgroup
 
 struct LrLayer {
     int64_t offset;     // into g / e
+    int64_t x_off;      // into LrParams::x
     int64_t q_off;      // into q0 / q (stride r_max)
     int64_t p_off;      // into the P scratch (rows x 64)
     int64_t qs_off;     // into the Q scratch (cols x 64)
@@ -59,6 +60,10 @@ struct LrTile {
 struct LrParams {
     const float* g;
     const float* e;          // may be null
+    // x = g + e, left there by the first contraction (x_out set) for everything that reads the matrix after it
+    // (e null, from_x set): a pass over one buffer instead of two.  Null: g and e are read every time.
+    float* x;
+    int32_t from_x;
     float* e_out;            // compress: error feedback (same buffer as e)
     const float* q0;         // warm start (stride r_max)
     float* q_out;            // compress: new Q (stride r_max), same buffer as q0
@@ -109,6 +114,11 @@ __device__ __forceinline__ float4 load_x4(const float* __restrict__ g, const flo
     return v;
 }
 
+// The matrix as everything behind the first contraction reads it.
+__device__ __forceinline__ const float* matrix_of(const LrParams& p, const LrLayer& L) {
+    return p.from_x ? p.x + L.x_off : p.g + L.offset;
+}
+
 // ------------------------------------------------------------------ P = X Q0 (and ||X||^2)
 // One workgroup: 128 rows x 64 columns of P over one column range of X; wavefront w owns rows
 // 32w .. 32w+31.  The A operand never passes through LDS: lane l keeps, for row l % 32, the 16
@@ -116,7 +126,8 @@ __device__ __forceinline__ float4 load_x4(const float* __restrict__ g, const flo
 // registers (four 128-bit loads; lanes l and l + 32 together read one 128-byte line of the row),
 // and MFMA step s contracts the column pair (k0 + s, k0 + 16 + s).  Only the 32 x 64 chunk of Q0,
 // shared by the four wavefronts, is staged in LDS (double buffered).
-template <bool HAS_E>
+// X_OUT: x is written to LrParams::x as it is formed.
+template <bool HAS_E, bool X_OUT>
 __global__ __launch_bounds__(256) void lr_gemm1_kernel(LrParams p) {
     __shared__ float Qs[2][kLrBK][kLrCols];
     __shared__ double s_red[4];
@@ -124,8 +135,9 @@ __global__ __launch_bounds__(256) void lr_gemm1_kernel(LrParams p) {
     const LrLayer L = p.layers[tile.layer];
     const int m = L.rows, n = L.cols, row0 = tile.a0;
     const int kbeg = tile.split * L.pksplit, kend = min(n, kbeg + L.pksplit);
-    const float* __restrict__ g = p.g + L.offset;
-    const float* __restrict__ e = HAS_E ? p.e + L.offset : nullptr;
+    const float* __restrict__ g = HAS_E ? p.g + L.offset : matrix_of(p, L);
+    const float* e = HAS_E ? p.e + L.offset : nullptr;      // (x may take its place: read before it is written, by the same lane)
+    float* const xo = X_OUT ? p.x + L.x_off : nullptr;
     // first power-iteration step: the caller's warm start (row stride r_max); later steps: the Q
     // of the previous step in the scratch buffer (row stride 64)
     const bool qscr = p.q_from_scratch != 0;
@@ -138,7 +150,8 @@ __global__ __launch_bounds__(256) void lr_gemm1_kernel(LrParams p) {
     const int row = row0 + 32 * wave + bj;               // this lane's row of X
     const bool row_ok = row < m;
     const float* __restrict__ grow = g + (int64_t)row * n;
-    const float* __restrict__ erow = HAS_E ? e + (int64_t)row * n : nullptr;
+    const float* erow = HAS_E ? e + (int64_t)row * n : nullptr;
+    float* const xrow = X_OUT ? xo + (int64_t)row * n : nullptr;
 
     float4 xg[4], xe[HAS_E ? 4 : 1], qr[2];
     bool add_e = false;
@@ -188,11 +201,22 @@ __global__ __launch_bounds__(256) void lr_gemm1_kernel(LrParams p) {
     float xsq = 0.0f;
     float cur[16];
     // take the fetched chunk into use: x = g + e, ||x||^2, Q0 rows to LDS
-    auto commit = [&](int buf) {
+    auto commit = [&](int buf, int k0) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             float4 v = xg[s];
             if (HAS_E && add_e) { v.x += xe[s].x; v.y += xe[s].y; v.z += xe[s].z; v.w += xe[s].w; }
+            if (X_OUT) {
+                const int kk = k0 + 16 * half + 4 * s;
+                if (add_e) {
+                    *reinterpret_cast<float4*>(xrow + kk) = v;
+                } else if (row_ok) {
+                    if (kk < kend) xrow[kk] = v.x;
+                    if (kk + 1 < kend) xrow[kk + 1] = v.y;
+                    if (kk + 2 < kend) xrow[kk + 2] = v.z;
+                    if (kk + 3 < kend) xrow[kk + 3] = v.w;
+                }
+            }
             cur[4 * s] = v.x; cur[4 * s + 1] = v.y; cur[4 * s + 2] = v.z; cur[4 * s + 3] = v.w;
             xsq = __builtin_fmaf(v.x, v.x, xsq);
             xsq = __builtin_fmaf(v.y, v.y, xsq);
@@ -209,7 +233,7 @@ __global__ __launch_bounds__(256) void lr_gemm1_kernel(LrParams p) {
     f32x16 acc0 = {0}, acc1 = {0};
     const int nchunks = (kend - kbeg + kLrBK - 1) / kLrBK;
     fetch(kbeg);
-    commit(0);
+    commit(0, kbeg);
     __syncthreads();
     for (int c = 0; c < nchunks; ++c) {
         const int buf = c & 1;
@@ -221,7 +245,7 @@ __global__ __launch_bounds__(256) void lr_gemm1_kernel(LrParams p) {
             acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(cur[s], b0, acc0, 0, 0, 0);
             acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(cur[s], b1, acc1, 0, 0, 0);
         }
-        if (c + 1 < nchunks) commit(buf ^ 1);
+        if (c + 1 < nchunks) commit(buf ^ 1, kbeg + (c + 1) * kLrBK);
         __syncthreads();
     }
     float* __restrict__ P = L.psplits > 1 ? p.ppart + L.ppart_off + (int64_t)tile.split * m * kLrCols
@@ -523,7 +547,7 @@ __global__ __launch_bounds__(256) void lr_gemm2_kernel(LrParams p) {
     const LrLayer L = p.layers[tile.layer];
     const int m = L.rows, n = L.cols, col0 = tile.a0;
     const int kbeg = tile.split * L.ksplit, kend = min(m, kbeg + L.ksplit);
-    const float* __restrict__ g = p.g + L.offset;
+    const float* __restrict__ g = HAS_E ? p.g + L.offset : matrix_of(p, L);
     const float* __restrict__ e = HAS_E ? p.e + L.offset : nullptr;
     const float* __restrict__ P = p.P + L.p_off;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -759,9 +783,10 @@ __global__ __launch_bounds__(256) void lr_ef_kernel(LrParams p) {
     }
     const int m = L.rows, n = L.cols;
     const int kmax = (r + 1) & ~1;
-    const float* __restrict__ g = DECODE ? (p.accumulate ? p.e_out + L.offset : nullptr) : p.g + L.offset;
-    const float* __restrict__ ein = DECODE ? nullptr : p.e;
-    float* __restrict__ e = p.e_out + L.offset;
+    // (the buffer written may be the one read: every element is read, then written, by the same lane)
+    const float* const g = DECODE ? (p.accumulate ? p.e_out + L.offset : nullptr) : matrix_of(p, L);
+    const float* const ein = DECODE ? nullptr : p.e;
+    float* const e = p.e_out + L.offset;
     const float* __restrict__ P =
         DECODE ? reinterpret_cast<const float*>(p.payload + L.payload) : p.P + L.p_off;
     const float* __restrict__ Q = DECODE ? P + (int64_t)m * r : p.Q + L.qs_off;
@@ -786,7 +811,7 @@ __global__ __launch_bounds__(256) void lr_ef_kernel(LrParams p) {
         float qs[16];
         bool fast_x, fast_q, add_e;
     };
-    const float* __restrict__ ebase = ein ? ein + L.offset : nullptr;
+    const float* const ebase = ein ? ein + L.offset : nullptr;
     auto fetch = [&](Stage& S, int c0) __attribute__((always_inline)) {
         S.fast_x = vec && g != nullptr && row0 + 64 <= m && c0 + kLrCols <= n;
         S.add_e = S.fast_x && ebase != nullptr;
@@ -1021,11 +1046,22 @@ static hipError_t lr_prepare(LowrankScratch* t, int slot, const DevLayer* hl, in
     H->gram_tiles.clear();
     H->q_chunks.clear();
     H->many_partials = false;
+    // x: in the place of the error feedback when compressing; packed after a profile, aligned layers first, so that
+    // they stay aligned
+    std::vector<int64_t> x_off((size_t)L, 0);
+    int64_t x_end = 0;
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int l = 0; l < L; ++l) {
+            const bool aligned = hl[l].offset % 4 == 0 && hl[l].cols % 4 == 0;
+            if (rank[l] > 0 && aligned == (pass == 0)) { x_off[l] = x_end; x_end += (int64_t)hl[l].rows * hl[l].cols; }
+        }
+    }
     int64_t p_off = 0, q_off = 0, part_off = 0, ppart_off = 0;
     for (int l = 0; l < L; ++l) {
         if (rank[l] <= 0) continue;
         LrLayer a{};
         a.offset = hl[l].offset;
+        a.x_off = slot == kLrSlotProfile ? x_off[l] : a.offset;
         a.q_off = hl[l].q_offset;
         a.rows = hl[l].rows;
         a.cols = hl[l].cols;
@@ -1128,13 +1164,18 @@ static void lr_fill_params(LrHost* H, LrParams* p) {
 static hipError_t lr_factorize(LrHost* H, LrParams p, int iters, Timing* tm, hipStream_t s) {
   for (int it = 0; it < iters; ++it) {
     p.q_from_scratch = it > 0 ? 1 : 0;
+    const bool x_out = p.e && p.x;
     {
         Section sec(tm, "lowrank_gemm_p", true);
-        if (p.e)
-            launch_timed(&sec, true, true, lr_gemm1_kernel<true>, dim3((unsigned)H->p_tiles.size()), dim3(256), 0, s, p);
-        else
-            launch_timed(&sec, true, true, lr_gemm1_kernel<false>, dim3((unsigned)H->p_tiles.size()), dim3(256), 0, s, p);
+        const dim3 grid((unsigned)H->p_tiles.size()), block(256);
+        if (x_out) launch_timed(&sec, true, true, lr_gemm1_kernel<true, true>, grid, block, 0, s, p);
+        else if (p.e) launch_timed(&sec, true, true, lr_gemm1_kernel<true, false>, grid, block, 0, s, p);
+        else launch_timed(&sec, true, true, lr_gemm1_kernel<false, false>, grid, block, 0, s, p);
         LR_CHECK(hipGetLastError());
+    }
+    if (x_out) {                                  // from here on x is read in one piece
+        p.e = nullptr;
+        p.from_x = 1;
     }
     {
         Section sec(tm, "lowrank_orth");
@@ -1168,7 +1209,8 @@ static hipError_t lr_factorize(LrHost* H, LrParams p, int iters, Timing* tm, hip
 
 hipError_t lowrank_profile(LowrankScratch* t, const float* g, const float* e, const DevLayer* d_layers,
                            const DevLayer* h_layers, int L, const float* q0, int r_max, const int* rank,
-                           const int* col, int nlr, double* d_errors, int stride, Timing* tm, hipStream_t s) {
+                           const int* col, int nlr, double* d_errors, int stride, float* x, Timing* tm,
+                           hipStream_t s) {
     (void)d_layers;
     LrHost* H = &((LrHost*)t->host)[kLrSlotProfile];
     std::vector<int> ranks(L, kLrCols);
@@ -1186,6 +1228,7 @@ hipError_t lowrank_profile(LowrankScratch* t, const float* g, const float* e, co
     p.stride = stride;
     p.nrank = nlr;
     for (int c = 0; c < nlr; ++c) { p.rank[c] = rank[c]; p.col[c] = col[c]; }
+    p.x = e ? x : nullptr;
     LR_CHECK(lr_factorize(H, p, t->power_iters, tm, s));
     Section sec(tm, "lowrank_errors");
     hipLaunchKernelGGL(lr_errors_kernel, dim3((unsigned)H->layers.size()), dim3(256), 0, s, p);
@@ -1207,11 +1250,14 @@ hipError_t lowrank_compress(LowrankScratch* t, const float* g, float* e, const D
     p.g = g;
     p.e = e;
     p.e_out = e;
+    p.x = e;                          // the error feedback becomes x, then what is left of it
     p.q0 = q;
     p.q_out = q;
     p.r_max = r_max;
     p.payload = payload;
     LR_CHECK(lr_factorize(H, p, t->power_iters, tm, s));
+    p.e = nullptr;
+    p.from_x = 1;
     Section sec(tm, "lowrank_ef", true);
     launch_timed(&sec, true, true, lr_ef_kernel<false>, dim3((unsigned)H->ef_tiles.size()), dim3(256), 0, s, p);
     return hipGetLastError();
@@ -1222,13 +1268,16 @@ hipError_t lowrank_compress(LowrankScratch* t, const float* g, float* e, const D
 // every rank's factors are their leading columns, so nothing is contracted again.  Uses the
 // profile's work tables (all layers); needs nothing from the host.
 hipError_t lowrank_compress_known(LowrankScratch* t, const float* g, float* e, const DevLayer* d_layers, float* q,
-                                  int r_max, uint8_t* payload, Timing* tm, hipStream_t s, bool e_is_zero) {
+                                  int r_max, uint8_t* payload, const float* x, Timing* tm, hipStream_t s,
+                                  bool e_is_zero) {
     LrHost* H = &((LrHost*)t->host)[kLrSlotProfile];
     if (H->layers.empty()) return hipSuccess;
     LrParams p{};
     lr_fill_params(H, &p);
     p.g = g;
-    p.e = e_is_zero ? nullptr : e;       // promised zeros are not fetched
+    p.x = const_cast<float*>(x);
+    p.from_x = x && !e_is_zero ? 1 : 0;
+    p.e = p.from_x || e_is_zero ? nullptr : e;       // promised zeros are not fetched
     p.e_is_zero = e_is_zero ? 1 : 0;
     p.e_out = e;
     p.q0 = q;
