@@ -1150,7 +1150,7 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
             // the Top-K layers' part, from the selection records the profile left for this very
             // data: the chosen density's record is picked on the device
             HIPCHK(topk_compress_known(&h->topk, d_grads, ec->d_ef, h->d_layers, h->d_tiles, L, (int)h->ht.size(),
-                                       ec->d_payload, h->tm, s, ec->x_in_e, beside));
+                                       ec->d_payload, h->tm, s, ec->x_in_e));
         }
         if (beside) HIPCHK(hipStreamWaitEvent(h->side, h->ev_fork, 0));
         if (any_quant) {

@@ -236,7 +236,6 @@ struct TopkScratch {
     bool hist_clean = false;          // the exact histogram is all zero (the last scan of a call clears it)
     int64_t* d_cand_base = nullptr;   // [max_layers] first candidate slot of every layer
     void* d_tilecnt = nullptr;        // per tile (above, equal) counts (compress)
-    void* d_tilebase = nullptr;       // per tile exclusive prefix of those counts
     void* d_tinfo = nullptr;          // per tile, per wavefront: candidates written and where
     double* d_base_part = nullptr;    // per tile energy below the collection bound
     double* d_below_part = nullptr;   // refinement partial sums
@@ -309,11 +308,9 @@ hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLaye
 // Top-K layers of a compression queued right behind a profile of the same data and the solver
 // kernel that wrote the layer records (family, k, payload offset, slot of the chosen density in
 // the profile's selection records): nothing here needs the host to know the assignment.
-// shared_chip: another stream's kernel fills most of the chip meanwhile (the scan of the counts
-// then runs in workgroups small enough to be placed beside it).
 hipError_t topk_compress_known(TopkScratch* t, const float* g, float* e, const DevLayer* d_layers,
                                const Tile* d_tiles, int L, int n_tiles, uint8_t* payload, Timing* tm, hipStream_t s,
-                               bool x_in_e = false, bool shared_chip = false);
+                               bool x_in_e = false);
 
 // ---- lowrank.hip
 struct LowrankScratch {

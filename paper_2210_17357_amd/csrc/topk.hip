@@ -23,8 +23,8 @@
 //      Histogram bins carry their energy as integers (entries of one coarse bin share the
 //      exponent: x^2 = m^2 2^(2(E-150)), m the 24-bit significand; sum (m^2 >> 16) is exact), so
 //      nothing depends on the order of atomics.
-// Compression then counts kept entries per tile from the candidates, scans the tile counts, and
-// writes values and indices in ascending index order (equal magnitudes: lowest indices first).
+// Compression then counts kept entries per tile from the candidates, and the last kernel sums the counts before
+// its own tiles and writes values and indices in ascending index order (equal magnitudes: lowest indices first).
 // A compression queued right behind a profile of the same data takes the candidates from that
 // profile, whose main pass then also records where each candidate is (16 bits: position in the
 // tile, sign), and reads the data no second time.
@@ -99,46 +99,64 @@ __device__ void block_suffix(const uint32_t* hist, int nbins, uint32_t* scan) {
     __syncthreads();
 }
 
-// After block_suffix: for each of n requests, the largest bin b with (entries in bins >= b) >=
-// need[j], and `above` = entries in bins > b, written to res[2j], res[2j+1].  If fewer than need[j]
-// entries exist, {0, total - hist[0]}.
-template <int N>
-__device__ void block_find(const uint32_t* hist, int nbins, const uint32_t (&need)[N], int n, const uint32_t* scan,
-                           uint32_t* res) {
-    const int tid = threadIdx.x;
-    const bool act = tid < 256;
-    const int per = (nbins + 255) / 256;
-    const int lo = min(tid * per, nbins), hi = min(lo + per, nbins);
-    if (tid == 0) {
-        const uint32_t rest = scan[0] - hist[0];
+// Entries in the bins above a thread's own: thread t of NT holds the bins [t * PER, (t + 1) * PER) in
+// c.  Threads past NT only join the barrier.  tot: NT / 64 words of LDS.
+template <int NT, int PER>
+__device__ __forceinline__ uint32_t entries_above(const uint32_t (&c)[PER], uint32_t* tot, uint32_t* mine) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t sum = 0;
 #pragma unroll
-        for (int j = 0; j < N; ++j)
-            if (j < n) { res[2 * j] = 0; res[2 * j + 1] = rest; }
+    for (int b = 0; b < PER; ++b) sum += c[b];
+    uint32_t inc = sum;
+    for (int o = 1; o < 64; o <<= 1) {        // inclusive suffix scan inside the wavefront
+        const uint32_t n = __shfl_down(inc, o, 64);
+        if (lane + o < 64) inc += n;
     }
+    if (tid < NT && lane == 0) tot[wave] = inc;
     __syncthreads();
-    if (act) {
-        uint32_t running = (tid + 1 < 256) ? scan[tid + 1] : 0;
-        for (int b = hi - 1; b >= lo; --b) {
-            const uint32_t c = hist[b];
+    uint32_t above = inc - sum;
 #pragma unroll
-            for (int j = 0; j < N; ++j) {
-                if (j < n && running < need[j] && running + c >= need[j]) {
-                    res[2 * j] = (uint32_t)b;
-                    res[2 * j + 1] = running;
-                }
-            }
-            running += c;
-        }
-    }
-    __syncthreads();
+    for (int w = 0; w < NT / 64; ++w) above += w > wave ? tot[w] : 0u;
+    *mine = sum;
+    return above;
 }
 
-// One request: result broadcast through res[2]; scan[0] is left holding the total.
-__device__ void block_kth_from_top(const uint32_t* hist, int nbins, uint32_t need, uint32_t* scan,
-                                   uint32_t* res) {
-    block_suffix(hist, nbins, scan);
-    const uint32_t one[1] = {need};
-    block_find<1>(hist, nbins, one, 1, scan, res);
+// For the thread that holds the entry of rank `need` from the top (above < need <= above + its own): the
+// bin among its PER, the entries in all higher bins and those in the bin.
+template <int PER>
+__device__ __forceinline__ void find_in_own(const uint32_t (&c)[PER], uint32_t above, uint32_t need, uint32_t* bin,
+                                            uint32_t* higher, uint32_t* count) {
+    uint32_t run = above;
+#pragma unroll
+    for (int b = PER - 1; b >= 0; --b) {
+        if (run < need && run + c[b] >= need) {
+            *bin = (uint32_t)(threadIdx.x * PER + b);
+            *higher = run;
+            *count = c[b];
+        }
+        run += c[b];
+    }
+}
+
+// The largest bin b of a histogram of 256 * PER bins in LDS with (entries in bins >= b) >= need in
+// res[0] and the entries in bins > b in res[1], for every thread of the block; {0, total - hist[0]} if
+// there are fewer than need entries.  The first 256 threads hold the bins; the others join the barriers.
+template <int PER>
+__device__ void block_kth_from_top(const uint32_t* hist, uint32_t need, uint32_t* tot, uint32_t* res) {
+    const bool act = threadIdx.x < 256;
+    uint32_t c[PER];
+#pragma unroll
+    for (int b = 0; b < PER; ++b) c[b] = act ? hist[threadIdx.x * PER + b] : 0u;
+    uint32_t mine;
+    const uint32_t above = entries_above<256, PER>(c, tot, &mine);
+    if (act && above < need && above + mine >= need) {
+        uint32_t count;
+        find_in_own<PER>(c, above, need, &res[0], &res[1], &count);
+    } else if (threadIdx.x == 0 && above + mine < need) {
+        res[0] = 0;
+        res[1] = above + mine - c[0];
+    }
+    __syncthreads();
 }
 
 // Exclusive scan of one uint32 per thread over the 256-thread block; returns the prefix and the
@@ -192,9 +210,11 @@ __global__ __launch_bounds__(kSampleThreads) void topk_bound_kernel(const float*
                                                                     const uint32_t* __restrict__ ks, int ntk,
                                                                     const DevLayer* __restrict__ layers,
                                                                     uint32_t* __restrict__ lo) {
-    __shared__ uint32_t s_hist[kHistBins];
-    __shared__ uint32_t s_scan[256];
-    __shared__ uint32_t s_res[2];
+    // a copy per residue of the lane, on other banks: most of a layer's elements lie in some 30 bins
+    constexpr int kCopies = 4, kPitch = kHistBins + 16, kBinsPer = kHistBins / kSampleThreads;
+    static_assert(kBinsPer == 4, "a thread's bins are one 128-bit read");
+    __shared__ __align__(16) uint32_t s_hist[kCopies][kPitch];
+    __shared__ uint32_t s_tot[kSampleThreads / 64];
     constexpr int kPer = kSampleSegs * kSampleSeg / kSampleThreads;
     const int l = blockIdx.x, tid = threadIdx.x;
     uint32_t kmax = 0;
@@ -227,11 +247,12 @@ __global__ __launch_bounds__(kSampleThreads) void topk_bound_kernel(const float*
 #pragma unroll
         for (int q = 0; q < kPer; ++q) y[q] = el[min(at[q], n - 1u)];
     }
-    for (int b = tid; b < kHistBins; b += kSampleThreads) s_hist[b] = 0;
+#pragma unroll
+    for (int h = 0; h < kCopies; ++h) *reinterpret_cast<uint4*>(&s_hist[h][kBinsPer * tid]) = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < kPer; ++q)
-        if (at[q] < n) atomicAdd(&s_hist[mag_bits(e ? x[q] + y[q] : x[q]) >> kHistShift], 1u);
+        if (at[q] < n) atomicAdd(&s_hist[tid % kCopies][mag_bits(e ? x[q] + y[q] : x[q]) >> kHistShift], 1u);
     __syncthreads();
     uint32_t want = kmax;
     if (!whole) {
@@ -244,8 +265,19 @@ __global__ __launch_bounds__(kSampleThreads) void topk_bound_kernel(const float*
         }
         want = (uint32_t)w;
     }
-    block_kth_from_top(s_hist, kHistBins, want, s_scan, s_res);
-    if (tid == 0) lo[l] = s_res[0];
+    uint32_t c[kBinsPer] = {0, 0, 0, 0};
+#pragma unroll
+    for (int h = 0; h < kCopies; ++h) {
+        const uint4 v = *reinterpret_cast<const uint4*>(&s_hist[h][kBinsPer * tid]);
+        c[0] += v.x; c[1] += v.y; c[2] += v.z; c[3] += v.w;
+    }
+    uint32_t mine;
+    const uint32_t above = entries_above<kSampleThreads, kBinsPer>(c, s_tot, &mine);
+    if (above < want && above + mine >= want) {          // one thread: the sample holds at least `want` entries
+        uint32_t bin, higher, count;
+        find_in_own<kBinsPer>(c, above, want, &bin, &higher, &count);
+        lo[l] = bin;
+    }
 }
 
 struct CollectParams {
@@ -562,7 +594,7 @@ __global__ __launch_bounds__(256) void topk_pick_known_kernel(const DevLayer* __
                                                               TopkLayer* __restrict__ tl,
                                                               uint32_t* __restrict__ cnt_b) {
     __shared__ uint32_t s_hist[kBinsB];
-    __shared__ uint32_t s_scan[256];
+    __shared__ uint32_t s_tot[4];
     __shared__ uint32_t s_res[2];
     const int l = blockIdx.x;
     const DevLayer L = layers[l];
@@ -574,7 +606,7 @@ __global__ __launch_bounds__(256) void topk_pick_known_kernel(const DevLayer* __
     }
     __syncthreads();
     const uint32_t need_a = S.need_a, prefix = (S.tbin << 10) | S.bin_a;
-    block_kth_from_top(s_hist, kBinsB, need_a, s_scan, s_res);
+    block_kth_from_top<kBinsB / 256>(s_hist, need_a, s_tot, s_res);
     if (threadIdx.x == 0) {
         S.thr = (prefix << 9) | s_res[0];
         S.ties_keep = need_a - s_res[1];
@@ -604,73 +636,71 @@ __global__ __launch_bounds__(256) void topk_scan_kernel(uint32_t* __restrict__ h
                                                         const int64_t* __restrict__ cand_base,
                                                         uint32_t* lo, TopkLayer* __restrict__ tl,
                                                         int n_layers, ScanReduce red) {
-    __shared__ __align__(16) unsigned char s_raw[sizeof(uint32_t) * kHistBins];   // 16 KB: the histogram, or the reduction's tree
-    static_assert(sizeof(s_raw) >= sizeof(double) * kMaxQuant * 256, "shared by both jobs");
+    __shared__ double s_tree[kMaxQuant][256];            // the reduction's
     if ((int)blockIdx.x >= n_layers) {
-        reduce_partials_block(red.partials, red.stride, red.cols, red.layers, red.errors, (int)blockIdx.x - n_layers,
-                              reinterpret_cast<double(*)[256]>(s_raw));
+        reduce_partials_block(red.partials, red.stride, red.cols, red.layers, red.errors, (int)blockIdx.x - n_layers, s_tree);
         return;
     }
-    uint32_t* const s_hist = reinterpret_cast<uint32_t*>(s_raw);
-    __shared__ uint32_t s_scan[256];
-    __shared__ uint32_t s_res[2 * kMaxTopk];
-    const int l = blockIdx.x;
+    constexpr int kPer = kHistBins / 256;
+    __shared__ uint32_t s_tot[4];
+    __shared__ uint32_t s_bin[kMaxTopk], s_higher[kMaxTopk], s_count[kMaxTopk];
+    const int l = blockIdx.x, tid = threadIdx.x;
     TopkLayer& T = tl[l];
-    if (ks[(size_t)l * kMaxTopk] == 0) {
-        if (threadIdx.x == 0) {
-            T.nlists = 0; T.min_tbin = 0; T.recollect = 0;
-            for (int j = 0; j < kMaxTopk; ++j) T.sel[j].k = 0;
-        }
-        for (int b = threadIdx.x; b < kHistBins; b += 256) hist[(size_t)l * kHistBins + b] = 0u;
-        return;
+    // thread t's 16 bins go straight to its registers, and the next call's main pass starts from zero
+    uint4* const h4 = reinterpret_cast<uint4*>(hist + (size_t)l * kHistBins) + tid * (kPer / 4);
+    uint32_t c[kPer], kk[kMaxTopk];
+#pragma unroll
+    for (int q = 0; q < kPer / 4; ++q) {
+        const uint4 v = h4[q];
+        c[4 * q] = v.x; c[4 * q + 1] = v.y; c[4 * q + 2] = v.z; c[4 * q + 3] = v.w;
     }
-    for (int b = threadIdx.x; b < kHistBins; b += 256) {
-        s_hist[b] = hist[(size_t)l * kHistBins + b];
-        hist[(size_t)l * kHistBins + b] = 0u;                // the next call's main pass starts from zero
-    }
-    __syncthreads();
-    // one suffix scan of the histogram serves every requested k
-    uint32_t kk[kMaxTopk];
 #pragma unroll
     for (int j = 0; j < kMaxTopk; ++j) kk[j] = j < ntk ? ks[(size_t)l * kMaxTopk + j] : 0u;
-    block_suffix(s_hist, kHistBins, s_scan);
-    block_find<kMaxTopk>(s_hist, kHistBins, kk, ntk, s_scan, s_res);
-    // the layer's record is put together in LDS and written out by the whole workgroup
-    __shared__ TopkLayer sT;
-    if (threadIdx.x == 0) {
-        uint32_t nl = 0, mn = 0xFFFFFFFFu;
-        for (int j = 0; j < kMaxTopk; ++j) {
-            TopkSel& S = sT.sel[j];
-            S = TopkSel{};
-            if (j >= ntk) continue;
-            const uint32_t k = ks[(size_t)l * kMaxTopk + j];
-            S.k = k;
-            S.tbin = s_res[2 * j];
-            S.need = k - s_res[2 * j + 1];
-            uint32_t u = nl;
-            for (uint32_t q = 0; q < nl; ++q)
-                if (sT.lists[q].bin == S.tbin) u = q;
-            if (u == nl) {
-                sT.lists[nl] = TopkList{S.tbin, s_hist[S.tbin]};
-                ++nl;
-            }
-            S.list = u;
-            mn = min(mn, S.tbin);
-        }
-        for (uint32_t q = nl; q < (uint32_t)kMaxTopk; ++q) sT.lists[q] = TopkList{0u, 0u};
-        sT.nlists = nl;
-        sT.min_tbin = mn;
-        sT.cand_base = cand_base[l];
-        // every element at or above the lowest threshold bin must be among the candidates
-        const uint32_t used = lo[l];
-        sT.recollect = used > mn ? 1u : 0u;
-        sT.pad = 0;
-        if (sT.recollect) lo[l] = mn;
+    const uint32_t used = lo[l];
+    const int64_t base = cand_base[l];
+#pragma unroll
+    for (int q = 0; q < kPer / 4; ++q) h4[q] = make_uint4(0u, 0u, 0u, 0u);
+    if (kk[0] == 0) {
+        if (tid == 0) { T.nlists = 0; T.min_tbin = 0; T.recollect = 0; }
+        if (tid < kMaxTopk) T.sel[tid].k = 0;
+        return;
     }
+    if (tid < kMaxTopk) s_bin[tid] = s_higher[tid] = s_count[tid] = 0u;
+    // one suffix scan of the histogram serves every requested k
+    uint32_t mine;
+    const uint32_t above = entries_above<256, kPer>(c, s_tot, &mine);
+#pragma unroll
+    for (int j = 0; j < kMaxTopk; ++j)
+        if (above < kk[j] && above + mine >= kk[j])
+            find_in_own<kPer>(c, above, kk[j], &s_bin[j], &s_higher[j], &s_count[j]);
     __syncthreads();
-    static_assert(sizeof(TopkLayer) % 4 == 0, "copied as 32-bit words");
-    for (int w = threadIdx.x; w < (int)(sizeof(TopkLayer) / 4); w += 256)
-        reinterpret_cast<uint32_t*>(&T)[w] = reinterpret_cast<const uint32_t*>(&sT)[w];
+    if (tid >= kMaxTopk) return;
+    // lane j: the record of the j-th k.  The k do not increase, so the bins do not decrease and a bin
+    // that is not the one before it opens a list.
+    const uint32_t k = tid < ntk ? ks[(size_t)l * kMaxTopk + tid] : 0u;
+    const bool head = tid < ntk && (tid == 0 || s_bin[tid - 1] != s_bin[tid]);
+    const unsigned long long m = __ballot(head);
+    const uint32_t nl = (uint32_t)__popcll(m), list = (uint32_t)__popcll(m & ((2ull << tid) - 1ull)) - 1u;
+    TopkSel S{};
+    if (tid < ntk) {
+        S.k = k;
+        S.tbin = s_bin[tid];
+        S.need = k - s_higher[tid];
+        S.list = list;
+    }
+    T.sel[tid] = S;
+    if (head) T.lists[list] = TopkList{s_bin[tid], s_count[tid]};
+    if ((uint32_t)tid >= nl) T.lists[tid] = TopkList{0u, 0u};
+    if (tid == 0) {
+        const uint32_t mn = s_bin[0];                    // of the largest k
+        T.nlists = nl;
+        T.min_tbin = mn;
+        T.cand_base = base;
+        // every element at or above the lowest threshold bin must be among the candidates
+        T.recollect = used > mn ? 1u : 0u;
+        T.pad = 0;
+        if (used > mn) lo[l] = mn;
+    }
 }
 
 // The bin that holds the entry of rank `need` from the top, and the entries in higher bins, by one
@@ -1029,7 +1059,7 @@ template <bool ENERGY, int kPickThreads>
 __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams p) {
     __shared__ uint32_t s_hist[kBinsA];
     __shared__ unsigned long long s_en[ENERGY ? kBinsA : 1];
-    __shared__ uint32_t s_scan[256];
+    __shared__ uint32_t s_tot[4];
     __shared__ uint32_t s_res[2];
     __shared__ unsigned long long s_e;
     __shared__ double s_sum[kPickThreads / 64];
@@ -1092,7 +1122,7 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
         }
     }
     __syncthreads();
-    block_kth_from_top(s_hist, kBinsA, S.need, s_scan, s_res);
+    block_kth_from_top<kBinsA / 256>(s_hist, S.need, s_tot, s_res);
     const uint32_t bin_a = s_res[0];
     if (ENERGY) {
         unsigned long long e = 0;
@@ -1130,7 +1160,7 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
     if (!s_exact[0]) return;                                  // workgroup-uniform
     const uint32_t prefix = s_exact[1], need_a = s_exact[2];
     count_sub_bin<kPickThreads>(p, l, T.cand_base, prefix, s_hist);
-    block_kth_from_top(s_hist, kBinsB, need_a, s_scan, s_res);
+    block_kth_from_top<kBinsB / 256>(s_hist, need_a, s_tot, s_res);
     const uint32_t thr_b = s_res[0], keep_at_thr = need_a - s_res[1];
     // dropped inside the sub-bin: every pattern below the threshold pattern, and the entries equal
     // to it that are not kept; a thread's cells in index order, then a fixed tree
@@ -1348,7 +1378,7 @@ __global__ __launch_bounds__(kRefThreads) void topk_refine_b_kernel(RefineParams
 // equal to it are kept.
 __global__ __launch_bounds__(256) void topk_pick_b_kernel(RefineParams p) {
     __shared__ uint32_t s_hist[kBinsB];
-    __shared__ uint32_t s_scan[256];
+    __shared__ uint32_t s_tot[4];
     __shared__ uint32_t s_res[2];
     const int l = blockIdx.x / kMaxTopk, j = blockIdx.x % kMaxTopk;
     TopkLayer& T = p.tl[l];
@@ -1369,7 +1399,7 @@ __global__ __launch_bounds__(256) void topk_pick_b_kernel(RefineParams p) {
         for (int q = 0; q < 2; ++q) s_hist[tid + 256 * q] = c[q];
     }
     __syncthreads();
-    block_kth_from_top(s_hist, kBinsB, S.need_a, s_scan, s_res);
+    block_kth_from_top<kBinsB / 256>(s_hist, S.need_a, s_tot, s_res);
     if (tid == 0) {
         T.sel[j].thr = (S.tbin << kHistShift) | (S.bin_a << 9) | s_res[0];
         T.sel[j].ties_keep = S.need_a - s_res[1];
@@ -1462,54 +1492,6 @@ __global__ __launch_bounds__(kThreads) void topk_count_kernel(const Tile* __rest
     }
 }
 
-// per layer: exclusive prefix of the per-wavefront counts, in element order.  Both counts travel
-// in one 64-bit word (each stays below 2^31: a layer has fewer elements than that) and a thread
-// takes four consecutive entries, so a round of 1024 threads covers 4096 entries with one scan
-// (the largest layer's entries, tiles x 4, are the critical path of this kernel); 256 threads when
-// the chip is shared with another stream's kernel and a workgroup of 16 wavefronts would wait long
-// for a compute unit with that much room.
-template <int kScanThreads>
-__global__ __launch_bounds__(kScanThreads) void topk_tilescan_kernel(const DevLayer* __restrict__ layers,
-                                                            const uint2* __restrict__ wavecnt,
-                                                            uint2* __restrict__ wavebase) {
-    __shared__ unsigned long long s_tmp[kScanThreads / 64];
-    const DevLayer L = layers[blockIdx.x];
-    if (L.family != LGRECO_TOPK) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    unsigned long long run = 0;             // (entries above the threshold) << 32 | entries equal to it
-    const int q0 = L.tile_begin * (kThreads / 64), q1 = L.tile_end * (kThreads / 64);
-    for (int b = q0; b < q1; b += 4 * kScanThreads) {
-        const int first = b + 4 * (int)threadIdx.x;
-        unsigned long long c[4], mine = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint2 v = first + i < q1 ? wavecnt[first + i] : make_uint2(0, 0);
-            c[i] = ((unsigned long long)v.x << 32) | v.y;
-            mine += c[i];
-        }
-        unsigned long long inc = mine;
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned long long n = __shfl_up(inc, o, 64);
-            if (lane >= o) inc += n;
-        }
-        __syncthreads();                     // the previous round is done with s_tmp
-        if (lane == 63) s_tmp[wave] = inc;
-        __syncthreads();
-        unsigned long long before = run, total = 0;
-        for (int w = 0; w < kScanThreads / 64; ++w) {
-            if (w < wave) before += s_tmp[w];
-            total += s_tmp[w];
-        }
-        before += inc - mine;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (first + i < q1) wavebase[first + i] = make_uint2((uint32_t)(before >> 32), (uint32_t)before);
-            before += c[i];
-        }
-        run += total;
-    }
-}
-
 __device__ __forceinline__ uint32_t lanes_below(unsigned long long m, uint32_t add) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, add));
 }
@@ -1518,6 +1500,10 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long m, uint32_t a
 // is a candidate, and a wavefront's candidates are stored in element order); the error feedback,
 // already written as x everywhere by the collection pass, is zeroed at the kept entries (KNOWN:
 // written as zero at every candidate by that pass, and set back to x at those not kept).
+// Where a wavefront's entries go is the sum of the counts of all wavefronts before it in the layer: the
+// workgroup adds up those before its first tile (of the largest layer of a 355 M-element model 50 KB at most,
+// 8 128-bit loads in flight per thread) and walks its own 16.  As a kernel of its own, a
+// workgroup per layer, that prefix took 4-5 us and its launch; 18 beside a kernel that fills the chip.
 template <bool KNOWN>
 __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__ e,
                                                               const DevLayer* __restrict__ layers,
@@ -1527,7 +1513,6 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__
                                                               const uint32_t* __restrict__ cand,
                                                               const uint32_t* __restrict__ cand_idx,
                                                               const uint2* __restrict__ wavecnt,
-                                                              const uint2* __restrict__ wavebase,
                                                               uint8_t* __restrict__ payload, int x_in_e) {
     // x_in_e (KNOWN only): the main pass left the buffer as it was (x everywhere), so the kept
     // entries are zeroed here, as without KNOWN, and nothing is put back
@@ -1558,7 +1543,39 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__
         S[q].n = tinfo[ti].cnt[wave];
         start[q] = tinfo[ti].start[wave];
         cnt[q] = wavecnt[slot];
-        before[q] = wavebase[slot];
+    }
+    // Both counts travel in one 64-bit word (each stays below 2^31: a layer has fewer elements than that).
+    constexpr int kWaves = kThreads / 64, kBatch = 8;
+    static_assert(kWaves % 2 == 0, "a tile's counts are read in pairs");
+    __shared__ unsigned long long s_before[kWaves];
+    unsigned long long sum = 0;                          // (entries above the threshold) << 32 | entries equal to it
+    {
+        const int begin = layers[layer[0]].tile_begin;
+        const uint4* const pairs = reinterpret_cast<const uint4*>(wavecnt + (size_t)begin * kWaves);
+        const int n_pairs = (first - begin) * (kWaves / 2);
+        for (int i = (int)threadIdx.x; i < n_pairs; i += kBatch * kThreads) {
+            uint4 v[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) v[u] = i + u * kThreads < n_pairs ? pairs[i + u * kThreads] : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) sum += ((unsigned long long)(v[u].x + v[u].z) << 32) + (v[u].y + v[u].w);
+        }
+        for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
+        if (lane == 0) s_before[wave] = sum;
+        __syncthreads();
+        sum = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) sum += s_before[w];
+    }
+#pragma unroll
+    for (int q = 0; q < kSliceBatch; ++q) {
+        const uint2* const c = wavecnt + (size_t)min(first + q, n_tiles - 1) * kWaves;
+        if (q > 0 && layer[q] != layer[q - 1]) sum = 0;  // the layer begins with this tile
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            if (w == wave) before[q] = make_uint2((uint32_t)(sum >> 32), (uint32_t)sum);
+            sum += ((unsigned long long)c[w].x << 32) + c[w].y;
+        }
     }
 #pragma unroll
     for (int q = 0; q < kSliceBatch; ++q) {
@@ -1648,7 +1665,6 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
     TK_CHECK(hipMalloc(&t->d_tinfo_kept, sizeof(TopkTileInfo) * (size_t)max_tiles));
     TK_CHECK(hipMalloc(&t->d_lo, sizeof(uint32_t) * (size_t)max_layers));
     TK_CHECK(hipMalloc(&t->d_tilecnt, sizeof(uint2) * (size_t)max_tiles * (kThreads / 64)));
-    TK_CHECK(hipMalloc(&t->d_tilebase, sizeof(uint2) * (size_t)max_tiles * (kThreads / 64)));
     TK_CHECK(hipMalloc(&t->d_tinfo, sizeof(TopkTileInfo) * (size_t)max_tiles));
     TK_CHECK(hipMalloc(&t->d_base_part, sizeof(double) * (size_t)max_tiles));
     t->max_work = (int)(max_elems / ((int64_t)kRefTiles * kTile)) + 2 * max_layers + 2 + 2 * kRefSlots;   // see topk_begin
@@ -1693,7 +1709,6 @@ void topk_scratch_destroy(TopkScratch* t) {
     (void)hipFree(t->d_tinfo_kept);
     (void)hipFree(t->d_lo);
     (void)hipFree(t->d_tilecnt);
-    (void)hipFree(t->d_tilebase);
     (void)hipFree(t->d_tinfo);
     (void)hipFree(t->d_base_part);
     (void)hipFree(t->d_below_part);
@@ -2013,18 +2028,12 @@ hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLaye
         TK_CHECK(hipGetLastError());
     }
     {
-        Section sec(tm, "topk_tilescan");
-        hipLaunchKernelGGL(topk_tilescan_kernel<1024>, dim3(L), dim3(1024), 0, s, d_layers, (const uint2*)t->d_tilecnt,
-                           (uint2*)t->d_tilebase);
-        TK_CHECK(hipGetLastError());
-    }
-    {
         Section sec(tm, "topk_emit");
         hipLaunchKernelGGL(topk_emit_kernel<false>, dim3((n_tiles + kSliceBatch - 1) / kSliceBatch), dim3(kThreads), 0, s, e,
                            d_layers, d_tiles, n_tiles, (const TopkLayer*)t->d_tl,
                            (const TopkTileInfo*)t->d_tinfo, (const uint32_t*)t->d_cand,
                            (const uint32_t*)t->d_cand_idx, (const uint2*)t->d_tilecnt,
-                           (const uint2*)t->d_tilebase, payload, 0);
+                           payload, 0);
         TK_CHECK(hipGetLastError());
     }
     return hipSuccess;
@@ -2038,10 +2047,10 @@ hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLaye
 // what lies at or above the sub-bin's lower edge is taken from the profile's candidates, the
 // sub-bin's entries counted by their last 9 bits, and the data is not read at all.  Otherwise one
 // pass over g and e writes x to the error feedback and collects the same set.  Then the exact
-// threshold, the per-wavefront counts, their scan and the ordered emit, as in topk_compress.
+// threshold, the per-wavefront counts and the ordered emit, as in topk_compress.
 hipError_t topk_compress_known(TopkScratch* t, const float* g, float* e, const DevLayer* d_layers,
                                const Tile* d_tiles, int L, int n_tiles, uint8_t* payload, Timing* tm, hipStream_t s,
-                               bool x_in_e, bool shared_chip) {
+                               bool x_in_e) {
     if (n_tiles <= 0) return hipSuccess;
     // the profile's control block (slot 0) holds every layer's candidate region
     uint8_t* const d = t->d_ctl[0];
@@ -2100,21 +2109,11 @@ hipError_t topk_compress_known(TopkScratch* t, const float* g, float* e, const D
         TK_CHECK(hipGetLastError());
     }
     {
-        Section sec(tm, "topk_tilescan");
-        if (shared_chip)
-            hipLaunchKernelGGL(topk_tilescan_kernel<256>, dim3(L), dim3(256), 0, s, d_layers, (const uint2*)t->d_tilecnt,
-                               (uint2*)t->d_tilebase);
-        else
-            hipLaunchKernelGGL(topk_tilescan_kernel<1024>, dim3(L), dim3(1024), 0, s, d_layers,
-                               (const uint2*)t->d_tilecnt, (uint2*)t->d_tilebase);
-        TK_CHECK(hipGetLastError());
-    }
-    {
         Section sec(tm, "topk_emit");
         hipLaunchKernelGGL(topk_emit_kernel<true>, dim3((n_tiles + kSliceBatch - 1) / kSliceBatch), dim3(kThreads), 0, s, e,
                            d_layers, d_tiles, n_tiles, (const TopkLayer*)t->d_tl, tinfo, cand, cand_idx,
                            (const uint2*)t->d_tilecnt,
-                           (const uint2*)t->d_tilebase, payload, x_in_e ? 1 : 0);
+                           payload, x_in_e ? 1 : 0);
         TK_CHECK(hipGetLastError());
     }
     return hipSuccess;

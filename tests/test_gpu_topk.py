@@ -374,3 +374,14 @@ def test_more_densities_than_one_column_each(count):
               rng.laplace(0, 1e-3, (1 << 20) + 77).astype(np.float32), np.float32([0.5]), np.float32([1, -2, 3])]
     densities = np.linspace(0.002, 0.4, count - 1).tolist() + [0.002]
     _check(_flat_batch(arrays), rng.permutation(densities))
+
+
+@pytest.mark.parametrize("n", [4 * 8192 - 1, 4 * 8192 + 1, 37 * 8192 + 5])
+def test_places_across_the_emit_kernels_batches_of_tiles(n):
+    """Where a kept entry goes is the sum of the counts before it: layers that end just before, at and behind a
+    batch of four tiles, the next layer's first tile inside a batch, and ties in every tile of which only
+    those of the lowest indices are kept."""
+    rng = np.random.default_rng(n)
+    ties = np.round(rng.standard_normal(n) * 2).astype(np.float32)
+    free = rng.laplace(size=n).astype(np.float32)
+    _check(_flat_batch([ties[:5], free, ties, free[:8192], ties[: n // 2 + 1]], pad=[3, 0, 1, 0, 2]), [0.3, 0.1, 0.013])
