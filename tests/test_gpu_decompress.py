@@ -72,6 +72,16 @@ def test_quant_every_bit_width_ragged_layers(stochastic):
         _roundtrip(w, batch, choice, stochastic=stochastic)
 
 
+@pytest.mark.parametrize("bits", range(1, 9))
+def test_quant_lengths_around_the_fetch_depth(bits):
+    # a workgroup's round is 4096 elements of an aligned tile, 1024 of one off alignment; then rounds of
+    # 1024 and 256 with remainders of them.  The second half of the layers starts behind a single element.
+    lengths = (512, 1024, 1536, 3584, 4096, 4608, 7680, 8192 + 512, 255 + 1024, 8191)
+    shapes = tuple((n,) for n in lengths + (1 + -sum(lengths) % 4,) + lengths)
+    w = W.Workload("lengths", shapes, ((W.QUANT, float(bits)),), 0, 100, "student_t3", "normal0.1", (-4.0, -2.0))
+    _roundtrip(w, W.generate(w), np.zeros(len(shapes), np.int32))
+
+
 def test_topk_ragged_layers_and_ties():
     w = _ragged(tuple((W.TOPK, d) for d in (0.001, 0.01, 0.1, 0.5, 1.0)), values="laplace", ef="same")
     batch = W.generate(w)
