@@ -20,7 +20,7 @@ Prints ONE JSON line (metric = gradient GB/s = 4 * N bytes / step time), with
   "phases_gpu_ms"   GPU time of the profile, solve and compress phases (events around everything a
                     phase queues: main kernels, the Top-K chains, list building, the DP);
   "roofline_phase"  algorithmic bytes of a phase (and of the whole step) / its time / 8 TB/s;
-  "cold"            the same loop with reuse_thresholds = 0 (every call samples the data first);
+  "cold"            the same loop with reuse_thresholds = 0 (the switch has no effect: every call samples the data);
   "other_workloads" the smaller workloads of BASELINE.json, same measurement, a few ms each;
   "cpu_baseline"    the CPU oracle timed on a bounded sample of the same workload.
 """
@@ -87,12 +87,12 @@ def parse_args():
     ap.add_argument("--power-iters", type=int, default=1,
                     help="power-iteration steps of the low-rank family (the configs use 1)")
     ap.add_argument("--sample-every-call", action="store_true",
-                    help="Top-K: the main loop itself runs with reuse_thresholds = 0 (the default run reports "
-                         "that case under \"cold\")")
+                    help="Top-K: the main loop itself runs with reuse_thresholds = 0 (without effect: every call samples "
+                         "the data; the default run reports that case under \"cold\")")
     ap.add_argument("--no-cold", action="store_true", help="leave out the reuse_thresholds = 0 loop")
     ap.add_argument("--dp-groups", type=int, default=0,
-                    help="layer groups of the solver: 0 = the library decides from the table's size, 1 = one "
-                         "sequential sweep, 2 / 4 / 8 = that many groups")
+                    help="layer groups of the solver: 0, 1 = one sweep over the cells an assignment of the smallest size "
+                         "can use, 2 / 4 / 8 = the whole table in that many groups")
     ap.add_argument("--keep-ef-on-failure", action="store_true",
                     help="create the handle with keep_ef_on_failure = 1: the profile of the one call does not "
                          "leave x in the error-feedback buffer (more memory traffic, same results)")
