@@ -18,6 +18,7 @@
 //   A (32 x 2): A[i = l % 32][k = l / 32];   B (2 x 32): B[k = l / 32][j = l % 32]
 //   D (32 x 32): register v (0..15) holds D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32]
 #include <cstring>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -768,11 +769,20 @@ __global__ __launch_bounds__(256) void lr_errors_kernel(LrParams p) {
 // KNOWN (compression right behind a profile of the same data): the factors are the leading columns
 // of the profile's rank-64 run, still in its scratch; whether the layer takes part and its rank
 // come from the layer records the solver kernel wrote.
+//
+// Bound by HBM: x once in, e' once out.  A workgroup takes 64 rows over a span of columns, 64 columns at a time, each
+// wavefront a 32 x 32 quadrant.  Its rows of Phat are the same for the whole span and stay in registers; Q passes
+// through LDS (two buffers, one barrier per 64 columns); the product never does: an accumulator of the 32x32x2
+// instruction holds two rows of 32 consecutive columns, so x is loaded and e' stored in that layout, two
+// whole lines per instruction, whatever the layer's alignment.  x is fetched two tiles ahead, Q one.
+// Operands in LDS: row c of Q as its even columns, then its odd ones (lane half h of step i contracts column
+// 2 i + h, so four steps are one 128-bit read), 68 words apart (16 lanes of such a read on different banks).
+// On 67 M elements of 97 layers: image at the receiver 112 -> 74 us, a whole compression 516 -> 495, a one-call
+// step 570 -> 554, against factors and product staged through LDS with two barriers a tile and 16-byte accesses.
+constexpr int kLrEfPitch = kLrCols + 4;
 template <bool DECODE, bool KNOWN = false>
-__global__ __launch_bounds__(256) void lr_ef_kernel(LrParams p) {
-    __shared__ float Ps[64][kLrCols + 1];
-    __shared__ float Qs[kLrCols][kLrCols + 1];
-    __shared__ float Ms[64][kLrCols + 4];
+__global__ __launch_bounds__(256, KNOWN ? 4 : 3) void lr_ef_kernel(LrParams p) {
+    __shared__ __align__(16) float Qs[2][kLrCols][kLrEfPitch];
     const LrTile tile = p.ef_tiles[blockIdx.x];
     const LrLayer L = p.layers[tile.layer];
     int r = L.rank;
@@ -782,139 +792,152 @@ __global__ __launch_bounds__(256) void lr_ef_kernel(LrParams p) {
         r = dl.iparam;
     }
     const int m = L.rows, n = L.cols;
-    const int kmax = (r + 1) & ~1;
     // (the buffer written may be the one read: every element is read, then written, by the same lane)
     const float* const g = DECODE ? (p.accumulate ? p.e_out + L.offset : nullptr) : matrix_of(p, L);
-    const float* const ein = DECODE ? nullptr : p.e;
     float* const e = p.e_out + L.offset;
     const float* __restrict__ P =
         DECODE ? reinterpret_cast<const float*>(p.payload + L.payload) : p.P + L.p_off;
     const float* __restrict__ Q = DECODE ? P + (int64_t)m * r : p.Q + L.qs_off;
-    const int pstride = DECODE ? r : kLrCols;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const bool vec = L.vec_ok != 0;
-    // the 4 wavefronts split a 64 x 64 output tile into 32 x 32 quadrants
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wr = wave >> 1, wc = wave & 1;
-    const int ar = 32 * wr + (lane & 31), ak = lane >> 5, bj = 32 * wc + (lane & 31);
+    const int half = lane >> 5, bj = 32 * wc + (lane & 31);
     const int row0 = tile.a0, cbeg = tile.split, cend = min(n, cbeg + kLrEfSpan);
-    for (int f = tid; f < 64 * kLrCols; f += 256) {
-        const int rr = f >> 6, c = f & 63;
-        Ps[rr][c] = (row0 + rr < m && c < r) ? P[(int64_t)(row0 + rr) * pstride + c] : 0.0f;
+
+    // A operand: step i holds column 2 i + half of this lane's row of Phat (zero from the rank on)
+    float a[kLrCols / 2];
+    {
+        const int row = row0 + 32 * wr + (lane & 31);
+        if (DECODE) {                                    // payload: r columns per row
+            const float* const src = P + (int64_t)min(row, m - 1) * r;
+#pragma unroll
+            for (int i = 0; i < kLrCols / 2; ++i) a[i] = row < m && 2 * i + half < r ? src[2 * i + half] : 0.0f;
+        } else {                                         // scratch: 64 columns per row
+            const float4* const src = reinterpret_cast<const float4*>(P + (int64_t)min(row, m - 1) * kLrCols);
+#pragma unroll
+            for (int j = 0; j < kLrCols / 4; ++j) {
+                const float4 v = src[j];
+                a[2 * j] = row < m && 4 * j + half < r ? (half ? v.y : v.x) : 0.0f;
+                a[2 * j + 1] = row < m && 4 * j + 2 + half < r ? (half ? v.w : v.z) : 0.0f;
+            }
+        }
     }
-    // Software pipeline over the 64-column tiles of the span, two tiles deep: the loads of tiles
-    // t+1 and t+2 (x and the rows of Q) are in flight while tile t is worked on, in two register
-    // sets that take turns (a workgroup has few neighbours on its compute unit - LDS allows three -
-    // so the bytes in flight per workgroup are what the memory latency is hidden with).  Interior
-    // tiles of aligned layers take a path without per-load conditions.
-    struct Stage {
-        float4 xn[4], en[4], qn[4];
-        float qs[16];
-        bool fast_x, fast_q, add_e;
-    };
-    const float* const ebase = ein ? ein + L.offset : nullptr;
-    auto fetch = [&](Stage& S, int c0) __attribute__((always_inline)) {
-        S.fast_x = vec && g != nullptr && row0 + 64 <= m && c0 + kLrCols <= n;
-        S.add_e = S.fast_x && ebase != nullptr;
-        if (S.fast_x) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int f = tid + 256 * q;
-                const int64_t idx = (int64_t)(row0 + (f >> 4)) * n + c0 + (f & 15) * 4;
-                S.xn[q] = *reinterpret_cast<const float4*>(g + idx);
-                if (ebase) S.en[q] = *reinterpret_cast<const float4*>(ebase + idx);
+    // element v of an accumulator: row 8 (v / 4) + 4 half + v % 4 of the quadrant, column bj
+    // (scalar row starts and one 32-bit offset per lane: below 2^31, where it is used, as the layer's size is)
+    const int row_v = row0 + 32 * wr + 4 * half;
+    const uint32_t at_v = 4u * (uint32_t)half * (uint32_t)n + (uint32_t)bj;
+    const auto row_of = [](int v) { return 8 * (v >> 2) + (v & 3); };
+    const auto start_of = [&](int v, int c0) { return (int64_t)(row0 + 32 * wr + row_of(v)) * n + c0; };
+    const bool rows_in = row0 + 64 <= m;
+    // Whole lines pass by the caches; pieces of lines don't, since their other half comes with the next tile (a
+    // compression of 9 layers of 211 x 1899: 284 us; 294 with the hint on everything).
+    // (Two copies of the loop: of a choice at each access the compiler makes one, without the hint.)
+    const auto span = [&](auto whole_lines) __attribute__((always_inline)) {
+        constexpr bool lines = decltype(whole_lines)::value;
+
+        auto fetch_x = [&](float (&x)[16], int c0) __attribute__((always_inline)) {
+            if (DECODE && g == nullptr) {
+    #pragma unroll
+                for (int v = 0; v < 16; ++v) x[v] = 0.0f;
+            } else if (rows_in && c0 + kLrCols <= n) {
+    #pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float* const src = g + start_of(v, c0) + at_v;
+                    if constexpr (lines) x[v] = __builtin_nontemporal_load(src);
+                    else x[v] = *src;
+                }
+            } else {
+    #pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    x[v] = row_v + row_of(v) < m && c0 + bj < n ? (g + start_of(v, c0))[at_v] : 0.0f;
             }
-        } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int f = tid + 256 * q;
-                const int row = row0 + (f >> 4), colx = c0 + (f & 15) * 4;
-                S.xn[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (g && row < m && colx < n) S.xn[q] = load_x4(g, ebase, (int64_t)row * n + colx, n - colx, vec);
-            }
-        }
-        S.fast_q = !DECODE && c0 + kLrCols <= n;        // scratch Q: 64 columns per row, 16-byte aligned
-        if (S.fast_q) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int f = tid + 256 * q;
-                S.qn[q] = *reinterpret_cast<const float4*>(Q + (int64_t)(c0 + (f >> 4)) * kLrCols + (f & 15) * 4);
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int f = tid + 256 * q;
-                const int cc = f >> 6, k = f & 63;
-                S.qs[q] = (c0 + cc < n && k < r) ? Q[(int64_t)(c0 + cc) * pstride + k] : 0.0f;
-            }
-        }
-    };
-    // one tile from the stage that holds it; the stage is refilled with the tile two further on
-    auto step = [&](Stage& S, int c0) __attribute__((always_inline)) {
-        float4 x[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            x[q] = S.xn[q];
-            if (S.add_e) { x[q].x += S.en[q].x; x[q].y += S.en[q].y; x[q].z += S.en[q].z; x[q].w += S.en[q].w; }
-            // zeros that are not read are still added (a gradient of -0 becomes the +0 the sum with
-            // a stored zero gives: every bit as without the promise)
-            if (!DECODE && p.e_is_zero) { x[q].x += 0.0f; x[q].y += 0.0f; x[q].z += 0.0f; x[q].w += 0.0f; }
-        }
-        if (S.fast_q) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int f = tid + 256 * q;
-                const int cc = f >> 4, k = (f & 15) * 4;
-                Qs[cc][k] = k < r ? S.qn[q].x : 0.0f;
-                Qs[cc][k + 1] = k + 1 < r ? S.qn[q].y : 0.0f;
-                Qs[cc][k + 2] = k + 2 < r ? S.qn[q].z : 0.0f;
-                Qs[cc][k + 3] = k + 3 < r ? S.qn[q].w : 0.0f;
-            }
-        } else {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int f = tid + 256 * q;
-                Qs[f >> 6][f & 63] = S.qs[q];
-            }
-        }
-        __syncthreads();
-        if (c0 + 2 * kLrCols < cend) fetch(S, c0 + 2 * kLrCols);
-        f32x16 acc = {0};
-        for (int kk = 0; kk < kmax; kk += 2)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Ps[ar][kk + ak], Qs[bj][kk + ak], acc, 0, 0, 0);
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-            Ms[32 * wr + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)][bj] = acc[v];
-        __syncthreads();
-        // coalesced update of the error feedback: 64 rows x 16 float4
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int f = tid + 256 * q;
-            const int rr = f >> 4, c4 = (f & 15) * 4;
-            const int row = row0 + rr, colx = c0 + c4;
-            if (row < m && colx < n) {
-                const int64_t idx = (int64_t)row * n + colx;
-                const int left = n - colx;
-                const float4 mh = *reinterpret_cast<const float4*>(&Ms[rr][c4]);
-                const float4 o = DECODE ? make_float4(x[q].x + mh.x, x[q].y + mh.y, x[q].z + mh.z, x[q].w + mh.w)
-                                        : make_float4(x[q].x - mh.x, x[q].y - mh.y, x[q].z - mh.z, x[q].w - mh.w);
-                if (vec && left >= 4) {
-                    *reinterpret_cast<float4*>(e + idx) = o;
-                } else {
-                    e[idx] = o.x;
-                    if (left > 1) e[idx + 1] = o.y;
-                    if (left > 2) e[idx + 2] = o.z;
-                    if (left > 3) e[idx + 3] = o.w;
+        };
+        float q[16];
+        auto fetch_q = [&](int c0) __attribute__((always_inline)) {
+            if (DECODE) {
+    #pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    const int c = c0 + wave + 4 * u;
+                    q[u] = c < n && lane < r ? (Q + (int64_t)c * r)[lane] : 0.0f;
+                }
+            } else {
+    #pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int f = tid + 256 * u;
+                    const float4 w = c0 + kLrCols <= n || c0 + (f >> 4) < n
+                                         ? *reinterpret_cast<const float4*>(Q + (int64_t)c0 * kLrCols + 1024 * u + 4 * tid)
+                                         : make_float4(0.f, 0.f, 0.f, 0.f);
+                    q[4 * u] = w.x; q[4 * u + 1] = w.y; q[4 * u + 2] = w.z; q[4 * u + 3] = w.w;
                 }
             }
+        };
+        auto store_q = [&](int buf) __attribute__((always_inline)) {
+            if (DECODE) {
+    #pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    Qs[buf][wave + 4 * u][(kLrCols / 2) * (lane & 1) + (lane >> 1)] = q[u];
+                }
+            } else {
+    #pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int f = tid + 256 * u, cc = f >> 4, k = (f & 15) * 4;
+                    *reinterpret_cast<float2*>(&Qs[buf][cc][k >> 1]) =
+                        make_float2(k < r ? q[4 * u] : 0.0f, k + 2 < r ? q[4 * u + 2] : 0.0f);
+                    *reinterpret_cast<float2*>(&Qs[buf][cc][kLrCols / 2 + (k >> 1)]) =
+                        make_float2(k + 1 < r ? q[4 * u + 1] : 0.0f, k + 3 < r ? q[4 * u + 3] : 0.0f);
+                }
+            }
+        };
+        // one tile; its x is replaced by that of the tile two further on
+        auto step = [&](float (&x)[16], int buf, int c0) __attribute__((always_inline)) {
+            store_q(buf);
+            __syncthreads();                                 // (the buffer's last readers were done before the barrier in between)
+            if (c0 + kLrCols < cend) fetch_q(c0 + kLrCols);
+            f32x16 acc = {0};
+            const float* const row = &Qs[buf][bj][(kLrCols / 2) * half];
+    #pragma unroll
+            for (int i = 0; i < kLrCols / 2; i += 4) {
+                if (2 * i < r) {
+                    const float4 b = *reinterpret_cast<const float4*>(row + i);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b.x, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i + 1], b.y, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i + 2], b.z, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i + 3], b.w, acc, 0, 0, 0);
+                }
+            }
+            float o[16];
+    #pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                // zeros that are not read are still added (a gradient of -0 becomes the +0 the sum with
+                // a stored zero gives: every bit as without the promise)
+                const float xv = !DECODE && p.e_is_zero ? x[v] + 0.0f : x[v];
+                o[v] = DECODE ? xv + acc[v] : xv - acc[v];
+            }
+            if (rows_in && c0 + kLrCols <= n) {
+    #pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    float* const dst = e + start_of(v, c0) + at_v;
+                    if constexpr (lines) __builtin_nontemporal_store(o[v], dst);
+                    else *dst = o[v];
+                }
+            } else {
+    #pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (row_v + row_of(v) < m && c0 + bj < n) (e + start_of(v, c0))[at_v] = o[v];
+            }
+            if (c0 + 2 * kLrCols < cend) fetch_x(x, c0 + 2 * kLrCols);
+        };
+        float x0[16], x1[16];
+        fetch_q(cbeg);
+        fetch_x(x0, cbeg);
+        if (cbeg + kLrCols < cend) fetch_x(x1, cbeg + kLrCols);
+        for (int c0 = cbeg; c0 < cend; c0 += 2 * kLrCols) {
+            step(x0, 0, c0);
+            if (c0 + kLrCols < cend) step(x1, 1, c0 + kLrCols);
         }
     };
-    Stage s0, s1;
-    fetch(s0, cbeg);
-    if (cbeg + kLrCols < cend) fetch(s1, cbeg + kLrCols);
-    for (int c0 = cbeg; c0 < cend; c0 += 2 * kLrCols) {
-        step(s0, c0);
-        if (c0 + kLrCols < cend) step(s1, c0 + kLrCols);
-    }
+    if (L.offset % 32 == 0 && n % 32 == 0) span(std::true_type());
+    else span(std::false_type());
 }
 
 // Payload and warm-start update of a layer from the profile's scratch (KNOWN, see lr_ef_kernel):
@@ -1276,8 +1299,7 @@ hipError_t lowrank_compress_known(LowrankScratch* t, const float* g, float* e, c
     lr_fill_params(H, &p);
     p.g = g;
     p.x = const_cast<float*>(x);
-    p.from_x = x && !e_is_zero ? 1 : 0;
-    p.e = p.from_x || e_is_zero ? nullptr : e;       // promised zeros are not fetched
+    p.from_x = e_is_zero ? 0 : 1;        // promised zeros: x is g, and the zeros are not fetched
     p.e_is_zero = e_is_zero ? 1 : 0;
     p.e_out = e;
     p.q0 = q;

@@ -110,3 +110,33 @@ def test_lowrank_transformer_subset():
     L = len(batch.numels)
     choice = np.array([l % len(w.candidates) for l in range(L)], np.int32)
     _roundtrip(w, batch, choice, fro_tol=1e-3)
+
+
+@pytest.mark.parametrize("rank", (1, 7, 8, 9, 33, 63, 64))
+def test_lowrank_reconstruction_at_tile_edges(rank):
+    """Feedback and image at remainders of the 64 x 64 tiles, the column spans of 512 and the steps of 8 ranks."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    shapes = ((1, 1), (63, 65), (64, 64), (65, 63), (128, 512), (64, 513), (66, 511), (3, 641), (130, 1100), (700, 5))
+    w = W.Workload("lr_edges", shapes, ((W.LOWRANK, float(rank)),), 0, 100, "lowrank64", "normal0.1", (-3.0, -1.0), r_max=64)
+    batch = W.generate(w)
+    L = len(batch.numels)
+    choice = np.zeros(L, np.int32)
+    # P and Q as the payload holds them are exact here; of the product and the sum with x every element is off by at
+    # most (r + 2) 2^-24 (|P| |Q|^T + |x|), and with orthonormal columns || |P| |Q|^T || <= sqrt(r) ||x||
+    tol = (rank + 2) * 2.0 ** -24 * (rank ** 0.5 + 1.0)
+    layers, ctab = tables(batch, list(w.candidates))
+    g, e, q = to_device(batch)
+    h = B.Handle(int(batch.grads.size), L, 1, r_max=64)
+    offsets = B.payload_layout(layers, ctab, choice)
+    payload = torch.zeros(int(offsets[-1]) + 16, dtype=torch.uint8, device="cuda")
+    h.compress(g, e, layers, ctab, choice, payload, offsets, q)
+    pay, left = payload.cpu().numpy(), e.cpu().numpy()
+    h.close()
+    for l in range(L):
+        o, n, m_, n_ = int(batch.offsets[l]), int(batch.numels[l]), int(batch.rows[l]), int(batch.cols[l])
+        f = pay[offsets[l]:offsets[l] + 4 * (m_ + n_) * rank].view(np.float32).astype(np.float64)
+        image = f[:m_ * rank].reshape(m_, rank) @ f[m_ * rank:].reshape(n_, rank).T
+        x = (batch.grads[o:o + n] + batch.ef[o:o + n]).astype(np.float64)
+        assert np.linalg.norm(left[o:o + n] - (x - image.ravel())) <= tol * np.linalg.norm(x), (l, shapes[l])
+    _roundtrip(w, batch, choice, fro_tol=1e-4)
