@@ -67,7 +67,8 @@ struct lgreco_handle {
     // the sizes of a table the caller holds, pinned, as the kernel reads them
     int64_t* h_sizes = nullptr;
     int64_t* d_sizes = nullptr;
-    size_t sizes_count = 0;            // entries of h_sizes / d_sizes in use
+    int sizes_L = 0, sizes_P = 0;      // shape of the table in h_sizes / d_sizes / d_order (0: none; the order of a
+                                       // layer's candidates depends on where the flat table's rows end)
     double* d_errors_dev = nullptr;
     int64_t* h_table_sizes = nullptr;
     int64_t* d_table_sizes = nullptr;
@@ -1078,13 +1079,16 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
     }
     begin_call(h, s, LGRECO_CALL_SOLVE);
     // the size table lives on the device and is uploaded when it changes (a training loop repeats it)
-    if (h->sizes_count != (size_t)L * P || std::memcmp(h->h_sizes, sizes, sizeof(int64_t) * (size_t)L * P) != 0) {
+    if (h->sizes_L != L || h->sizes_P != P ||
+        std::memcmp(h->h_sizes, sizes, sizeof(int64_t) * (size_t)L * P) != 0) {
+        h->sizes_L = h->sizes_P = 0;          // (a copy that fails leaves nothing to go by)
         std::memcpy(h->h_sizes, sizes, sizeof(int64_t) * (size_t)L * P);
-        h->sizes_count = (size_t)L * P;
         HIPCHK(hipMemcpyAsync(h->d_sizes, h->h_sizes, sizeof(int64_t) * (size_t)L * P, hipMemcpyHostToDevice, s));
         size_order(sizes, L, P, h->h_order);
         HIPCHK(hipMemcpyAsync(h->d_order, h->h_order, (size_t)L * P, hipMemcpyHostToDevice, s));
         HIPCHK(hipStreamSynchronize(s));      // h_sizes may be rewritten by the next call
+        h->sizes_L = L;
+        h->sizes_P = P;
     }
     SolveParams sp = solve_params(h, L, P, n_bins);
     sp.order = h->d_order;

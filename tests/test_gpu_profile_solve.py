@@ -775,3 +775,59 @@ def test_strict_budget_through_the_one_call():
         assert torch.equal(pay, ref_pay) and torch.equal(ef.view(torch.int32), ref_ef.view(torch.int32))
     assert np.array_equal(choice, np.full(L, w.default, np.int32)), "the last case must have fallen back to the default"
     h.close()
+
+
+def _topk_tables(numels, densities):
+    from paper_2210_17357_amd import binding as B
+    offsets = np.concatenate([[0], np.cumsum(numels)[:-1]])
+    zero = np.zeros(len(numels), np.int64)
+    return B.layer_table(offsets, numels, zero, zero), B.cand_table([(W.TOPK, d) for d in densities])
+
+
+@pytest.mark.parametrize("first,second", [
+    # (layers, densities): flat size tables [800, 1600], eight times 8, [80, 160, 80, 160]
+    (((1000,), (0.1, 0.2)), ((1000, 2000), (0.1,))),
+    (((40, 20), (0.01, 0.02, 0.03, 0.005)), ((30, 40, 20, 25), (0.02, 0.01))),
+    (((1000, 1000), (0.01, 0.02)), ((1000, 2000, 1000, 2000), (0.01,))),
+    (((12, 9), (0.01, 0.02, 0.03)), ((12, 9, 7), (0.01, 0.02)))])
+@pytest.mark.parametrize("swap", [False, True])
+def test_equal_size_tables_of_different_shapes_on_one_handle(first, second, swap):
+    """Two problems whose flat size tables hold the same numbers, cut into rows differently, one after the
+    other on one handle: the order of each layer's candidates belongs to the second one's rows.  Both
+    calls against the oracle's solver and, with the payload, against a handle that has seen neither."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    rng = np.random.default_rng(11)
+    problems = [second, first] if swap else [first, second]
+    tabs = [_topk_tables(*p) for p in problems]
+    flat = [B.sizes(*t).reshape(-1) for t in tabs]
+    assert np.array_equal(flat[0], flat[1])
+    data = [torch.from_numpy(rng.standard_t(3, int(sum(p[0]))).astype(np.float32)).cuda() for p in problems]
+    n_max = max(d.numel() for d in data)
+    L_max, P_max = (max(len(p[i]) for p in problems) for i in (0, 1))
+
+    def step(h, i, bins=300):
+        pay = torch.zeros(int(flat[i].sum()) + 16 * 64, dtype=torch.uint8, device="cuda")
+        ef = torch.full_like(data[i], 0.125)
+        out = h.profile_solve_compress(data[i], ef, *tabs[i], len(problems[i][1]) - 1, bins, pay)
+        torch.cuda.synchronize()
+        return out, pay, ef
+
+    for one_call in (False, True):
+        h = B.Handle(n_max, L_max, P_max)
+        for i in (0, 1, 0):
+            L, P = (len(v) for v in problems[i])
+            if one_call:
+                out, pay, ef = step(h, i)
+                fresh = B.Handle(n_max, L_max, P_max)
+                want, pay_want, ef_want = step(fresh, i)
+                fresh.close()
+                assert torch.equal(pay, pay_want) and torch.equal(ef.view(torch.int32), ef_want.view(torch.int32))
+                assert np.array_equal(out[4], want[4])
+            else:
+                out = h.profile_solve(data[i], None, *tabs[i], P - 1, 300)
+            st, errors, sizes, e_max, choice, tsize = out[:6]
+            assert st == B.OK and errors.shape == (L, P)
+            ref_choice, ref_size, _ = solver.solve(errors, sizes, e_max, 300)
+            assert np.array_equal(choice, ref_choice) and tsize == ref_size, (one_call, i)
+        h.close()
