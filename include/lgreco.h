@@ -234,8 +234,9 @@ int lgreco_solve_static(const double* d_errors, const int64_t* d_sizes, int32_t 
  *   choice        host out [L]
  * Returns LGRECO_EINFEASIBLE with the minimum-error choice as lgreco_solve does.  Problems the
  * device-side step does not take (more than 1024 layers, more than 16384 table entries, more than
- * 4096 candidates left when those that cannot be used are dropped, total size of 2^30 bytes or
- * more, layer groups asked for) go through the three calls internally. */
+ * 4096 candidates left when those that cannot be used are dropped, rows of the table that do not
+ * fit on chip beside the candidates left, total size of 2^30 bytes or more, layer groups asked for)
+ * go through the three calls internally. */
 int lgreco_profile_solve(lgreco_handle_t* h, const float* d_grads, const float* d_ef,
                          const lgreco_layer_t* layers, int32_t L, const lgreco_cand_t* cands,
                          int32_t P, const float* d_q0, int32_t default_cand, int32_t n_bins,

@@ -1206,7 +1206,7 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
         }
         return LGRECO_EINFEASIBLE;
     }
-    if (status == 4) {                                      // more entries than the kernel holds
+    if (status == 4) {                                      // not taken by the kernel
         HIPCHK(hipStreamSynchronize(s));
         st = lgreco_solve(h, errors, sizes, L, P, *e_max, n_bins, choice, total_size, total_error, stream);
         if (st == LGRECO_EINFEASIBLE && h->cfg.strict_budget) return strict_default(errors, sizes);

@@ -202,10 +202,12 @@ struct SolveParams {
     int32_t have_e_max;           // ... unless the caller gives it
     double e_max;
     int32_t e_limit;              // the bins of an accepted assignment sum to at most min(D, e_limit)
+    int32_t last_resort;          // 1: the caller has nothing to fall back to (lists of up to 64 candidates only)
     int32_t check_sizes;          // 1: reject (status 3) sizes this path's 32-bit costs cannot hold
     int32_t* choice;              // out [L] candidate per layer, -1 when not solved
-    int64_t* result;              // out [16]: [0] status (0 ok, 1 infeasible, 2 inconsistent, 3 invalid input, 4 table too
-                                  //      large for this kernel), [1] size and [2] bins of the layers that were not fixed at
+    int64_t* result;              // out [16]: [0] status (0 ok, 1 infeasible, 2 inconsistent, 3 invalid input, 4 not
+                                  //      taken here: more than kSolveMaxEntries candidates left, or rows that do not fit
+                                  //      beside them, see last_resort), [1] size and [2] bins of the layers that were not fixed at
                                   //      bin 0, [3] ticks, [5] L, [6] bit pattern of E_max, [8] records written, [9] 0,
                                   //      [10] / [11] check words over choice / error table, [4], [15] and, last, [7] seq
     int64_t seq;

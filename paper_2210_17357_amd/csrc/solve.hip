@@ -36,6 +36,7 @@ constexpr int kMaxLayersS = kSolveMaxLayers;
 constexpr int kMaxT = kSolveMaxEntries;
 constexpr uint32_t kUnusable = 0xFFFFu;      // bin of a candidate whose error exceeds the budget (bins are at most 16384)
 constexpr uint32_t kInfS = 1u << 30;
+constexpr int kMaxRow = 17 * kThreadsS;      // cells of a row: at least LGRECO_MAX_BINS + 1
 constexpr int kRowCells = 4096;              // past this many bins intervals are worked out in any case
 constexpr size_t kRegionBytes = (size_t)kSolveMaxLP * 6;      // LDS: the table's bins and sizes, later see Relax and Core
 
@@ -314,54 +315,78 @@ __device__ __forceinline__ const uint32_t* sweep(const Sweep& p) {
     return n_core & 1 ? row1 : row0;
 }
 
-// The last resort where a row's margins do not fit LDS: every shifted read is clamped into the row, which
-// has a cell of infinity on either side.
+// Where survivors, rows and margins do not fit LDS together (tables whose candidates all stay and whose bins reach
+// far) and the caller has no other solver (SolveParams::last_resort): layer records and one row, no wider than the
+// widest interval, with a cell of infinity on either side into which every shifted read is clamped.  The
+// candidates are taken from the lists (Lds) and their bits of `keep`: lane k of every wavefront holds the k-th of a
+// layer in candidate order, so that a list has at most 64.  Arg-mins: candidates.  K cells per thread.
+// cand_bits: the candidate rides in that many low bits of the costs (0: beside them).  Bound by the instructions
+// issued, per entry and cell an address, its clamp, a read, a sum and a minimum (or a compare and two selects):
+// 628 layers of 6 candidates, 6656 bins: 1.8 ms; 256 of 16, 16380 bins: 2.7 ms.  Callers that do have another solver
+// take it: on 60 layers of 40 candidates, 10000 bins, the layer groups of dp.hip take 0.87 ms with this kernel's
+// attempt in front, a clamped sweep 2.1.
 __device__ __forceinline__ int clamp_i32(int v, int lo, int hi) {
     int r;
     asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(v), "s"(lo), "v"(hi));
     return r;
 }
-constexpr int kClampCells = 17;              // per thread: rows of up to 17407 cells
-__device__ __forceinline__ const uint32_t* sweep_clamped(const Sweep& p) {
-    constexpr int NT = kThreadsS, KMAX = kClampCells;
-    const int tid = threadIdx.x;
-    uint32_t* const cur = p.buffer + 1;
+template <int K, bool PACK>
+__device__ __forceinline__ const uint32_t* sweep_lists(const Lds& s, const Core* core, uint32_t* buffer, uint8_t* pd, int n_core,
+                                                       int cand_bits) {
+    const uint32_t cands = (1u << cand_bits) - 1u;
+    constexpr int NT = kThreadsS;
+    const int tid = threadIdx.x, lane = tid & 63;
+    uint32_t* const cur = buffer + 1;
+    static_assert(kInfS == kInfPacked, "one infinity");
     if (tid == 0) { cur[-1] = kInfS; cur[0] = 0; cur[1] = kInfS; }
-    const uint2* e = p.ent;
-    uint8_t* out = p.pd + tid;
+    uint8_t* out = pd + tid;
+    const int row_at = __builtin_amdgcn_readfirstlane((int)lds_address(cur));
+    int w_front = 1, lo_front = 0;
     __syncthreads();
-    for (int j = 0; j < p.n_core; ++j) {
-        const Core c0 = p.core[j];
-        const int nw = (int)(c0.shape & 0xFFFFu), n = __builtin_amdgcn_readfirstlane((int)(c0.shape >> 16));
-        const int before = __builtin_amdgcn_readfirstlane(j ? (int)(p.core[j - 1].shape & 0xFFFFu) : 1);
-        uint32_t nv[KMAX], na[KMAX];
+    for (int j = 0; j < n_core; ++j) {
+        const int nw = __builtin_amdgcn_readfirstlane((int)(core[j].shape & 0xFFFFu));
+        const int lo = __builtin_amdgcn_readfirstlane(core[j].lo), i = s.lo[j];
+        const int first = __builtin_amdgcn_readfirstlane(s.off[i]), count = __builtin_amdgcn_readfirstlane(s.off[i + 1]) - first;
+        // this lane's entry of the list, then the one whose rank among the layer's candidates it is
+        const int at = first + min(lane, count - 1);
+        const bool kept = lane < count && ((s.keep[at >> 6] >> (at & 63)) & 1);
+        const unsigned long long m = __ballot(kept);
+        const int cand = s.cand[at];
+        int rank = 0;
+        for (unsigned long long w = m; w; w &= w - 1) rank += (int)lane_u32((uint32_t)cand, (int)__builtin_ctzll(w)) < cand ? 1 : 0;
+        const int n = (int)__popcll(m), to = 4 * (kept ? rank : 63);           // (with 64 kept nobody is sent to 63 beside its owner)
+        const uint32_t bin_cand = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)((uint32_t)s.bin[at] << 8 | (uint32_t)cand));
+        const uint32_t size = (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(PACK ? s.size[at] << cand_bits | (uint32_t)cand : s.size[at]));
+        const int behind = row_at + 4 * w_front, from = row_at + 4 * (tid + lo - lo_front);
+        uint32_t nv[K], na[K];
 #pragma unroll
-        for (int k = 0; k < KMAX; ++k) { nv[k] = kInfS; na[k] = 255u; }
-        const uint32_t row_at = lds_address(cur);
-        const int from = (int)row_at + 4 * tid, below = __builtin_amdgcn_readfirstlane((int)row_at - 4);
-        const int behind = (int)row_at + 4 * before;
+        for (int k = 0; k < K; ++k) { nv[k] = kInfS; na[k] = 255u; }
         for (int c = 0; c < n; ++c) {
-            const uint2 x = e[c];
-            const uint32_t z = x.y == kInfPacked ? kInfS : x.y >> p.bits;
-            const int f = from + (int)x.x;
+            const uint32_t bc = lane_u32(bin_cand, c), z = lane_u32(size, c), cd = bc & 255u;
+            const int f = from - 4 * (int)(bc >> 8);
 #pragma unroll
-            for (int k = 0; k < KMAX; ++k) {
-                const uint32_t v = lds_load((uint32_t)clamp_i32(f + 4 * k * NT, below, behind)) + z;
-                const bool lt = v < nv[k];
-                nv[k] = lt ? v : nv[k];
-                na[k] = lt ? (uint32_t)c : na[k];
+            for (int k = 0; k < K; ++k) {
+                const uint32_t v = lds_load((uint32_t)clamp_i32(f + 4 * k * NT, row_at - 4, behind)) + z;
+                if (PACK) {
+                    nv[k] = min(nv[k], v);
+                } else {
+                    const bool lt = v < nv[k];
+                    nv[k] = lt ? v : nv[k];
+                    na[k] = lt ? cd : na[k];
+                }
             }
         }
-        e += (n + 3) & ~3;
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < KMAX; ++k) {
+        for (int k = 0; k < K; ++k) {
             const int t = tid + k * NT;
-            if (t <= nw) cur[t] = t < nw ? nv[k] : kInfS;
-            if (t < nw) out[k * NT] = (uint8_t)na[k];
+            if (t <= nw) cur[t] = t < nw ? (PACK ? nv[k] & ~cands : nv[k]) : kInfS;
+            if (t < nw) out[k * NT] = (uint8_t)(PACK ? nv[k] & cands : na[k]);
         }
         __syncthreads();
         out += nw;
+        w_front = nw;
+        lo_front = lo;
     }
     return cur;
 }
@@ -1073,28 +1098,38 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
             Sweep sw{rec, ent, reinterpret_cast<uint32_t*>(region + at_row), p.pd, (int)s.facts[0],
                      (int)(s.facts[0] + s.facts[1]) + row_cells, n_core, 0};
             size_t row_bytes = sizeof(uint32_t) * (size_t)sw.cells * (form.two ? 2 : 1);
-            const bool clamped = at_row + row_bytes > kRegionBytes;
-            if (clamped) row_bytes = sizeof(uint32_t) * (kClampCells * kThreadsS + 2);
-            const bool pd_lds = !clamped && at_row + row_bytes + cells + (size_t)row_cells <= kRegionBytes;
+            const bool lists = at_row + row_bytes > kRegionBytes;
+            const bool pd_lds = !lists && at_row + row_bytes + cells + (size_t)row_cells <= kRegionBytes;
             if (pd_lds) sw.pd = region + at_row + row_bytes;
             sw.bits = bits;
             // (lists long enough that the positions do not fit the costs or a word are swept with bytes)
-            const bool words = !clamped && !pd_lds && bits && s.facts[2] <= 64 && form.threads == kThreadsS && form.per * bits <= 32 &&
+            const bool words = !lists && !pd_lds && bits && s.facts[2] <= 64 && form.threads == kThreadsS && form.per * bits <= 32 &&
                                ((size_t)p.pd & 3) == 0 && (size_t)n_core * 4 * kThreadsS <= (size_t)L * (size_t)(p.D + 1);
             if (s.flags & 4) {
                 status = 2;
             } else if ((s.flags & 8) || (int)shift_all > D) {        // a layer no bin sum can reach
                 status = reduce ? 2 : 1;
-            } else if (at_row + row_bytes > kRegionBytes) {
+            } else if (lists && !(p.last_resort && P <= 64)) {
                 status = 4;
             } else {
                 const uint32_t* last = sw.buffer;
-                const int row_bits = clamped ? 0 : bits;
+                const int cand_bits = 32 - __builtin_clz(P - 1);                       // (lists: P is at least 2)
+                const bool pack_cand = ((unsigned long long)s.facts[3] << cand_bits) < kInfPacked;
+                const int row_bits = lists ? (pack_cand ? cand_bits : 0) : bits;
                 if (n_core == 0) {
                     if (tid == 0) sw.buffer[0] = 0;
                     __syncthreads();
-                } else if (clamped) {
-                    last = sweep_clamped(sw);
+                } else if (lists) {              // (the row takes the survivors' place)
+                    uint32_t* const buffer = reinterpret_cast<uint32_t*>(ent);
+                    if (w_max < 6 * kThreadsS)
+                        last = pack_cand ? sweep_lists<6, true>(s, rec, buffer, p.pd, n_core, cand_bits)
+                                         : sweep_lists<6, false>(s, rec, buffer, p.pd, n_core, 0);
+                    else if (w_max < 10 * kThreadsS)
+                        last = pack_cand ? sweep_lists<10, true>(s, rec, buffer, p.pd, n_core, cand_bits)
+                                         : sweep_lists<10, false>(s, rec, buffer, p.pd, n_core, 0);
+                    else
+                        last = pack_cand ? sweep_lists<kMaxRow / kThreadsS, true>(s, rec, buffer, p.pd, n_core, cand_bits)
+                                         : sweep_lists<kMaxRow / kThreadsS, false>(s, rec, buffer, p.pd, n_core, 0);
                 } else if (words) {
                     last = sweep_shaped<true, true, false>(form, sw);
                 } else if (bits) {
@@ -1126,7 +1161,20 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
                     // ---- back-trace: one arg-min byte per core layer is the chain; records and survivors'
                     // bins are fetched ahead of it.  A byte that cannot be is caught by the sums below
                     // (LDS reads stay in range by themselves; the walk in device memory is clamped).
-                    if (wave == 0 && n_core > 0) {
+                    if (lists && wave == 0) {
+                        int t = (int)(uint32_t)b - base;
+                        for (int j = n_core - 1; j >= 0; --j) {
+                            const int a = min(max(rec[j].trace + t, 0), (int)cells - 1), i = s.lo[j];
+                            const uint32_t cd = (uint32_t)__builtin_amdgcn_readfirstlane((int)p.pd[a]);
+                            const int first = s.off[i], k0 = first + lane;       // (a list holds a candidate once)
+                            const unsigned long long m = __ballot(k0 < s.off[i + 1] && s.cand[min(k0, kMaxT - 1)] == cd);
+                            if (!m) break;                // (the sums below differ)
+                            const int k = first + (int)__builtin_ctzll(m);
+                            if (lane == 0) s.hi[j] = k;
+                            t += rec[j].step - (int)s.bin[k];
+                        }
+                        if (lane == 0 && t != 0) atomicOr(&s.flags, 16);
+                    } else if (wave == 0 && n_core > 0) {
                         // (in places of the rows: the sum of bins less the row's first; in front of the first layer 0)
                         int t = (int)(uint32_t)b - base;
                         const uint32_t pd_at = lds_address(reinterpret_cast<const uint32_t*>(region)) + (uint32_t)(at_row + row_bytes);
@@ -1183,7 +1231,12 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
                         pz = s.size[only];
                         s.chosen[s.layer[tid]] = s.cand[only];
                     }
-                    if (tid < n_core) {
+                    if (lists && tid < n_core) {          // (the walk left the entries)
+                        const int at = min(s.hi[tid], kMaxT - 1);
+                        pb += s.bin[at];
+                        pz += s.size[at];
+                        s.chosen[s.layer[s.lo[tid]]] = s.cand[at];
+                    } else if (tid < n_core) {
                         const int at = s.hi[tid] + min((int)s.pick[tid], (int)(rec[tid].shape >> 16) - 1);
                         const uint2 x = ent[at];
                         pb += (uint32_t)(rec[tid].step - ((int)x.x >> 2));
@@ -1285,6 +1338,9 @@ hipError_t launch_solve(const SolveParams& p, hipStream_t s, Section* sec) {
     const size_t lds = sizeof(Lds) + kRegionBytes;
     static_assert(sizeof(Lds) % 16 == 0 && sizeof(Lds) + kRegionBytes <= 160 * 1024, "LDS of one compute unit");
     static_assert(kRegionBytes >= sizeof(Relax), "the intervals' tables fit");
+    static_assert(kMaxRow > LGRECO_MAX_BINS, "a thread's cells cover the widest row");
+    static_assert(kRegionBytes >= sizeof(Core) * kSolveMaxLayers + sizeof(uint32_t) * (LGRECO_MAX_BINS + 3),
+                  "records and the widest row always fit");
     static bool configured = false;
     if (!configured) {
         hipError_t e = hipFuncSetAttribute((const void*)solve_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -19,6 +19,7 @@ constexpr size_t kStaticPdBytes = LGRECO_STATIC_MAX_PD_BYTES;   // arg-min table
 constexpr size_t kOffResult = kStaticPdBytes;                   // int64 [16] (+ pad)
 static_assert(kOffResult + 256 == sizeof(scratch), "the array above is declared with this size");
 static_assert(kStaticMaxLP <= kSolveMaxEntries, "such a table never has too many entries for the kernel");
+static_assert(kStaticMaxP <= 64, "nor too long a list for its last resort");
 
 constexpr int kMaxDevices = 64;
 unsigned char* g_scratch_ptr[kMaxDevices] = {};
@@ -100,6 +101,7 @@ extern "C" int lgreco_solve_static(const double* d_errors, const int64_t* d_size
     sp.default_cand = default_cand;
     sp.e_limit = n_bins;
     sp.check_sizes = 1;
+    sp.last_resort = 1;
     sp.choice = d_choice;
     sp.result = result;
     sp.seq = 1;

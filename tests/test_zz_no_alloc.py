@@ -99,3 +99,37 @@ def test_paper_default_bins_and_limits():
     assert st == 3 and (choice == -1).all()
     choice, st, *_ = _run_static(np.array([[1.0, np.nan], [1.0, 1.0]]), np.ones((2, 2), np.int64), 0, 10)
     assert st == 3 and (choice == -1).all()
+
+
+@pytest.mark.parametrize("L,P,D,reach", [
+    # records, survivors, row and margins together past what a compute unit holds (rows of up to 6143 cells, and wider)
+    (1024, 4, 4095, 4000), (819, 5, 5000, 1000), (682, 6, 6140, 6000), (628, 6, 6656, 3000), (256, 16, 16380, 16000),
+    # lists of unequal lengths
+    (500, 8, 8000, 7000)])
+@pytest.mark.parametrize("shuffled,unit", [(False, 1), (True, 1), (True, 40)])
+def test_tables_on_which_nothing_can_be_dropped(L, P, D, reach, shuffled, unit):
+    """Every layer's sizes fall linearly with its bins at the same rate, so that no bound takes a candidate
+    out and almost every choice ties: within its limits the call solves these like any other, with Algorithm 1's
+    tie-breaks (candidates in order of size and in any order, costs with and without room for the candidate)."""
+    from oracle import solver
+    rng = np.random.default_rng(L + P)
+    step = reach // (P - 1)
+    bins = np.tile(step * np.arange(P - 1, -1, -1), (L, 1))
+    errors = bins + 0.25
+    errors[0, P - 1] = D - 0.25 * (L - 1)                  # the default's errors add up to D: an error is its bin
+    sizes = unit * (1000 + step * (P - 1) - bins).astype(np.int64)
+    if L == 500:                                           # candidates another one beats
+        drop = rng.random((L, P)) < 0.4
+        drop[:, [0, P - 1]] = False
+        errors[drop] += step
+    default = P - 1
+    if shuffled:
+        for l in range(1, L):
+            order = np.concatenate([rng.permutation(P - 1), [P - 1]])
+            errors[l], sizes[l] = errors[l][order], sizes[l][order]
+    e_max = solver.e_max_uniform(errors, default)
+    assert e_max == D
+    ref_choice, ref_size, _ = solver.solve(errors, sizes, e_max, D)
+    choice, status, tsize, terr, emax_dev = _run_static(errors, sizes, default, D)
+    assert status == 0 and emax_dev == e_max
+    assert np.array_equal(choice, ref_choice) and tsize == ref_size
