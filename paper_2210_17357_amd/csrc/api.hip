@@ -844,78 +844,35 @@ int lgreco_profile(lgreco_handle_t* h, const float* d_grads, const float* d_ef, 
     return LGRECO_OK;
 }
 
-int lgreco_solve(lgreco_handle_t* h, const double* errors, const int64_t* sizes, int32_t L, int32_t P,
-                 double e_max, int32_t n_bins, int32_t* choice, int64_t* total_size, double* total_error,
-                 void* stream) {
-    if (!h || !errors || !sizes || !choice || L <= 0 || P <= 0) return LGRECO_EINVAL;
-    if (n_bins < 1 || n_bins > LGRECO_MAX_BINS || !(e_max == e_max)) return LGRECO_EINVAL;
-    if (L > h->max_layers || P > h->max_cands) return LGRECO_ENOSPACE;
-    hipStream_t s = (hipStream_t)stream;
-    begin_call(h, s, LGRECO_CALL_SOLVE);
-    auto infeasible = [&]() {
-        for (int l = 0; l < L; ++l) {           // report each layer's minimum-error candidate
-            int best = 0;
-            for (int c = 1; c < P; ++c)
-                if (errors[(size_t)l * P + c] < errors[(size_t)l * P + best]) best = c;
-            choice[l] = best;
-        }
-        return LGRECO_EINFEASIBLE;
-    };
-    auto totals = [&]() {
-        double terr = 0.0;
-        int64_t tsize = 0;
-        for (int l = 0; l < L; ++l) {
-            terr += errors[(size_t)l * P + choice[l]];
-            tsize += sizes[(size_t)l * P + choice[l]];
-        }
-        if (total_size) *total_size = tsize;
-        if (total_error) *total_error = terr;
-        return LGRECO_OK;
-    };
-    // One kernel takes the table as it is, read from pinned memory, wherever 32-bit costs hold it and
-    // no layer groups are asked for.
-    if (one_kernel_solve(h, L, P)) {
-        int64_t all = 0;
-        for (int l = 0; l < L; ++l) {
-            int64_t big = 0;
-            for (int c = 0; c < P; ++c) {
-                const size_t i = (size_t)l * P + c;
-                if (sizes[i] < 0 || sizes[i] >= ((int64_t)1 << 45) || !(errors[i] == errors[i])) return LGRECO_EINVAL;
-                big = std::max(big, sizes[i]);
-            }
-            all += big;
-        }
-        if (all < ((int64_t)1 << 30)) {
-            std::memcpy(h->h_errors, errors, sizeof(double) * (size_t)L * P);
-            std::memcpy(h->h_table_sizes, sizes, sizeof(int64_t) * (size_t)L * P);
-            size_order(sizes, L, P, h->h_order);
-            SolveParams sp = solve_params(h, L, P, n_bins);
-            sp.order = h->d_order_host;
-            sp.errors = h->d_errors;
-            sp.sizes = h->d_table_sizes;
-            sp.have_e_max = 1;
-            sp.e_max = e_max;
-            {
-                Section sec(h->tm, "dp_solve", true);
-                HIPCHK(launch_solve(sp, s, &sec));
-            }
-            harvest_others(h);
-            const int wst = wait_for_solver(h, h->dp_seq, s, L);
-            if (wst != LGRECO_OK) return wst;
-            const int64_t status = h->h_result[0];
-            if (status == 1) return infeasible();
-            if (status == 0) {
-                h->last_solve_groups = 0;
-                if (h->tm->active) record_dp_sub(h);
-                std::memcpy(choice, h->h_choice, sizeof(int32_t) * (size_t)L);
-                return totals();
-            }
-            if (status != 4) {
-                h->hip_error = "dp back-trace inconsistent";
-                return LGRECO_EHIP;
-            }
-        }
+// What a solve that found no assignment reports: each layer's minimum-error candidate.
+static int infeasible_choice(const double* errors, int32_t L, int32_t P, int32_t* choice) {
+    for (int l = 0; l < L; ++l) {
+        int best = 0;
+        for (int c = 1; c < P; ++c)
+            if (errors[(size_t)l * P + c] < errors[(size_t)l * P + best]) best = c;
+        choice[l] = best;
     }
+    return LGRECO_EINFEASIBLE;
+}
+
+static int assignment_totals(const double* errors, const int64_t* sizes, int32_t L, int32_t P, const int32_t* choice,
+                             int64_t* total_size, double* total_error) {
+    double terr = 0.0;
+    int64_t tsize = 0;
+    for (int l = 0; l < L; ++l) {
+        terr += errors[(size_t)l * P + choice[l]];
+        tsize += sizes[(size_t)l * P + choice[l]];
+    }
+    if (total_size) *total_size = tsize;
+    if (total_error) *total_error = terr;
+    return LGRECO_OK;
+}
+
+// The solve over the whole table (dp.hip), for what the one-kernel solve does not take: lists built here, swept
+// in as many layer groups as the configuration asks for (dp_groups 0: chosen from the table's size).
+static int solve_whole_table(lgreco_handle_t* h, const double* errors, const int64_t* sizes, int32_t L, int32_t P,
+                             double e_max, int32_t n_bins, int32_t* choice, int64_t* total_size, double* total_error,
+                             hipStream_t s) {
     const double D = (double)n_bins;
     int64_t worst = 0;                  // sum over layers of the largest usable size
     int max_bin = 0;
@@ -983,8 +940,8 @@ int lgreco_solve(lgreco_handle_t* h, const double* errors, const int64_t* sizes,
             ++n_sweep;
         }
     }
-    if (dead_layer) return infeasible();
-    if (h->cfg.strict_budget && n_bins - L < 0) return infeasible();      // more layers than bins: nothing is certain to fit
+    if (dead_layer) return infeasible_choice(errors, L, P, choice);
+    if (h->cfg.strict_budget && n_bins - L < 0) return infeasible_choice(errors, L, P, choice);      // more layers than bins: nothing is certain to fit
     if (n_sweep > 0) {
         const bool narrow = worst < ((int64_t)1 << 30);
         // the kernel's table has max_count entries per layer: the upload carries no unused slots
@@ -1008,14 +965,69 @@ int lgreco_solve(lgreco_handle_t* h, const double* errors, const int64_t* sizes,
         }
         h->last_solve_groups = h->h_result[9];
         if (h->tm->active) record_dp_sub(h);
-        if (h->h_result[0] == 1) return infeasible();
+        if (h->h_result[0] == 1) return infeasible_choice(errors, L, P, choice);
         if (h->h_result[0] != 0) {
             h->hip_error = "dp back-trace inconsistent";
             return LGRECO_EHIP;
         }
         for (int i = 0; i < n_sweep; ++i) choice[h->h_bins[i]] = h->h_choice[i];
     }
-    return totals();
+    return assignment_totals(errors, sizes, L, P, choice, total_size, total_error);
+}
+
+int lgreco_solve(lgreco_handle_t* h, const double* errors, const int64_t* sizes, int32_t L, int32_t P,
+                 double e_max, int32_t n_bins, int32_t* choice, int64_t* total_size, double* total_error,
+                 void* stream) {
+    if (!h || !errors || !sizes || !choice || L <= 0 || P <= 0) return LGRECO_EINVAL;
+    if (n_bins < 1 || n_bins > LGRECO_MAX_BINS || !(e_max == e_max)) return LGRECO_EINVAL;
+    if (L > h->max_layers || P > h->max_cands) return LGRECO_ENOSPACE;
+    hipStream_t s = (hipStream_t)stream;
+    begin_call(h, s, LGRECO_CALL_SOLVE);
+    // One kernel takes the table as it is, read from pinned memory, wherever 32-bit costs hold it and
+    // no layer groups are asked for.
+    if (one_kernel_solve(h, L, P)) {
+        int64_t all = 0;
+        for (int l = 0; l < L; ++l) {
+            int64_t big = 0;
+            for (int c = 0; c < P; ++c) {
+                const size_t i = (size_t)l * P + c;
+                if (sizes[i] < 0 || sizes[i] >= ((int64_t)1 << 45) || !(errors[i] == errors[i])) return LGRECO_EINVAL;
+                big = std::max(big, sizes[i]);
+            }
+            all += big;
+        }
+        if (all < ((int64_t)1 << 30)) {
+            std::memcpy(h->h_errors, errors, sizeof(double) * (size_t)L * P);
+            std::memcpy(h->h_table_sizes, sizes, sizeof(int64_t) * (size_t)L * P);
+            size_order(sizes, L, P, h->h_order);
+            SolveParams sp = solve_params(h, L, P, n_bins);
+            sp.order = h->d_order_host;
+            sp.errors = h->d_errors;
+            sp.sizes = h->d_table_sizes;
+            sp.have_e_max = 1;
+            sp.e_max = e_max;
+            {
+                Section sec(h->tm, "dp_solve", true);
+                HIPCHK(launch_solve(sp, s, &sec));
+            }
+            harvest_others(h);
+            const int wst = wait_for_solver(h, h->dp_seq, s, L);
+            if (wst != LGRECO_OK) return wst;
+            const int64_t status = h->h_result[0];
+            if (status == 1) return infeasible_choice(errors, L, P, choice);
+            if (status == 0) {
+                h->last_solve_groups = 0;
+                if (h->tm->active) record_dp_sub(h);
+                std::memcpy(choice, h->h_choice, sizeof(int32_t) * (size_t)L);
+                return assignment_totals(errors, sizes, L, P, choice, total_size, total_error);
+            }
+            if (status != 4) {
+                h->hip_error = "dp back-trace inconsistent";
+                return LGRECO_EHIP;
+            }
+        }
+    }
+    return solve_whole_table(h, errors, sizes, L, P, e_max, n_bins, choice, total_size, total_error, s);
 }
 
 // lgreco_profile_solve; with `ec`, also the compression's first kernel (see EarlyCompress).
@@ -1197,18 +1209,10 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
     if (status == 3) return LGRECO_EINVAL;                  // a NaN in the error table
     if (h->tm->active && status == 0) record_dp_sub(h);
     if (status == 1 && h->cfg.strict_budget) return strict_default(errors, sizes);
-    if (status == 1) {                                      // report each layer's minimum-error candidate
-        for (int l = 0; l < L; ++l) {
-            int best = 0;
-            for (int c = 1; c < P; ++c)
-                if (errors[(size_t)l * P + c] < errors[(size_t)l * P + best]) best = c;
-            choice[l] = best;
-        }
-        return LGRECO_EINFEASIBLE;
-    }
+    if (status == 1) return infeasible_choice(errors, L, P, choice);
     if (status == 4) {                                      // not taken by the kernel
-        HIPCHK(hipStreamSynchronize(s));
-        st = lgreco_solve(h, errors, sizes, L, P, *e_max, n_bins, choice, total_size, total_error, stream);
+        begin_call(h, s, LGRECO_CALL_SOLVE);
+        st = solve_whole_table(h, errors, sizes, L, P, *e_max, n_bins, choice, total_size, total_error, s);
         if (st == LGRECO_EINFEASIBLE && h->cfg.strict_budget) return strict_default(errors, sizes);
         return st;
     }

@@ -831,3 +831,49 @@ def test_equal_size_tables_of_different_shapes_on_one_handle(first, second, swap
             ref_choice, ref_size, _ = solver.solve(errors, sizes, e_max, 300)
             assert np.array_equal(choice, ref_choice) and tsize == ref_size, (one_call, i)
         h.close()
+
+
+@pytest.mark.parametrize("groups", [0, 1])
+@pytest.mark.parametrize("kind", ["many densities", "known thresholds"])
+def test_tables_with_more_entries_than_the_one_kernel_takes(kind, groups):
+    """More than 4096 candidates worth keeping: the kernel behind the profile reports that it does not take
+    the table, the compression kernels queued behind it must find no layer to work on, and the solve over the
+    whole table (in layer groups, or with dp_groups 1 in one sweep) and the host's compression route take over, once."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    rng = np.random.default_rng(4)
+    if kind == "many densities":
+        numels, densities, default = rng.integers(3000, 5000, 110), [i / 1000 for i in range(1, 101)], 9
+    else:                               # up to 8 densities: the Top-K kernels are queued behind the solver too
+        numels, densities, default = rng.integers(300, 900, 700), [0.02, 0.05, 0.1, 0.15, 0.22, 0.3, 0.45, 0.6], 0
+    n_bins = 16384
+    layers, ctab = _topk_tables(numels.tolist(), densities)
+    g = torch.from_numpy(rng.standard_normal(int(numels.sum())).astype(np.float32)).cuda()
+    e = 0.25 * torch.roll(g, 3)
+    L, P = len(numels), len(densities)
+    capacity = int(B.sizes(layers, ctab).max(axis=1).sum()) + 16 * (L + 1)
+    h = B.Handle(g.numel(), L, P, dp_groups=groups)
+    plain = B.Handle(g.numel(), L, P)
+    h.set_timing(1)
+    out = h.profile_solve(g, e, layers, ctab, default, n_bins)
+    route = h.last_solve_groups()
+    solves = {n: c for n, _, c in h.get_timing_totals(B.CALL_SOLVE)}["dp_solve"]
+    h.set_timing(0)
+    assert out[0] == B.OK
+    bins = solver.discretise(out[1], out[3], n_bins)
+    kept = 0
+    for l in range(L):                  # sizes rise with the density: what has a bin of its own below all before it
+        lowest = np.minimum.accumulate(np.concatenate([[n_bins + 1], bins[l]]))[:-1]
+        kept += int(((bins[l] != solver.UNUSABLE) & (bins[l] < lowest)).sum())
+    assert kept > 4096
+    ref_choice, ref_size, _ = solver.solve(out[1], out[2], out[3], n_bins)
+    assert np.array_equal(out[4], ref_choice) and out[5] == ref_size
+    assert (route != 0) == (groups == 0 and P <= 64), "layer groups take lists of up to 64"
+    assert solves == 2, "the kernel behind the profile, then the whole table"
+    one = _one_call_against_separate(h, plain, g, e, layers, ctab, default, n_bins, capacity, kind)
+    assert np.array_equal(one[4], ref_choice)
+    # the handle's next, smaller problem takes the usual route
+    few_layers, few = _topk_tables([1000, 800], densities[:2])
+    _one_call_against_separate(h, plain, g, e, few_layers, few, 0, 100, capacity, "after")
+    h.close()
+    plain.close()
