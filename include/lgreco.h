@@ -93,11 +93,12 @@ typedef struct {
                             * the previous call's thresholds instead of sampling the data first;
                             * the sample of every call now costs less than one step whose gradient
                             * differs from the last one's in size did.) */
-    int32_t  dp_groups;    /* solver: 0, 1 = one sequential sweep, over the cells and candidates an
-                            * assignment of the smallest size can use; 2, 4, 8 = sweep the whole table
-                            * with the layers in that many groups side by side and join the groups'
-                            * tables (results are the same in every case, Algorithm 1's tie-breaks
-                            * included) */
+    int32_t  dp_groups;    /* solver: 0, 1 = one sweep, over the cells and candidates an assignment of the
+                            * smallest size can use; 2, 4, 8 = sweep the whole table with the layers
+                            * in that many groups side by side and join the groups' tables.  What the
+                            * one sweep does not take (see lgreco_profile_solve) is swept whole, with 1
+                            * sequentially, with 0 in a number of groups chosen from its size.
+                            * (Results are the same in every case, Algorithm 1's tie-breaks included) */
     int32_t  strict_budget; /* solver: 0 = Algorithm 1's constraint on the discretised errors, sum of
                             * bins <= n_bins, under which the real errors may exceed e_max by up to
                             * L steps (see lgreco_solve); 1 = only assignments whose bins sum to at
