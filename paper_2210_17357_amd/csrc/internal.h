@@ -258,9 +258,6 @@ struct TopkScratch {
     uint32_t* d_many_in = nullptr;
     int nk_many = 0;                  // densities of the current call, 0: at most kMaxTopk
     void* d_many = nullptr;           // per-layer records
-    unsigned long long* d_cell_many = nullptr;   // per (work item, list): partial histogram, and
-    double* d_below_many = nullptr;              // the energy below the list's bin
-    size_t many_lists = 0;            // (work item, list) pairs the two hold
     void* d_work = nullptr;           // refinement work table and per-layer ranges
     void* d_work_range = nullptr;
     void* h_work = nullptr;

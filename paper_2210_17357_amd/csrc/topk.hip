@@ -788,14 +788,14 @@ struct RefineParams {
     int32_t stride;
     int32_t ntk;
     int32_t col[kMaxTopk];
-    // more than kMaxTopk densities: the layers' records, and per (work item, list), nk lists in a
-    // row, the partial histogram and the energy below the list's bin
+    // more than kMaxTopk densities: the layers' records, and per (work item, list of this pass), `room` lists
+    // in a row, the partial histogram and the energy below the list's bin
     const TopkMany* many;
     const int64_t* cand_base;
     const int32_t* cols;              // [nk] column of every density
     unsigned long long* cell_many;
     double* below_many;
-    int32_t nk;
+    int32_t list0, room;              // the lists of this pass: [list0, list0 + room) of every layer
     // the second collection of a layer whose predicted bound was too high (flagged by the scan):
     // every workgroup of the first refinement kernel makes it for its own tiles before it looks at
     // their candidates (rc.ef_out not null: the compression's form, which also writes x)
@@ -1185,7 +1185,9 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
 // ---- more than kMaxTopk densities
 // All of them are resolved at once on the candidates collected once.  What is shared between densities is worked
 // out once per list (distinct threshold bin; 100 densities between 0.1 % and 10 % have about 25), and the lists
-// are dealt to workgroups in chunks of 8, as many as keep two workgroups on a compute unit.  In groups of 8
+// are dealt to workgroups in chunks of 8, as many as keep two workgroups on a compute unit.  The partial histograms go
+// where those of up to 8 densities do, 14 lists or more per work item; what does not fit (many layers with many
+// lists each) takes further passes of these two kernels.  In groups of 8
 // densities, each with its own upload, scan, refinement and pick, the 100 densities of a 26 M-element
 // model took 13 times 80 us, nearly all of it the latency of short kernels.
 
@@ -1195,18 +1197,18 @@ __global__ __launch_bounds__(kRefThreads) void topk_recollect_many_kernel(Refine
     if (p.many[w.layer].recollect) collect_again<false>(p.rc, w.t0, w.t1);
 }
 
-// As topk_refine_a_kernel with energies, for the chunks blockIdx.y, blockIdx.y + kManySplit, ... of the layer's lists.
+// As topk_refine_a_kernel with energies, for the chunks blockIdx.y, blockIdx.y + gridDim.y, ... of the pass's lists.
 __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_many_kernel(RefineParams p) {
     extern __shared__ unsigned char refine_smem[];
     __shared__ double s_red[kRefThreads / 64][kManyChunk];
     const RefWork w = p.work[blockIdx.x];
     const TopkMany& T = p.many[w.layer];
     const int64_t cand_base = p.cand_base[w.layer];
-    const int nlists = (int)T.nlists, tid = threadIdx.x;
+    const int end = min((int)T.nlists, p.list0 + p.room), tid = threadIdx.x;
     unsigned long long* const s_cell = reinterpret_cast<unsigned long long*>(refine_smem);
     uint8_t* const s_tab = refine_smem + (size_t)kManyChunk * kBinsA * 8;
-    for (int c0 = (int)blockIdx.y * kManyChunk; c0 < nlists; c0 += kManySplit * kManyChunk) {
-        const int n = min(kManyChunk, nlists - c0);
+    for (int c0 = p.list0 + (int)blockIdx.y * kManyChunk; c0 < end; c0 += (int)gridDim.y * kManyChunk) {
+        const int n = min(kManyChunk, end - c0);
         for (int i = tid; i < n * kBinsA; i += kRefThreads) s_cell[i] = 0;
         uint32_t lb[kManyChunk];                        // ascending; past the end nothing lies above
 #pragma unroll
@@ -1233,7 +1235,7 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_many_kernel(Refine
             if ((tid & 63) == 0) s_red[tid >> 6][j] = s;
         }
         __syncthreads();
-        const size_t out = (size_t)blockIdx.x * p.nk + c0;
+        const size_t out = (size_t)blockIdx.x * p.room + (c0 - p.list0);
         if (tid < n) {
             double s = 0.0;
             for (int wv = 0; wv < kRefThreads / 64; ++wv) s += s_red[wv][tid];
@@ -1245,7 +1247,7 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_many_kernel(Refine
     }
 }
 
-// A workgroup takes the lists blockIdx.y, blockIdx.y + kManySlots, ... of a layer: the list's histogram over the
+// A workgroup takes the lists blockIdx.y, blockIdx.y + gridDim.y, ... of a layer's in this pass: the list's histogram over the
 // layer's work items, then a thread per density for what topk_pick_a_kernel's thread 0 does.
 __global__ __launch_bounds__(256) void topk_pick_many_kernel(RefineParams p) {
     __shared__ uint32_t s_hist[kBinsA];
@@ -1258,20 +1260,20 @@ __global__ __launch_bounds__(256) void topk_pick_many_kernel(RefineParams p) {
     __shared__ uint32_t s_prefix;
     const int l = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const TopkMany& T = p.many[l];
-    const int nlists = (int)T.nlists;
-    if ((int)blockIdx.y >= nlists) return;
+    const int end = min((int)T.nlists, p.list0 + p.room);
+    if (p.list0 + (int)blockIdx.y >= end) return;
     const int2 wr = p.work_range[l];
     const double base = base_energy(p, l);
-    for (int li = blockIdx.y; li < nlists; li += kManySlots) {
+    for (int li = p.list0 + (int)blockIdx.y; li < end; li += (int)gridDim.y) {
         const uint32_t tbin = T.bin[li], first = T.first[li], count = T.first[li + 1] - first;
         double part = base;
-        for (int wg = wr.x + tid; wg < wr.y; wg += 256) part += p.below_many[(size_t)wg * p.nk + li];
+        for (int wg = wr.x + tid; wg < wr.y; wg += 256) part += p.below_many[(size_t)wg * p.room + (li - p.list0)];
         // cells 4 t .. 4 t + 3
         uint32_t c[4] = {0, 0, 0, 0};
         unsigned long long e[4] = {0, 0, 0, 0};
 #pragma unroll 8
         for (int wg = wr.x; wg < wr.y; ++wg) {
-            const ulonglong2* const v2 = reinterpret_cast<const ulonglong2*>(p.cell_many + ((size_t)wg * p.nk + li) * kBinsA + 4 * tid);
+            const ulonglong2* const v2 = reinterpret_cast<const ulonglong2*>(p.cell_many + ((size_t)wg * p.room + (li - p.list0)) * kBinsA + 4 * tid);
             const ulonglong2 v0 = v2[0], v1 = v2[1];
             const unsigned long long v[4] = {v0.x, v0.y, v1.x, v1.y};
 #pragma unroll
@@ -1671,6 +1673,7 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
     TK_CHECK(hipMalloc(&t->d_below_part, sizeof(double) * (size_t)t->max_work * kMaxTopk));
     t->ref_words = (size_t)t->max_work * kMaxTopk * (3 * kBinsA + kBinsB);      // u64 + u32 level A, u32 level B
     TK_CHECK(hipMalloc(&t->d_ref, sizeof(uint32_t) * t->ref_words));
+    if (max_cands > (int)kMaxTopk) TK_CHECK(hipMalloc(&t->d_many, sizeof(TopkMany) * (size_t)max_layers));
     // control block layout (every part a multiple of 16 bytes)
     const size_t o_k = 0;
     const size_t o_many = o_k + sizeof(uint32_t) * (size_t)max_layers * kMaxTopk;
@@ -1714,8 +1717,6 @@ void topk_scratch_destroy(TopkScratch* t) {
     (void)hipFree(t->d_below_part);
     (void)hipFree(t->d_ref);
     (void)hipFree(t->d_many);
-    (void)hipFree(t->d_cell_many);
-    (void)hipFree(t->d_below_many);
     for (int i = 0; i < 2; ++i) {
         (void)hipFree(t->d_ctl[i]);
         std::free(t->h_ctl_last[i]);
@@ -1757,24 +1758,10 @@ static hipError_t upload_ctl(TopkScratch* t, int slot, hipStream_t s) {
     return hipSuccess;
 }
 
-// What only calls with more than kMaxTopk densities need, allocated by the first one and grown by
-// one that needs more: the layers' records and the work items' partial histograms (8 KB per item and density at
-// most, touched only for the lists there are).
-static hipError_t many_reserve(TopkScratch* t, int n_work, int nk) {
-    if (!t->d_many) TK_CHECK(hipMalloc(&t->d_many, sizeof(TopkMany) * (size_t)t->max_layers));
-    const size_t n = (size_t)std::max(n_work, 1) * nk;
-    if (n > t->many_lists) {
-        (void)hipFree(t->d_cell_many);
-        (void)hipFree(t->d_below_many);
-        t->d_cell_many = nullptr;
-        t->d_below_many = nullptr;
-        t->many_lists = 0;
-        TK_CHECK(hipMalloc(&t->d_cell_many, sizeof(unsigned long long) * kBinsA * n));
-        TK_CHECK(hipMalloc(&t->d_below_many, sizeof(double) * n));
-        t->many_lists = n;
-    }
-    return hipSuccess;
-}
+// Partial histograms (and the energies beside them) of a call with more than kMaxTopk densities that the
+// refinement's buffer holds, in (work item, list) pairs; at least 13 per work item.
+constexpr size_t kManyBytes = sizeof(unsigned long long) * kBinsA + sizeof(double);
+static size_t many_capacity(const TopkScratch* t) { return t->ref_words * sizeof(uint32_t) / kManyBytes; }
 
 // Upload the requested k per (layer, candidate) (0 = layer inactive) and predict the collection bound
 // of every layer from a sample.
@@ -1834,7 +1821,6 @@ hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevL
     t->n_work = nw;
     t->max_items = max_items;
     t->cand_has_idx = false;
-    if (range) TK_CHECK(many_reserve(t, nw, t->nk_many));
     TK_CHECK(upload_ctl(t, slot, s));
     Section sec(tm, "topk_sample");
     // (the previous call's last scan left the exact histogram cleared)
@@ -1953,10 +1939,10 @@ hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d
     if (t->nk_many) {
         p.many = (const TopkMany*)t->d_many;
         p.cand_base = t->d_cand_base;
-        p.nk = t->nk_many;
         p.cols = (const int32_t*)t->d_many_in;
-        p.cell_many = t->d_cell_many;
-        p.below_many = t->d_below_many;
+        p.room = (int)std::min<size_t>((size_t)t->nk_many, many_capacity(t) / t->n_work);
+        p.cell_many = reinterpret_cast<unsigned long long*>(t->d_ref);
+        p.below_many = reinterpret_cast<double*>(p.cell_many + (size_t)t->n_work * p.room * kBinsA);
         static bool configured_many = false;
         const size_t lds = refine_a_lds(kManyChunk, true);
         if (!configured_many) {
@@ -1966,10 +1952,15 @@ hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d
         }
         hipLaunchKernelGGL(topk_recollect_many_kernel, dim3(t->n_work), dim3(kRefThreads), 0, s, p);
         TK_CHECK(hipGetLastError());
-        hipLaunchKernelGGL(topk_refine_many_kernel, dim3(t->n_work, kManySplit), dim3(kRefThreads), lds, s, p);
-        TK_CHECK(hipGetLastError());
-        hipLaunchKernelGGL(topk_pick_many_kernel, dim3(L, kManySlots), dim3(256), 0, s, p);
-        return hipGetLastError();
+        for (p.list0 = 0; p.list0 < t->nk_many; p.list0 += p.room) {
+            // (a pass after the first finds nothing to do unless the layers have that many lists: small grids.  100
+            // densities of a 26 M-element model, 27 lists in a buffer of 73: 264 us a run, 261 with one pass)
+            hipLaunchKernelGGL(topk_refine_many_kernel, dim3(t->n_work, p.list0 ? 1 : kManySplit), dim3(kRefThreads), lds, s, p);
+            TK_CHECK(hipGetLastError());
+            hipLaunchKernelGGL(topk_pick_many_kernel, dim3(L, p.list0 ? 4 : kManySlots), dim3(256), 0, s, p);
+            TK_CHECK(hipGetLastError());
+        }
+        return hipSuccess;
     }
     if (d_errors) {       // profile: level A gives the dropped energy, no exact threshold is needed
         const size_t lds = refine_a_lds(ntk, true);

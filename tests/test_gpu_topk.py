@@ -385,3 +385,48 @@ def test_places_across_the_emit_kernels_batches_of_tiles(n):
     ties = np.round(rng.standard_normal(n) * 2).astype(np.float32)
     free = rng.laplace(size=n).astype(np.float32)
     _check(_flat_batch([ties[:5], free, ties, free[:8192], ties[: n // 2 + 1]], pad=[3, 0, 1, 0, 2]), [0.3, 0.1, 0.013])
+
+
+def test_more_lists_than_the_refinement_buffer_holds_at_a_time():
+    """Many layers whose 128 densities have a threshold bin each: the partial histograms are made and read in
+    several passes over the buffer the handle was created with; nothing is allocated by the call."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    rng = np.random.default_rng(9)
+    numels = rng.integers(1000, 2000, 1200)
+    batch = _flat_batch([(2.0 ** rng.uniform(-12, 2, n)).astype(np.float32) * rng.choice([-1, 1], n).astype(np.float32)
+                         for n in numels], pad=[3 * (l % 2) for l in range(1200)])
+    cands = [(W.TOPK, 0.005 * (c + 1)) for c in rng.permutation(128)]
+    layers, ctab = tables(batch, cands)
+    g, e, _ = to_device(batch)
+    h = B.Handle(int(batch.grads.size), len(numels), len(cands))
+    few, _ = h.profile(g, e, layers, B.cand_table(cands[:8]))      # (the library's kernels are loaded)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    errors, _ = h.profile(g, e, layers, ctab)
+    again, _ = h.profile(g, e, layers, ctab)
+    assert free - torch.cuda.mem_get_info()[0] < 64 << 20          # (code objects, but not 8 KB per layer and density)
+    ref = pipeline.profile(batch.grads, batch.ef, batch.offsets, batch.numels, batch.rows, batch.cols, cands)
+    assert rel_err(errors, ref).max() < 1e-4 and np.array_equal(errors, again)
+    assert rel_err(errors[:, :8], few).max() < 1e-5
+    h.close()
+
+
+@pytest.mark.parametrize("n", [(1 << 24) + 5, 3 << 25])
+def test_many_densities_of_a_large_layer_against_64_bits(n):
+    """Work items at their largest.  A lane sums the squares of at most 2^19 / 1024 candidates of an item in
+    fp32: positive terms whose roundings are as often up as down, sqrt(512) * 2^-24 = 1.3e-6 of a lane's sum, less of
+    the sum of many lanes.  The dropped part of the boundary sub-bin is taken to within 1e-5."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    g = torch.empty(n, device="cuda").normal_(generator=torch.Generator("cuda").manual_seed(3)) ** 3
+    densities = np.linspace(0.001, 0.5, 24).tolist()
+    layers, ctab = B.layer_table([0], [n], [0], [0]), B.cand_table([(W.TOPK, d) for d in densities])
+    h = B.Handle(n, 1, len(densities))
+    errors, _ = h.profile(g, None, layers, ctab)
+    h.close()
+    below = torch.cumsum(torch.sort(g.abs()).values.double() ** 2, 0)
+    ref = np.array([float(below[n - topk.k_of(n, d) - 1]) for d in densities])
+    worst = rel_err(errors[0], ref).max()
+    print("largest relative error", worst)
+    assert worst < 1.13e-5
