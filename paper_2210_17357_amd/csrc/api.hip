@@ -36,6 +36,7 @@ struct lgreco_handle {
     Tile* d_tiles = nullptr;
     int32_t max_tiles = 0;
     int32_t tile_elems = kTile;     // tile size of the current layer table
+    int32_t layer_tiles = 0;        // tiles of its largest layer
     double* d_partials = nullptr;   // [max_tiles x max_cands]
     double* h_errors = nullptr;     // [max_layers x max_cands], pinned host memory
     double* d_errors = nullptr;     // the same memory as the kernels address it
@@ -249,6 +250,7 @@ int prepare_layers(lgreco_handle* h, const lgreco_layer_t* layers, int32_t L) {
     int tile = kTile;
     while (tile > kTileMin && total / tile < kTilesFill) tile /= 2;
     h->tile_elems = tile;
+    h->layer_tiles = 0;
     h->hl.assign(L, DevLayer{});
     h->ht.clear();
     int64_t qoff = 0;
@@ -278,6 +280,7 @@ int prepare_layers(lgreco_handle* h, const lgreco_layer_t* layers, int32_t L) {
             push(rem, 0);
         }
         d.tile_end = (int32_t)h->ht.size();
+        h->layer_tiles = std::max(h->layer_tiles, d.tile_end - d.tile_begin);
     }
     if ((int64_t)h->ht.size() > h->max_tiles) return LGRECO_ENOSPACE;
     h->cached.assign(layers, layers + L);
@@ -1166,7 +1169,7 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
             // the Top-K layers' part, from the selection records the profile left for this very
             // data: the chosen density's record is picked on the device
             HIPCHK(topk_compress_known(&h->topk, d_grads, ec->d_ef, h->d_layers, h->d_tiles, L, (int)h->ht.size(),
-                                       ec->d_payload, h->tm, s, ec->x_in_e));
+                                       h->layer_tiles, ec->d_payload, h->tm, s, ec->x_in_e));
         }
         if (beside) HIPCHK(hipStreamWaitEvent(h->side, h->ev_fork, 0));
         if (any_quant) {
@@ -1336,7 +1339,7 @@ static int compress_impl(lgreco_handle_t* h, const float* d_grads, float* d_ef, 
     }
     if (any[LGRECO_TOPK] && !(quant_done && ec->topk_known)) {
         HIPCHK(topk_compress(&h->topk, x_in_e ? d_ef : d_grads, d_ef, h->d_layers, h->hl.data(), h->d_tiles, L,
-                             n_tiles, h->tile_elems, d_payload, h->tm, s, x_in_e));
+                             n_tiles, h->tile_elems, h->layer_tiles, d_payload, h->tm, s, x_in_e));
     }
     if (any[LGRECO_LOWRANK] && !(quant_done && ec->lowrank_known)) {
         HIPCHK(lowrank_compress(&h->lowrank, d_grads, d_ef, h->d_layers, h->hl.data(), L, d_q, h->cfg.r_max,

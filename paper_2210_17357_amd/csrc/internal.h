@@ -238,6 +238,7 @@ struct TopkScratch {
     bool hist_clean = false;          // the exact histogram is all zero (the last scan of a call clears it)
     int64_t* d_cand_base = nullptr;   // [max_layers] first candidate slot of every layer
     void* d_tilecnt = nullptr;        // per tile (above, equal) counts (compress)
+    unsigned long long* d_runs = nullptr;   // ... and their sums over runs of tiles
     void* d_tinfo = nullptr;          // per tile, per wavefront: candidates written and where
     double* d_base_part = nullptr;    // per tile energy below the collection bound
     double* d_below_part = nullptr;   // refinement partial sums
@@ -300,16 +301,17 @@ hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef
 // refinement on the candidates: exact thresholds; writes the dropped energy to errors (if not null)
 hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d_tiles, int L, int ntk,
                          const int* col, double* d_errors, int stride, Timing* tm, hipStream_t s);
+// layer_tiles: tiles of the largest layer
 hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLayer* d_layers,
                          const DevLayer* h_layers, const Tile* d_tiles, int L, int n_tiles, int tile_elems,
-                         uint8_t* payload, Timing* tm, hipStream_t s, bool x_in_e = false);
+                         int layer_tiles, uint8_t* payload, Timing* tm, hipStream_t s, bool x_in_e = false);
 
 // Top-K layers of a compression queued right behind a profile of the same data and the solver
 // kernel that wrote the layer records (family, k, payload offset, slot of the chosen density in
 // the profile's selection records): nothing here needs the host to know the assignment.
 hipError_t topk_compress_known(TopkScratch* t, const float* g, float* e, const DevLayer* d_layers,
-                               const Tile* d_tiles, int L, int n_tiles, uint8_t* payload, Timing* tm, hipStream_t s,
-                               bool x_in_e = false);
+                               const Tile* d_tiles, int L, int n_tiles, int layer_tiles, uint8_t* payload, Timing* tm,
+                               hipStream_t s, bool x_in_e = false);
 
 // ---- lowrank.hip
 struct LowrankScratch {

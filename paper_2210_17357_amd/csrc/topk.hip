@@ -1498,6 +1498,28 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long m, uint32_t a
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, add));
 }
 
+// Counts of every run of kRunTiles tiles (by tile number; runs that reach past a layer's end are not looked at):
+// one workgroup per run.  Both counts travel in one 64-bit word, (entries above the threshold) << 32 | entries equal
+// to it (each stays below 2^31: a layer has fewer elements than that).
+constexpr int kRunTiles = 1024;
+__global__ __launch_bounds__(kThreads) void topk_runs_kernel(const uint2* __restrict__ wavecnt, int n_tiles,
+                                                             unsigned long long* __restrict__ runs) {
+    __shared__ unsigned long long s_sum[kThreads / 64];
+    const int first = blockIdx.x * kRunTiles, n_pairs = min(kRunTiles, n_tiles - first) * (kThreads / 64 / 2);
+    const uint4* const pairs = reinterpret_cast<const uint4*>(wavecnt + (size_t)first * (kThreads / 64));
+    unsigned long long sum = 0;
+#pragma unroll
+    for (int u = 0; u < kRunTiles * (kThreads / 64 / 2) / kThreads; ++u) {
+        const int i = (int)threadIdx.x + u * kThreads;
+        const uint4 v = i < n_pairs ? pairs[i] : make_uint4(0u, 0u, 0u, 0u);
+        sum += ((unsigned long long)(v.x + v.z) << 32) + (v.y + v.w);
+    }
+    for (int o = 1; o < 64; o <<= 1) sum += __shfl_xor(sum, o, 64);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x == 0) runs[blockIdx.x] = (s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3]);
+}
+
 // Kept values and indices in ascending index order, from the candidates alone (every kept entry
 // is a candidate, and a wavefront's candidates are stored in element order); the error feedback,
 // already written as x everywhere by the collection pass, is zeroed at the kept entries (KNOWN:
@@ -1506,6 +1528,8 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long m, uint32_t a
 // workgroup adds up those before its first tile (of the largest layer of a 355 M-element model 50 KB at most,
 // 8 128-bit loads in flight per thread) and walks its own 16.  As a kernel of its own, a
 // workgroup per layer, that prefix took 4-5 us and its launch; 18 beside a kernel that fills the chip.
+// `runs` (not null where a layer has more than kTilesInRuns tiles): the whole runs of tiles before its first come as
+// their sums, so that what a workgroup reads stays bounded.
 template <bool KNOWN>
 __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__ e,
                                                               const DevLayer* __restrict__ layers,
@@ -1515,6 +1539,7 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__
                                                               const uint32_t* __restrict__ cand,
                                                               const uint32_t* __restrict__ cand_idx,
                                                               const uint2* __restrict__ wavecnt,
+                                                              const unsigned long long* __restrict__ runs,
                                                               uint8_t* __restrict__ payload, int x_in_e) {
     // x_in_e (KNOWN only): the main pass left the buffer as it was (x everywhere), so the kept
     // entries are zeroed here, as without KNOWN, and nothing is put back
@@ -1546,7 +1571,6 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__
         start[q] = tinfo[ti].start[wave];
         cnt[q] = wavecnt[slot];
     }
-    // Both counts travel in one 64-bit word (each stays below 2^31: a layer has fewer elements than that).
     constexpr int kWaves = kThreads / 64, kBatch = 8;
     static_assert(kWaves % 2 == 0, "a tile's counts are read in pairs");
     __shared__ unsigned long long s_before[kWaves];
@@ -1554,11 +1578,23 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__
     {
         const int begin = layers[layer[0]].tile_begin;
         const uint4* const pairs = reinterpret_cast<const uint4*>(wavecnt + (size_t)begin * kWaves);
-        const int n_pairs = (first - begin) * (kWaves / 2);
+        int n_pairs = (first - begin) * (kWaves / 2), head = n_pairs, skip = 0;       // pairs in front of the whole runs, in them
+        if (runs) {
+            const int r0 = (begin + kRunTiles - 1) / kRunTiles, r1 = first / kRunTiles;
+            if (r0 < r1) {
+                head = (r0 * kRunTiles - begin) * (kWaves / 2);
+                skip = (r1 - r0) * kRunTiles * (kWaves / 2);
+                n_pairs -= skip;
+                for (int r = r0 + (int)threadIdx.x; r < r1; r += kThreads) sum += runs[r];
+            }
+        }
         for (int i = (int)threadIdx.x; i < n_pairs; i += kBatch * kThreads) {
             uint4 v[kBatch];
 #pragma unroll
-            for (int u = 0; u < kBatch; ++u) v[u] = i + u * kThreads < n_pairs ? pairs[i + u * kThreads] : make_uint4(0u, 0u, 0u, 0u);
+            for (int u = 0; u < kBatch; ++u) {
+                const int j = i + u * kThreads;
+                v[u] = j < n_pairs ? pairs[j < head ? j : j + skip] : make_uint4(0u, 0u, 0u, 0u);
+            }
 #pragma unroll
             for (int u = 0; u < kBatch; ++u) sum += ((unsigned long long)(v[u].x + v[u].z) << 32) + (v[u].y + v[u].w);
         }
@@ -1667,6 +1703,7 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
     TK_CHECK(hipMalloc(&t->d_tinfo_kept, sizeof(TopkTileInfo) * (size_t)max_tiles));
     TK_CHECK(hipMalloc(&t->d_lo, sizeof(uint32_t) * (size_t)max_layers));
     TK_CHECK(hipMalloc(&t->d_tilecnt, sizeof(uint2) * (size_t)max_tiles * (kThreads / 64)));
+    TK_CHECK(hipMalloc(&t->d_runs, sizeof(unsigned long long) * (size_t)(max_tiles / kRunTiles + 1)));
     TK_CHECK(hipMalloc(&t->d_tinfo, sizeof(TopkTileInfo) * (size_t)max_tiles));
     TK_CHECK(hipMalloc(&t->d_base_part, sizeof(double) * (size_t)max_tiles));
     t->max_work = (int)(max_elems / ((int64_t)kRefTiles * kTile)) + 2 * max_layers + 2 + 2 * kRefSlots;   // see topk_begin
@@ -1712,6 +1749,7 @@ void topk_scratch_destroy(TopkScratch* t) {
     (void)hipFree(t->d_tinfo_kept);
     (void)hipFree(t->d_lo);
     (void)hipFree(t->d_tilecnt);
+    (void)hipFree(t->d_runs);
     (void)hipFree(t->d_tinfo);
     (void)hipFree(t->d_base_part);
     (void)hipFree(t->d_below_part);
@@ -1996,10 +2034,23 @@ hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d
     return hipGetLastError();
 }
 
+// Sums over runs of tiles for the emission, where some layer has so many tiles that every workgroup's own sum costs
+// more than this launch: emission of 1 % of one layer of 9155 tiles (300 M elements) 104 us without, 106 with; of 30518
+// tiles 495 without, 426 with; of 65536 tiles 1107 and 968.
+constexpr int kTilesInRuns = 10240;
+static hipError_t sum_runs(TopkScratch* t, int n_tiles, int layer_tiles, hipStream_t s, const unsigned long long** runs) {
+    *runs = nullptr;
+    if (layer_tiles <= kTilesInRuns) return hipSuccess;
+    hipLaunchKernelGGL(topk_runs_kernel, dim3((n_tiles + kRunTiles - 1) / kRunTiles), dim3(kThreads), 0, s,
+                       (const uint2*)t->d_tilecnt, n_tiles, t->d_runs);
+    *runs = t->d_runs;
+    return hipGetLastError();
+}
+
 // x_in_e: g is the error-feedback buffer itself, which already holds x = fl32(g + e) (nothing is added)
 hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLayer* d_layers,
                          const DevLayer* h_layers, const Tile* d_tiles, int L, int n_tiles, int tile_elems,
-                         uint8_t* payload, Timing* tm, hipStream_t s, bool x_in_e) {
+                         int layer_tiles, uint8_t* payload, Timing* tm, hipStream_t s, bool x_in_e) {
     std::vector<uint32_t> ks((size_t)L * kMaxTopk, 0u);
     for (int l = 0; l < L; ++l)
         if (h_layers[l].family == LGRECO_TOPK) ks[(size_t)l * kMaxTopk] = (uint32_t)h_layers[l].iparam;
@@ -2020,10 +2071,12 @@ hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLaye
     }
     {
         Section sec(tm, "topk_emit");
+        const unsigned long long* runs;
+        TK_CHECK(sum_runs(t, n_tiles, layer_tiles, s, &runs));
         hipLaunchKernelGGL(topk_emit_kernel<false>, dim3((n_tiles + kSliceBatch - 1) / kSliceBatch), dim3(kThreads), 0, s, e,
                            d_layers, d_tiles, n_tiles, (const TopkLayer*)t->d_tl,
                            (const TopkTileInfo*)t->d_tinfo, (const uint32_t*)t->d_cand,
-                           (const uint32_t*)t->d_cand_idx, (const uint2*)t->d_tilecnt,
+                           (const uint32_t*)t->d_cand_idx, (const uint2*)t->d_tilecnt, runs,
                            payload, 0);
         TK_CHECK(hipGetLastError());
     }
@@ -2040,8 +2093,8 @@ hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLaye
 // pass over g and e writes x to the error feedback and collects the same set.  Then the exact
 // threshold, the per-wavefront counts and the ordered emit, as in topk_compress.
 hipError_t topk_compress_known(TopkScratch* t, const float* g, float* e, const DevLayer* d_layers,
-                               const Tile* d_tiles, int L, int n_tiles, uint8_t* payload, Timing* tm, hipStream_t s,
-                               bool x_in_e) {
+                               const Tile* d_tiles, int L, int n_tiles, int layer_tiles, uint8_t* payload, Timing* tm,
+                               hipStream_t s, bool x_in_e) {
     if (n_tiles <= 0) return hipSuccess;
     // the profile's control block (slot 0) holds every layer's candidate region
     uint8_t* const d = t->d_ctl[0];
@@ -2101,9 +2154,11 @@ hipError_t topk_compress_known(TopkScratch* t, const float* g, float* e, const D
     }
     {
         Section sec(tm, "topk_emit");
+        const unsigned long long* runs;
+        TK_CHECK(sum_runs(t, n_tiles, layer_tiles, s, &runs));
         hipLaunchKernelGGL(topk_emit_kernel<true>, dim3((n_tiles + kSliceBatch - 1) / kSliceBatch), dim3(kThreads), 0, s, e,
                            d_layers, d_tiles, n_tiles, (const TopkLayer*)t->d_tl, tinfo, cand, cand_idx,
-                           (const uint2*)t->d_tilecnt,
+                           (const uint2*)t->d_tilecnt, runs,
                            payload, x_in_e ? 1 : 0);
         TK_CHECK(hipGetLastError());
     }

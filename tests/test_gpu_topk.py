@@ -430,3 +430,38 @@ def test_many_densities_of_a_large_layer_against_64_bits(n):
     worst = rel_err(errors[0], ref).max()
     print("largest relative error", worst)
     assert worst < 1.13e-5
+
+
+@pytest.mark.parametrize("one_call", [False, True])
+def test_places_in_a_layer_of_more_tiles_than_a_workgroup_adds_up(one_call):
+    """Past 10240 tiles in a layer the counts before a workgroup's tiles come as sums over runs of 1024 tiles, but
+    for the layer's first, shared with the layers before it, and the last.  Against a sort on the GPU."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    numels, density = [5 * 32768 + 12, 10300 * 32768 + 700, 70001], 0.002
+    offsets = np.concatenate([[0], np.cumsum(numels)[:-1]])
+    total = int(sum(numels))
+    g = torch.empty(total, device="cuda").normal_(generator=torch.Generator("cuda").manual_seed(1))
+    g = (g * 64).round_() / 64                                     # ties at every threshold
+    layers, ctab = B.layer_table(offsets, numels, [0] * 3, [0] * 3), B.cand_table([(W.TOPK, density)])
+    h = B.Handle(total, 3, 1)
+    e = torch.zeros_like(g)
+    choice = np.zeros(3, np.int32)
+    place = B.payload_layout(layers, ctab, choice)
+    payload = torch.zeros(int(place[-1]), dtype=torch.uint8, device="cuda")
+    if one_call:
+        assert h.profile_solve_compress(g, e, layers, ctab, 0, 100, payload)[0] == B.OK
+    else:
+        h.compress(g, e, layers, ctab, choice, payload, place)
+    for l in range(3):
+        x = g[offsets[l]:offsets[l] + numels[l]]
+        k = topk.k_of(numels[l], density)
+        thr = torch.topk(x.abs(), k, sorted=True).values[-1]
+        above, ties = x.abs() > thr, x.abs() == thr
+        kept = above | (ties & (torch.cumsum(ties, 0, dtype=torch.int32) <= k - int(above.sum())))
+        idx = torch.nonzero(kept)[:, 0]
+        got = payload[int(place[l]):int(place[l]) + 8 * k].view(torch.int32)
+        assert torch.equal(got[k:].long(), idx), l
+        assert torch.equal(got[:k].view(torch.float32), x[idx]), l
+        assert torch.equal(e[offsets[l]:offsets[l] + numels[l]], torch.where(kept, torch.zeros_like(x), x)), l
+    h.close()
