@@ -159,33 +159,7 @@ __device__ void block_kth_from_top(const uint32_t* hist, uint32_t need, uint32_t
     __syncthreads();
 }
 
-// Exclusive scan of one uint32 per thread over the 256-thread block; returns the prefix and the
-// block total through *total.  tmp: 4 words of LDS.
-__device__ uint32_t block_excl_scan(uint32_t v, uint32_t* tmp, uint32_t* total) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    uint32_t inc = v;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t n = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += n;
-    }
-    __syncthreads();
-    if (lane == 63) tmp[wave] = inc;
-    __syncthreads();
-    uint32_t base = 0, tot = 0;
-    for (int w = 0; w < kThreads / 64; ++w) {
-        if (w < wave) base += tmp[w];
-        tot += tmp[w];
-    }
-    *total = tot;
-    return base + inc - v;
-}
-
 // ------------------------------------------------------------------------ kernels
-__global__ void copy_u32_kernel(uint32_t* dst, const uint32_t* src, size_t n) {
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) dst[i] = src[i];
-}
-
 __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
         p[i] = v;
