@@ -129,16 +129,20 @@ bool one_kernel_solve(const lgreco_handle* h, int L, int P) {
     return h->cfg.dp_groups <= 1 && L <= kSolveMaxLayers && (int64_t)L * P <= kSolveMaxLP;
 }
 
-// Candidates of every layer in order of size, the lowest index first among equals (insertion: the lists
-// are runs in order, one per family).
+// Candidates of every layer in order of size, the lowest index first among equals.  The lists are runs in order,
+// one per family, whose next member usually goes to the end; others are placed by halving (a list of 100 in falling
+// order shifted one by one took 4950 steps).
 void size_order(const int64_t* sizes, int L, int P, uint8_t* order) {
     for (int l = 0; l < L; ++l) {
         const int64_t* const z = sizes + (size_t)l * P;
         uint8_t* const o = order + (size_t)l * P;
         for (int c = 0; c < P; ++c) {
-            int k = c;
-            for (; k > 0 && z[o[k - 1]] > z[c]; --k) o[k] = o[k - 1];
-            o[k] = (uint8_t)c;
+            int at = c;
+            if (c > 0 && z[o[c - 1]] > z[c]) {
+                at = (int)(std::upper_bound(o, o + c, z[c], [&](int64_t v, uint8_t k) { return v < z[k]; }) - o);
+                std::memmove(o + at + 1, o + at, (size_t)(c - at));
+            }
+            o[at] = (uint8_t)c;
         }
     }
 }

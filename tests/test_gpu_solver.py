@@ -226,6 +226,7 @@ def test_strict_budget_keeps_the_real_errors_within_e_max(groups):
     (5, 4, 16384, "free"), (3, 2, 16384, "fall"), (70, 16, 2000, "free"), (70, 17, 2000, "free"),    # whole rows; 16 / 64 candidates
     (20, 64, 3000, "fall"), (20, 65, 3000, "free"), (24, 128, 9000, "fall"),                        # a wavefront per list, two lists' halves
     (1024, 8, 3000, "free"), (1000, 16, 9000, "fall"),                                              # most layers; more entries than LDS takes
+    (97, 49, 4000, "rise"), (24, 128, 3000, "rise"), (30, 100, 3000, "saw"),                        # sizes that fall along the list, and by runs
     (300, 7, 2000, "same"), (64, 13, 1000, "ties"), (200, 5, 4000, "one")])
 def test_reduced_sweep_on_its_edges(L, P, D, kind):
     """The one-kernel solve sweeps only cells and candidates an optimal assignment can use; widths,
@@ -250,6 +251,11 @@ def test_reduced_sweep_on_its_edges(L, P, D, kind):
             sizes = rng.integers(1, 1 << 17, (L, P)).astype(np.int64)
             if kind == "fall":
                 sizes = np.sort(sizes, axis=1)
+            if kind in ("rise", "saw"):
+                errors = np.ascontiguousarray(errors[:, ::-1])
+                sizes = np.ascontiguousarray(np.sort(sizes // 2000 * 2000, axis=1)[:, ::-1])
+            if kind == "saw":
+                errors, sizes = (np.ascontiguousarray(np.roll(a.reshape(L, 4, -1)[:, ::-1].reshape(L, P), 3, axis=1)) for a in (errors, sizes))
             if kind == "one":                            # one layer holds nearly all of the error and the size
                 errors[0] *= 1e4
                 sizes[0] *= 1000
