@@ -8,8 +8,7 @@ by default through lgreco_profile_solve_compress, which is those calls in one (-
 go through the separate entry points; same kernels, same results).
 Inputs are resident in HBM before the timed region.  The data MOVES from step to step as in a
 training loop: the steps rotate over --grad-buffers independent draws of the workload (same
-per-layer scales, fresh values and error feedback, each scaled by 1, 1.03, 0.97, ...), so the Top-K
-thresholds a call remembers from the previous one are never exactly right.  Every step works on
+per-layer scales, fresh values and error feedback, each scaled by 1, 1.03, 0.97, ...).  Every step works on
 its own copy of the error-feedback buffer, so nothing is restored inside the timed region.
 
 Prints ONE JSON line (metric = gradient GB/s = 4 * N bytes / step time), with
@@ -18,9 +17,8 @@ Prints ONE JSON line (metric = gradient GB/s = 4 * N bytes / step time), with
                     carry the events; the library sums them, the loop never stops to read them),
                     against the 8 TB/s HBM peak;
   "phases_gpu_ms"   GPU time of the profile, solve and compress phases (events around everything a
-                    phase queues: main kernels, the Top-K chains, list building, the DP);
+                    phase queues: main kernels, the Top-K chains, the solver);
   "roofline_phase"  algorithmic bytes of a phase (and of the whole step) / its time / 8 TB/s;
-  "cold"            the same loop with reuse_thresholds = 0 (the switch has no effect: every call samples the data);
   "other_workloads" the smaller workloads of BASELINE.json, same measurement, a few ms each;
   "cpu_baseline"    the CPU oracle timed on a bounded sample of the same workload.
 """
@@ -86,13 +84,11 @@ def parse_args():
                     help="independent draws of the workload the steps rotate over (1: the same data every step)")
     ap.add_argument("--power-iters", type=int, default=1,
                     help="power-iteration steps of the low-rank family (the configs use 1)")
-    ap.add_argument("--sample-every-call", action="store_true",
-                    help="Top-K: the main loop itself runs with reuse_thresholds = 0 (without effect: every call samples "
-                         "the data; the default run reports that case under \"cold\")")
-    ap.add_argument("--no-cold", action="store_true", help="leave out the reuse_thresholds = 0 loop")
+    ap.add_argument("--sample-every-call", action="store_true", help="accepted, no effect: every call samples the data")
+    ap.add_argument("--no-cold", action="store_true", help="accepted, no effect")
     ap.add_argument("--dp-groups", type=int, default=0,
                     help="layer groups of the solver: 0, 1 = one sweep over the cells an assignment of the smallest size "
-                         "can use, 2 / 4 / 8 = the whole table in that many groups")
+                         "can use where the table fits it, 2 / 4 / 8 = the whole table in that many groups")
     ap.add_argument("--keep-ef-on-failure", action="store_true",
                     help="create the handle with keep_ef_on_failure = 1: the profile of the one call does not "
                          "leave x in the error-feedback buffer (more memory traffic, same results)")
@@ -139,7 +135,7 @@ def cpu_baseline(w, sample_tensors, power_iters=1):
                                "elems": n, "total_s": t3 - t0}
 
 
-def measure(wname, args, steps, warmup, with_cold, with_decompress):
+def measure(wname, args, steps, warmup, with_decompress):
     """The timed loop on one workload.  Returns (result dict, context for the CPU baseline)."""
     import torch
     from paper_2210_17357_amd import binding as B
@@ -182,12 +178,11 @@ def measure(wname, args, steps, warmup, with_cold, with_decompress):
     sizes_tab = B.sizes(layers, ctab, w.bucket)
     payload = torch.empty(int(sizes_tab.max(axis=1).sum()) + 16 * (L + 1), dtype=torch.uint8, device=dev)
     stream = torch.cuda.current_stream().cuda_stream      # the stream every call of the run is given
-    has_topk = any(f == W.TOPK for f, _ in cands)
 
-    def loop(reuse, timing_level):
+    def loop(timing_level):
         """warm-up + timed steps on a handle of its own; returns (elapsed s, kernel totals, last results)."""
         h = B.Handle(int(batch.grads.size), L, len(cands), bucket=w.bucket, stochastic=w.stochastic,
-                     seed=w.seed, r_max=w.r_max, power_iters=args.power_iters, reuse_thresholds=reuse,
+                     seed=w.seed, r_max=w.r_max, power_iters=args.power_iters,
                      keep_ef_on_failure=args.keep_ef_on_failure, dp_groups=args.dp_groups)
         h.set_timing(timing_level)
         h.set_timing_stride(max(1, args.time_every))
@@ -236,7 +231,7 @@ def measure(wname, args, steps, warmup, with_cold, with_decompress):
         del ef_pool, q_pool
         return h, elapsed, kern, last
 
-    h, elapsed, kern, last = loop(not args.sample_every_call, level)
+    h, elapsed, kern, last = loop(level)
     ms_per_step = elapsed * 1e3 / steps
     value = 4.0 * N / (elapsed / steps) / 1e9
 
@@ -356,7 +351,7 @@ def measure(wname, args, steps, warmup, with_cold, with_decompress):
         "value": round(value, 2), "unit": "GB/s", "ms_per_step": round(ms_per_step, 4),
         "config": {"workload": w.name, "elements": N, "layers": L, "candidates": len(cands),
                    "n_bins": w.n_bins, "stochastic": bool(w.stochastic), "power_iters": args.power_iters,
-                   "reuse_thresholds": not args.sample_every_call, "grad_buffers": n_buf,
+                   "grad_buffers": n_buf,
                    "calls_per_step": calls, "x_in_ef_buffer": bool(in_place),
                    "steps": steps, "warmup": warmup,
                    "kernels_timed_every_n_steps": None if args.no_kernel_timing else max(1, args.time_every),
@@ -395,12 +390,6 @@ def measure(wname, args, steps, warmup, with_cold, with_decompress):
         del out_buf
     h.close()
 
-    if with_cold and has_topk and not args.sample_every_call:
-        # the same loop when no call may start from the previous call's thresholds
-        hc, el_c, _, _ = loop(False, 0)
-        hc.close()
-        out["cold"] = {"reuse_thresholds": False, "ms_per_step": round(el_c * 1e3 / steps, 4),
-                       "value": round(4.0 * N / (el_c / steps) / 1e9, 2), "unit": "GB/s"}
     ctx = {"w": w, "batch": batch, "last": last, "errors0": errors0}
     del g_list, ef0_list, payload
     gc.collect()
@@ -419,8 +408,7 @@ def main():
         print("bench.py: no GPU visible", file=sys.stderr)
         sys.exit(3)
 
-    res, ctx = measure(args.workload, args, args.steps, args.warmup, with_cold=not args.no_cold,
-                       with_decompress=True)
+    res, ctx = measure(args.workload, args, args.steps, args.warmup, with_decompress=True)
     w, batch, last = ctx["w"], ctx["batch"], ctx["last"]
     out = {
         "metric": "profile+solve+compress gradient GB/s at 1 MI355X",
@@ -428,7 +416,7 @@ def main():
         "ms_per_step": res["ms_per_step"], "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32", "data": "synthetic",
     }
-    for k in ("config", "roofline", "phases_gpu_ms", "roofline_phase", "cold", "kernels", "result", "decompress"):
+    for k in ("config", "roofline", "phases_gpu_ms", "roofline_phase", "kernels", "result", "decompress"):
         if k in res:
             out[k] = res[k]
 
@@ -437,10 +425,9 @@ def main():
         # microseconds): same loop, milliseconds each
         others = {}
         for name in OTHER_WORKLOADS:
-            r, _ = measure(name, args, max(args.steps, 20), max(args.warmup, 3), with_cold=not args.no_cold,
-                           with_decompress=False)
+            r, _ = measure(name, args, max(args.steps, 20), max(args.warmup, 3), with_decompress=False)
             others[name] = {k: r[k] for k in ("value", "unit", "ms_per_step", "roofline", "phases_gpu_ms",
-                                              "roofline_phase", "cold", "result") if k in r}
+                                              "roofline_phase", "result") if k in r}
             others[name]["elements"] = r["config"]["elements"]
             others[name]["kernels"] = {k: v for k, v in r["kernels"].items() if "GBps" in v or "TFLOPs" in v}
         out["other_workloads"] = others

@@ -169,12 +169,10 @@ def test_full_size_gpt2_medium_sampled_layers():
         assert np.array_equal(ef_dev[off:off + n].cpu().numpy().view(np.uint32), e_ref.view(np.uint32)), l
     h.close()
 
-    # The benchmark's loop itself: a handle that starts every call from the thresholds of the
-    # previous one, the whole path as one call (the solver kernel writes the compression's layer
+    # The benchmark's loop itself: the whole path as one call (the solver kernel writes the compression's layer
     # records, the quantization kernel is queued behind it before the host knows the result), a
     # fresh copy of the error feedback per step.  Every step reproduces what was verified above:
-    # errors to rounding (the bound under which energies are summed in fp32 moves), the oracle's
-    # assignment for the step's own tables, payload and error feedback bit for bit.
+    # the errors, the oracle's assignment for the step's own tables, payload and error feedback bit for bit.
     h2 = B.Handle(int(batch.grads.size), L, len(cands), reuse_thresholds=True)
     stream = torch.cuda.current_stream().cuda_stream
     n_pay = int(offsets[-1])

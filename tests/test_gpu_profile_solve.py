@@ -310,7 +310,7 @@ def test_whole_path_call_on_degenerate_topk_layers(default, n_bins):
     L = len(numels)
     capacity = int(B.sizes(layers, ctab).max(axis=1).sum()) + 16 * (L + 1)
     h = B.Handle(int(batch.grads.size), L, len(cands), reuse_thresholds=True)
-    for rep in range(2):                                                 # the second call starts from the first's thresholds
+    for rep in range(2):
         pay = torch.zeros(capacity, dtype=torch.uint8, device="cuda")
         ef = ed.clone()
         st, errors, sizes, e_max, choice, tsize, terr, offsets = h.profile_solve_compress(
@@ -405,14 +405,11 @@ def test_whole_path_call_keeping_much_of_every_slice(default, n_bins):
 
 
 @pytest.mark.parametrize("kind", ["mixed", "topk"])
-def test_whole_path_call_when_the_data_moves_past_the_remembered_thresholds(kind):
-    """The one call on a handle that starts every profile from the previous call's thresholds,
-    with data that is scaled far down between calls (every remembered bound is too high: the
-    layers are collected a second time, from the buffer the first collection left x in, and the
-    compression works from the second collection's candidate records), far up (everything becomes
-    a candidate) and by the few per cent of a training loop.  Payload and error feedback of every
-    call against the separate calls on a handle that samples every time, and against the oracle's
-    compressor on a sample of layers."""
+def test_whole_path_call_when_the_data_changes_scale_between_calls(kind):
+    """The one call on a handle whose data is scaled far down and far up between calls, and by the few per
+    cent of a training loop: every call samples its own data.  Payload and error feedback of every
+    call against the separate calls on another handle, and against the oracle's compressor on a sample
+    of layers."""
     from oracle import pipeline
     from paper_2210_17357_amd import binding as B
     torch = torch_cuda()
@@ -498,7 +495,7 @@ def test_whole_path_calls_back_to_back_without_waiting_for_the_gpu(kind):
 
 @pytest.mark.parametrize("name", ["c1_resnet18_quant", "c2_resnet50_topk"])
 def test_whole_path_call_at_full_size_of_the_smaller_workloads(name):
-    """The one call as the benchmark times it (history on, three steps over buffers scaled by
+    """The one call as the benchmark times it (three steps over buffers scaled by
     1, 1.03, 0.97) on the whole 11.7 M-element quantization workload (stochastic rounding) and the
     whole 25.6 M-element Top-K workload: assignment against the oracle's solver on the call's own
     tables, payload and error feedback against the separate calls bit for bit and, on the largest
@@ -560,8 +557,7 @@ def _one_call_against_separate(reuse, plain, g, e, layers, ctab, default, n_bins
 
 
 def test_whole_path_call_when_the_assignment_changes_between_calls():
-    """One handle with history on (every profile starts from the previous call's thresholds, the
-    device's layer records are those the previous call's solver kernel wrote), and an assignment
+    """One handle (the device's layer records are those the previous call's solver kernel wrote) and an assignment
     that changes from call to call: the budget and the default move so that layers go from
     quantization to Top-K and back.  Nothing a call leaves behind may leak into the next: every
     call against the separate calls and the oracle's solver; the last calls repeat one setting."""
@@ -590,8 +586,8 @@ def test_whole_path_call_when_the_assignment_changes_between_calls():
     plain.close()
 
 
-def test_whole_path_call_failing_after_good_calls_with_history_on():
-    """History on, a good call, then calls that end without compressing (payload buffer too small,
+def test_whole_path_call_failing_after_good_calls():
+    """A good call, then calls that end without compressing (payload buffer too small,
     a non-finite gradient): the error-feedback buffer must hold x = fl32(g + e) everywhere and the
     payload buffer nothing, and the handle goes on working; a call whose solve falls back to the
     uniform default (strict budget, nothing fits) compresses through the host's route, which
@@ -723,8 +719,7 @@ def test_zero_error_feedback_promise_changes_nothing(kind):
     def handle():
         return B.Handle(int(batch.grads.size), L, len(cands), stochastic=w.stochastic, seed=w.seed, r_max=w.r_max,
                         reuse_thresholds=True)
-    # two handles side by side, call for call (with reuse_thresholds a handle's n-th call sums the
-    # energies below a bound that depends on its earlier calls, so only equal histories compare bit for bit)
+    # two handles side by side, call for call
     plain, promised = handle(), handle()
     promised.set_ef_zero_on_entry(True)
     for _ in range(3):
