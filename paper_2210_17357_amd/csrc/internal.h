@@ -202,7 +202,7 @@ struct SolveParams {
     int32_t have_e_max;           // ... unless the caller gives it
     double e_max;
     int32_t e_limit;              // the bins of an accepted assignment sum to at most min(D, e_limit)
-    int32_t last_resort;          // 1: the caller has nothing to fall back to (lists of up to 64 candidates only)
+    int32_t last_resort;          // 1: the caller has nothing to fall back to (at most 4096 table entries, 64 candidates)
     int32_t check_sizes;          // 1: reject (status 3) sizes this path's 32-bit costs cannot hold
     int32_t* choice;              // out [L] candidate per layer, -1 when not solved
     int64_t* result;              // out [16]: [0] status (0 ok, 1 infeasible, 2 inconsistent, 3 invalid input, 4 not

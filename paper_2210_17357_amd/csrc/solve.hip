@@ -421,8 +421,9 @@ __device__ __forceinline__ const uint32_t* sweep_shaped(SweepShape f, const Swee
     }
 }
 
-// NE: table entries per thread (L x P <= NE x 1024)
-template <int NE>
+// NE: table entries per thread (L x P <= NE x 1024).  LAST: with the last resort (SolveParams::last_resort).  It is left out
+// where a caller has another solver: in one kernel with the rest its code cost a solve 0.2 to 1.9 us.
+template <int NE, bool LAST>
 __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
     extern __shared__ __align__(16) unsigned char solve_smem[];
     Lds& s = *reinterpret_cast<Lds*>(solve_smem);
@@ -1109,27 +1110,29 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
                 status = 2;
             } else if ((s.flags & 8) || (int)shift_all > D) {        // a layer no bin sum can reach
                 status = reduce ? 2 : 1;
-            } else if (lists && !(p.last_resort && P <= 64)) {
+            } else if (lists && !(LAST && P <= 64)) {
                 status = 4;
             } else {
                 const uint32_t* last = sw.buffer;
                 const int cand_bits = 32 - __builtin_clz(P - 1);                       // (lists: P is at least 2)
                 const bool pack_cand = ((unsigned long long)s.facts[3] << cand_bits) < kInfPacked;
-                const int row_bits = lists ? (pack_cand ? cand_bits : 0) : bits;
+                const int row_bits = LAST && lists ? (pack_cand ? cand_bits : 0) : bits;
                 if (n_core == 0) {
                     if (tid == 0) sw.buffer[0] = 0;
                     __syncthreads();
-                } else if (lists) {              // (the row takes the survivors' place)
+                } else if (LAST && lists) {      // (the row takes the survivors' place)
                     uint32_t* const buffer = reinterpret_cast<uint32_t*>(ent);
-                    if (w_max < 6 * kThreadsS)
-                        last = pack_cand ? sweep_lists<6, true>(s, rec, buffer, p.pd, n_core, cand_bits)
-                                         : sweep_lists<6, false>(s, rec, buffer, p.pd, n_core, 0);
-                    else if (w_max < 10 * kThreadsS)
-                        last = pack_cand ? sweep_lists<10, true>(s, rec, buffer, p.pd, n_core, cand_bits)
-                                         : sweep_lists<10, false>(s, rec, buffer, p.pd, n_core, 0);
-                    else
-                        last = pack_cand ? sweep_lists<kMaxRow / kThreadsS, true>(s, rec, buffer, p.pd, n_core, cand_bits)
-                                         : sweep_lists<kMaxRow / kThreadsS, false>(s, rec, buffer, p.pd, n_core, 0);
+                    if constexpr (LAST) {
+                        if (w_max < 6 * kThreadsS)
+                            last = pack_cand ? sweep_lists<6, true>(s, rec, buffer, p.pd, n_core, cand_bits)
+                                             : sweep_lists<6, false>(s, rec, buffer, p.pd, n_core, 0);
+                        else if (w_max < 10 * kThreadsS)
+                            last = pack_cand ? sweep_lists<10, true>(s, rec, buffer, p.pd, n_core, cand_bits)
+                                             : sweep_lists<10, false>(s, rec, buffer, p.pd, n_core, 0);
+                        else
+                            last = pack_cand ? sweep_lists<kMaxRow / kThreadsS, true>(s, rec, buffer, p.pd, n_core, cand_bits)
+                                             : sweep_lists<kMaxRow / kThreadsS, false>(s, rec, buffer, p.pd, n_core, 0);
+                    }
                 } else if (words) {
                     last = sweep_shaped<true, true, false>(form, sw);
                 } else if (bits) {
@@ -1161,7 +1164,7 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
                     // ---- back-trace: one arg-min byte per core layer is the chain; records and survivors'
                     // bins are fetched ahead of it.  A byte that cannot be is caught by the sums below
                     // (LDS reads stay in range by themselves; the walk in device memory is clamped).
-                    if (lists && wave == 0) {
+                    if (LAST && lists && wave == 0) {
                         int t = (int)(uint32_t)b - base;
                         for (int j = n_core - 1; j >= 0; --j) {
                             const int a = min(max(rec[j].trace + t, 0), (int)cells - 1), i = s.lo[j];
@@ -1231,7 +1234,7 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
                         pz = s.size[only];
                         s.chosen[s.layer[tid]] = s.cand[only];
                     }
-                    if (lists && tid < n_core) {          // (the walk left the entries)
+                    if (LAST && lists && tid < n_core) {  // (the walk left the entries)
                         const int at = min(s.hi[tid], kMaxT - 1);
                         pb += s.bin[at];
                         pz += s.size[at];
@@ -1343,14 +1346,17 @@ hipError_t launch_solve(const SolveParams& p, hipStream_t s, Section* sec) {
                   "records and the widest row always fit");
     static bool configured = false;
     if (!configured) {
-        hipError_t e = hipFuncSetAttribute((const void*)solve_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute((const void*)solve_kernel<16>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
+        for (const void* k : {(const void*)solve_kernel<4, false>, (const void*)solve_kernel<16, false>, (const void*)solve_kernel<4, true>}) {
+            const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
         configured = true;
     }
-    if (p.L * p.P <= 4 * kThreadsS) launch_timed(sec, true, true, solve_kernel<4>, dim3(1), dim3(kThreadsS), lds, s, p);
-    else launch_timed(sec, true, true, solve_kernel<16>, dim3(1), dim3(kThreadsS), lds, s, p);
+    const bool small = p.L * p.P <= 4 * kThreadsS;
+    if (p.last_resort && !small) return hipErrorInvalidValue;
+    if (p.last_resort) launch_timed(sec, true, true, solve_kernel<4, true>, dim3(1), dim3(kThreadsS), lds, s, p);
+    else if (small) launch_timed(sec, true, true, solve_kernel<4, false>, dim3(1), dim3(kThreadsS), lds, s, p);
+    else launch_timed(sec, true, true, solve_kernel<16, false>, dim3(1), dim3(kThreadsS), lds, s, p);
     return hipGetLastError();
 }
 
