@@ -196,8 +196,10 @@ int64_t quant_size(int64_t n, int bits, int bucket) {
     return s;
 }
 
+// (The conversion rounds down, as v is positive.  A call of floor here took 24 or 33 us for the table of 161 layers
+// and 100 densities, with the place the linker gave the code; without it 20.)
 int64_t topk_k(int64_t n, double d) {
-    const double v = std::floor(d * (double)n + 0.5);
+    const double v = d * (double)n + 0.5;
     int64_t k = (v >= 9.0e18) ? n : (int64_t)v;
     if (k < 1) k = 1;
     if (k > n) k = n;

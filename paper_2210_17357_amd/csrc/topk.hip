@@ -1966,7 +1966,7 @@ hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d
         TK_CHECK(hipGetLastError());
         for (p.list0 = 0; p.list0 < t->nk_many; p.list0 += p.room) {
             // (a pass after the first finds nothing to do unless the layers have that many lists: small grids.  100
-            // densities of a 26 M-element model, about 25 lists in a buffer of 73: 264 us a run, 261 with one pass)
+            // densities of a 26 M-element model, about 25 lists in a buffer of 73: 3 of a run's 245 us)
             hipLaunchKernelGGL(topk_refine_many_kernel, dim3(t->n_work, p.list0 ? 1 : kManySplit), dim3(kRefThreads), lds, s, p);
             TK_CHECK(hipGetLastError());
             hipLaunchKernelGGL(topk_pick_many_kernel, dim3(L, p.list0 ? 4 : kManySlots), dim3(256), 0, s, p);

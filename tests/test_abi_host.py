@@ -119,3 +119,16 @@ def test_candidate_range_rule(lib):
     for bad in ((W.QUANT, 9), (W.QUANT, 2.5), (W.TOPK, 0.0), (W.TOPK, 1.5), (7, 1)):
         with pytest.raises(B.LgrecoError):
             B.candidate_range(*bad)
+
+
+def test_topk_sizes_where_the_rounding_decides():
+    """k = floor(d n + 0.5) in fp64: products at and beside half-integers, the smallest and largest layers and
+    densities, against the oracle's floor."""
+    from oracle import topk
+    from paper_2210_17357_amd import binding as B
+    from paper_2210_17357_amd import workloads as W
+    for n in (1, 2, 3, 10, 127, 1000, 65537, (1 << 24) + 1, (1 << 31) - 1):
+        halves = [(k + 0.5) / n for k in (0, 1, 2, n // 3, n - 1) if k < n]
+        densities = sorted({x for h in halves for x in (h, np.nextafter(h, 0), np.nextafter(h, 1))} | {1.0, 0.5, 1e-300, np.nextafter(1, 0)})
+        got = B.sizes(B.layer_table([0], [n], [0], [0]), B.cand_table([(W.TOPK, float(d)) for d in densities]))
+        assert got[0].tolist() == [topk.size_bytes(n, float(d)) for d in densities], n
