@@ -147,6 +147,11 @@ void size_order(const int64_t* sizes, int L, int P, uint8_t* order) {
     }
 }
 
+// Where the low-rank profile leaves x = g + e for what reads the matrix after its first contraction, the compression of
+// the one call included (the error feedback itself stays as it is until the assignment is known): a Top-K buffer that
+// is used with x in place of the error feedback only, hence never with a low-rank candidate in the list.
+float* lowrank_x(const lgreco_handle* h) { return reinterpret_cast<float*>(h->topk.d_kept); }
+
 SolveParams solve_params(lgreco_handle* h, int L, int P, int n_bins) {
     SolveParams p{};
     p.L = L;
@@ -716,7 +721,7 @@ int lgreco_emax(const double* errors, int32_t L, int32_t P, int32_t default_cand
 // forms it (the error-feedback buffer itself in the one-call path) and everything after it reads x from there
 static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float* d_ef, const lgreco_layer_t* layers,
                            int32_t L, const lgreco_cand_t* cands, int32_t P, const float* d_q0, int64_t* sizes,
-                           double* d_err, hipStream_t s, float* x_out = nullptr, float* lowrank_x = nullptr) {
+                           double* d_err, hipStream_t s, float* x_out = nullptr) {
     if (!h || !d_grads || !layers || !cands || L <= 0 || P <= 0) return LGRECO_EINVAL;
     if (P > h->max_cands) return LGRECO_ENOSPACE;
     begin_call(h, s, LGRECO_CALL_PROFILE);
@@ -835,7 +840,7 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
     if (ntk) HIPCHK(topk_finalize(&h->topk, h->d_layers, h->d_tiles, L, ntk, tk_col, d_err, P, h->tm, s));
     if (nlr) {
         HIPCHK(lowrank_profile(&h->lowrank, d_grads, d_ef, h->d_layers, h->hl.data(), L, d_q0, h->cfg.r_max,
-                               lr_rank, lr_col, nlr, d_err, P, lowrank_x, h->tm, s));
+                               lr_rank, lr_col, nlr, d_err, P, lowrank_x(h), h->tm, s));
     }
     return LGRECO_OK;
 }
@@ -1064,15 +1069,10 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
         if (total_error) *total_error = terr;
         return (int)LGRECO_OK;
     };
-    // where the low-rank profile leaves x = g + e for the compression (the error feedback itself stays as it is until the
-    // assignment is known): a Top-K buffer that is used with x in place of the error feedback only, hence
-    // never with a low-rank candidate in the list
-    float* const lowrank_x = reinterpret_cast<float*>(h->topk.d_kept);
     // the solver kernel reads the error table from device memory and passes it on to the host
     const bool on_device = one_kernel_solve(h, L, P);
     int st = profile_enqueue(h, d_grads, d_ef, layers, L, cands, P, d_q0, sizes,
-                             on_device ? h->d_errors_dev : h->d_errors, s, (ec && ec->x_in_e) ? ec->d_ef : nullptr,
-                             ec ? lowrank_x : nullptr);
+                             on_device ? h->d_errors_dev : h->d_errors, s, (ec && ec->x_in_e) ? ec->d_ef : nullptr);
     if (st != LGRECO_OK) return st;
     // The one-kernel solve takes 32-bit costs only; anything it does not take goes the three
     // calls' route (same results, one more host round trip).
@@ -1194,7 +1194,7 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
             // ... and the low-rank layers': the factors of every rank are the leading columns of
             // the rank-64 run the profile just made on this data
             HIPCHK(lowrank_compress_known(&h->lowrank, d_grads, ec->d_ef, h->d_layers, ec->d_q, h->cfg.r_max,
-                                          ec->d_payload, d_ef ? lowrank_x : nullptr, h->tm, s, h->ef_zero_on_entry));
+                                          ec->d_payload, d_ef ? lowrank_x(h) : nullptr, h->tm, s, h->ef_zero_on_entry));
         }
         // the compress call stays open until lgreco_compress's part has queued the rest: nobody
         // reads its events out before (that would wait for the kernel just queued)

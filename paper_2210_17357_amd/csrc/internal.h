@@ -322,7 +322,8 @@ struct LowrankScratch {
 hipError_t lowrank_scratch_create(LowrankScratch* t, int64_t max_elems, int max_layers, int r_max,
                                   int power_iters);
 void lowrank_scratch_destroy(LowrankScratch* t);
-// x (may be null): room for the layers' elements; a compression that follows on the same data reads g + e there
+// x: room for the layers' elements, where g + e is left (e not null) for the passes behind the first and for a
+// compression that follows on the same data
 hipError_t lowrank_profile(LowrankScratch* t, const float* g, const float* e, const DevLayer* d_layers,
                            const DevLayer* h_layers, int L, const float* q0, int r_max, const int* rank,
                            const int* col, int nlr, double* d_errors, int stride, float* x, Timing* tm, hipStream_t s);

@@ -50,7 +50,6 @@ struct LrLayer {
     int32_t gram_begin, gram_end;   // Gram partial range
     int32_t rt_begin, rt_end;       // row-tile range (||X||^2 partials)
     int32_t qc_begin, qc_end;       // Q-chunk range (column-norm partials)
-    int32_t vec_ok;     // 16-byte aligned rows: offset % 4 == 0 and cols % 4 == 0
     int32_t index;      // index in the caller's layer table
     int32_t pad;
 };
@@ -61,8 +60,8 @@ struct LrTile {
 struct LrParams {
     const float* g;
     const float* e;          // may be null
-    // x = g + e, left there by the first contraction (x_out set) for everything that reads the matrix after it
-    // (e null, from_x set): a pass over one buffer instead of two.  Null: g and e are read every time.
+    // x = g + e, left there by the first contraction where there is an e for everything that reads the matrix after it
+    // (e null, from_x set): a pass over one buffer instead of two.
     float* x;
     int32_t from_x;
     float* e_out;            // compress: error feedback (same buffer as e)
@@ -96,84 +95,91 @@ struct LrParams {
     const DevLayer* dev_layers;   // KNOWN kernels: the caller's layer records (family, rank, payload offset) on the device
 };
 
-// 4 consecutive elements of x = g + e starting at idx of a row that has `left` elements left.
-__device__ __forceinline__ float4 load_x4(const float* __restrict__ g, const float* __restrict__ e, int64_t idx,
-                                          int left, bool vec_ok) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (left >= 4 && vec_ok) {
-        v = *reinterpret_cast<const float4*>(g + idx);
-        if (e) {
-            const float4 w = *reinterpret_cast<const float4*>(e + idx);
-            v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
-        }
-    } else {
-        if (left > 0) v.x = e ? g[idx] + e[idx] : g[idx];
-        if (left > 1) v.y = e ? g[idx + 1] + e[idx + 1] : g[idx + 1];
-        if (left > 2) v.z = e ? g[idx + 2] + e[idx + 2] : g[idx + 2];
-        if (left > 3) v.w = e ? g[idx + 3] + e[idx + 3] : g[idx + 3];
-    }
-    return v;
-}
-
 // The matrix as everything behind the first contraction reads it.
 __device__ __forceinline__ const float* matrix_of(const LrParams& p, const LrLayer& L) {
     return p.from_x ? p.x + L.x_off : p.g + L.offset;
 }
 
+// 4 consecutive floats as one access wherever they start: fp32 elements lie on 4-byte boundaries, which is all that a
+// 128-bit global access of this GPU asks for (offset and columns of a layer may be odd).
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load4_any(const float* p) {
+    const f32x4_any v = *reinterpret_cast<const f32x4_any*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void store4_any(float* p, const float4 v) {
+    f32x4_any w;
+    w.x = v.x; w.y = v.y; w.z = v.z; w.w = v.w;
+    *reinterpret_cast<f32x4_any*>(p) = w;
+}
+
 // ------------------------------------------------------------------ P = X Q0 (and ||X||^2)
-// One workgroup: 128 rows x 64 columns of P over one column range of X; wavefront w owns rows
-// 32w .. 32w+31.  The A operand never passes through LDS: lane l keeps, for row l % 32, the 16
-// consecutive elements X[row][k0 + 16 (l / 32) .. + 15] of the current 32-column chunk in
-// registers (four 128-bit loads; lanes l and l + 32 together read one 128-byte line of the row),
-// and MFMA step s contracts the column pair (k0 + s, k0 + 16 + s).  Only the 32 x 64 chunk of Q0,
-// shared by the four wavefronts, is staged in LDS (double buffered).
-// X_OUT: x is written to LrParams::x as it is formed.
-template <bool HAS_E, bool X_OUT>
-__global__ __launch_bounds__(256) void lr_gemm1_kernel(LrParams p) {
-    __shared__ float Qs[2][kLrBK][kLrCols];
+// One workgroup: 128 rows x 64 columns of P over one column range of X, 32 columns at a time; wavefront w owns rows
+// 32w .. 32w+31.  Bound by HBM (g and e in, x out).  A wavefront's loads take 8 rows of 128 bytes each, x leaves the
+// same way, and the operand (a lane holds a row) is formed through the wavefront's own LDS rows, which no other
+// wavefront touches; the 32 x 64 chunk of Q0, shared by the four, is staged behind a barrier (two buffers).
+// MFMA step (i, u) contracts the columns 8 i + u and 8 i + 4 + u of the chunk, so that a lane's four values of an i
+// are one 128-bit read of its row; rows are 36 words apart, 16 lanes of such a read on different banks.
+// 67 M elements of 66 matrices: 165 us, 4.9 TB/s of g, e and x (190 with a lane loading and storing 16 consecutive elements
+// of its own row, 64 pieces of lines an instruction).  Rows off 16-byte alignment take the same path: 73 M
+// elements of odd widths 1905 us a step, 811 with both contractions so (four scalar loads a lane before).
+// HAS_E: x = g + e is formed here and written to LrParams::x.
+constexpr int kLrXPitch = kLrBK + 4;
+template <bool HAS_E>
+__global__ __launch_bounds__(256, 4) void lr_gemm1_kernel(LrParams p) {
+    __shared__ __align__(16) float Xs[4][32][kLrXPitch];
+    __shared__ __align__(16) float Qs[2][kLrBK][kLrCols];
     __shared__ double s_red[4];
     const LrTile tile = p.p_tiles[blockIdx.x];
     const LrLayer L = p.layers[tile.layer];
     const int m = L.rows, n = L.cols, row0 = tile.a0;
     const int kbeg = tile.split * L.pksplit, kend = min(n, kbeg + L.pksplit);
-    const float* __restrict__ g = HAS_E ? p.g + L.offset : matrix_of(p, L);
-    const float* e = HAS_E ? p.e + L.offset : nullptr;      // (x may take its place: read before it is written, by the same lane)
-    float* const xo = X_OUT ? p.x + L.x_off : nullptr;
+    const float* __restrict__ g = (HAS_E ? p.g + L.offset : matrix_of(p, L)) + (int64_t)row0 * n;
+    // (x may take the place of e: read before it is written, by the same lane)
+    const float* e = HAS_E ? p.e + L.offset + (int64_t)row0 * n : nullptr;
+    float* const xo = HAS_E ? p.x + L.x_off + (int64_t)row0 * n : nullptr;
     // first power-iteration step: the caller's warm start (row stride r_max); later steps: the Q
     // of the previous step in the scratch buffer (row stride 64)
     const bool qscr = p.q_from_scratch != 0;
     const float* __restrict__ q = qscr ? p.Q + L.qs_off : p.q0 + L.q_off;
     const int qstride = qscr ? kLrCols : p.r_max;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const bool vec = L.vec_ok != 0;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const bool qvec = (qstride == kLrCols) && (qscr || L.q_off % 4 == 0);
     const int half = lane >> 5, bj = lane & 31;
-    const int row = row0 + 32 * wave + bj;               // this lane's row of X
-    const bool row_ok = row < m;
-    const float* __restrict__ grow = g + (int64_t)row * n;
-    const float* erow = HAS_E ? e + (int64_t)row * n : nullptr;
-    float* const xrow = X_OUT ? xo + (int64_t)row * n : nullptr;
+    // this lane's share of a chunk: rows 8 s + lane / 8 of the wavefront's, columns lc .. lc + 3.  Rows past the end
+    // read the last one; nothing of theirs is written, summed or stored.
+    const int lc = 4 * (lane & 7);
+    uint32_t at[4];                                      // (below 2^31, as the layer's size is)
+    bool row_ok[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const int r = 32 * wave + 8 * s + (lane >> 3);
+        row_ok[s] = row0 + r < m;
+        at[s] = (uint32_t)min(r, m - 1 - row0) * (uint32_t)n + (uint32_t)lc;
+    }
 
     float4 xg[4], xe[HAS_E ? 4 : 1], qr[2];
-    bool add_e = false;
     // issue the loads of one chunk (their values are first used after the MFMAs of the chunk
     // that is being multiplied)
-    auto fetch = [&](int k0) {
-        const int kx = k0 + 16 * half;
-        add_e = false;
-        if (vec && row_ok && k0 + kLrBK <= kend) {           // uniform except for the row test
-            add_e = HAS_E;
+    auto fetch = [&](int k0) __attribute__((always_inline)) {
+        const float* const gk = g + k0;
+        const float* const ek = HAS_E ? e + k0 : nullptr;
+        if (k0 + kLrBK <= kend) {                            // uniform
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                xg[s] = *reinterpret_cast<const float4*>(grow + kx + 4 * s);
-                if (HAS_E) xe[s] = *reinterpret_cast<const float4*>(erow + kx + 4 * s);
+                xg[s] = load4_any(gk + at[s]);
+                if (HAS_E) xe[s] = load4_any(ek + at[s]);
             }
         } else {
+            const int left = kend - k0 - lc;
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                xg[s] = make_float4(0.f, 0.f, 0.f, 0.f);
-                const int kk = kx + 4 * s;
-                if (row_ok && kk < kend) xg[s] = load_x4(grow, erow, kk, kend - kk, vec);
+                const float* const gs = gk + at[s];
+                xg[s] = make_float4(left > 0 ? gs[0] : 0.f, left > 1 ? gs[1] : 0.f, left > 2 ? gs[2] : 0.f, left > 3 ? gs[3] : 0.f);
+                if (HAS_E) {
+                    const float* const es = ek + at[s];
+                    xe[s] = make_float4(left > 0 ? es[0] : 0.f, left > 1 ? es[1] : 0.f, left > 2 ? es[2] : 0.f, left > 3 ? es[3] : 0.f);
+                }
             }
         }
         if (qvec && k0 + kLrBK <= kend) {
@@ -200,29 +206,31 @@ __global__ __launch_bounds__(256) void lr_gemm1_kernel(LrParams p) {
         }
     };
     float xsq = 0.0f;
-    float cur[16];
-    // take the fetched chunk into use: x = g + e, ||x||^2, Q0 rows to LDS
-    auto commit = [&](int buf, int k0) {
+    // take the fetched chunk into use: x = g + e, ||x||^2, x to memory and LDS, Q0 rows to LDS
+    auto commit = [&](int buf, int k0) __attribute__((always_inline)) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             float4 v = xg[s];
-            if (HAS_E && add_e) { v.x += xe[s].x; v.y += xe[s].y; v.z += xe[s].z; v.w += xe[s].w; }
-            if (X_OUT) {
-                const int kk = k0 + 16 * half + 4 * s;
-                if (add_e) {
-                    *reinterpret_cast<float4*>(xrow + kk) = v;
-                } else if (row_ok) {
-                    if (kk < kend) xrow[kk] = v.x;
-                    if (kk + 1 < kend) xrow[kk + 1] = v.y;
-                    if (kk + 2 < kend) xrow[kk + 2] = v.z;
-                    if (kk + 3 < kend) xrow[kk + 3] = v.w;
+            if (HAS_E) { v.x += xe[s].x; v.y += xe[s].y; v.z += xe[s].z; v.w += xe[s].w; }
+            if (HAS_E && row_ok[s]) {
+                float* const xs = xo + k0 + at[s];
+                const int left = kend - k0 - lc;
+                if (k0 + kLrBK <= kend) {                    // uniform
+                    store4_any(xs, v);
+                } else {
+                    if (left > 0) xs[0] = v.x;
+                    if (left > 1) xs[1] = v.y;
+                    if (left > 2) xs[2] = v.z;
+                    if (left > 3) xs[3] = v.w;
                 }
             }
-            cur[4 * s] = v.x; cur[4 * s + 1] = v.y; cur[4 * s + 2] = v.z; cur[4 * s + 3] = v.w;
-            xsq = __builtin_fmaf(v.x, v.x, xsq);
-            xsq = __builtin_fmaf(v.y, v.y, xsq);
-            xsq = __builtin_fmaf(v.z, v.z, xsq);
-            xsq = __builtin_fmaf(v.w, v.w, xsq);
+            *reinterpret_cast<float4*>(&Xs[wave][8 * s + (lane >> 3)][lc]) = v;
+            if (row_ok[s]) {
+                xsq = __builtin_fmaf(v.x, v.x, xsq);
+                xsq = __builtin_fmaf(v.y, v.y, xsq);
+                xsq = __builtin_fmaf(v.z, v.z, xsq);
+                xsq = __builtin_fmaf(v.w, v.w, xsq);
+            }
         }
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -239,12 +247,19 @@ __global__ __launch_bounds__(256) void lr_gemm1_kernel(LrParams p) {
     for (int c = 0; c < nchunks; ++c) {
         const int buf = c & 1;
         if (c + 1 < nchunks) fetch(kbeg + (c + 1) * kLrBK);
+        float4 a[4];
 #pragma unroll
-        for (int s = 0; s < 16; ++s) {
-            const float b0 = Qs[buf][16 * half + s][bj];
-            const float b1 = Qs[buf][16 * half + s][32 + bj];
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(cur[s], b0, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(cur[s], b1, acc1, 0, 0, 0);
+        for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const float4*>(&Xs[wave][bj][8 * i + 4 * half]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float av = u == 0 ? a[i].x : u == 1 ? a[i].y : u == 2 ? a[i].z : a[i].w;
+                const float b0 = Qs[buf][8 * i + 4 * half + u][bj];
+                const float b1 = Qs[buf][8 * i + 4 * half + u][32 + bj];
+                acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(av, b0, acc0, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av, b1, acc1, 0, 0, 0);
+            }
         }
         if (c + 1 < nchunks) commit(buf ^ 1, kbeg + (c + 1) * kLrBK);
         __syncthreads();
@@ -540,65 +555,62 @@ __global__ __launch_bounds__(256) void lr_apply_kernel(LrParams p) {
 }
 
 // ------------------------------------------------------------------ Q partials = X^T Phat
-template <bool HAS_E>
+// One workgroup: 128 columns of X (rows of Q) over one range of its rows, X and Phat in chunks of 32 rows through LDS
+// (two buffers).  Bound by the fp32 matrix pipe (67 M elements: 89 us; the products alone take 70 at the 2.1 GHz the
+// chip holds in a burst this short).  Every load of a chunk is issued without a condition and used after the
+// products of the chunk before it; rows past the range and columns past the matrix are made zero as they go to LDS.
+// (With both operands loaded straight in the layout of the instruction, no LDS and no barriers, 102-121 us: 204 registers
+// leave two wavefronts on a SIMD, too few to cover the loads.)
 __global__ __launch_bounds__(256) void lr_gemm2_kernel(LrParams p) {
-    __shared__ float Xs[2][kLrBK][kLrBM];
-    __shared__ float Ps[2][kLrBK][kLrCols];
+    __shared__ __align__(16) float Xs[2][kLrBK][kLrBM];
+    __shared__ __align__(16) float Ps[2][kLrBK][kLrCols];
     const LrTile tile = p.col_tiles[blockIdx.x];
     const LrLayer L = p.layers[tile.layer];
     const int m = L.rows, n = L.cols, col0 = tile.a0;
     const int kbeg = tile.split * L.ksplit, kend = min(m, kbeg + L.ksplit);
-    const float* __restrict__ g = HAS_E ? p.g + L.offset : matrix_of(p, L);
-    const float* __restrict__ e = HAS_E ? p.e + L.offset : nullptr;
+    const float* __restrict__ X = matrix_of(p, L);
     const float* __restrict__ P = p.P + L.p_off;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const bool vec = L.vec_ok != 0;
+    // this thread's columns of X: col .. col + 3, loaded `shift` columns further left where they would reach past the
+    // row's end (a matrix of fewer than 4 columns: element by element)
+    const int col = col0 + (tid & 31) * 4, from = max(min(col, n - 4), 0), shift = n >= 4 ? col - from : 0;
+    const bool cols_full = col0 + kLrBM <= n;
 
     float4 xr[4], pr[2];
-    const bool cols_full = col0 + kLrBM <= n;
-    float4 er[HAS_E ? 4 : 1];
-    bool add_e = false;
-    auto fetch = [&](int k0) {
-        add_e = false;
-        if (vec && cols_full && k0 + kLrBK <= kend) {       // no per-load condition (see lr_gemm1_kernel)
-            add_e = HAS_E;
+    auto fetch = [&](int k0) __attribute__((always_inline)) {
+        const int last = kend - 1 - k0;                      // rows past the range read the last one
+        const float* const x0 = X + (int64_t)k0 * n + from;
+        if (n >= 4) {                                        // (uniform)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) xr[s] = load4_any(x0 + (uint32_t)min((tid >> 5) + 8 * s, last) * (uint32_t)n);
+        } else {
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                const int f = tid + 256 * s;
-                const int64_t idx = (int64_t)(k0 + (f >> 5)) * n + col0 + (f & 31) * 4;
-                xr[s] = *reinterpret_cast<const float4*>(g + idx);
-                if (HAS_E) er[s] = *reinterpret_cast<const float4*>(e + idx);
+                const float* const row = x0 + min((tid >> 5) + 8 * s, last) * n;
+                xr[s] = make_float4(col < n ? row[col] : 0.f, col + 1 < n ? row[col + 1] : 0.f, col + 2 < n ? row[col + 2] : 0.f, 0.f);
             }
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const int f = tid + 256 * s;
-                pr[s] = *reinterpret_cast<const float4*>(P + (int64_t)(k0 + (f >> 4)) * kLrCols + (f & 15) * 4);
-            }
-            return;
         }
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int f = tid + 256 * s;
-            const int kr = f >> 5, c = (f & 31) * 4;
-            const int row = k0 + kr, col = col0 + c;
-            xr[s] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (row < kend && col < n) xr[s] = load_x4(g, e, (int64_t)row * n + col, n - col, vec);
-        }
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int f = tid + 256 * s;
-            const int kr = f >> 4, c = (f & 15) * 4;
-            const int row = k0 + kr;
-            pr[s] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (row < kend) pr[s] = *reinterpret_cast<const float4*>(P + (int64_t)row * kLrCols + c);
-        }
+        for (int s = 0; s < 2; ++s)
+            pr[s] = *reinterpret_cast<const float4*>(P + (int64_t)(k0 + min((tid >> 4) + 16 * s, last)) * kLrCols + (tid & 15) * 4);
     };
-    auto stash = [&](int buf) {
-        if (HAS_E && add_e) {
+    auto stash = [&](int buf, int k0) __attribute__((always_inline)) {
+        if (!cols_full) {                                    // (uniform)
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-                xr[s].x += er[s].x; xr[s].y += er[s].y; xr[s].z += er[s].z; xr[s].w += er[s].w;
+                float4 v = xr[s];
+                v = shift == 0 ? v : shift == 1 ? make_float4(v.y, v.z, v.w, 0.f) : shift == 2 ? make_float4(v.z, v.w, 0.f, 0.f)
+                                 : shift == 3 ? make_float4(v.w, 0.f, 0.f, 0.f) : make_float4(0.f, 0.f, 0.f, 0.f);
+                xr[s] = v;
             }
+        }
+        if (k0 + kLrBK > kend) {                             // (uniform)
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+                if (k0 + (tid >> 5) + 8 * s >= kend) xr[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                if (k0 + (tid >> 4) + 16 * s >= kend) pr[s] = make_float4(0.f, 0.f, 0.f, 0.f);
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -615,7 +627,7 @@ __global__ __launch_bounds__(256) void lr_gemm2_kernel(LrParams p) {
     f32x16 acc0 = {0}, acc1 = {0};
     const int nchunks = (kend - kbeg + kLrBK - 1) / kLrBK;
     fetch(kbeg);
-    stash(0);
+    stash(0, kbeg);
     __syncthreads();
     const int ai = 32 * wave + (lane & 31), ak = lane >> 5, bj = lane & 31;
     for (int c = 0; c < nchunks; ++c) {
@@ -629,16 +641,16 @@ __global__ __launch_bounds__(256) void lr_gemm2_kernel(LrParams p) {
             acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b0, acc0, 0, 0, 0);
             acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b1, acc1, 0, 0, 0);
         }
-        if (c + 1 < nchunks) stash(buf ^ 1);
+        if (c + 1 < nchunks) stash(buf ^ 1, kbeg + (c + 1) * kLrBK);
         __syncthreads();
     }
     float* __restrict__ out = p.part + L.part_off + (int64_t)tile.split * n * kLrCols;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        const int col = col0 + 32 * wave + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (col < n) {
-            out[(int64_t)col * kLrCols + bj] = acc0[v];
-            out[(int64_t)col * kLrCols + 32 + bj] = acc1[v];
+        const int oc = col0 + 32 * wave + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+        if (oc < n) {
+            out[(int64_t)oc * kLrCols + bj] = acc0[v];
+            out[(int64_t)oc * kLrCols + 32 + bj] = acc1[v];
         }
     }
 }
@@ -1091,14 +1103,13 @@ static hipError_t lr_prepare(LowrankScratch* t, int slot, const DevLayer* hl, in
         a.rank = rank[l];
         a.payload = hl[l].payload;
         a.index = l;
-        a.vec_ok = (a.offset % 4 == 0 && a.cols % 4 == 0) ? 1 : 0;
         a.p_off = p_off;
         a.qs_off = q_off;
         a.part_off = part_off;
         // split the contraction over rows so that every column tile gets enough workgroups
         const int col_tiles = (a.cols + kLrBM - 1) / kLrBM;
         int splits = 1;
-        while (splits < 64 && (int64_t)a.rows / (splits * 2) >= 512 && col_tiles * splits < 128) splits *= 2;
+        while (splits < 64 && (int64_t)a.rows / (splits * 2) >= 512 && col_tiles * splits < 256) splits *= 2;
         a.ksplit = ((a.rows + splits - 1) / splits + kLrBK - 1) / kLrBK * kLrBK;
         a.splits = (a.rows + a.ksplit - 1) / a.ksplit;
         const int li = (int)H->layers.size();
@@ -1187,13 +1198,12 @@ static void lr_fill_params(LrHost* H, LrParams* p) {
 static hipError_t lr_factorize(LrHost* H, LrParams p, int iters, Timing* tm, hipStream_t s) {
   for (int it = 0; it < iters; ++it) {
     p.q_from_scratch = it > 0 ? 1 : 0;
-    const bool x_out = p.e && p.x;
+    const bool x_out = p.e != nullptr;
     {
         Section sec(tm, "lowrank_gemm_p", true);
         const dim3 grid((unsigned)H->p_tiles.size()), block(256);
-        if (x_out) launch_timed(&sec, true, true, lr_gemm1_kernel<true, true>, grid, block, 0, s, p);
-        else if (p.e) launch_timed(&sec, true, true, lr_gemm1_kernel<true, false>, grid, block, 0, s, p);
-        else launch_timed(&sec, true, true, lr_gemm1_kernel<false, false>, grid, block, 0, s, p);
+        if (x_out) launch_timed(&sec, true, true, lr_gemm1_kernel<true>, grid, block, 0, s, p);
+        else launch_timed(&sec, true, true, lr_gemm1_kernel<false>, grid, block, 0, s, p);
         LR_CHECK(hipGetLastError());
     }
     if (x_out) {                                  // from here on x is read in one piece
@@ -1215,10 +1225,7 @@ static hipError_t lr_factorize(LrHost* H, LrParams p, int iters, Timing* tm, hip
     }
     {
         Section sec(tm, "lowrank_gemm_q", true);
-        if (p.e)
-            launch_timed(&sec, true, true, lr_gemm2_kernel<true>, dim3((unsigned)H->col_tiles.size()), dim3(256), 0, s, p);
-        else
-            launch_timed(&sec, true, true, lr_gemm2_kernel<false>, dim3((unsigned)H->col_tiles.size()), dim3(256), 0, s, p);
+        launch_timed(&sec, true, true, lr_gemm2_kernel, dim3((unsigned)H->col_tiles.size()), dim3(256), 0, s, p);
         LR_CHECK(hipGetLastError());
     }
     {

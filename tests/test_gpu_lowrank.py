@@ -97,6 +97,20 @@ def test_odd_shapes_and_error_feedback():
     _check(w, batch, (1, 3, 4, 5))
 
 
+# Edges of the contractions' tiles (128 rows, 32-column chunks, 512-column splits; 128 columns, 32-row chunks) with
+# layers that start and whose rows end off 16-byte boundaries; fewer than 4 columns; one row or column.
+@pytest.mark.parametrize("shapes", [
+    [(128, 512), (127, 513), (129, 511)],
+    [(3, 7), (128, 544), (160, 128), (33, 129)],
+    [(1, 131), (65, 127), (31, 33), (1030, 5)],
+    [(5, 3), (97, 2), (64, 1), (1, 1), (258, 1026), (511, 130)],
+], ids=lambda s: "x".join(str(a) for a in s[0]))
+def test_contraction_tile_edges(shapes):
+    w = W.Workload("lr_edges", tuple(shapes), tuple((W.LOWRANK, float(r)) for r in (1, 7, 64)), 1, 100,
+                   "lowrank64", "normal0.1", (-3.0, -1.0), r_max=64, only_2d=True)
+    _check(w, W.generate(w), (1, 7, 64))
+
+
 def test_full_workload_errors_and_solve():
     from oracle import solver
     from paper_2210_17357_amd import binding as B
