@@ -35,9 +35,8 @@
  *     throws, nothing prints.  Inputs must be finite; NaN/Inf gradients give undefined
  *     numerical results (never a fault).
  *   - Gradients of all layers live in one flat fp32 buffer; layer l is the range
- *     [offset, offset + numel).  Ranges must not overlap.  16-byte aligned layer starts
- *     (offset % 4 == 0 with a 16-byte aligned buffer) take the fast path; other offsets work
- *     through a slower path.
+ *     [offset, offset + numel).  Ranges must not overlap.  A layer may start at any
+ *     element; starts at multiples of 4 elements are up to a tenth faster.
  */
 #ifndef LGRECO_H
 #define LGRECO_H

@@ -275,21 +275,18 @@ int prepare_layers(lgreco_handle* h, const lgreco_layer_t* layers, int32_t L) {
         d.q_offset = qoff;
         qoff += (int64_t)a.cols * h->cfg.r_max;
         d.tile_begin = (int32_t)h->ht.size();
-        const bool aligned = (a.offset % 4) == 0;
         int64_t pos = 0, n = a.numel;
         auto push = [&](int64_t cnt, int fast) {
             h->ht.push_back(Tile{pos, l, (int32_t)cnt, fast, 0});
             pos += cnt;
         };
-        while (n - pos >= tile) push(tile, aligned ? 1 : 0);
-        const int64_t rem = n - pos;
-        if (aligned) {
-            const int64_t mid = (rem / kChunk) * kChunk;
-            if (mid) push(mid, 1);
-            if (rem - mid) push(rem - mid, 0);
-        } else if (rem) {
-            push(rem, 0);
-        }
+        // whole chunks take the vector path wherever the layer starts, the rest of a layer the scalar one (73 M elements
+        // of odd widths with the scalar path for every layer off 16 bytes: 504 us a quantization step, 573 a mixed and
+        // 370 a Top-K one; now 352, 365 and 336, against 318, 338 and 312 where layers are aligned)
+        while (n - pos >= tile) push(tile, 1);
+        const int64_t rem = n - pos, mid = rem / kChunk * kChunk;
+        if (mid) push(mid, 1);
+        if (rem - mid) push(rem - mid, 0);
         d.tile_end = (int32_t)h->ht.size();
         h->layer_tiles = std::max(h->layer_tiles, d.tile_end - d.tile_begin);
     }

@@ -30,7 +30,7 @@ struct Tile {
     int64_t pos;      // first element, relative to the layer start
     int32_t layer;
     int32_t count;    // elements in this tile
-    int32_t fast;     // 1: 16-byte aligned and count % kChunk == 0 (vector path)
+    int32_t fast;     // 1: count % kChunk == 0 (vector path)
     int32_t pad;
 };
 
@@ -56,16 +56,27 @@ constexpr int kDppQuadXor2 = 0x4E;       // quad_perm:[2,3,0,1]
 constexpr int kDppRowHalfMirror = 0x141;
 constexpr int kDppRowMirror = 0x140;
 
-// 128-bit loads and stores marked as streaming (the data is used once): the caches need not keep it
-typedef float f32x4_native __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ float4 load_stream(const float4* p) {
-    const f32x4_native v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_native*>(p));
+// 4 consecutive floats as one access wherever they start: fp32 elements lie on 4-byte boundaries, which is all that a
+// 128-bit global access of this GPU asks for (a layer may start at any element).
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load4_any(const float* p) {
+    const f32x4_any v = *reinterpret_cast<const f32x4_any*>(p);
     return make_float4(v.x, v.y, v.z, v.w);
 }
-__device__ __forceinline__ void store_stream(float4* p, const float4 v) {
-    f32x4_native n;
+__device__ __forceinline__ void store4_any(float* p, const float4 v) {
+    f32x4_any w;
+    w.x = v.x; w.y = v.y; w.z = v.z; w.w = v.w;
+    *reinterpret_cast<f32x4_any*>(p) = w;
+}
+// the same marked as streaming (the data is used once): the caches need not keep it
+__device__ __forceinline__ float4 load_stream(const float* p) {
+    const f32x4_any v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void store_stream(float* p, const float4 v) {
+    f32x4_any n;
     n.x = v.x; n.y = v.y; n.z = v.z; n.w = v.w;
-    __builtin_nontemporal_store(n, reinterpret_cast<f32x4_native*>(p));
+    __builtin_nontemporal_store(n, reinterpret_cast<f32x4_any*>(p));
 }
 
 template <int CTRL>

@@ -25,7 +25,7 @@ struct DecodeParams {
 // 4 consecutive elements, so that a wavefront's accesses of the output are whole lines, and their 4 * bits
 // code bits from the one or two aligned words that hold them (a bucket starts on a word: 16 * bits bytes behind
 // payloads aligned to 16 and 8 bytes a bucket); kDepth of these are fetched before the first is used.
-// Tiles off 16-byte alignment and ragged ends take an element per thread.  Adding 355 M elements of 4 bits to the
+// Ragged ends take an element per thread.  Adding 355 M elements of 4 bits to the
 // output: 580 us, 5.2 TB/s (690 when a thread took 8 elements, loaded their bits byte by byte and touched
 // half a line per instruction, one group at a time).
 constexpr int kDepth = 4;
@@ -45,7 +45,6 @@ __global__ __launch_bounds__(kThreads) void quant_decode_kernel(DecodeParams p) 
 
     if (t.fast) {                                        // full buckets only
         const uint32_t* const words = reinterpret_cast<const uint32_t*>(codes);
-        float4* const out4 = reinterpret_cast<float4*>(out);
         const int nq = t.count / 4;
         const auto decode = [&](int q, uint32_t w0, uint32_t w1, float2 mu, float4 old) {
             const uint32_t v = __builtin_amdgcn_alignbit(w1, w0, (uint32_t)(4 * bits * q) & 31u);
@@ -55,7 +54,7 @@ __global__ __launch_bounds__(kThreads) void quant_decode_kernel(DecodeParams p) 
             x.z = __builtin_fmaf((float)__builtin_amdgcn_ubfe(v, 2 * bits, bits), mu.y, mu.x);
             x.w = __builtin_fmaf((float)__builtin_amdgcn_ubfe(v, 3 * bits, bits), mu.y, mu.x);
             if (ACCUMULATE) { x.x += old.x; x.y += old.y; x.z += old.z; x.w += old.w; }
-            store_stream(out4 + q, x);
+            store_stream(out + 4 * q, x);
         };
         // the word that holds the first and the word that holds the last of a thread's bits
         const auto word0 = [&](int q) { return words[(uint32_t)(4 * bits * q) >> 5]; };
@@ -72,13 +71,13 @@ __global__ __launch_bounds__(kThreads) void quant_decode_kernel(DecodeParams p) 
                 w0[u] = word0(qu);
                 w1[u] = word1(qu);
                 mu[u] = meta[qu / (kBucket / 4)];
-                old[u] = ACCUMULATE ? load_stream(out4 + qu) : zero;
+                old[u] = ACCUMULATE ? load_stream(out + 4 * qu) : zero;
             }
 #pragma unroll
             for (int u = 0; u < kDepth; ++u) decode(q + u * kThreads, w0[u], w1[u], mu[u], old[u]);
         }
         for (; q < nq; q += kThreads)
-            decode(q, word0(q), word1(q), meta[q / (kBucket / 4)], ACCUMULATE ? load_stream(out4 + q) : zero);
+            decode(q, word0(q), word1(q), meta[q / (kBucket / 4)], ACCUMULATE ? load_stream(out + 4 * q) : zero);
         return;
     }
     // a code lies in one byte or two; a short bucket's stream ends with the byte of its last code
@@ -116,7 +115,7 @@ __global__ __launch_bounds__(kThreads) void topk_decode_zero_kernel(DecodeParams
     float* const out = p.out + L.offset + t.pos;
     if (t.fast) {
         const float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int v = threadIdx.x; v < t.count / 4; v += kThreads) store_stream(reinterpret_cast<float4*>(out) + v, z);
+        for (int v = threadIdx.x; v < t.count / 4; v += kThreads) store_stream(out + 4 * v, z);
     } else {
         for (int i = threadIdx.x; i < t.count; i += kThreads) out[i] = 0.0f;
     }
@@ -146,12 +145,12 @@ __global__ __launch_bounds__(kThreads) void accumulate_kernel(float* __restrict_
     const int64_t n4 = n / 4;
     const int64_t stride = (int64_t)gridDim.x * kThreads;
     for (int64_t v = (int64_t)blockIdx.x * kThreads + threadIdx.x; v < n4; v += stride) {
-        float4 a = load_stream(reinterpret_cast<const float4*>(g) + v);
+        float4 a = load_stream(g + 4 * v);
         if (!reset) {
-            const float4 o = load_stream(reinterpret_cast<const float4*>(acc) + v);
+            const float4 o = load_stream(acc + 4 * v);
             a.x += o.x; a.y += o.y; a.z += o.z; a.w += o.w;
         }
-        store_stream(reinterpret_cast<float4*>(acc) + v, a);
+        store_stream(acc + 4 * v, a);
     }
     if (blockIdx.x == 0 && threadIdx.x < n - 4 * n4) {
         const int64_t i = 4 * n4 + threadIdx.x;

@@ -100,19 +100,6 @@ __device__ __forceinline__ const float* matrix_of(const LrParams& p, const LrLay
     return p.from_x ? p.x + L.x_off : p.g + L.offset;
 }
 
-// 4 consecutive floats as one access wherever they start: fp32 elements lie on 4-byte boundaries, which is all that a
-// 128-bit global access of this GPU asks for (offset and columns of a layer may be odd).
-typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ float4 load4_any(const float* p) {
-    const f32x4_any v = *reinterpret_cast<const f32x4_any*>(p);
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ void store4_any(float* p, const float4 v) {
-    f32x4_any w;
-    w.x = v.x; w.y = v.y; w.z = v.z; w.w = v.w;
-    *reinterpret_cast<f32x4_any*>(p) = w;
-}
-
 // ------------------------------------------------------------------ P = X Q0 (and ||X||^2)
 // One workgroup: 128 rows x 64 columns of P over one column range of X, 32 columns at a time; wavefront w owns rows
 // 32w .. 32w+31.  Bound by HBM (g and e in, x out).  A wavefront's loads take 8 rows of 128 bytes each, x leaves the

@@ -96,8 +96,8 @@ __global__ __launch_bounds__(kThreads) void quant_profile_kernel(QuantParams p) 
                 b.x += eb.x; b.y += eb.y; b.z += eb.z; b.w += eb.w;
             }
             if (xo) {                                   // uniform
-                store_stream(reinterpret_cast<float4*>(xo + base), a);
-                store_stream(reinterpret_cast<float4*>(xo + base + 64), b);
+                store_stream(xo + base, a);
+                store_stream(xo + base + 64, b);
             }
             float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
             if (HIST) {
@@ -162,10 +162,10 @@ __global__ __launch_bounds__(kThreads) void quant_profile_kernel(QuantParams p) 
             __attribute__((always_inline)) {
             if (c >= c_end) return;                     // uniform over the wavefront
             const int base = c * kChunk + lane_off;
-            a = load_stream(reinterpret_cast<const float4*>(g + base));
-            b = load_stream(reinterpret_cast<const float4*>(g + base + 64));
-            ea = HAS_EF ? load_stream(reinterpret_cast<const float4*>(e + base)) : zero4;
-            eb = HAS_EF ? load_stream(reinterpret_cast<const float4*>(e + base + 64)) : zero4;
+            a = load_stream(g + base);
+            b = load_stream(g + base + 64);
+            ea = HAS_EF ? load_stream(e + base) : zero4;
+            eb = HAS_EF ? load_stream(e + base + 64) : zero4;
         };
         if (c_begin < c_end) {
             float4 a0, b0, ea0, eb0, a1, b1, ea1, eb1;
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kThreads) void quant_profile_kernel(QuantParams p) 
             }
         }
     } else {
-        // Slow path (tail of a layer, or a layer that is not 16-byte aligned): one wavefront per
+        // Slow path (ragged end of a layer): one wavefront per
         // bucket, two elements per lane, out-of-range lanes masked.
         const int nb = (t.count + kBucket - 1) / kBucket;
         int b_begin, b_end;
@@ -315,11 +315,11 @@ __global__ __launch_bounds__(kThreads) void quant_compress_kernel(QuantCompressP
         wave_range(t.count / kChunk, wave, &c_begin, &c_end);
         for (int c = c_begin; c < c_end; ++c) {
             const int base = c * kChunk + row * kBucket + j * 4;
-            float4 a = load_stream(reinterpret_cast<const float4*>(e + base));
-            float4 b = load_stream(reinterpret_cast<const float4*>(e + base + 64));
+            float4 a = load_stream(e + base);
+            float4 b = load_stream(e + base + 64);
             if (!x_in_e) {                              // uniform
-                const float4 ga = load_stream(reinterpret_cast<const float4*>(g + base));
-                const float4 gb = load_stream(reinterpret_cast<const float4*>(g + base + 64));
+                const float4 ga = load_stream(g + base);
+                const float4 gb = load_stream(g + base + 64);
                 a.x = ga.x + a.x; a.y = ga.y + a.y; a.z = ga.z + a.z; a.w = ga.w + a.w;
                 b.x = gb.x + b.x; b.y = gb.y + b.y; b.z = gb.z + b.z; b.w = gb.w + b.w;
             }
@@ -355,8 +355,8 @@ __global__ __launch_bounds__(kThreads) void quant_compress_kernel(QuantCompressP
                 if (k < 4) wa |= qi << (bits * k);
                 else wb |= qi << (bits * (k - 4));
             }
-            store_stream(reinterpret_cast<float4*>(e + base), make_float4(ne[0], ne[1], ne[2], ne[3]));
-            store_stream(reinterpret_cast<float4*>(e + base + 64), make_float4(ne[4], ne[5], ne[6], ne[7]));
+            store_stream(e + base, make_float4(ne[0], ne[1], ne[2], ne[3]));
+            store_stream(e + base + 64, make_float4(ne[4], ne[5], ne[6], ne[7]));
             const int64_t bk = bucket0 + (int64_t)c * 4 + row;
             if (j == 0) meta[bk] = make_float2(mn, unit);
 

@@ -337,17 +337,17 @@ __device__ __forceinline__ void collect_tile(const CollectParams& p, const int t
         for (int v = c0 * (kChunk / 4) + lane; v < c1 * (kChunk / 4); v += kChunk / 4) {
             float4 a[2];
 #pragma unroll
-            for (int h = 0; h < 2; ++h) a[h] = load_stream(reinterpret_cast<const float4*>(gp) + v + 64 * h);
+            for (int h = 0; h < 2; ++h) a[h] = load_stream(gp + 4 * (v + 64 * h));
             if (ep) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const float4 b = load_stream(reinterpret_cast<const float4*>(ep) + v + 64 * h);
+                    const float4 b = load_stream(ep + 4 * (v + 64 * h));
                     a[h].x += b.x; a[h].y += b.y; a[h].z += b.z; a[h].w += b.w;
                 }
             }
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                if (!EMIT && xo) store_stream(reinterpret_cast<float4*>(xo) + v + 64 * h, a[h]);
+                if (!EMIT && xo) store_stream(xo + 4 * (v + 64 * h), a[h]);
                 if (EMIT && KNOWN) {
                     // nearly every candidate is kept here: candidates are written as zero at once, the
                     // emit step puts the few that are not kept back
@@ -356,9 +356,9 @@ __device__ __forceinline__ void collect_tile(const CollectParams& p, const int t
                     w.y = mag_bits(w.y) >= bound ? 0.0f : w.y;
                     w.z = mag_bits(w.z) >= bound ? 0.0f : w.z;
                     w.w = mag_bits(w.w) >= bound ? 0.0f : w.w;
-                    store_stream(reinterpret_cast<float4*>(eo) + v + 64 * h, w);
+                    store_stream(eo + 4 * (v + 64 * h), w);
                 } else if (EMIT) {
-                    store_stream(reinterpret_cast<float4*>(eo) + v + 64 * h, a[h]);
+                    store_stream(eo + 4 * (v + 64 * h), a[h]);
                 }
                 if (HIST) {
                     atomicAdd(&s_hist[mag_bits(a[h].x) >> kHistShift], 1u);

@@ -74,7 +74,7 @@ def test_quant_every_bit_width_ragged_layers(stochastic):
 
 @pytest.mark.parametrize("bits", range(1, 9))
 def test_quant_lengths_around_the_fetch_depth(bits):
-    # a workgroup's round is 4096 elements of an aligned tile, 1024 of one off alignment; then rounds of
+    # a workgroup's round is 4096 elements of whole chunks, 1024 of a ragged end; then rounds of
     # 1024 and 256 with remainders of them.  The second half of the layers starts behind a single element.
     lengths = (512, 1024, 1536, 3584, 4096, 4608, 7680, 8192 + 512, 255 + 1024, 8191)
     shapes = tuple((n,) for n in lengths + (1 + -sum(lengths) % 4,) + lengths)

@@ -94,6 +94,50 @@ def test_forced_mix_of_families_in_compress():
     h.close()
 
 
+# Layers that start at every offset from a 16-byte boundary, of whole tiles, whole chunks and ragged ends: profile,
+# compression and image.  Bytes and feedback are exact; errors are fp32 sums of squares (1e-4, as everywhere).
+@pytest.mark.parametrize("stochastic", [False, True])
+@pytest.mark.parametrize("start", [0, 1, 2, 3])
+def test_layers_at_every_alignment(start, stochastic):
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    base = W.workload("c4_gpt2_medium_mixed")
+    sizes = [4 + start, 8192, 8192 + 512, 33001, 511, 70003, 8191, 1, 513, 128, 1027]
+    w = W.Workload("alignment", tuple((n,) for n in sizes), base.candidates, base.default, 300, base.values, base.ef,
+                   (-3.0, -2.0), stochastic=stochastic)
+    batch = W.generate(w)
+    cands = list(w.candidates)
+    layers, ctab = tables(batch, cands)
+    g, e, _ = to_device(batch)
+    L, total = len(sizes), int(batch.grads.size)
+    x = batch.grads + batch.ef
+    h = B.Handle(total, L, len(cands), stochastic=stochastic, seed=11)
+    errors, _ = h.profile(g, e, layers, ctab)
+    ref = pipeline.profile(batch.grads, batch.ef, batch.offsets, batch.numels, batch.rows, batch.cols, cands,
+                           stochastic=stochastic, seed=11)
+    assert rel_err(errors, ref).max() < 1e-4
+    for turn in range(2):
+        choice = np.array([(5 * l + 6 * turn) % len(cands) for l in range(L)], np.int32)
+        offsets = B.payload_layout(layers, ctab, choice)
+        payload = torch.zeros(int(offsets[-1]) + 16, dtype=torch.uint8, device="cuda")
+        ef_dev = e.clone()
+        h.compress(g, ef_dev, layers, ctab, choice, payload, offsets)
+        out = torch.full((total,), 3.0, device="cuda")
+        h.decompress(payload, offsets, layers, ctab, choice, out)
+        acc = torch.from_numpy(x).cuda()
+        h.decompress(payload, offsets, layers, ctab, choice, acc, accumulate=True)
+        pay, new_ef, image, added = payload.cpu().numpy(), ef_dev.cpu().numpy(), out.cpu().numpy(), acc.cpu().numpy()
+        for l in range(L):
+            off, n = int(batch.offsets[l]), int(batch.numels[l])
+            p_ref, e_ref, _ = pipeline.compress_layer(batch.grads, batch.ef, off, n, 0, 0, cands[choice[l]], l,
+                                                      stochastic=stochastic, seed=11)
+            assert np.array_equal(pay[offsets[l]:offsets[l] + p_ref.size], p_ref), (l, cands[choice[l]])
+            assert np.array_equal(new_ef[off:off + n].view(np.uint32), e_ref.view(np.uint32)), l
+            assert np.array_equal(x[off:off + n] - image[off:off + n], new_ef[off:off + n]), l
+            assert np.array_equal(x[off:off + n] + image[off:off + n], added[off:off + n]), l
+    h.close()
+
+
 def test_full_size_gpt2_medium_sampled_layers():
     """The 355 M-element workload, first through the separate calls (one handle, one profile call
     over all 292 layers and 13 candidates, solve with 4000 bins, one compress call), then in the
