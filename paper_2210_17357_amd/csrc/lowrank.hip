@@ -29,7 +29,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int kLrCols = 64;       // columns computed per layer (r_max <= 64)
 constexpr int kLrBM = 128;        // rows (GEMM1, reconstruction) / columns (GEMM2) per workgroup
 constexpr int kLrBK = 32;         // contraction chunk staged in LDS
-constexpr int kLrGramSpan = 256;  // rows per Gram partial (one workgroup)
+constexpr int kLrGramSpan = 128;  // rows per Gram partial (one workgroup)
 constexpr int kLrQChunk = 64;     // Q rows per workgroup in the split-K reduction
 constexpr int kLrPSplit = 512;    // columns contracted per workgroup in P = X Q0
 constexpr int kLrEfSpan = 512;    // columns reconstructed per workgroup
@@ -277,8 +277,9 @@ __global__ __launch_bounds__(256, 4) void lr_gemm1_kernel(LrParams p) {
 // that none has more than three and each finishes its own: nothing is added up across wavefronts.
 // The span goes through LDS once; where P was computed in column splits their sum is formed on the way
 // in (split order) and written to P.  LDS word 16 (b ^ (row & 3)) + c of a row holds column 16 b + c: the four rows
-// of a step lie on different banks.  On 106 k rows of 66 layers: 45 us with a kernel of its own for the sum
-// and all 16 blocks, each wavefront a quarter of the rows.
+// of a step lie on different banks.  On 106 k rows of 66 layers: 21 us, of which the products are 12 (30 with spans of
+// 256 rows, whose registers and LDS leave two workgroups on a compute unit; 24 with 64 rows, and the sum of the
+// partials behind it 10 instead of 6).
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 template <int... AB>
 struct GramBlocks {                          // row block, column block; ...
@@ -289,7 +290,7 @@ struct GramBlocks {                          // row block, column block; ...
     __device__ static constexpr bool uses(int v) { return ((AB == v) || ...); }
 };
 
-__global__ __launch_bounds__(256) void lr_gram_kernel(LrParams p) {
+__global__ __launch_bounds__(256, 4) void lr_gram_kernel(LrParams p) {
     __shared__ float Ps[kLrGramSpan][kLrCols];
     const LrTile tile = p.gram_tiles[blockIdx.x];
     const LrLayer L = p.layers[tile.layer];
@@ -420,15 +421,20 @@ __global__ __launch_bounds__(kLrOrthThreads) void lr_orth_kernel(LrParams p) {
     {
         const int n = L.gram_end - L.gram_begin;
         const double* __restrict__ src = p.gram_part + (size_t)L.gram_begin * kLrCols * kLrCols + w * kLrCols + j;
+        double v[kLrFewPartials][kRows];                 // (all of them in flight together)
+#pragma unroll
+        for (int c = 0; c < kLrFewPartials; ++c)
+#pragma unroll
+            for (int m = 0; m < kRows; ++m) {
+                v[c][m] = 0.0;
+                if ((c == 0 || (c < n && n <= kLrFewPartials)) && ((kWaves * m + w) >> 4) <= (j >> 4))
+                    v[c][m] = src[((size_t)c * kLrCols + kWaves * m) * kLrCols];
+            }
 #pragma unroll
         for (int m = 0; m < kRows; ++m) {
-            const int k = kWaves * m + w;
-            x[m] = 0.0;
-            if ((k >> 4) <= (j >> 4)) {
-                x[m] = src[kWaves * m * kLrCols];
-                if (n <= kLrFewPartials)
-                    for (int c = 1; c < n; ++c) x[m] += src[((size_t)c * kLrCols + kWaves * m) * kLrCols];
-            }
+            x[m] = v[0][m];
+#pragma unroll
+            for (int c = 1; c < kLrFewPartials; ++c) x[m] += v[c][m];
         }
     }
 #pragma unroll
@@ -475,13 +481,14 @@ __global__ __launch_bounds__(kLrOrthThreads) void lr_orth_kernel(LrParams p) {
 }
 
 // ------------------------------------------------------------------ Phat = P T
-// fp64 MFMA: a wavefront takes 64 rows of P, 16 per row operand, all of their loads issued before anything
-// else (and before any store, so the update is in place), against T in LDS.  The contraction index of
-// step (q, u) is 16 q + 4 (lane / 16) + u, so that a lane's four values of a q are one 128-bit load of its row.
+// fp64 MFMA on the transposes, Phat^T = T^T P^T: a wavefront takes 32 rows of P, 16 per operand, all of their loads
+// issued before anything else (and before any store, so the update is in place), against T in LDS.  The contraction
+// index of step (q, u) is 16 q + 4 (lane / 16) + u, so that a lane's four values of a q are one 128-bit load of its row,
+// and operand place i of block b is column 16 b + 4 (i % 4) + i / 4, so that its four results are one 128-bit store.
 // T is upper triangular: column block b needs only q <= b.  What bounds it is the matrix pipe (40 steps of 64
-// cycles per 16 rows); every value of T fetched from LDS serves four of them.  (One 16-row group at a time
-// with 16 scattered 4-byte loads each took 35 us on 106 k rows.)
-__global__ __launch_bounds__(256) void lr_apply_kernel(LrParams p) {
+// cycles per 16 rows, 10 us of it on 106 k rows); every value of T fetched from LDS serves two of them.  106 k rows of
+// 66 layers: 21 us (23 with 64 rows a wavefront, two wavefronts on a SIMD, and a 4-byte store per result).
+__global__ __launch_bounds__(256, 4) void lr_apply_kernel(LrParams p) {
     __shared__ double Tl[kLrCols][kLrCols + 4];     // padded: rows four apart half the banks apart
     const LrTile tile = p.gram_tiles[blockIdx.x];          // one workgroup per span of kLrGramSpan rows
     const LrLayer L = p.layers[tile.layer];
@@ -489,14 +496,14 @@ __global__ __launch_bounds__(256) void lr_apply_kernel(LrParams p) {
     const double* __restrict__ T = p.T + (size_t)tile.layer * kLrCols * kLrCols;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int lr = lane >> 4, lc = lane & 15;
-    static_assert(kLrGramSpan == 4 * 64, "a wavefront takes 64 rows");
-    const int row0 = tile.a0 + 64 * wave;
+    constexpr int kGroups = kLrGramSpan / 64;                // 16-row groups of a wavefront
+    const int row0 = tile.a0 + 16 * kGroups * wave;
     double2 t[kLrCols * kLrCols / 2 / 256];
 #pragma unroll
     for (int q = 0; q < kLrCols * kLrCols / 2 / 256; ++q) t[q] = reinterpret_cast<const double2*>(T)[tid + 256 * q];
-    float4 a[4][4];                                        // [16-row group][q]
+    float4 a[kGroups][4];                                        // [16-row group][q]
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < kGroups; ++g) {
         const int row = row0 + 16 * g + lc;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -513,31 +520,38 @@ __global__ __launch_bounds__(256) void lr_apply_kernel(LrParams p) {
     if (row0 >= L.rows) return;                            // (behind the only barrier)
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        f64x4 acc[4];
+        f64x4 acc[kGroups];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) acc[g] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int g = 0; g < kGroups; ++g) acc[g] = f64x4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int q = 0; q <= b; ++q)
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const double tv = Tl[16 * q + 4 * lr + u][16 * b + lc];
+                const double tv = Tl[16 * q + 4 * lr + u][16 * b + 4 * (lc & 3) + (lc >> 2)];
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
+                for (int g = 0; g < kGroups; ++g) {
                     const float av = u == 0 ? a[g][q].x : u == 1 ? a[g][q].y : u == 2 ? a[g][q].z : a[g][q].w;
-                    acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)av, tv, acc[g], 0, 0, 0);
+                    acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(tv, (double)av, acc[g], 0, 0, 0);
                 }
             }
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = row0 + 16 * g + 4 * v + lr, col = 16 * b + lc;
-                if (row < L.rows) {
-                    const float val = (float)acc[g][v];
-                    P[(int64_t)row * kLrCols + col] = val;
-                    if (pay && col < L.rank) pay[(int64_t)row * L.rank + col] = val;
+        for (int g = 0; g < kGroups; ++g) {
+            const int row = row0 + 16 * g + lc, col = 16 * b + 4 * lr;
+            if (row < L.rows) {
+                const float4 v = make_float4((float)acc[g][0], (float)acc[g][1], (float)acc[g][2], (float)acc[g][3]);
+                *reinterpret_cast<float4*>(P + (int64_t)row * kLrCols + col) = v;
+                if (pay) {
+                    float* const dst = pay + (int64_t)row * L.rank + col;
+                    if (col + 4 <= L.rank) {
+                        store4_any(dst, v);
+                    } else {
+                        if (col < L.rank) dst[0] = v.x;
+                        if (col + 1 < L.rank) dst[1] = v.y;
+                        if (col + 2 < L.rank) dst[2] = v.z;
+                    }
                 }
             }
+        }
     }
 }
 
