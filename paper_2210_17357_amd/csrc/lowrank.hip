@@ -92,6 +92,7 @@ struct LrParams {
     int32_t accumulate;      // decode: add the image to the output instead of replacing it
     int32_t q_from_scratch;  // P = X Q reads the previous step's Q instead of the warm start
     int32_t e_is_zero;       // compression: e is null because the caller promised zeros; x = fl32(g + 0) all the same
+    int32_t n_ef_tiles, n_row_tiles;     // KNOWN: workgroups behind the first n_ef_tiles fill payload and warm start
     const DevLayer* dev_layers;   // KNOWN kernels: the caller's layer records (family, rank, payload offset) on the device
 };
 
@@ -776,6 +777,39 @@ __global__ __launch_bounds__(256) void lr_errors_kernel(LrParams p) {
         if (j == p.rank[c] - 1) p.errors[(size_t)L.index * p.stride + p.col[c]] = fmax(xn - pre, 0.0);
 }
 
+// Payload and warm-start update of a layer from the profile's scratch (KNOWN, see lr_ef_kernel): the first `rank`
+// columns of Phat (row tiles, block < n_row_tiles) and of Q (its chunks after them); Q also replaces the first `rank`
+// columns of the layer's warm start.  Nothing waits for them: workgroups of the reconstruction's launch make them (in
+// front of it, as a launch of their own, they took 14 us of a step of 67 M elements).
+__device__ __forceinline__ void emit_known(const LrParams& p, int block) {
+    const bool is_p = block < p.n_row_tiles;
+    const LrTile tile = is_p ? p.row_tiles[block] : p.q_chunks[block - p.n_row_tiles];
+    const LrLayer L = p.layers[tile.layer];
+    const DevLayer& dl = p.dev_layers[L.index];
+    if (dl.family != LGRECO_LOWRANK || dl.iparam < 1 || dl.iparam > kLrCols) return;
+    const int r = dl.iparam;
+    float* const pay = reinterpret_cast<float*>(p.payload + dl.payload);
+    const int tid = threadIdx.x;
+    if (is_p) {
+        const float* __restrict__ P = p.P + L.p_off;
+        const int nr = min(kLrBM, L.rows - tile.a0);
+        for (int f = tid; f < nr * r; f += 256) {
+            const int rr = f / r, c = f - rr * r;
+            pay[(int64_t)(tile.a0 + rr) * r + c] = P[(int64_t)(tile.a0 + rr) * kLrCols + c];
+        }
+    } else {
+        const float* __restrict__ Q = p.Q + L.qs_off;
+        float* const payq = pay + (int64_t)L.rows * r;
+        const int nr = min(tile.split, L.cols - tile.a0);      // tile.split = rows of this chunk
+        for (int f = tid; f < nr * r; f += 256) {
+            const int rr = f / r, c = f - rr * r;
+            const float v = Q[(int64_t)(tile.a0 + rr) * kLrCols + c];
+            payq[(int64_t)(tile.a0 + rr) * r + c] = v;
+            p.q_out[L.q_off + (int64_t)(tile.a0 + rr) * p.r_max + c] = v;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ e' = X - Phat Q^T
 // DECODE (receiver side): the factors come from the payload (row stride = rank) and the product
 // is written, or added, to the output buffer instead of being subtracted from x.
@@ -796,6 +830,10 @@ constexpr int kLrEfPitch = kLrCols + 4;
 template <bool DECODE, bool KNOWN = false>
 __global__ __launch_bounds__(256, KNOWN ? 4 : 3) void lr_ef_kernel(LrParams p) {
     __shared__ __align__(16) float Qs[2][kLrCols][kLrEfPitch];
+    if (KNOWN && (int)blockIdx.x >= p.n_ef_tiles) {
+        emit_known(p, (int)blockIdx.x - p.n_ef_tiles);
+        return;
+    }
     const LrTile tile = p.ef_tiles[blockIdx.x];
     const LrLayer L = p.layers[tile.layer];
     int r = L.rank;
@@ -951,38 +989,6 @@ __global__ __launch_bounds__(256, KNOWN ? 4 : 3) void lr_ef_kernel(LrParams p) {
     };
     if (L.offset % 32 == 0 && n % 32 == 0) span(std::true_type());
     else span(std::false_type());
-}
-
-// Payload and warm-start update of a layer from the profile's scratch (KNOWN, see lr_ef_kernel):
-// the first `rank` columns of Phat (row tiles, blockIdx < n_row_tiles) and of Q (chunks of
-// kLrQChunk rows after them); Q also replaces the first `rank` columns of the layer's warm start.
-__global__ __launch_bounds__(256) void lr_emit_known_kernel(LrParams p, int n_row_tiles) {
-    const bool is_p = (int)blockIdx.x < n_row_tiles;
-    const LrTile tile = is_p ? p.row_tiles[blockIdx.x] : p.q_chunks[blockIdx.x - n_row_tiles];
-    const LrLayer L = p.layers[tile.layer];
-    const DevLayer& dl = p.dev_layers[L.index];
-    if (dl.family != LGRECO_LOWRANK || dl.iparam < 1 || dl.iparam > kLrCols) return;
-    const int r = dl.iparam;
-    float* const pay = reinterpret_cast<float*>(p.payload + dl.payload);
-    const int tid = threadIdx.x;
-    if (is_p) {
-        const float* __restrict__ P = p.P + L.p_off;
-        const int nr = min(kLrBM, L.rows - tile.a0);
-        for (int f = tid; f < nr * r; f += 256) {
-            const int rr = f / r, c = f - rr * r;
-            pay[(int64_t)(tile.a0 + rr) * r + c] = P[(int64_t)(tile.a0 + rr) * kLrCols + c];
-        }
-    } else {
-        const float* __restrict__ Q = p.Q + L.qs_off;
-        float* const payq = pay + (int64_t)L.rows * r;
-        const int nr = min(tile.split, L.cols - tile.a0);      // tile.split = rows of this chunk
-        for (int f = tid; f < nr * r; f += 256) {
-            const int rr = f / r, c = f - rr * r;
-            const float v = Q[(int64_t)(tile.a0 + rr) * kLrCols + c];
-            payq[(int64_t)(tile.a0 + rr) * r + c] = v;
-            p.q_out[L.q_off + (int64_t)(tile.a0 + rr) * p.r_max + c] = v;
-        }
-    }
 }
 
 // ------------------------------------------------------------------------ host side
@@ -1315,14 +1321,11 @@ hipError_t lowrank_compress_known(LowrankScratch* t, const float* g, float* e, c
     p.r_max = r_max;
     p.payload = payload;
     p.dev_layers = d_layers;
-    {
-        Section sec(tm, "lowrank_emit");
-        hipLaunchKernelGGL(lr_emit_known_kernel, dim3((unsigned)(H->row_tiles.size() + H->q_chunks.size())), dim3(256), 0,
-                           s, p, (int)H->row_tiles.size());
-        LR_CHECK(hipGetLastError());
-    }
+    p.n_ef_tiles = (int)H->ef_tiles.size();
+    p.n_row_tiles = (int)H->row_tiles.size();
     Section sec(tm, "lowrank_ef", true);
-    launch_timed(&sec, true, true, lr_ef_kernel<false, true>, dim3((unsigned)H->ef_tiles.size()), dim3(256), 0, s, p);
+    launch_timed(&sec, true, true, lr_ef_kernel<false, true>,
+                 dim3((unsigned)(H->ef_tiles.size() + H->row_tiles.size() + H->q_chunks.size())), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
