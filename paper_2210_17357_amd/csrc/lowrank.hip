@@ -51,7 +51,7 @@ struct LrLayer {
     int32_t rt_begin, rt_end;       // row-tile range (||X||^2 partials)
     int32_t qc_begin, qc_end;       // Q-chunk range (column-norm partials)
     int32_t index;      // index in the caller's layer table
-    int32_t pad;
+    int32_t tall;       // reconstruction: 128 rows x 32 columns at a time instead of 64 x 64 (see lr_ef_kernel)
 };
 struct LrTile {
     int32_t layer, a0, split, pad;
@@ -818,7 +818,12 @@ __device__ __forceinline__ void emit_known(const LrParams& p, int block) {
 // come from the layer records the solver kernel wrote.
 //
 // Bound by HBM: x once in, e' once out.  A workgroup takes 64 rows over a span of columns, 64 columns at a time, each
-// wavefront a 32 x 32 quadrant.  Its rows of Phat are the same for the whole span and stay in registers; Q passes
+// wavefront a 32 x 32 quadrant; where every row piece of 32 elements is a whole line (LrLayer::tall, sender only) 128 rows,
+// 32 columns at a time, the wavefronts below each other: half the reads of Q, as many bytes as x otherwise, for the
+// same lines of x (67 M elements: 131 -> 117 us behind a profile, 127 -> 123 in a compression; off the lines 64 columns
+// at a time cut fewer lines in two, 73 M elements of odd widths 781 us a step against 822, and the receiver has no x to
+// wait for, 147 us against 159).  Wavefronts on a SIMD: four behind a profile; three in a compression (four: 73 M elements 538
+// instead of 529 us, of odd widths 697 instead of 687).  Its rows of Phat are the same for the whole span and stay in registers; Q passes
 // through LDS (two buffers, one barrier per 64 columns); the product never does: an accumulator of the 32x32x2
 // instruction holds two rows of 32 consecutive columns, so x is loaded and e' stored in that layout, two
 // whole lines per instruction, whatever the layer's alignment.  x is fetched two tiles ahead, Q one.
@@ -828,7 +833,7 @@ __device__ __forceinline__ void emit_known(const LrParams& p, int block) {
 // step 570 -> 554, against factors and product staged through LDS with two barriers a tile and 16-byte accesses.
 constexpr int kLrEfPitch = kLrCols + 4;
 template <bool DECODE, bool KNOWN = false>
-__global__ __launch_bounds__(256, KNOWN ? 4 : 3) void lr_ef_kernel(LrParams p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KNOWN ? 4 : 3, KNOWN ? 4 : 3))) void lr_ef_kernel(LrParams p) {
     __shared__ __align__(16) float Qs[2][kLrCols][kLrEfPitch];
     if (KNOWN && (int)blockIdx.x >= p.n_ef_tiles) {
         emit_known(p, (int)blockIdx.x - p.n_ef_tiles);
@@ -851,7 +856,9 @@ __global__ __launch_bounds__(256, KNOWN ? 4 : 3) void lr_ef_kernel(LrParams p) {
     const float* __restrict__ Q = DECODE ? P + (int64_t)m * r : p.Q + L.qs_off;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wr = wave >> 1, wc = wave & 1;
+    // whole lines (every row piece of 32 elements is one): the wavefronts lie below each other, else in a square
+    const bool tall = !DECODE && L.tall;
+    const int wr = tall ? wave : wave >> 1, wc = tall ? 0 : wave & 1;
     const int half = lane >> 5, bj = 32 * wc + (lane & 31);
     const int row0 = tile.a0, cbeg = tile.split, cend = min(n, cbeg + kLrEfSpan);
 
@@ -879,18 +886,19 @@ __global__ __launch_bounds__(256, KNOWN ? 4 : 3) void lr_ef_kernel(LrParams p) {
     const uint32_t at_v = 4u * (uint32_t)half * (uint32_t)n + (uint32_t)bj;
     const auto row_of = [](int v) { return 8 * (v >> 2) + (v & 3); };
     const auto start_of = [&](int v, int c0) { return (int64_t)(row0 + 32 * wr + row_of(v)) * n + c0; };
-    const bool rows_in = row0 + 64 <= m;
+    const bool rows_in = row0 + 32 * wr + 32 <= m;
     // Whole lines pass by the caches; pieces of lines don't, since their other half comes with the next tile (a
     // compression of 9 layers of 211 x 1899: 284 us; 294 with the hint on everything).
     // (Two copies of the loop: of a choice at each access the compiler makes one, without the hint.)
     const auto span = [&](auto whole_lines) __attribute__((always_inline)) {
         constexpr bool lines = decltype(whole_lines)::value;
+        constexpr int kCols = lines && !DECODE ? 32 : kLrCols;     // columns at a time
 
         auto fetch_x = [&](float (&x)[16], int c0) __attribute__((always_inline)) {
             if (DECODE && g == nullptr) {
     #pragma unroll
                 for (int v = 0; v < 16; ++v) x[v] = 0.0f;
-            } else if (rows_in && c0 + kLrCols <= n) {
+            } else if (rows_in && c0 + kCols <= n) {
     #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     const float* const src = g + start_of(v, c0) + at_v;
@@ -913,9 +921,9 @@ __global__ __launch_bounds__(256, KNOWN ? 4 : 3) void lr_ef_kernel(LrParams p) {
                 }
             } else {
     #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < kCols / 16; ++u) {
                     const int f = tid + 256 * u;
-                    const float4 w = c0 + kLrCols <= n || c0 + (f >> 4) < n
+                    const float4 w = c0 + kCols <= n || c0 + (f >> 4) < n
                                          ? *reinterpret_cast<const float4*>(Q + (int64_t)c0 * kLrCols + 1024 * u + 4 * tid)
                                          : make_float4(0.f, 0.f, 0.f, 0.f);
                     q[4 * u] = w.x; q[4 * u + 1] = w.y; q[4 * u + 2] = w.z; q[4 * u + 3] = w.w;
@@ -930,7 +938,7 @@ __global__ __launch_bounds__(256, KNOWN ? 4 : 3) void lr_ef_kernel(LrParams p) {
                 }
             } else {
     #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < kCols / 16; ++u) {
                     const int f = tid + 256 * u, cc = f >> 4, k = (f & 15) * 4;
                     *reinterpret_cast<float2*>(&Qs[buf][cc][k >> 1]) =
                         make_float2(k < r ? q[4 * u] : 0.0f, k + 2 < r ? q[4 * u + 2] : 0.0f);
@@ -943,7 +951,7 @@ __global__ __launch_bounds__(256, KNOWN ? 4 : 3) void lr_ef_kernel(LrParams p) {
         auto step = [&](float (&x)[16], int buf, int c0) __attribute__((always_inline)) {
             store_q(buf);
             __syncthreads();                                 // (the buffer's last readers were done before the barrier in between)
-            if (c0 + kLrCols < cend) fetch_q(c0 + kLrCols);
+            if (c0 + kCols < cend) fetch_q(c0 + kCols);
             f32x16 acc = {0};
             const float* const row = &Qs[buf][bj][(kLrCols / 2) * half];
     #pragma unroll
@@ -964,7 +972,7 @@ __global__ __launch_bounds__(256, KNOWN ? 4 : 3) void lr_ef_kernel(LrParams p) {
                 const float xv = !DECODE && p.e_is_zero ? x[v] + 0.0f : x[v];
                 o[v] = DECODE ? xv + acc[v] : xv - acc[v];
             }
-            if (rows_in && c0 + kLrCols <= n) {
+            if (rows_in && c0 + kCols <= n) {
     #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     float* const dst = e + start_of(v, c0) + at_v;
@@ -976,18 +984,18 @@ __global__ __launch_bounds__(256, KNOWN ? 4 : 3) void lr_ef_kernel(LrParams p) {
                 for (int v = 0; v < 16; ++v)
                     if (row_v + row_of(v) < m && c0 + bj < n) (e + start_of(v, c0))[at_v] = o[v];
             }
-            if (c0 + 2 * kLrCols < cend) fetch_x(x, c0 + 2 * kLrCols);
+            if (c0 + 2 * kCols < cend) fetch_x(x, c0 + 2 * kCols);
         };
         float x0[16], x1[16];
         fetch_q(cbeg);
         fetch_x(x0, cbeg);
-        if (cbeg + kLrCols < cend) fetch_x(x1, cbeg + kLrCols);
-        for (int c0 = cbeg; c0 < cend; c0 += 2 * kLrCols) {
+        if (cbeg + kCols < cend) fetch_x(x1, cbeg + kCols);
+        for (int c0 = cbeg; c0 < cend; c0 += 2 * kCols) {
             step(x0, 0, c0);
-            if (c0 + kLrCols < cend) step(x1, 1, c0 + kLrCols);
+            if (c0 + kCols < cend) step(x1, 1, c0 + kCols);
         }
     };
-    if (L.offset % 32 == 0 && n % 32 == 0) span(std::true_type());
+    if (DECODE ? L.offset % 32 == 0 && n % 32 == 0 : tall) span(std::true_type());
     else span(std::false_type());
 }
 
@@ -1132,7 +1140,8 @@ static hipError_t lr_prepare(LowrankScratch* t, int slot, const DevLayer* hl, in
             for (int sp = 0; sp < a.psplits; ++sp) H->p_tiles.push_back(LrTile{li, r0, sp, 0});
         }
         a.rt_end = (int)H->p_tiles.size();
-        for (int r0 = 0; r0 < a.rows; r0 += 64)
+        a.tall = slot != kLrSlotDecode && a.offset % 32 == 0 && a.cols % 32 == 0 ? 1 : 0;
+        for (int r0 = 0; r0 < a.rows; r0 += a.tall ? 128 : 64)
             for (int c0 = 0; c0 < a.cols; c0 += kLrEfSpan) H->ef_tiles.push_back(LrTile{li, r0, c0, 0});
         for (int c0 = 0; c0 < a.cols; c0 += kLrBM)
             for (int sp = 0; sp < a.splits; ++sp) H->col_tiles.push_back(LrTile{li, c0, sp, 0});
