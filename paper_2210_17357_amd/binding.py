@@ -236,8 +236,8 @@ class Handle:
         """profile + emax + solve in one call: (status, errors, sizes, e_max, choice, total_size,
         total_error); status is OK or EINFEASIBLE."""
         L, P = len(layers), len(cands)
-        errors = np.zeros((L, P), np.float64)
-        szs = np.zeros((L, P), np.int64)
+        errors = np.empty((L, P), np.float64)
+        szs = np.empty((L, P), np.int64)
         choice = np.zeros(L, np.int32)
         e_max, tsize, terr = C.c_double(), C.c_int64(), C.c_double()
         st = lib().lgreco_profile_solve(self._h, _dptr(d_grads), _dptr(d_ef), C.addressof(layers), L,
@@ -252,8 +252,8 @@ class Handle:
         """The whole path as one call: (status, errors, sizes, e_max, choice, total_size,
         total_error, offsets); the compression kernels are queued when it returns."""
         L, P = len(layers), len(cands)
-        errors = np.zeros((L, P), np.float64)
-        szs = np.zeros((L, P), np.int64)
+        errors = np.empty((L, P), np.float64)
+        szs = np.empty((L, P), np.int64)
         choice = np.zeros(L, np.int32)
         offsets = np.zeros(L + 1, np.int64)
         e_max, tsize, terr = C.c_double(), C.c_int64(), C.c_double()

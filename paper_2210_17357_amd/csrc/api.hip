@@ -376,17 +376,27 @@ void begin_call(lgreco_handle* h, hipStream_t s, int kind) {
 // up any error, and a block that still does not add up then is reported, never used.
 //   n_choice: entries of the assignment behind the block
 //   LP: entries of the error table the kernel forwarded to h_errors (0: none), which has a check word
-//   of its own (slot 11)
-int wait_for_solver(lgreco_handle* h, int64_t seq, hipStream_t s, int n_choice, int LP = 0) {
+//   of its own (slot 11), and where they go: the table is copied out first and added up where it is then, so that
+//   what was checked is what the caller gets and memory the device has just written is read once
+int wait_for_solver(lgreco_handle* h, int64_t seq, hipStream_t s, int n_choice, int LP = 0, double* errors = nullptr) {
     volatile const int64_t* const r = h->h_result;
     volatile const int32_t* const ch = h->h_choice;
     auto complete = [&]() -> bool {
         if (r[7] != seq || r[4] != seq || r[15] != seq) return false;
         if (LP > 0) {
-            volatile const uint64_t* const eb = reinterpret_cast<volatile const uint64_t*>(h->h_errors);
-            uint64_t ce = 0;
-            for (int i = 0; i < LP; ++i) ce += eb[i] * (uint64_t)(i + 1);
-            if (ce != (uint64_t)r[11]) return false;
+            std::atomic_thread_fence(std::memory_order_acquire);
+            std::memcpy(errors, h->h_errors, sizeof(double) * (size_t)LP);
+            uint64_t ce[4] = {0, 0, 0, 0}, word[4];
+            int i = 0;
+            for (; i + 4 <= LP; i += 4) {
+                std::memcpy(word, errors + i, sizeof(word));
+                for (int u = 0; u < 4; ++u) ce[u] += word[u] * (uint64_t)(i + u + 1);
+            }
+            for (; i < LP; ++i) {
+                std::memcpy(word, errors + i, sizeof(double));
+                ce[0] += word[0] * (uint64_t)(i + 1);
+            }
+            if ((ce[0] + ce[1]) + (ce[2] + ce[3]) != (uint64_t)r[11]) return false;
         }
         if (r[0] != 0) return true;                          // nothing was traced back
         uint64_t sum = 0;
@@ -656,17 +666,24 @@ int lgreco_get_timing_totals(lgreco_handle_t* h, int32_t call, const char** name
 int lgreco_sizes(const lgreco_layer_t* layers, int32_t L, const lgreco_cand_t* cands, int32_t P,
                  int32_t bucket, int64_t* sizes) {
     if (!layers || !cands || !sizes || L <= 0 || P <= 0 || bucket <= 0) return LGRECO_EINVAL;
+    bool lowrank = false;
+    for (int c = 0; c < P; ++c) {
+        const int st = check_cand(cands[c], nullptr, 0);
+        if (st != LGRECO_OK) return st;
+        lowrank = lowrank || cands[c].family == LGRECO_LOWRANK;
+    }
     for (int l = 0; l < L; ++l) {
-        if (layers[l].numel <= 0) return LGRECO_EINVAL;
+        const lgreco_layer_t& a = layers[l];
+        if (a.numel <= 0 || (lowrank && (a.rows <= 0 || a.cols <= 0))) return LGRECO_EINVAL;
+    }
+    for (int l = 0; l < L; ++l) {
+        const int64_t n = layers[l].numel, sides = (int64_t)layers[l].rows + layers[l].cols;
+        int64_t* const out = sizes + (size_t)l * P;
         for (int c = 0; c < P; ++c) {
-            const int st = check_cand(cands[c], &layers[l], 0);
-            if (st != LGRECO_OK) return st;
-            const int64_t n = layers[l].numel;
-            int64_t s = 0;
-            if (cands[c].family == LGRECO_QUANT) s = quant_size(n, (int)cands[c].param, bucket);
-            else if (cands[c].family == LGRECO_TOPK) s = 8 * topk_k(n, cands[c].param);
-            else s = 4 * ((int64_t)layers[l].rows + layers[l].cols) * (int64_t)cands[c].param;
-            sizes[(size_t)l * P + c] = s;
+            const double par = cands[c].param;
+            out[c] = cands[c].family == LGRECO_QUANT  ? quant_size(n, (int)par, bucket)
+                     : cands[c].family == LGRECO_TOPK ? 8 * topk_k(n, par)
+                                                      : 4 * sides * (int64_t)par;
         }
     }
     return LGRECO_OK;
@@ -756,10 +773,6 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
         for (int l = 0; l < L; ++l)
             if (layers[l].rows <= 0 || layers[l].cols <= 0) return LGRECO_EINVAL;
     }
-    if (sizes) {
-        st = lgreco_sizes(layers, L, cands, P, h->cfg.bucket, sizes);
-        if (st != LGRECO_OK) return st;
-    }
     st = upload_layers(h, s, false);
     if (st != LGRECO_OK) return st;
     phase.idx = h->tm->open_phase("phase_profile");
@@ -772,7 +785,7 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
                      [](const std::pair<double, int>& a, const std::pair<double, int>& b) { return a.first > b.first; });
     const int ntk_all = (int)tk_all.size();
     // up to kMaxTopk of them have a column each in the kernels' k table; more than that go through
-    // the tables of TopkRange, and the k table holds the largest alone
+    // topk_densities, and the k table holds the largest alone
     const bool many = ntk_all > (int)kMaxTopk;
     const int ntk = many ? 1 : ntk_all;
     h->last_ntk = ntk_all;
@@ -782,17 +795,20 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
         h->last_tk_col[j] = tk_col[j] = tk_all[j].second;
         for (int l = 0; l < L; ++l) ks[(size_t)l * kMaxTopk + j] = (uint32_t)topk_k(layers[l].numel, tk_all[j].first);
     }
-    TopkRange range;
-    if (many) {
-        range.ks.resize((size_t)L * ntk_all);
-        for (int j = 0; j < ntk_all; ++j) range.cols.push_back(tk_all[j].second);
-        for (int l = 0; l < L; ++l)
-            for (int j = 0; j < ntk_all; ++j)
-                range.ks[(size_t)l * ntk_all + j] = (uint32_t)topk_k(layers[l].numel, tk_all[j].first);
-    }
+    // The size table is worked out while the GPU runs what is queued so far: nothing on the device reads it before the
+    // refinement (100 densities of 161 layers: 25 us, in front of the first launch before, as were the k of the same
+    // densities; a run of 26 M elements 244 -> 194 us with it, with the error table read once, and with all densities in one pass).  (Its checks are among those above.)
+    std::vector<int64_t> own_sizes;
+    auto fill_sizes = [&]() -> int {
+        if (!sizes) {
+            if (!many) return LGRECO_OK;
+            own_sizes.resize((size_t)L * P);
+        }
+        return lgreco_sizes(layers, L, cands, P, h->cfg.bucket, sizes ? sizes : own_sizes.data());
+    };
     if (ntk)
         HIPCHK(topk_begin(&h->topk, d_grads, d_ef, h->d_layers, h->hl.data(), h->d_tiles, L, n_tiles,
-                          h->tile_elems, ks.data(), ntk, 0, h->tm, s, many ? &range : nullptr));
+                          h->tile_elems, ks.data(), ntk, 0, h->tm, s, many ? ntk_all : 0));
     if (qp.nq) {
         qp.g = d_grads;
         qp.e = d_ef;
@@ -823,6 +839,13 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
         Section sec(h->tm, "topk_collect", true);
         HIPCHK(topk_collect(&h->topk, d_grads, d_ef, nullptr, h->d_layers, h->d_tiles, n_tiles, s, &sec, x_out));
     }
+    if (many) {
+        st = fill_sizes();
+        if (st != LGRECO_OK) return st;
+        std::vector<int32_t> cols;
+        for (const auto& d : tk_all) cols.push_back(d.second);
+        HIPCHK(topk_densities(&h->topk, cols.data(), ntk_all, sizes ? sizes : own_sizes.data(), P, L, s));
+    }
     // behind the main pass x is read from where it was left
     const float* const g_after = x_out ? x_out : d_grads;
     const float* const e_after = x_out ? nullptr : d_ef;
@@ -839,7 +862,7 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
         HIPCHK(lowrank_profile(&h->lowrank, d_grads, d_ef, h->d_layers, h->hl.data(), L, d_q0, h->cfg.r_max,
                                lr_rank, lr_col, nlr, d_err, P, lowrank_x(h), h->tm, s));
     }
-    return LGRECO_OK;
+    return many ? LGRECO_OK : fill_sizes();
 }
 
 int lgreco_profile(lgreco_handle_t* h, const float* d_grads, const float* d_ef, const lgreco_layer_t* layers,
@@ -1201,10 +1224,9 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
     harvest_others(h);
     {
         // error table and solver output are in pinned memory
-        const int wst = wait_for_solver(h, h->dp_seq, s, L, L * P);
+        const int wst = wait_for_solver(h, h->dp_seq, s, L, L * P, errors);
         if (wst != LGRECO_OK) return wst;
     }
-    std::memcpy(errors, h->h_errors, sizeof(double) * (size_t)L * P);
     const int64_t status = h->h_result[0];
     h->last_solve_groups = 0;
     if (ec) ec->applied = h->h_result[8] == 1;

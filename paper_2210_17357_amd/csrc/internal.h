@@ -245,14 +245,14 @@ struct TopkScratch {
     uint32_t* d_ref = nullptr;        // per-workgroup refinement histograms (counts, integer energies)
     size_t ref_words = 0;
     // control block, one upload per call and none when it repeats the last one:
-    // [k | cand_base | work_range | work]; the pointers above and below are views into it
+    // [k | cand_base | work_range | work], then [many], uploaded on its own; the pointers above and below are views into it
     // (two device copies: profile calls and compress calls alternate and each repeats itself)
     uint8_t* d_ctl[2] = {nullptr, nullptr};
     uint8_t* h_ctl = nullptr;         // pinned
     hipEvent_t ctl_copied = nullptr;  // recorded behind every upload from h_ctl
     bool ctl_pending = false;         // an upload was queued since h_ctl was last known to be free
     uint8_t* h_ctl_last[2] = {nullptr, nullptr};    // what each d_ctl holds
-    size_t ctl_bytes = 0, ctl_last_bytes[2] = {0, 0};
+    size_t ctl_bytes = 0, ctl_last_bytes[2] = {0, 0}, many_last_bytes = 0;
     size_t ctl_off[5] = {};           // byte offsets of k, cand_base, work_range, work, many
     // more than kMaxTopk densities in one profile
     uint32_t* h_many = nullptr;       // (in the control block) column of every density, then k per (layer, density)
@@ -272,15 +272,14 @@ struct TopkScratch {
 };
 hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers, int max_tiles, int max_cands);
 void topk_scratch_destroy(TopkScratch* t);
-// More than kMaxTopk densities: their columns and k per (layer, density), the largest density first.
-struct TopkRange {
-    std::vector<int32_t> cols;
-    std::vector<uint32_t> ks;         // [L x cols.size()]
-};
-// upload k per (layer, candidate), sample the data and predict every layer's collection bound
+// Upload k per (layer, candidate), sample the data and predict every layer's collection bound.
+// nk_many: more than kMaxTopk densities, so many (ks holds the largest alone); topk_densities brings them.
 hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevLayer* d_layers,
                       const DevLayer* h_layers, const Tile* d_tiles, int L, int n_tiles, int tile_elems,
-                      const uint32_t* ks, int ntk, int slot, Timing* tm, hipStream_t s, const TopkRange* range);
+                      const uint32_t* ks, int ntk, int slot, Timing* tm, hipStream_t s, int nk_many);
+// More than kMaxTopk densities: upload their columns, the largest density first, and k per (layer, density) from the
+// size table (8 k bytes).  What comes before topk_select does not need them: the host works them out while it runs.
+hipError_t topk_densities(TopkScratch* t, const int32_t* cols, int nk, const int64_t* sizes, int P, int L, hipStream_t s);
 // main pass (exact coarse histogram + candidate collection) when no quantization candidate shares
 // the read; otherwise the quantization profile kernel does the same work
 hipError_t topk_collect(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers,

@@ -1165,13 +1165,9 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
 // densities, each with its own upload, scan, refinement and pick, the 100 densities of a 26 M-element
 // model took 13 times 80 us, nearly all of it the latency of short kernels.
 
-// Layers whose predicted bound was too high are collected again (flagged by the scan; usually none).
-__global__ __launch_bounds__(kRefThreads) void topk_recollect_many_kernel(RefineParams p) {
-    const RefWork w = p.work[blockIdx.x];
-    if (p.many[w.layer].recollect) collect_again<false>(p.rc, w.t0, w.t1);
-}
-
-// As topk_refine_a_kernel with energies, for the chunks blockIdx.y, blockIdx.y + gridDim.y, ... of the pass's lists.
+// As topk_refine_a_kernel with energies, for the chunks blockIdx.y, blockIdx.y + gridDim.y, ... of the pass's lists.  A
+// layer whose predicted bound was too high (flagged by the scan; usually none) is collected again first, by the
+// workgroups with blockIdx.y = 0, which then take all of the chunks.
 __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_many_kernel(RefineParams p) {
     extern __shared__ unsigned char refine_smem[];
     __shared__ double s_red[kRefThreads / 64][kManyChunk];
@@ -1179,9 +1175,15 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_many_kernel(Refine
     const TopkMany& T = p.many[w.layer];
     const int64_t cand_base = p.cand_base[w.layer];
     const int end = min((int)T.nlists, p.list0 + p.room), tid = threadIdx.x;
+    int split = (int)blockIdx.y, splits = (int)gridDim.y;
+    if (T.recollect) {                  // workgroup-uniform
+        if (split) return;
+        splits = 1;
+        if (p.list0 == 0) collect_again<false>(p.rc, w.t0, w.t1);
+    }
     unsigned long long* const s_cell = reinterpret_cast<unsigned long long*>(refine_smem);
     uint8_t* const s_tab = refine_smem + (size_t)kManyChunk * kBinsA * 8;
-    for (int c0 = p.list0 + (int)blockIdx.y * kManyChunk; c0 < end; c0 += (int)gridDim.y * kManyChunk) {
+    for (int c0 = p.list0 + split * kManyChunk; c0 < end; c0 += splits * kManyChunk) {
         const int n = min(kManyChunk, end - c0);
         for (int i = tid; i < n * kBinsA; i += kRefThreads) s_cell[i] = 0;
         uint32_t lb[kManyChunk];                        // ascending; past the end nothing lies above
@@ -1657,6 +1659,11 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__
         if (_e != hipSuccess) return _e;   \
     } while (0)
 
+// Partial histograms (and the energies beside them) of a call with more than kMaxTopk densities that the
+// refinement's buffer holds, in (work item, list) pairs; at least 13 per work item.
+constexpr size_t kManyBytes = sizeof(unsigned long long) * kBinsA + sizeof(double);
+static size_t many_capacity(const TopkScratch* t) { return t->ref_words * sizeof(uint32_t) / kManyBytes; }
+
 hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers, int max_tiles, int max_cands) {
     t->max_elems = max_elems;
     t->max_layers = max_layers;
@@ -1683,16 +1690,23 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
     t->max_work = (int)(max_elems / ((int64_t)kRefTiles * kTile)) + 2 * max_layers + 2 + 2 * kRefSlots;   // see topk_begin
     TK_CHECK(hipMalloc(&t->d_below_part, sizeof(double) * (size_t)t->max_work * kMaxTopk));
     t->ref_words = (size_t)t->max_work * kMaxTopk * (3 * kBinsA + kBinsB);      // u64 + u32 level A, u32 level B
+    if (max_cands > (int)kMaxTopk) {
+        // more densities than that: room for a list of each in every work item (see topk_begin for their number), up to half
+        // a gigabyte; what does not fit takes further passes
+        const size_t items = (size_t)std::max<int64_t>(2 * kRefSlots / kManySplit, max_elems / ((int64_t)kRefTiles * kTile)) + 2 * (size_t)max_layers + 2;
+        const size_t room = std::min<size_t>(items * (size_t)max_cands * kManyBytes, (size_t)512 << 20);
+        t->ref_words = std::max(t->ref_words, (room + sizeof(uint32_t) - 1) / sizeof(uint32_t));
+    }
     TK_CHECK(hipMalloc(&t->d_ref, sizeof(uint32_t) * t->ref_words));
     if (max_cands > (int)kMaxTopk) TK_CHECK(hipMalloc(&t->d_many, sizeof(TopkMany) * (size_t)max_layers));
     // control block layout (every part a multiple of 16 bytes)
     const size_t o_k = 0;
-    const size_t o_many = o_k + sizeof(uint32_t) * (size_t)max_layers * kMaxTopk;
-    const size_t many_words = max_cands > kMaxTopk ? (size_t)max_layers * max_cands + max_cands : 0;    // columns, k
-    const size_t o_base = o_many + (sizeof(uint32_t) * many_words + 15) / 16 * 16;
+    const size_t o_base = o_k + sizeof(uint32_t) * (size_t)max_layers * kMaxTopk;
     const size_t o_range = o_base + (sizeof(int64_t) * (size_t)max_layers + 15) / 16 * 16;
     const size_t o_work = o_range + (sizeof(int2) * (size_t)max_layers + 15) / 16 * 16;
-    t->ctl_bytes = o_work + sizeof(RefWork) * (size_t)t->max_work;
+    const size_t o_many = o_work + sizeof(RefWork) * (size_t)t->max_work;
+    const size_t many_words = max_cands > kMaxTopk ? (size_t)max_layers * max_cands + max_cands : 0;    // columns, k
+    t->ctl_bytes = o_many + sizeof(uint32_t) * many_words;
     t->ctl_off[0] = o_k; t->ctl_off[1] = o_base; t->ctl_off[2] = o_range; t->ctl_off[3] = o_work;
     t->ctl_off[4] = o_many;
     TK_CHECK(hipHostMalloc(&t->h_ctl, t->ctl_bytes, hipHostMallocDefault));
@@ -1704,6 +1718,7 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
         if (!t->h_ctl_last[i]) return hipErrorOutOfMemory;
         t->ctl_last_bytes[i] = 0;
     }
+    t->many_last_bytes = 0;
     t->h_k = reinterpret_cast<uint32_t*>(t->h_ctl + o_k);
     t->h_many = reinterpret_cast<uint32_t*>(t->h_ctl + o_many);
     t->h_cand_base = reinterpret_cast<int64_t*>(t->h_ctl + o_base);
@@ -1770,16 +1785,35 @@ static hipError_t upload_ctl(TopkScratch* t, int slot, hipStream_t s) {
     return hipSuccess;
 }
 
-// Partial histograms (and the energies beside them) of a call with more than kMaxTopk densities that the
-// refinement's buffer holds, in (work item, list) pairs; at least 13 per work item.
-constexpr size_t kManyBytes = sizeof(unsigned long long) * kBinsA + sizeof(double);
-static size_t many_capacity(const TopkScratch* t) { return t->ref_words * sizeof(uint32_t) / kManyBytes; }
+hipError_t topk_densities(TopkScratch* t, const int32_t* cols, int nk, const int64_t* sizes, int P, int L, hipStream_t s) {
+    // (the last upload from this part of the pinned block is over: topk_begin waited for it)
+    uint32_t* const ks = t->h_many + nk;
+    for (int j = 0; j < nk; ++j) t->h_many[j] = (uint32_t)cols[j];
+    bool ordered = true;
+    for (int l = 0; l < L; ++l) {
+        const int64_t* const z = sizes + (size_t)l * P;
+        uint32_t* const k = ks + (size_t)l * nk;
+        for (int j = 0; j < nk; ++j) k[j] = (uint32_t)(z[cols[j]] >> 3);
+        for (int j = 1; j < nk; ++j) ordered &= k[j] != 0 && k[j] <= k[j - 1];
+    }
+    if (!ordered) return hipErrorInvalidValue;
+    const size_t used = sizeof(uint32_t) * ((size_t)nk + (size_t)L * nk), off = t->ctl_off[4];
+    if (used != t->many_last_bytes || std::memcmp(t->h_many, t->h_ctl_last[0] + off, used) != 0) {
+        t->many_last_bytes = 0;
+        TK_CHECK(hipMemcpyAsync(t->d_ctl[0] + off, t->h_many, used, hipMemcpyHostToDevice, s));
+        TK_CHECK(hipEventRecord(t->ctl_copied, s));
+        t->ctl_pending = true;
+        std::memcpy(t->h_ctl_last[0] + off, t->h_many, used);
+        t->many_last_bytes = used;
+    }
+    return hipSuccess;
+}
 
 // Upload the requested k per (layer, candidate) (0 = layer inactive) and predict the collection bound
 // of every layer from a sample.
 hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevLayer* d_layers,
                       const DevLayer* h_layers, const Tile* d_tiles, int L, int n_tiles, int tile_elems,
-                      const uint32_t* ks, int ntk, int slot, Timing* tm, hipStream_t s, const TopkRange* range) {
+                      const uint32_t* ks, int ntk, int slot, Timing* tm, hipStream_t s, int nk_many) {
     (void)n_tiles;
     (void)d_tiles;
     // Tiles per work item of the refinement kernels: 2^19 elements, fewer when that would
@@ -1792,20 +1826,10 @@ hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevL
         for (int l = 0; l < L; ++l)
             if (ks[(size_t)l * kMaxTopk]) active += h_layers[l].tile_end - h_layers[l].tile_begin;
         // (more than kMaxTopk densities: kManySplit workgroups share an item's lists)
-        group = (int)std::max<int64_t>(1, std::min<int64_t>(group, active * (range ? kManySplit : 1) / kRefSlots));
+        group = (int)std::max<int64_t>(1, std::min<int64_t>(group, active * (nk_many ? kManySplit : 1) / kRefSlots));
     }
     TK_CHECK(ctl_writable(t));
-    t->nk_many = 0;
-    if (range) {
-        const size_t nk = range->cols.size();
-        for (size_t j = 0; j < nk; ++j) t->h_many[j] = (uint32_t)range->cols[j];
-        std::memcpy(t->h_many + nk, range->ks.data(), sizeof(uint32_t) * range->ks.size());
-        for (int l = 0; l < L; ++l)
-            for (size_t j = 1; j < nk; ++j)
-                if (range->ks[l * nk + j] == 0 || range->ks[l * nk + j] > range->ks[l * nk + j - 1])
-                    return hipErrorInvalidValue;
-        t->nk_many = (int)nk;
-    }
+    t->nk_many = nk_many;
     int64_t base = 0;
     RefWork* const work = (RefWork*)t->h_work;
     int2* const wrange = (int2*)t->h_work_range;
@@ -1962,8 +1986,6 @@ hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d
                                          (int)lds));
             configured_many = true;
         }
-        hipLaunchKernelGGL(topk_recollect_many_kernel, dim3(t->n_work), dim3(kRefThreads), 0, s, p);
-        TK_CHECK(hipGetLastError());
         for (p.list0 = 0; p.list0 < t->nk_many; p.list0 += p.room) {
             // (a pass after the first finds nothing to do unless the layers have that many lists: small grids.  100
             // densities of a 26 M-element model, about 25 lists in a buffer of 73: 3 of a run's 245 us)
@@ -2029,7 +2051,7 @@ hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLaye
     for (int l = 0; l < L; ++l)
         if (h_layers[l].family == LGRECO_TOPK) ks[(size_t)l * kMaxTopk] = (uint32_t)h_layers[l].iparam;
     const float* const e_in = x_in_e ? nullptr : e;
-    TK_CHECK(topk_begin(t, g, e_in, d_layers, h_layers, d_tiles, L, n_tiles, tile_elems, ks.data(), 1, 1, tm, s, nullptr));
+    TK_CHECK(topk_begin(t, g, e_in, d_layers, h_layers, d_tiles, L, n_tiles, tile_elems, ks.data(), 1, 1, tm, s, 0));
     {
         Section sec(tm, "topk_collect", true);
         TK_CHECK(topk_collect(t, g, e_in, e, d_layers, d_tiles, n_tiles, s, &sec));
