@@ -23,7 +23,12 @@
 // work divided by 5 (few layers) to 5000 (49 or 100 candidates per layer).
 //
 // One workgroup, because every step needs the step before it: what bounds this kernel is the
-// chain of LDS round trips and barriers, not their number of operations.
+// chain of LDS round trips and barriers, not their number of operations.  So the order of the candidates comes with the
+// table into LDS (read from device or host memory list by list it was a round trip for every group of lists: 11 of 53 us on
+// 163 layers of 49 candidates, now 2.6), sums over the block that do not depend on each other share a barrier, and
+// sums and minima over a wavefront move in registers.  Whole kernel, before and after: 163 x 49 candidates in 10000 bins 53 ->
+// 43 us, 292 x 13 in 4000 54 -> 51, 161 x 6 in 1000 25 -> 22, 62 x 7 in 1000 22.3 -> 20.6, 16 x 7 in 50 12.6 -> 11.3.
+// (A reciprocal and a test in place of the bins' divisions: nothing gained, 1 us lost on the 292 layers.)
 #include "internal.h"
 
 namespace lgreco {
@@ -51,6 +56,11 @@ __device__ __forceinline__ double dpp_or0(double v) {
     const uint32_t lo = dpp_or0<CTRL, ROWS>((uint32_t)b), hi = dpp_or0<CTRL, ROWS>((uint32_t)(b >> 32));
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long dpp_or0(unsigned long long b) {
+    const uint32_t lo = dpp_or0<CTRL, ROWS>((uint32_t)b), hi = dpp_or0<CTRL, ROWS>((uint32_t)(b >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
 // inclusive sum over the lanes up to this one: row_shr 1, 2, 4, 8, then the rows' totals carried on
 template <typename T>
 __device__ __forceinline__ T wave_scan(T v) {
@@ -71,6 +81,10 @@ __device__ __forceinline__ double lane_f64(double v, int lane) {
 }
 __device__ __forceinline__ uint32_t wave_total(uint32_t v) { return lane_u32(wave_scan(v), 63); }
 __device__ __forceinline__ double wave_total(double v) { return lane_f64(wave_scan(v), 63); }
+__device__ __forceinline__ unsigned long long wave_total(unsigned long long v) {
+    v = wave_scan(v);
+    return ((unsigned long long)lane_u32((uint32_t)(v >> 32), 63) << 32) | lane_u32((uint32_t)v, 63);
+}
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     v = max(v, dpp_or0<0x111, 0xF>(v));
     v = max(v, dpp_or0<0x112, 0xF>(v));
@@ -80,6 +94,7 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     v = max(v, dpp_or0<0x143, 0xC>(v));
     return lane_u32(v, 63);
 }
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) { return ~wave_max_u32(~v); }
 
 // value CTRL lanes below inside the row of 16 (row_shr), all ones where there is none
 template <int CTRL>
@@ -95,8 +110,7 @@ __device__ __forceinline__ uint32_t wave_min_before(uint32_t v) {
     m = min(m, min16<0x118>(m));
     m = min(m, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)m, 0x142, 0xA, 0xF, false));
     m = min(m, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)m, 0x143, 0xC, 0xF, false));
-    const uint32_t below = (uint32_t)__shfl_up((int)m, 1, 64);
-    return (threadIdx.x & 63) ? below : 0xFFFFFFFFu;
+    return (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)m, 0x138, 0xF, 0xF, false);      // wave_shr:1
 }
 
 // Exclusive sum over the block, one value per thread; *total = sum of all.  Two barriers.
@@ -112,13 +126,33 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t* s_tmp, uint
     return inc - v + (w ? lane_u32(t, (int)w - 1) : 0u);
 }
 
+// The same for two values, through a table nothing else uses: one barrier.
+__device__ __forceinline__ void block_scan2(uint32_t a, uint32_t b, uint32_t (*s_tmp)[kWavesS], uint32_t* before_a,
+                                            uint32_t* before_b, uint32_t* total_a, uint32_t* total_b) {
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t ia = wave_scan(a), ib = wave_scan(b);
+    if (lane == 63) {
+        s_tmp[0][wave] = ia;
+        s_tmp[1][wave] = ib;
+    }
+    __syncthreads();
+    const uint32_t ta = wave_scan(lane < kWavesS ? s_tmp[0][lane] : 0u), tb = wave_scan(lane < kWavesS ? s_tmp[1][lane] : 0u);
+    *total_a = lane_u32(ta, kWavesS - 1);
+    *total_b = lane_u32(tb, kWavesS - 1);
+    *before_a = ia - a + (wave ? lane_u32(ta, wave - 1) : 0u);
+    *before_b = ib - b + (wave ? lane_u32(tb, wave - 1) : 0u);
+}
+
 struct alignas(16) Lds {
     union {
         double def[kMaxLayersS];             // the default candidate's errors, until E_max is known
         int32_t first[kMaxLayersS];          // first entry of a swept layer, by layer (-1: not swept)
     };
     // entries of the swept layers, layer after layer, largest bin first (hence smallest size first)
-    uint32_t size[kMaxT];
+    union {
+        uint32_t size[kMaxT];
+        uint8_t order[kSolveMaxLP];          // before that: the table's candidates in order of size
+    };
     uint16_t bin[kMaxT];
     uint16_t of[kMaxT];                      // swept layer of an entry
     uint8_t cand[kMaxT];
@@ -135,11 +169,12 @@ struct alignas(16) Lds {
     uint8_t chosen[kMaxLayersS];             // candidate per layer; 255: none
     uint64_t keep[kMaxT / 64];               // one bit per entry: hull vertices, then survivors
     uint32_t before[kMaxT / 64];             // bits of `keep` set in front of every word
-    uint32_t tmp[kWavesS];
+    uint32_t tmp[kWavesS], tmp2[2][2][kWavesS];
     double tmp_d[kWavesS];
     unsigned long long worst;                // sum of the layers' largest sizes
     unsigned long long chk_err, chk_choice;
     unsigned long long best;                 // smallest total and its cell
+    unsigned long long sums;                 // of the assignment: bins << 32 | sizes
     double total_star;
     double emax;
     uint32_t ub;
@@ -443,6 +478,7 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
         s.chk_choice = 0;
         s.worst = 0;
         s.best = ~0ull;
+        s.sums = 0;
         s.ub = kInfS;
     }
     if (tid < 4) s.acc[tid] = s.facts[tid] = 0;
@@ -456,6 +492,8 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
         sz[q] = i < LP ? p.sizes[i] : 0;
     }
     if (tid < L) s.def[tid] = p.have_e_max ? 0.0 : p.errors[(size_t)tid * P + p.default_cand];
+    // (the table of the order is allocated in whole 16-byte words)
+    if (p.order && 16 * tid < LP) reinterpret_cast<uint4*>(s.order)[tid] = reinterpret_cast<const uint4*>(p.order)[tid];
 #pragma unroll
     for (int q = 0; q < NE; ++q) {
         const int i = tid + q * kThreadsS;
@@ -488,7 +526,7 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
         if (!(sum == sum)) bad = true;
     }
     if (p.errors_host) {
-        for (int o = 1; o < 64; o <<= 1) chk += (unsigned long long)__shfl_xor((long long)chk, o, 64);
+        chk = wave_total(chk);
         if (lane == 0) atomicAdd(&s.chk_err, chk);
     }
     if (p.check_sizes) {                                 // a caller whose table the host has not seen
@@ -524,15 +562,13 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
     }
     __syncthreads();
     // ---- candidates in order of size (lowest index first among equals): the caller's table, or sorted here
-    const uint8_t* order = p.order;
-    uint8_t* const t_order = region + (size_t)6 * NE * kThreadsS;
-    if (!order) {                                        // (NE = 4: LDS holds the table)
+    if (!p.order) {
         for (int i = tid; i < LP; i += kThreadsS) {
             const int l = i / P, head = l * P;
             const uint32_t z = t_size[i];
             int rank = 0;
             for (int o = head; o < head + P; ++o) rank += t_size[o] < z || (t_size[o] == z && o < i) ? 1 : 0;
-            t_order[head + rank] = (uint8_t)(i - head);
+            s.order[head + rank] = (uint8_t)(i - head);
         }
         __syncthreads();
     }
@@ -542,7 +578,7 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
     // larger size.  A group of 16 lanes (P <= 16) or a wavefront (two candidates a lane) takes a
     // layer.
     auto slot_of = [&](int l, int rank) -> int {         // table position of the candidate at this rank
-        return l * P + (order ? (int)order[l * P + rank] : (int)t_order[l * P + rank]);
+        return l * P + (int)s.order[l * P + rank];
     };
     const int words = P > 64 ? 2 : 1;                    // (P > 64: at most 252 layers)
     if (P <= 16) {
@@ -570,6 +606,21 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
         }
     } else {
         for (int l = wave; l < L; l += kWavesS) {
+            if (words == 1) {
+                const bool in = lane < P;
+                const int i = in ? slot_of(l, lane) : 0;
+                const uint32_t b = in ? t_bin[i] : kUnusable, z = in ? t_size[i] : 0u;
+                const bool k = b < min(wave_min_before(b), kUnusable);
+                const unsigned long long low = __ballot(k);
+                const uint64_t up = lane < 63 ? low >> (lane + 1) : 0ull;
+                const uint32_t zn = (uint32_t)__shfl((int)z, up ? lane + 1 + (int)__builtin_ctzll(up) : lane, 64);
+                const unsigned long long kept = __ballot(k && !(up && zn == z)), moved = __ballot(in && i != l * P + lane);
+                if (lane == 0) {
+                    s.list[l] = kept;
+                    s.mixed[l] = moved ? 1 : 0;
+                }
+                continue;
+            }
             const bool in0 = lane < P, in1 = 64 + lane < P;
             const int i0 = in0 ? slot_of(l, lane) : 0, i1 = in1 ? slot_of(l, 64 + lane) : 0;
             const uint32_t b0 = in0 ? t_bin[i0] : kUnusable, b1 = in1 ? t_bin[i1] : kUnusable;
@@ -588,8 +639,8 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
             const unsigned long long kept1 = __ballot(((k1 >> lane) & 1) && !beaten1);
             const unsigned long long moved = __ballot((in0 && i0 != l * P + lane) || (in1 && i1 != l * P + 64 + lane));
             if (lane == 0) {
-                s.list[words * l] = kept0;
-                if (words == 2) s.list[2 * l + 1] = kept1;
+                s.list[2 * l] = kept0;
+                s.list[2 * l + 1] = kept1;
                 s.mixed[l] = moved ? 1 : 0;
             }
         }
@@ -630,7 +681,6 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
             const int i = slot_of(l, rank);
             const uint32_t at = (f & 0xFFFFu) + place;
             s.bin[at] = t_bin[i];
-            s.size[at] = t_size[i];
             s.cand[at] = (uint8_t)(i - l * P);
             s.of[at] = (uint16_t)(f >> 16);
         };
@@ -649,6 +699,14 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
                 if ((m0 >> lane) & 1) put(l, lane, f, (uint32_t)__popcll(m0 & below));
                 if ((m1 >> lane) & 1) put(l, 64 + lane, f, (uint32_t)(__popcll(m0) + __popcll(m1 & below)));
             }
+        }
+    }
+    __syncthreads();
+    if (status == 0) {                                   // the sizes take the place of the order
+#pragma unroll
+        for (int q = 0; q < kMaxT / kThreadsS; ++q) {
+            const int t = tid + q * kThreadsS;
+            if (q * kThreadsS < T && t < T) s.size[t] = t_size[(int)s.layer[s.of[t]] * P + (int)s.cand[t]];
         }
     }
     __syncthreads();                                     // from here on the table's region is free
@@ -1003,10 +1061,10 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
                 if (left == 0) atomicOr(&s.flags, 4);
             }
             const bool single = on && left == 1, core = on && left > 1;
-            uint32_t both_c, shift_all, cells;
-            const uint32_t before_c = block_scan(core ? (1u << 20) + (((uint32_t)left + 3u) & ~3u) : 0u, s.tmp, &both_c);
+            uint32_t both_c, shift_all, cells, before_c, sh, unused, unused_total;
+            block_scan2(core ? (1u << 20) + (((uint32_t)left + 3u) & ~3u) : 0u, single ? (uint32_t)s.bin[only] : 0u, s.tmp2[0],
+                        &before_c, &sh, &both_c, &shift_all);
             const uint32_t j = before_c >> 20, ce = before_c & 0xFFFFFu, ents = both_c & 0xFFFFFu;
-            const uint32_t sh = block_scan(single ? (uint32_t)s.bin[only] : 0u, s.tmp, &shift_all);
             {
                 const uint32_t part = wave_total(single ? s.size[only] : 0u);
                 if (lane == 0 && part) atomicAdd(&s.acc[2], part);
@@ -1014,7 +1072,8 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
             // cells of the core layer's row: bins summed over the core layers alone
             const int my_lo = on ? max(0, s.lo[tid + 1] - (int)sh) : 0, my_hi = on ? s.hi[tid + 1] - (int)sh : 0;
             const uint32_t w = core ? (uint32_t)max(my_hi - my_lo + 1, 0) : 0u;
-            const uint32_t cell0 = block_scan(w, s.tmp, &cells);
+            uint32_t cell0;
+            block_scan2(w, 0u, s.tmp2[1], &cell0, &unused, &cells, &unused_total);
             const int n_core = (int)(both_c >> 20);
             {
                 const uint32_t wm = wave_max_u32(w), lm = wave_max_u32(core ? (uint32_t)left : 0u);
@@ -1142,18 +1201,17 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
                 }
                 // smallest total, lowest cell among equals, inside the budget
                 const int base = n_core ? (int)s.acc[0] : 0, top = n_core ? base + (int)s.acc[1] - 1 : 0;
-                unsigned long long best = ~0ull;
+                uint32_t low = kInfS, cell = ~0u;            // (cells in rising order: the first of equals stays)
                 for (int e = base + tid; e <= min(top, D - (int)shift_all); e += kThreadsS) {
-                    const uint32_t v = last[e - base];
-                    const unsigned long long x = ((unsigned long long)(v >= kInfS ? kInfS : v >> row_bits) << 32) | (uint32_t)e;
-                    best = x < best ? x : best;
+                    const uint32_t raw = last[e - base], v = raw >= kInfS ? kInfS : raw >> row_bits;
+                    if (v < low) {
+                        low = v;
+                        cell = (uint32_t)e;
+                    }
                 }
                 if ((tid & ~63) <= top - base) {
-                    for (int d = 1; d < 64; d <<= 1) {
-                        const unsigned long long x = (unsigned long long)__shfl_xor((long long)best, d, 64);
-                        best = x < best ? x : best;
-                    }
-                    if (lane == 0) atomicMin(&s.best, best);
+                    const uint32_t v = wave_min_u32(low), e = wave_min_u32(low == v ? cell : ~0u);
+                    if (lane == 0) atomicMin(&s.best, ((unsigned long long)v << 32) | e);
                 }
                 if (tid == 0) t_sweep = wall_clock64();
                 __syncthreads();
@@ -1246,9 +1304,10 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
                         pz += x.y >> bits;
                         s.chosen[s.layer[s.lo[tid]]] = ent_cand[at];
                     }
-                    uint32_t tb, tz;
-                    (void)block_scan(pb, s.tmp, &tb);
-                    (void)block_scan(pz, s.tmp, &tz);
+                    const uint32_t wb = wave_total(pb), wz = wave_total(pz);
+                    if (lane == 0 && (wb | wz)) atomicAdd(&s.sums, ((unsigned long long)wb << 32) | wz);
+                    __syncthreads();
+                    const uint32_t tb = (uint32_t)(s.sums >> 32), tz = (uint32_t)s.sums;
                     total_bins = tb;
                     total_size = tz;
                     if ((s.flags & 16) || tb != (uint32_t)b + shift_all || tz != (uint32_t)(b >> 32) + s.acc[2]) status = 2;
@@ -1303,7 +1362,7 @@ __global__ __launch_bounds__(kThreadsS) void solve_kernel(SolveParams p) {
         p.choice[tid] = out;
         cs = (unsigned long long)(uint32_t)(out + 1) * (unsigned long long)(tid + 1);
     }
-    for (int o = 1; o < 64; o <<= 1) cs += (unsigned long long)__shfl_xor((long long)cs, o, 64);
+    cs = wave_total(cs);
     if (lane == 0 && cs) atomicAdd(&s.chk_choice, cs);
     __syncthreads();
     if (wave == 0) {
