@@ -220,7 +220,9 @@ hipError_t launch_solve(const SolveParams& p, hipStream_t s, Section* sec);
 struct TopkScratch {
     uint32_t* d_hist = nullptr;       // [max_layers x kHistBins] exact coarse histogram
     void* d_tl = nullptr;             // per-layer selection records
-    uint32_t* d_cnt_known = nullptr;  // [max_layers x 512] sub-bin counts of topk_compress_known
+    uint32_t* d_cnt_a = nullptr;      // [max_layers x 1024] counts of a compression inside the threshold bin, and
+    uint32_t* d_cnt_b = nullptr;      // [max_layers x 512] inside the boundary sub-bin
+    bool counts_clean = false;        // both are all zero (the last kernel of a compression clears them)
     uint32_t* d_cand = nullptr;       // bit patterns of the candidates, tile i at its own first element
     uint32_t* d_cand_idx = nullptr;   // compress: index within the layer (+ sign bit) of every candidate; a profile that
                                       // records where its candidates are uses it for 16-bit entries (place in tile, sign)

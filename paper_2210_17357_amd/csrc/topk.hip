@@ -160,6 +160,33 @@ __device__ void block_kth_from_top(const uint32_t* hist, uint32_t need, uint32_t
     __syncthreads();
 }
 
+// The same by one wavefront, whose lane t holds the bins [t * PER, (t + 1) * PER) in c; the results are uniform.
+template <int PER>
+__device__ __forceinline__ void wave_kth_from_top(const uint32_t (&c)[PER], uint32_t need, uint32_t* bin, uint32_t* higher) {
+    const int lane = threadIdx.x & 63;
+    uint32_t sum = 0;
+#pragma unroll
+    for (int b = 0; b < PER; ++b) sum += c[b];
+    uint32_t inc = sum;
+    for (int o = 1; o < 64; o <<= 1) {        // inclusive suffix scan
+        const uint32_t n = __shfl_down(inc, o, 64);
+        if (lane + o < 64) inc += n;
+    }
+    uint32_t run = inc - sum, at = 0, above = inc - c[0];          // (lane 0: what there is if nothing is found)
+    const unsigned long long found = __ballot(run < need && inc >= need);
+#pragma unroll
+    for (int b = PER - 1; b >= 0; --b) {
+        if (run < need && run + c[b] >= need) {
+            at = (uint32_t)(lane * PER + b);
+            above = run;
+        }
+        run += c[b];
+    }
+    const int src = found ? (int)__builtin_ctzll(found) : 0;
+    *bin = (uint32_t)__builtin_amdgcn_readlane((int)at, src);
+    *higher = (uint32_t)__builtin_amdgcn_readlane((int)above, src);
+}
+
 // ------------------------------------------------------------------------ kernels
 __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
@@ -563,31 +590,6 @@ __global__ __launch_bounds__(kThreads) void topk_filter_known_kernel(FilterParam
     }
 }
 
-// One workgroup per layer: the exact threshold pattern and the number of entries equal to it that
-// are kept, from the counts the main pass above left; the counts are cleared for the next call.
-__global__ __launch_bounds__(256) void topk_pick_known_kernel(const DevLayer* __restrict__ layers,
-                                                              TopkLayer* __restrict__ tl,
-                                                              uint32_t* __restrict__ cnt_b) {
-    __shared__ uint32_t s_hist[kBinsB];
-    __shared__ uint32_t s_tot[4];
-    __shared__ uint32_t s_res[2];
-    const int l = blockIdx.x;
-    const DevLayer L = layers[l];
-    if (L.family != LGRECO_TOPK || L.slot < 0 || L.slot >= kMaxTopk) return;
-    TopkSel& S = tl[l].sel[L.slot];
-    for (int b = threadIdx.x; b < kBinsB; b += 256) {
-        s_hist[b] = cnt_b[(size_t)l * kBinsB + b];
-        cnt_b[(size_t)l * kBinsB + b] = 0u;
-    }
-    __syncthreads();
-    const uint32_t need_a = S.need_a, prefix = (S.tbin << 10) | S.bin_a;
-    block_kth_from_top<kBinsB / 256>(s_hist, need_a, s_tot, s_res);
-    if (threadIdx.x == 0) {
-        S.thr = (prefix << 9) | s_res[0];
-        S.ties_keep = need_a - s_res[1];
-    }
-}
-
 template <bool HIST, bool EMIT>
 __global__ __launch_bounds__(kThreads) void topk_collect_kernel(CollectParams p) {
     __shared__ uint32_t s_hist[HIST ? kHistBins : 1];
@@ -755,10 +757,11 @@ struct RefineParams {
     const int2* work_range;           // [L] the layer's workgroups [x, y)
     const double* base_part;          // [n_tiles]
     double* below_part;               // [n_work x kMaxTopk] energy of candidates below each threshold bin
-    // per-workgroup partial histograms (plain stores, summed in workgroup order by the pick kernels)
-    uint32_t* cnt_a;                  // [n_work x kMaxTopk x kBinsA] compress: counts
+    // per-workgroup partial histograms (plain stores, summed by the pick kernel)
     unsigned long long* cell_a;       // [n_work x kMaxTopk x kBinsA] profile: packed count + energy
-    uint32_t* cnt_b;                  // [n_work x kMaxTopk x kBinsB] compress: counts
+    // compression: a layer's counts, added up where they are (all zero between calls)
+    uint32_t* cnt_a;                  // [L x kBinsA]
+    uint32_t* cnt_b;                  // [L x kBinsB]
     double* errors;                   // may be null (compress)
     int32_t stride;
     int32_t ntk;
@@ -881,8 +884,8 @@ __device__ __forceinline__ void below_chain(float (&b)[kMaxTopk], const uint32_t
 // and integer energy into one 64-bit LDS atomic, and per requested k the energy of the candidates
 // below its threshold bin (fp32 per lane - a lane sees some tens of candidates - fp64 from the
 // wavefront up).  NTK = 0 (compress): counts only.  Which list a candidate belongs to comes from a
-// table over the 4096 coarse keys the workgroup builds first.  Partial histograms go to global
-// memory with plain stores.
+// table over the 4096 coarse keys the workgroup builds first.  Partial histograms with energies go to global
+// memory with plain stores; the compression's counts (few cells of a layer are not zero) are added to the layer's.
 __host__ __device__ constexpr size_t refine_a_lds(int ntk, bool energy) {
     return (size_t)ntk * kBinsA * (energy ? 8 : 4) + kHistBins;
 }
@@ -952,8 +955,9 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_a_kernel(RefinePar
         unsigned long long* const gc = p.cell_a + (size_t)blockIdx.x * kMaxTopk * kBinsA;
         for (int i = tid; i < nlists * kBinsA; i += kRefThreads) gc[i] = s_cell[i];
     } else {
-        uint32_t* const gc = p.cnt_a + (size_t)blockIdx.x * kMaxTopk * kBinsA;
-        for (int i = tid; i < nlists * kBinsA; i += kRefThreads) gc[i] = s_cnt[i];
+        static_assert(kBinsA == kRefThreads, "a thread per cell");
+        const uint32_t c = nlists ? s_cnt[tid] : 0u;
+        if (c) atomicAdd(&p.cnt_a[(size_t)l * kBinsA + tid], c);
     }
 }
 
@@ -972,8 +976,8 @@ __device__ __forceinline__ double base_energy(const RefineParams& p, int l) {
     return part;
 }
 
-// One workgroup per (layer, requested k): sub-bin of level A holding the k-th magnitude.
-// ENERGY (profile): the dropped energy is written here.  Everything outside the boundary sub-bin is
+// Profile: one workgroup per (layer, requested k): sub-bin of level A holding the k-th magnitude, and
+// the dropped energy.  Everything outside the boundary sub-bin is
 // summed exactly (integer energies).  Inside it the dropped entries are the `drop` smallest of
 // `cnt` entries whose integer energies lie in [e_lo, e_hi] and sum to S, so their sum lies in
 //     [ max(drop * e_lo, S - keep * e_hi),  drop * S / cnt ]
@@ -1030,10 +1034,10 @@ __device__ void count_sub_bin(const RefineParams& p, int l, int64_t cand_base, u
     __syncthreads();
 }
 
-template <bool ENERGY, int kPickThreads>
+template <int kPickThreads>
 __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams p) {
     __shared__ uint32_t s_hist[kBinsA];
-    __shared__ unsigned long long s_en[ENERGY ? kBinsA : 1];
+    __shared__ unsigned long long s_en[kBinsA];
     __shared__ uint32_t s_tot[4];
     __shared__ uint32_t s_res[2];
     __shared__ unsigned long long s_e;
@@ -1048,7 +1052,7 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
     const int tid = threadIdx.x, t = tid & 255, grp = tid >> 8;
     for (int b = tid; b < kBinsA; b += kPickThreads) {
         s_hist[b] = 0;
-        if (ENERGY) s_en[b] = 0;
+        s_en[b] = 0;
     }
     if (tid == 0) {
         s_e = 0;
@@ -1058,13 +1062,13 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
     // bin (workgroup partials): loaded first so that the histogram work hides the latency; both
     // are summed in a fixed order (per thread, then a fixed tree)
     double part = 0.0;
-    if (ENERGY && tid < 256) {
+    if (tid < 256) {
         part = base_energy(p, l);
         for (int wg = wr.x + tid; wg < wr.y; wg += 256) part += p.below_part[(size_t)wg * kMaxTopk + j];
     }
     __syncthreads();
     // sum the layer's workgroup partials of this k's list: 4 bins per thread as 16-byte loads (two
-    // pairs of packed cells, or four counts), the workgroups dealt round-robin to the thread groups,
+    // pairs of packed cells), the workgroups dealt round-robin to the thread groups,
     // integer LDS atomics join them (order does not matter).  The loop is a chain of memory round
     // trips with a fixed number of loads in flight: wide loads halve its length.
     {
@@ -1075,31 +1079,26 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
 #pragma unroll(kPickThreads == 256 ? 8 : 4)
         for (int wg = wr.x + grp; wg < wr.y; wg += kPickThreads / 256) {
             const size_t i = (size_t)wg * kMaxTopk * kBinsA + off;
-            if (ENERGY) {
-                const ulonglong2 v0 = *reinterpret_cast<const ulonglong2*>(p.cell_a + i + 2 * t);
-                const ulonglong2 v1 = *reinterpret_cast<const ulonglong2*>(p.cell_a + i + 512 + 2 * t);
-                const unsigned long long v[4] = {v0.x, v0.y, v1.x, v1.y};
+            const ulonglong2 v0 = *reinterpret_cast<const ulonglong2*>(p.cell_a + i + 2 * t);
+            const ulonglong2 v1 = *reinterpret_cast<const ulonglong2*>(p.cell_a + i + 512 + 2 * t);
+            const unsigned long long v[4] = {v0.x, v0.y, v1.x, v1.y};
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    c[q] += (uint32_t)(v[q] & ((1ull << kPackCountBits) - 1));
-                    e[q] += v[q] >> kPackCountBits;
-                }
-            } else {
-                const uint4 v = *reinterpret_cast<const uint4*>(p.cnt_a + i + 4 * t);
-                c[0] += v.x; c[1] += v.y; c[2] += v.z; c[3] += v.w;
+            for (int q = 0; q < 4; ++q) {
+                c[q] += (uint32_t)(v[q] & ((1ull << kPackCountBits) - 1));
+                e[q] += v[q] >> kPackCountBits;
             }
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int cell = ENERGY ? (q >> 1) * 512 + 2 * t + (q & 1) : 4 * t + q;
+            const int cell = (q >> 1) * 512 + 2 * t + (q & 1);
             if (c[q]) atomicAdd(&s_hist[cell], c[q]);
-            if (ENERGY && e[q]) atomicAdd(&s_en[cell], e[q]);
+            if (e[q]) atomicAdd(&s_en[cell], e[q]);
         }
     }
     __syncthreads();
     block_kth_from_top<kBinsA / 256>(s_hist, S.need, s_tot, s_res);
     const uint32_t bin_a = s_res[0];
-    if (ENERGY) {
+    {
         unsigned long long e = 0;
         for (uint32_t b = tid; b < bin_a; b += kPickThreads) e += s_en[b];
         if (e) atomicAdd(&s_e, e);
@@ -1114,23 +1113,20 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
         const uint32_t need_a = S.need - s_res[1];
         T.sel[j].bin_a = bin_a;
         T.sel[j].need_a = need_a;
-        if (ENERGY) {
-            const uint32_t cnt = s_hist[bin_a];
-            const double outside = ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3])) + ldexp((double)s_e, sh);
-            double inside = 0.0;      // dropped part of the sub-bin, in integer-energy units
-            const bool exact = cnt > need_a && !dropped_inside((S.tbin << 10) | bin_a, cnt, need_a, s_en[bin_a], sh,
-                                                               outside, &inside);
-            if (exact) {
-                s_outside = outside;
-                s_exact[1] = (S.tbin << 10) | bin_a;
-                s_exact[2] = need_a;
-                s_exact[0] = 1;
-            } else {
-                p.errors[(size_t)l * p.stride + p.col[j]] = outside + ldexp(inside, sh);
-            }
+        const uint32_t cnt = s_hist[bin_a];
+        const double outside = ((s_sum[0] + s_sum[1]) + (s_sum[2] + s_sum[3])) + ldexp((double)s_e, sh);
+        double inside = 0.0;      // dropped part of the sub-bin, in integer-energy units
+        const bool exact = cnt > need_a && !dropped_inside((S.tbin << 10) | bin_a, cnt, need_a, s_en[bin_a], sh,
+                                                           outside, &inside);
+        if (exact) {
+            s_outside = outside;
+            s_exact[1] = (S.tbin << 10) | bin_a;
+            s_exact[2] = need_a;
+            s_exact[0] = 1;
+        } else {
+            p.errors[(size_t)l * p.stride + p.col[j]] = outside + ldexp(inside, sh);
         }
     }
-    if (!ENERGY) return;
     __syncthreads();
     if (!s_exact[0]) return;                                  // workgroup-uniform
     const uint32_t prefix = s_exact[1], need_a = s_exact[2];
@@ -1327,62 +1323,38 @@ __global__ __launch_bounds__(256) void topk_pick_many_kernel(RefineParams p) {
     }
 }
 
-// Refinement level B (compress only): histogram of bits 8..0 of the candidates inside each k's
-// level-A sub-bin.
+// Refinement level B (compression, one density): the level-A sub-bin that holds the k-th magnitude, found by every
+// workgroup for itself in the layer's counts, and the counts of bits 8..0 of the candidates inside it.  (In
+// a kernel of its own between the two levels, a workgroup per layer, that search cost a launch; see topk_count_kernel.)
 __global__ __launch_bounds__(kRefThreads) void topk_refine_b_kernel(RefineParams p) {
-    extern __shared__ unsigned char refine_smem[];
+    __shared__ uint32_t s_cnt[kBinsB], s_tot[kRefThreads / 64], s_res[2];
     const RefWork w = p.work[blockIdx.x];
-    const TopkLayer& T = p.tl[w.layer];
-    const int ntk = p.ntk;
-    uint32_t* const s_cnt = reinterpret_cast<uint32_t*>(refine_smem);
+    TopkLayer& T = p.tl[w.layer];
     const int tid = threadIdx.x;
-    for (int i = tid; i < ntk * kBinsB; i += kRefThreads) s_cnt[i] = 0;
-    uint32_t prefix[kMaxTopk];       // top 22 bits (coarse bin, level-A bin) of each k
-#pragma unroll
-    for (int j = 0; j < kMaxTopk; ++j)
-        prefix[j] = (j < ntk && T.sel[j].k) ? ((T.sel[j].tbin << 10) | T.sel[j].bin_a) : 0xFFFFFFFFu;
+    const uint32_t c[1] = {p.cnt_a[(size_t)w.layer * kBinsA + tid]};
+    const uint32_t need = T.sel[0].need, tbin = T.sel[0].tbin;
+    const int64_t cand_base = T.cand_base;
+    if (tid < kBinsB) s_cnt[tid] = 0;
+    uint32_t mine;
+    const uint32_t above = entries_above<kRefThreads, 1>(c, s_tot, &mine);      // (one barrier)
+    if (above < need && above + mine >= need) {          // one thread: the bin holds at least `need` entries
+        s_res[0] = (uint32_t)tid;
+        s_res[1] = above;
+    } else if (tid == 0 && above + mine < need) {
+        s_res[0] = 0;
+        s_res[1] = above + mine - c[0];
+    }
     __syncthreads();
-    for_each_candidate(p, T.cand_base, w.t0, w.t1, [&](uint32_t pat) {
-        const uint32_t pre = pat >> 9;
-#pragma unroll
-        for (int j = 0; j < kMaxTopk; ++j)
-            if (pre == prefix[j]) atomicAdd(&s_cnt[j * kBinsB + (pat & (kBinsB - 1))], 1u);
+    const uint32_t prefix = (tbin << 10) | s_res[0];
+    if (tid == 0 && (int)blockIdx.x == p.work_range[w.layer].x) {
+        T.sel[0].bin_a = s_res[0];
+        T.sel[0].need_a = need - s_res[1];
+    }
+    for_each_candidate(p, cand_base, w.t0, w.t1, [&](uint32_t pat) {
+        if ((pat >> 9) == prefix) atomicAdd(&s_cnt[pat & (kBinsB - 1)], 1u);
     });
     __syncthreads();
-    uint32_t* const gc = p.cnt_b + (size_t)blockIdx.x * kMaxTopk * kBinsB;
-    for (int i = tid; i < ntk * kBinsB; i += kRefThreads) gc[i] = s_cnt[i];
-}
-
-// One workgroup per (layer, requested k): exact threshold pattern and how many of the entries
-// equal to it are kept.
-__global__ __launch_bounds__(256) void topk_pick_b_kernel(RefineParams p) {
-    __shared__ uint32_t s_hist[kBinsB];
-    __shared__ uint32_t s_tot[4];
-    __shared__ uint32_t s_res[2];
-    const int l = blockIdx.x / kMaxTopk, j = blockIdx.x % kMaxTopk;
-    TopkLayer& T = p.tl[l];
-    if (j >= p.ntk || T.sel[j].k == 0) return;
-    const TopkSel S = T.sel[j];
-    const int2 wr = p.work_range[l];
-    const int tid = threadIdx.x;
-    {
-        uint32_t c[2] = {0, 0};
-        const size_t off = (size_t)j * kBinsB + tid;
-#pragma unroll 8
-        for (int wg = wr.x; wg < wr.y; ++wg) {
-            const size_t i = (size_t)wg * kMaxTopk * kBinsB + off;
-#pragma unroll
-            for (int q = 0; q < 2; ++q) c[q] += p.cnt_b[i + 256 * q];
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) s_hist[tid + 256 * q] = c[q];
-    }
-    __syncthreads();
-    block_kth_from_top<kBinsB / 256>(s_hist, S.need_a, s_tot, s_res);
-    if (tid == 0) {
-        T.sel[j].thr = (S.tbin << kHistShift) | (S.bin_a << 9) | s_res[0];
-        T.sel[j].ties_keep = S.need_a - s_res[1];
-    }
+    if (tid < kBinsB && s_cnt[tid]) atomicAdd(&p.cnt_b[(size_t)w.layer * kBinsB + tid], s_cnt[tid]);
 }
 
 // ---------------------------------------------------------------- compression kernels
@@ -1398,15 +1370,24 @@ constexpr int kSliceBatch = 4;
 
 // per (tile, wavefront): entries above the threshold, entries equal to it (from its candidates)
 // KNOWN: the layer records say which layers take part and which selection record holds the threshold.
+// The exact threshold and the number of entries equal to it that are kept come from the layer's counts inside the
+// boundary sub-bin: wavefront q of every workgroup finds them for the batch's tile q, and the one with a layer's first
+// tile leaves them in its record.  (A kernel of its own in front of this one, a workgroup per layer, took 4-5 us and
+// its launch; 2 KB a wavefront from the caches and six exchanges between lanes cost a fraction of that.)
+static_assert(kSliceBatch == kThreads / 64, "a wavefront per tile of a batch");
 template <bool KNOWN>
 __global__ __launch_bounds__(kThreads) void topk_count_kernel(const Tile* __restrict__ tiles, int n_tiles,
                                                                const DevLayer* __restrict__ layers,
-                                                               const TopkLayer* __restrict__ tl,
+                                                               TopkLayer* tl, const uint32_t* __restrict__ cnt_b,
                                                                const TopkTileInfo* __restrict__ tinfo,
                                                                const uint32_t* __restrict__ cand,
                                                                uint2* __restrict__ wavecnt) {
+    __shared__ uint32_t s_thr[kSliceBatch];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int first = blockIdx.x * kSliceBatch;
+    const Tile own = tiles[min(first + wave, n_tiles - 1)];
+    const uint4* const own_cnt = reinterpret_cast<const uint4*>(cnt_b + (size_t)own.layer * kBinsB) + 2 * lane;
+    const uint4 c0 = own_cnt[0], c1 = own_cnt[1];
     const uint32_t* items[kSliceBatch];
     uint32_t n[kSliceBatch], thr[kSliceBatch], gt[kSliceBatch], eq[kSliceBatch];
     bool active[kSliceBatch];
@@ -1438,9 +1419,35 @@ __global__ __launch_bounds__(kThreads) void topk_count_kernel(const Tile* __rest
     for (int q = 0; q < kSliceBatch; ++q) {
         const TopkLayer& T = tl[layer[q]];
         if (!KNOWN) k[q] = T.sel[0].k;
-        thr[q] = T.sel[slot[q]].thr;
         base[q] = T.cand_base;
     }
+    {
+        int own_slot = 0;
+        bool own_on = first + wave < n_tiles;
+        if (KNOWN) {
+            const DevLayer& L = layers[own.layer];
+            own_on = own_on && L.family == LGRECO_TOPK && L.slot >= 0 && L.slot < kMaxTopk;
+            own_slot = own_on ? L.slot : 0;
+        }
+        TopkSel& S = tl[own.layer].sel[own_slot];
+        const uint32_t need_a = S.need_a, prefix = (S.tbin << 10) | S.bin_a;
+        if (!KNOWN) own_on = own_on && S.k != 0;
+        static_assert(kBinsB == 64 * 8, "8 cells a lane");
+        const uint32_t c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+        uint32_t bin, higher;
+        wave_kth_from_top<8>(c, need_a, &bin, &higher);
+        const uint32_t own_thr = (prefix << 9) | bin;
+        if (lane == 0) {
+            s_thr[wave] = own_thr;
+            if (own_on && own.pos == 0) {
+                S.thr = own_thr;
+                S.ties_keep = need_a - higher;
+            }
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSliceBatch; ++q) thr[q] = s_thr[q];
 #pragma unroll
     for (int q = 0; q < kSliceBatch; ++q) {
         // a layer that is not compressed with Top-K has k = 0 in its record (and no candidates)
@@ -1505,6 +1512,7 @@ __global__ __launch_bounds__(kThreads) void topk_runs_kernel(const uint2* __rest
 // workgroup adds up those before its first tile (of the largest layer of a 355 M-element model 50 KB at most,
 // 8 128-bit loads in flight per thread) and walks its own 16.  As a kernel of its own, a
 // workgroup per layer, that prefix took 4-5 us and its launch; 18 beside a kernel that fills the chip.
+// The counts of a layer that the thresholds came from are cleared by the workgroup with its first tile.
 // `runs` (not null where a layer has more than kTilesInRuns tiles): the whole runs of tiles before its first come as
 // their sums, so that what a workgroup reads stays bounded.
 template <bool KNOWN>
@@ -1517,6 +1525,7 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__
                                                               const uint32_t* __restrict__ cand_idx,
                                                               const uint2* __restrict__ wavecnt,
                                                               const unsigned long long* __restrict__ runs,
+                                                              uint32_t* __restrict__ cnt_a, uint32_t* __restrict__ cnt_b,
                                                               uint8_t* __restrict__ payload, int x_in_e) {
     // x_in_e (KNOWN only): the main pass left the buffer as it was (x everywhere), so the kept
     // entries are zeroed here, as without KNOWN, and nothing is put back
@@ -1615,6 +1624,14 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__
         S[q].out = before[q].x + min(before[q].y, keep_eq);
         S[q].eq_seen = before[q].y;
         nmax = max(nmax, S[q].n);
+        if (active && pos[q] == 0) {                         // (uniform; the count kernel was the last to read them)
+            uint32_t* const b = cnt_b + (size_t)layer[q] * kBinsB;
+            for (int i = (int)threadIdx.x; i < kBinsB; i += kThreads) b[i] = 0u;
+            if (!KNOWN) {
+                uint32_t* const a = cnt_a + (size_t)layer[q] * kBinsA;
+                for (int i = (int)threadIdx.x; i < kBinsA; i += kThreads) a[i] = 0u;
+            }
+        }
     }
     for (uint32_t i0 = 0; i0 < nmax; i0 += 64) {
         const uint32_t i = i0 + lane;
@@ -1661,7 +1678,7 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__
     } while (0)
 
 // Partial histograms (and the energies beside them) of a call with more than kMaxTopk densities that the
-// refinement's buffer holds, in (work item, list) pairs; at least 13 per work item.
+// refinement's buffer holds, in (work item, list) pairs; at least 7 per work item.
 constexpr size_t kManyBytes = sizeof(unsigned long long) * kBinsA + sizeof(double);
 static size_t many_capacity(const TopkScratch* t) { return t->ref_words * sizeof(uint32_t) / kManyBytes; }
 
@@ -1675,9 +1692,12 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
     TK_CHECK(hipMemset(t->d_hist, 0, sizeof(uint32_t) * (size_t)max_layers * kHistBins));
     t->hist_clean = true;
     TK_CHECK(hipMalloc(&t->d_tl, sizeof(TopkLayer) * (size_t)max_layers));
-    // counts of the known-threshold compression: all zero between calls (the pick kernel clears what it reads)
-    TK_CHECK(hipMalloc(&t->d_cnt_known, sizeof(uint32_t) * (size_t)max_layers * kBinsB));
-    TK_CHECK(hipMemset(t->d_cnt_known, 0, sizeof(uint32_t) * (size_t)max_layers * kBinsB));
+    // counts of a compression: all zero between calls (the emit kernel clears them), counts_clean as above
+    const size_t counts = (size_t)max_layers * (kBinsA + kBinsB);
+    TK_CHECK(hipMalloc(&t->d_cnt_a, sizeof(uint32_t) * counts));
+    TK_CHECK(hipMemset(t->d_cnt_a, 0, sizeof(uint32_t) * counts));
+    t->d_cnt_b = t->d_cnt_a + (size_t)max_layers * kBinsA;
+    t->counts_clean = true;
     TK_CHECK(hipMalloc(&t->d_cand, sizeof(uint32_t) * (size_t)max_elems));
     TK_CHECK(hipMalloc(&t->d_cand_idx, sizeof(uint32_t) * (size_t)max_elems));
     TK_CHECK(hipMalloc(&t->d_kept, sizeof(uint32_t) * (size_t)max_elems));
@@ -1690,7 +1710,7 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
     TK_CHECK(hipMalloc(&t->d_base_part, sizeof(double) * (size_t)max_tiles));
     t->max_work = (int)(max_elems / ((int64_t)kRefTiles * kTile)) + 2 * max_layers + 2 + 2 * kRefSlots;   // see topk_begin
     TK_CHECK(hipMalloc(&t->d_below_part, sizeof(double) * (size_t)t->max_work * kMaxTopk));
-    t->ref_words = (size_t)t->max_work * kMaxTopk * (3 * kBinsA + kBinsB);      // u64 + u32 level A, u32 level B
+    t->ref_words = (size_t)t->max_work * kMaxTopk * 2 * kBinsA;
     if (max_cands > (int)kMaxTopk) {
         // more densities than that: room for a list of each in every work item (see topk_begin for their number), up to half
         // a gigabyte; what does not fit takes further passes
@@ -1731,7 +1751,7 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
 void topk_scratch_destroy(TopkScratch* t) {
     (void)hipFree(t->d_hist);
     (void)hipFree(t->d_tl);
-    (void)hipFree(t->d_cnt_known);
+    (void)hipFree(t->d_cnt_a);
     (void)hipFree(t->d_cand);
     (void)hipFree(t->d_cand_idx);
     (void)hipFree(t->d_kept);
@@ -1959,6 +1979,19 @@ hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef
     return hipSuccess;
 }
 
+// The counts of a compression are all zero, for it to add to; the emit kernel's launch makes them so again.
+static hipError_t take_counts(TopkScratch* t, hipStream_t s) {
+    if (!t->counts_clean) {
+        const size_t n = (size_t)t->max_layers * (kBinsA + kBinsB);
+        hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)std::min<size_t>((n + 255) / 256, 2048)), dim3(256), 0, s, t->d_cnt_a,
+                           n, 0u);
+        TK_CHECK(hipGetLastError());
+    }
+    t->counts_clean = false;
+    return hipSuccess;
+}
+
+// d_errors null: the compression's refinement, one density
 hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d_tiles, int L, int ntk,
                          const int* col, double* d_errors, int stride, Timing* tm, hipStream_t s) {
     if (t->n_work <= 0) return hipSuccess;
@@ -1975,11 +2008,9 @@ hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d
     p.work_range = (const int2*)t->d_work_range;
     p.base_part = t->d_base_part;
     p.below_part = t->d_below_part;
-    // per-workgroup partial histograms: [packed cells A (u64)][counts A][counts B]
-    const size_t na = (size_t)t->max_work * kMaxTopk * kBinsA;
     p.cell_a = reinterpret_cast<unsigned long long*>(t->d_ref);
-    p.cnt_a = t->d_ref + 2 * na;
-    p.cnt_b = p.cnt_a + na;
+    p.cnt_a = t->d_cnt_a;
+    p.cnt_b = t->d_cnt_b;
     p.errors = d_errors;
     p.stride = stride;
     p.ntk = ntk;
@@ -2031,18 +2062,14 @@ hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d
         }
 #undef LG_REFINE_A
         TK_CHECK(hipGetLastError());
-        if (wide_pick) hipLaunchKernelGGL((topk_pick_a_kernel<true, 512>), dim3(L * ntk), dim3(512), 0, s, p);
-        else hipLaunchKernelGGL((topk_pick_a_kernel<true, 256>), dim3(L * ntk), dim3(256), 0, s, p);
+        if (wide_pick) hipLaunchKernelGGL((topk_pick_a_kernel<512>), dim3(L * ntk), dim3(512), 0, s, p);
+        else hipLaunchKernelGGL((topk_pick_a_kernel<256>), dim3(L * ntk), dim3(256), 0, s, p);
         return hipGetLastError();
     }
+    if (ntk != 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(topk_refine_a_kernel<0>, dim3(t->n_work), dim3(kRefThreads), refine_a_lds(ntk, false), s, p);
     TK_CHECK(hipGetLastError());
-    if (wide_pick) hipLaunchKernelGGL((topk_pick_a_kernel<false, 512>), dim3(L * ntk), dim3(512), 0, s, p);
-    else hipLaunchKernelGGL((topk_pick_a_kernel<false, 256>), dim3(L * ntk), dim3(256), 0, s, p);
-    TK_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(topk_refine_b_kernel, dim3(t->n_work), dim3(kRefThreads), (size_t)ntk * kBinsB * 4, s, p);
-    TK_CHECK(hipGetLastError());
-    hipLaunchKernelGGL(topk_pick_b_kernel, dim3(L * kMaxTopk), dim3(256), 0, s, p);
+    hipLaunchKernelGGL(topk_refine_b_kernel, dim3(t->n_work), dim3(kRefThreads), 0, s, p);
     return hipGetLastError();
 }
 
@@ -2073,12 +2100,13 @@ hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLaye
         TK_CHECK(topk_collect(t, g, e_in, e, d_layers, d_tiles, n_tiles, s, &sec));
     }
     TK_CHECK(topk_select(t, g, e_in, e, d_layers, L, 1, tm, s, nullptr));
+    TK_CHECK(take_counts(t, s));
     TK_CHECK(topk_finalize(t, d_layers, d_tiles, L, 1, nullptr, nullptr, 0, tm, s));
     {
         Section sec(tm, "topk_count");
         hipLaunchKernelGGL(topk_count_kernel<false>, dim3((n_tiles + kSliceBatch - 1) / kSliceBatch), dim3(kThreads), 0,
-                           s, d_tiles, n_tiles, d_layers, (const TopkLayer*)t->d_tl, (const TopkTileInfo*)t->d_tinfo,
-                           (const uint32_t*)t->d_cand, (uint2*)t->d_tilecnt);
+                           s, d_tiles, n_tiles, d_layers, (TopkLayer*)t->d_tl, (const uint32_t*)t->d_cnt_b,
+                           (const TopkTileInfo*)t->d_tinfo, (const uint32_t*)t->d_cand, (uint2*)t->d_tilecnt);
         TK_CHECK(hipGetLastError());
     }
     {
@@ -2089,8 +2117,9 @@ hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLaye
                            d_layers, d_tiles, n_tiles, (const TopkLayer*)t->d_tl,
                            (const TopkTileInfo*)t->d_tinfo, (const uint32_t*)t->d_cand,
                            (const uint32_t*)t->d_cand_idx, (const uint2*)t->d_tilecnt, runs,
-                           payload, 0);
+                           t->d_cnt_a, t->d_cnt_b, payload, 0);
         TK_CHECK(hipGetLastError());
+        t->counts_clean = true;
     }
     return hipSuccess;
 }
@@ -2122,13 +2151,14 @@ hipError_t topk_compress_known(TopkScratch* t, const float* g, float* e, const D
     p.cand_base = reinterpret_cast<const int64_t*>(d + t->ctl_off[1]);
     p.tinfo = (TopkTileInfo*)t->d_tinfo;
     p.base_part = t->d_base_part;
-    p.cnt_b = t->d_cnt_known;
+    p.cnt_b = t->d_cnt_b;
     const TopkTileInfo* tinfo = (const TopkTileInfo*)t->d_tinfo;
     const uint32_t* cand = t->d_cand;
     const uint32_t* cand_idx = t->d_cand_idx;
+    if (x_in_e && !t->cand_has_idx) return hipErrorInvalidValue;
+    TK_CHECK(take_counts(t, s));
     if (x_in_e) {
         // the profile recorded where its candidates are: what is kept is taken from them
-        if (!t->cand_has_idx) return hipErrorInvalidValue;
         FilterParams f{};
         f.layers = d_layers;
         f.tiles = d_tiles;
@@ -2140,7 +2170,7 @@ hipError_t topk_compress_known(TopkScratch* t, const float* g, float* e, const D
         f.tinfo_out = (TopkTileInfo*)t->d_tinfo_kept;
         f.cand_out = t->d_kept;
         f.cand_idx_out = t->d_kept_idx;
-        f.cnt_b = t->d_cnt_known;
+        f.cnt_b = t->d_cnt_b;
         Section sec(tm, "topk_filter", true);
         launch_timed(&sec, true, true, topk_filter_known_kernel, dim3(n_tiles), dim3(kThreads), 0, s, f);
         TK_CHECK(hipGetLastError());
@@ -2153,15 +2183,10 @@ hipError_t topk_compress_known(TopkScratch* t, const float* g, float* e, const D
         TK_CHECK(hipGetLastError());
     }
     {
-        Section sec(tm, "topk_pick");
-        hipLaunchKernelGGL(topk_pick_known_kernel, dim3(L), dim3(256), 0, s, d_layers, (TopkLayer*)t->d_tl,
-                           t->d_cnt_known);
-        TK_CHECK(hipGetLastError());
-    }
-    {
         Section sec(tm, "topk_count");
         hipLaunchKernelGGL(topk_count_kernel<true>, dim3((n_tiles + kSliceBatch - 1) / kSliceBatch), dim3(kThreads), 0,
-                           s, d_tiles, n_tiles, d_layers, (const TopkLayer*)t->d_tl, tinfo, cand, (uint2*)t->d_tilecnt);
+                           s, d_tiles, n_tiles, d_layers, (TopkLayer*)t->d_tl, (const uint32_t*)t->d_cnt_b, tinfo, cand,
+                           (uint2*)t->d_tilecnt);
         TK_CHECK(hipGetLastError());
     }
     {
@@ -2171,8 +2196,9 @@ hipError_t topk_compress_known(TopkScratch* t, const float* g, float* e, const D
         hipLaunchKernelGGL(topk_emit_kernel<true>, dim3((n_tiles + kSliceBatch - 1) / kSliceBatch), dim3(kThreads), 0, s, e,
                            d_layers, d_tiles, n_tiles, (const TopkLayer*)t->d_tl, tinfo, cand, cand_idx,
                            (const uint2*)t->d_tilecnt, runs,
-                           payload, x_in_e ? 1 : 0);
+                           t->d_cnt_a, t->d_cnt_b, payload, x_in_e ? 1 : 0);
         TK_CHECK(hipGetLastError());
+        t->counts_clean = true;
     }
     return hipSuccess;
 }
