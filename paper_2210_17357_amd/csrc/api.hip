@@ -850,14 +850,14 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
     const float* const g_after = x_out ? x_out : d_grads;
     const float* const e_after = x_out ? nullptr : d_ef;
     if (ntk) {
-        // (the per-layer sums of the quantization errors ride on the scan's launch)
+        // (the per-layer sums of the quantization errors ride on a launch of it)
         const QuantReduce qr{h->d_partials, d_err, P, qp.col, qp.nq};
-        HIPCHK(topk_select(&h->topk, g_after, e_after, nullptr, h->d_layers, L, ntk, h->tm, s, qp.nq ? &qr : nullptr));
+        HIPCHK(topk_resolve(&h->topk, g_after, e_after, nullptr, h->d_layers, h->d_tiles, L, ntk, tk_col, d_err, P, h->tm, s,
+                            qp.nq ? &qr : nullptr));
     } else if (qp.nq) {
         Section sec(h->tm, "reduce_partials");
         HIPCHK(launch_reduce_partials(h->d_partials, P, qp.col, qp.nq, h->d_layers, L, d_err, s));
     }
-    if (ntk) HIPCHK(topk_finalize(&h->topk, h->d_layers, h->d_tiles, L, ntk, tk_col, d_err, P, h->tm, s));
     if (nlr) {
         HIPCHK(lowrank_profile(&h->lowrank, d_grads, d_ef, h->d_layers, h->hl.data(), L, d_q0, h->cfg.r_max,
                                lr_rank, lr_col, nlr, d_err, P, lowrank_x(h), h->tm, s));

@@ -233,11 +233,7 @@ struct TopkScratch {
     void* d_tinfo_kept = nullptr;
     uint32_t* d_k = nullptr;          // [max_layers x kMaxTopk] requested k (0 = layer inactive)
     uint32_t* d_lo = nullptr;         // [max_layers] lowest coarse key collected as a candidate
-    // what a second collection reads and writes (noted by topk_select for the refinement kernel)
-    const float* rc_g = nullptr;
-    const float* rc_e = nullptr;
-    float* rc_ef_out = nullptr;
-    bool hist_clean = false;          // the exact histogram is all zero (the last scan of a call clears it)
+    bool hist_clean = false;          // the exact histogram is all zero (a kernel behind the search of every call clears it)
     int64_t* d_cand_base = nullptr;   // [max_layers] first candidate slot of every layer
     void* d_tilecnt = nullptr;        // per tile (above, equal) counts (compress)
     unsigned long long* d_runs = nullptr;   // ... and their sums over runs of tiles
@@ -280,16 +276,14 @@ hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevL
                       const DevLayer* h_layers, const Tile* d_tiles, int L, int n_tiles, int tile_elems,
                       const uint32_t* ks, int ntk, int slot, Timing* tm, hipStream_t s, int nk_many);
 // More than kMaxTopk densities: upload their columns, the largest density first, and k per (layer, density) from the
-// size table (8 k bytes).  What comes before topk_select does not need them: the host works them out while it runs.
+// size table (8 k bytes).  What comes before topk_resolve does not need them: the host works them out while it runs.
 hipError_t topk_densities(TopkScratch* t, const int32_t* cols, int nk, const int64_t* sizes, int P, int L, hipStream_t s);
 // main pass (exact coarse histogram + candidate collection) when no quantization candidate shares
 // the read; otherwise the quantization profile kernel does the same work
 hipError_t topk_collect(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers,
                         const Tile* d_tiles, int n_tiles, hipStream_t s, Section* sec, float* x_out = nullptr);
-// exact threshold bins from the histogram; layers whose predicted bound was too high are
-// collected again with the exact one
 // quant (may be null): the quantization profile's per-tile partial sums, reduced per layer by extra
-// workgroups of the scan's launch instead of a kernel of their own
+// workgroups of a launch that depends on the main pass only, instead of a kernel of their own
 struct QuantReduce {
     const double* partials;
     double* errors;
@@ -297,11 +291,12 @@ struct QuantReduce {
     const int* cols;
     int ncols;
 };
-hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers, int L,
-                       int ntk, Timing* tm, hipStream_t s, const QuantReduce* quant);
-// refinement on the candidates: exact thresholds; writes the dropped energy to errors (if not null)
-hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d_tiles, int L, int ntk,
-                         const int* col, double* d_errors, int stride, Timing* tm, hipStream_t s);
+// Behind the main pass: threshold bins from the histogram (layers whose predicted bound was too high are
+// collected again with the exact one), then the refinement on the candidates.  Profile: the dropped energy to d_errors.
+// Compression (d_errors null, one density; ef_out holds x): the boundary sub-bin and its counts, which the exact threshold follows from.
+hipError_t topk_resolve(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers,
+                        const Tile* d_tiles, int L, int ntk, const int* col, double* d_errors, int stride, Timing* tm,
+                        hipStream_t s, const QuantReduce* quant);
 // layer_tiles: tiles of the largest layer
 hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLayer* d_layers,
                          const DevLayer* h_layers, const Tile* d_tiles, int L, int n_tiles, int tile_elems,

@@ -37,19 +37,14 @@
 
 namespace lgreco {
 
-struct TopkList {
-    uint32_t bin, count;
-};
 struct TopkSel {
-    uint32_t k, tbin, need, list;   // need: entries to take from the threshold bin (1..count)
+    uint32_t k, tbin, need, list;   // need: entries to take from the threshold bin; list: its number among the layer's
+                                    // distinct threshold bins
     uint32_t bin_a, need_a;         // refinement level A (bits 18..9)
     uint32_t thr, ties_keep;        // exact threshold pattern; equal entries kept (compress)
 };
 struct TopkLayer {
     int64_t cand_base;              // first slot of this layer's region in the candidate buffer
-    uint32_t nlists, min_tbin;
-    uint32_t recollect, pad;        // 1: the predicted bound was too high, collect again
-    TopkList lists[kMaxTopk];
     TopkSel sel[kMaxTopk];
 };
 // The same for a profile of more than kMaxTopk densities.  The requested k do not increase with j, so
@@ -316,10 +311,10 @@ struct CollectParams {
 // TEAM (the second collection, made by the refinement kernel's workgroup for its own tiles): the
 // workgroup is several teams of kThreads threads, each with a tile of its own (or none: `active`
 // false; the teams still meet at the barrier) and its own s_red; the caller has checked that the
-// layer takes part.
+// layer takes part and gives the bound, team_lo.
 template <bool HIST, bool EMIT, bool KNOWN = false, bool TEAM = false>
 __device__ __forceinline__ void collect_tile(const CollectParams& p, const int tile, uint32_t* s_hist, double* s_red,
-                                             const bool active = true) {
+                                             const bool active = true, const uint32_t team_lo = 0) {
     static_assert(!(HIST && KNOWN), "the coarse histogram is not built when the thresholds are known");
     static_assert(!TEAM || (!HIST && !KNOWN), "teams collect, nothing else");
     if (TEAM && !active) {             // (uniform over the team)
@@ -337,7 +332,7 @@ __device__ __forceinline__ void collect_tile(const CollectParams& p, const int t
         if (!TEAM) {
             if (p.ks[(size_t)t.layer * kMaxTopk] == 0) return;
         }
-        bound = bound_of_key(p.lo[t.layer]);
+        bound = bound_of_key(TEAM ? team_lo : p.lo[t.layer]);
     }
     const float* gp = p.g + L.offset + t.pos;
     const float* ep = p.e ? p.e + L.offset + t.pos : nullptr;
@@ -597,10 +592,8 @@ __global__ __launch_bounds__(kThreads) void topk_collect_kernel(CollectParams p)
     collect_tile<HIST, EMIT>(p, (int)blockIdx.x, s_hist, s_red);
 }
 
-// One workgroup per layer: threshold bin and in-bin rank for every requested k; threshold-bin
-// lists; check of the predicted bound.
-// Workgroups past the first n_layers (when the call also profiles quantization) sum that family's
-// tile partials per layer instead: the two jobs depend on the main pass only and share a launch.
+// The sums of the quantization profile's tile partials per layer, when the call profiles both families: further
+// workgroups of the launch that resolves the threshold bins make them, which depends on the main pass only, too.
 struct ScanReduce {
     const double* partials;     // null: no such workgroups
     double* errors;
@@ -608,78 +601,6 @@ struct ScanReduce {
     int32_t stride;
     ReduceCols cols;
 };
-__global__ __launch_bounds__(256) void topk_scan_kernel(uint32_t* __restrict__ hist,
-                                                        const uint32_t* __restrict__ ks, int ntk,
-                                                        const int64_t* __restrict__ cand_base,
-                                                        uint32_t* lo, TopkLayer* __restrict__ tl,
-                                                        int n_layers, ScanReduce red) {
-    __shared__ double s_tree[kMaxQuant][256];            // the reduction's
-    if ((int)blockIdx.x >= n_layers) {
-        reduce_partials_block(red.partials, red.stride, red.cols, red.layers, red.errors, (int)blockIdx.x - n_layers, s_tree);
-        return;
-    }
-    constexpr int kPer = kHistBins / 256;
-    __shared__ uint32_t s_tot[4];
-    __shared__ uint32_t s_bin[kMaxTopk], s_higher[kMaxTopk], s_count[kMaxTopk];
-    const int l = blockIdx.x, tid = threadIdx.x;
-    TopkLayer& T = tl[l];
-    // thread t's 16 bins go straight to its registers, and the next call's main pass starts from zero
-    uint4* const h4 = reinterpret_cast<uint4*>(hist + (size_t)l * kHistBins) + tid * (kPer / 4);
-    uint32_t c[kPer], kk[kMaxTopk];
-#pragma unroll
-    for (int q = 0; q < kPer / 4; ++q) {
-        const uint4 v = h4[q];
-        c[4 * q] = v.x; c[4 * q + 1] = v.y; c[4 * q + 2] = v.z; c[4 * q + 3] = v.w;
-    }
-#pragma unroll
-    for (int j = 0; j < kMaxTopk; ++j) kk[j] = j < ntk ? ks[(size_t)l * kMaxTopk + j] : 0u;
-    const uint32_t used = lo[l];
-    const int64_t base = cand_base[l];
-#pragma unroll
-    for (int q = 0; q < kPer / 4; ++q) h4[q] = make_uint4(0u, 0u, 0u, 0u);
-    if (kk[0] == 0) {
-        if (tid == 0) { T.nlists = 0; T.min_tbin = 0; T.recollect = 0; }
-        if (tid < kMaxTopk) T.sel[tid].k = 0;
-        return;
-    }
-    if (tid < kMaxTopk) s_bin[tid] = s_higher[tid] = s_count[tid] = 0u;
-    // one suffix scan of the histogram serves every requested k
-    uint32_t mine;
-    const uint32_t above = entries_above<256, kPer>(c, s_tot, &mine);
-#pragma unroll
-    for (int j = 0; j < kMaxTopk; ++j)
-        if (above < kk[j] && above + mine >= kk[j])
-            find_in_own<kPer>(c, above, kk[j], &s_bin[j], &s_higher[j], &s_count[j]);
-    __syncthreads();
-    if (tid >= kMaxTopk) return;
-    // lane j: the record of the j-th k.  The k do not increase, so the bins do not decrease and a bin
-    // that is not the one before it opens a list.
-    const uint32_t k = tid < ntk ? ks[(size_t)l * kMaxTopk + tid] : 0u;
-    const bool head = tid < ntk && (tid == 0 || s_bin[tid - 1] != s_bin[tid]);
-    const unsigned long long m = __ballot(head);
-    const uint32_t nl = (uint32_t)__popcll(m), list = (uint32_t)__popcll(m & ((2ull << tid) - 1ull)) - 1u;
-    TopkSel S{};
-    if (tid < ntk) {
-        S.k = k;
-        S.tbin = s_bin[tid];
-        S.need = k - s_higher[tid];
-        S.list = list;
-    }
-    T.sel[tid] = S;
-    if (head) T.lists[list] = TopkList{s_bin[tid], s_count[tid]};
-    if ((uint32_t)tid >= nl) T.lists[tid] = TopkList{0u, 0u};
-    if (tid == 0) {
-        const uint32_t mn = s_bin[0];                    // of the largest k
-        T.nlists = nl;
-        T.min_tbin = mn;
-        T.cand_base = base;
-        // every element at or above the lowest threshold bin must be among the candidates
-        T.recollect = used > mn ? 1u : 0u;
-        T.pad = 0;
-        if (used > mn) lo[l] = mn;
-    }
-}
-
 // The bin that holds the entry of rank `need` from the top, and the entries in higher bins, by one
 // thread alone (after block_suffix; need <= scan[0]).
 __device__ __forceinline__ void thread_find(const uint32_t* hist, int nbins, uint32_t need, const uint32_t* scan,
@@ -755,6 +676,9 @@ struct RefineParams {
     const uint32_t* cand;
     const RefWork* work;              // [n_work]
     const int2* work_range;           // [L] the layer's workgroups [x, y)
+    int32_t n_work;
+    uint32_t* hist;                   // [L x kHistBins] exact coarse histogram
+    ScanReduce red;
     const double* base_part;          // [n_tiles]
     double* below_part;               // [n_work x kMaxTopk] energy of candidates below each threshold bin
     // per-workgroup partial histograms (plain stores, summed by the pick kernel)
@@ -769,13 +693,12 @@ struct RefineParams {
     // more than kMaxTopk densities: the layers' records, and per (work item, list of this pass), `room` lists
     // in a row, the partial histogram and the energy below the list's bin
     const TopkMany* many;
-    const int64_t* cand_base;
+    const int64_t* cand_base;         // [L]
     const int32_t* cols;              // [nk] column of every density
     unsigned long long* cell_many;
     double* below_many;
     int32_t list0, room;              // the lists of this pass: [list0, list0 + room) of every layer
-    // the second collection of a layer whose predicted bound was too high (flagged by the scan):
-    // every workgroup of the first refinement kernel makes it for its own tiles before it looks at
+    // the second collection of a layer whose predicted bound was too high (rare): every workgroup of the first refinement kernel makes it for its own tiles before it looks at
     // their candidates (rc.ef_out not null: the compression's form, which also writes x)
     CollectParams rc;
 };
@@ -784,13 +707,13 @@ struct RefineParams {
 // teams of kThreads threads, a tile each per round.
 static_assert(kRefThreads % kThreads == 0, "whole teams");
 template <bool EMIT>
-__device__ __forceinline__ void collect_again(const CollectParams& rc, int t0, int t1) {
+__device__ __forceinline__ void collect_again(const CollectParams& rc, int t0, int t1, uint32_t lo) {
     constexpr int kTeams = kRefThreads / kThreads;
     __shared__ double s_team_red[kTeams][kThreads / 64];
     const int team = threadIdx.x / kThreads;
     for (int first = t0; first < t1; first += kTeams) {
         const int tile = first + team;
-        collect_tile<false, EMIT, false, true>(rc, min(tile, t1 - 1), nullptr, s_team_red[team], tile < t1);
+        collect_tile<false, EMIT, false, true>(rc, min(tile, t1 - 1), nullptr, s_team_red[team], tile < t1, lo);
         __syncthreads();                                // s_team_red is reused; the tile's records are written
     }
 }
@@ -879,7 +802,9 @@ __device__ __forceinline__ void below_chain(float (&b)[kMaxTopk], const uint32_t
 #undef LG_BELOW_ASM
 #undef LG_BELOW_STEP
 
-// Refinement level A over the candidates of a run of tiles.  NTK > 0 (profile, NTK = number of
+// Threshold bins, and refinement level A over the candidates of a run of tiles.  Every workgroup finds its layer's
+// threshold bins for itself in the exact histogram (16 KB from the caches; a kernel of its own for them, a workgroup
+// per layer, took 5-6 us and its launch), the layer's first leaves them in the record.  NTK > 0 (profile, NTK = number of
 // requested k): per list (distinct threshold bin) a histogram of bits 18..9 whose cells pack count
 // and integer energy into one 64-bit LDS atomic, and per requested k the energy of the candidates
 // below its threshold bin (fp32 per lane - a lane sees some tens of candidates - fp64 from the
@@ -892,41 +817,88 @@ __host__ __device__ constexpr size_t refine_a_lds(int ntk, bool energy) {
 template <int NTK>
 __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_a_kernel(RefineParams p) {
     constexpr bool ENERGY = NTK > 0;
+    constexpr int kN = ENERGY ? NTK : 1, kPer = kHistBins / kRefThreads;
     extern __shared__ unsigned char refine_smem[];
     __shared__ double s_red[kRefThreads / 64][kMaxTopk];
+    __shared__ uint32_t s_tot[kRefThreads / 64], s_bin[kMaxTopk], s_higher[kMaxTopk];
+    const int tid = threadIdx.x;
+    if (ENERGY && (int)blockIdx.x >= p.n_work) {
+        if (tid < 256)                   // (the other wavefronts end here: a barrier is for those that are left)
+            reduce_partials_block(p.red.partials, p.red.stride, p.red.cols, p.red.layers, p.red.errors,
+                                  (int)blockIdx.x - p.n_work, reinterpret_cast<double(*)[256]>(refine_smem));
+        return;
+    }
     const RefWork w = p.work[blockIdx.x];
     const int l = w.layer;
-    const TopkLayer& T = p.tl[l];
-    if (T.recollect) {                  // workgroup-uniform; rare: the predicted bound was too high
-        if (ENERGY) collect_again<false>(p.rc, w.t0, w.t1);
-        else collect_again<true>(p.rc, w.t0, w.t1);
-    }
-    const int nlists = (int)T.nlists;
-    const int tid = threadIdx.x, ntk = p.ntk;
+    static_assert(kPer == 4, "a thread's bins are one 128-bit load");
+    const uint4 h = reinterpret_cast<const uint4*>(p.hist + (size_t)l * kHistBins)[tid];
+    uint32_t kk[kN];
+#pragma unroll
+    for (int j = 0; j < kN; ++j) kk[j] = p.rc.ks[(size_t)l * kMaxTopk + j];
+    const uint32_t used = p.rc.lo[l];
+    const int64_t cand_base = p.cand_base[l];
+    const bool first_item = (int)blockIdx.x == p.work_range[l].x;
     unsigned long long* const s_cell = reinterpret_cast<unsigned long long*>(refine_smem);   // ENERGY
     uint32_t* const s_cnt = reinterpret_cast<uint32_t*>(refine_smem);                        // !ENERGY
-    uint8_t* const s_tab = refine_smem + (size_t)ntk * kBinsA * (ENERGY ? 8 : 4);
-    for (int i = tid; i < nlists * kBinsA; i += kRefThreads) {
-        if (ENERGY) s_cell[i] = 0; else s_cnt[i] = 0;
+    uint8_t* const s_tab = refine_smem + (size_t)kN * kBinsA * (ENERGY ? 8 : 4);
+#pragma unroll
+    for (int j = 0; j < kN; ++j) {
+        if (ENERGY) s_cell[j * kBinsA + tid] = 0; else s_cnt[tid] = 0;
     }
-    // workgroup-uniform: threshold bin of every k and the distinct threshold bins ("lists")
-    uint32_t tb[kMaxTopk], lb[kMaxTopk];
+    if (tid < kMaxTopk) s_bin[tid] = s_higher[tid] = 0u;
+    // threshold bin of every k: one suffix scan of the histogram serves all of them
+    {
+        const uint32_t c[kPer] = {h.x, h.y, h.z, h.w};
+        uint32_t mine;
+        const uint32_t above = entries_above<kRefThreads, kPer>(c, s_tot, &mine);
+#pragma unroll
+        for (int j = 0; j < kN; ++j)
+            if (above < kk[j] && above + mine >= kk[j]) {
+                uint32_t count;
+                find_in_own<kPer>(c, above, kk[j], &s_bin[j], &s_higher[j], &count);
+            }
+    }
+    __syncthreads();
+    // workgroup-uniform.  The k do not increase, so the bins do not decrease and a bin that is not the one before
+    // it opens a list.
+    uint32_t tb[kMaxTopk], list[kMaxTopk], nlists = 0;
 #pragma unroll
     for (int j = 0; j < kMaxTopk; ++j) {
-        tb[j] = __builtin_amdgcn_readfirstlane(j < ntk ? T.sel[j].tbin : 0u);
-        lb[j] = j < nlists ? T.lists[j].bin : 0xFFFFFFFFu;
+        tb[j] = j < kN ? __builtin_amdgcn_readfirstlane(s_bin[j]) : 0u;
+        if (j < kN && (j == 0 || tb[j] != tb[j - 1])) ++nlists;
+        list[j] = nlists - 1u;
+    }
+    if (first_item && tid < kMaxTopk) {
+        TopkSel S{};
+#pragma unroll
+        for (int j = 0; j < kN; ++j)
+            if (tid == j) {
+                S.k = kk[j];
+                S.list = list[j];
+            }
+        if (tid < kN) {
+            S.tbin = s_bin[tid];
+            S.need = S.k - s_higher[tid];
+        }
+        p.tl[l].sel[tid] = S;
+        if (tid == 0) p.tl[l].cand_base = cand_base;
+    }
+    // every element at or above the lowest threshold bin must be among the candidates
+    if (used > tb[0]) {
+        if (ENERGY) collect_again<false>(p.rc, w.t0, w.t1, tb[0]);
+        else collect_again<true>(p.rc, w.t0, w.t1, tb[0]);
     }
     for (uint32_t key = tid; key < (uint32_t)kHistBins; key += kRefThreads) {
-        uint32_t hit = 0;               // 1 + index of the list whose bin the key is
+        uint32_t hit = 0;               // 1 + number of the list whose bin the key is
 #pragma unroll
-        for (int j = 0; j < kMaxTopk; ++j) hit = key == lb[j] ? (uint32_t)(j + 1) : hit;
+        for (int j = 0; j < kN; ++j) hit = key == tb[j] ? list[j] + 1u : hit;
         s_tab[key] = (uint8_t)hit;
     }
     __syncthreads();
     float below[kMaxTopk];
 #pragma unroll
     for (int j = 0; j < kMaxTopk; ++j) below[j] = 0.0f;
-    for_each_candidate(p, T.cand_base, w.t0, w.t1, [&](uint32_t pat) {
+    for_each_candidate(p, cand_base, w.t0, w.t1, [&](uint32_t pat) {
         const uint32_t key = pat >> kHistShift;
         const uint32_t hit = s_tab[key];
         if constexpr (ENERGY) below_chain<NTK>(below, tb, key, __uint_as_float(pat));
@@ -939,24 +911,24 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_a_kernel(RefinePar
     if (ENERGY) {
 #pragma unroll
         for (int j = 0; j < kMaxTopk; ++j) {
-            if (j < ntk) {
+            if (j < kN) {
                 const double s = wave_sum((double)below[j]);
                 if ((tid & 63) == 0) s_red[tid >> 6][j] = s;
             }
         }
     }
     __syncthreads();
-    if (ENERGY && tid < ntk) {
+    if (ENERGY && tid < kN) {
         double s = 0.0;
         for (int wv = 0; wv < kRefThreads / 64; ++wv) s += s_red[wv][tid];
         p.below_part[(size_t)blockIdx.x * kMaxTopk + tid] = s;
     }
     if (ENERGY) {
         unsigned long long* const gc = p.cell_a + (size_t)blockIdx.x * kMaxTopk * kBinsA;
-        for (int i = tid; i < nlists * kBinsA; i += kRefThreads) gc[i] = s_cell[i];
+        for (int i = tid; i < (int)nlists * kBinsA; i += kRefThreads) gc[i] = s_cell[i];
     } else {
         static_assert(kBinsA == kRefThreads, "a thread per cell");
-        const uint32_t c = nlists ? s_cnt[tid] : 0u;
+        const uint32_t c = s_cnt[tid];
         if (c) atomicAdd(&p.cnt_a[(size_t)l * kBinsA + tid], c);
     }
 }
@@ -1046,10 +1018,13 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
     __shared__ uint32_t s_exact[3];     // [0] resolve the sub-bin exactly, [1] its prefix (pattern >> 9), [2] entries kept in it
     const int l = blockIdx.x / p.ntk, j = blockIdx.x % p.ntk;      // the grid holds L x ntk workgroups
     TopkLayer& T = p.tl[l];
-    if (T.sel[j].k == 0) return;
+    if (p.rc.ks[(size_t)l * kMaxTopk + j] == 0) return;
     const TopkSel S = T.sel[j];
     const int2 wr = p.work_range[l];
     const int tid = threadIdx.x, t = tid & 255, grp = tid >> 8;
+    if (j == 0)                          // the next call's main pass starts from zero
+        for (int b = tid; b < kHistBins / 4; b += kPickThreads)
+            reinterpret_cast<uint4*>(p.hist + (size_t)l * kHistBins)[b] = make_uint4(0u, 0u, 0u, 0u);
     for (int b = tid; b < kBinsA; b += kPickThreads) {
         s_hist[b] = 0;
         s_en[b] = 0;
@@ -1176,7 +1151,7 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_many_kernel(Refine
     if (T.recollect) {                  // workgroup-uniform
         if (split) return;
         splits = 1;
-        if (p.list0 == 0) collect_again<false>(p.rc, w.t0, w.t1);
+        if (p.list0 == 0) collect_again<false>(p.rc, w.t0, w.t1, p.rc.lo[w.layer]);
     }
     unsigned long long* const s_cell = reinterpret_cast<unsigned long long*>(refine_smem);
     uint8_t* const s_tab = refine_smem + (size_t)kManyChunk * kBinsA * 8;
@@ -1346,9 +1321,13 @@ __global__ __launch_bounds__(kRefThreads) void topk_refine_b_kernel(RefineParams
     }
     __syncthreads();
     const uint32_t prefix = (tbin << 10) | s_res[0];
-    if (tid == 0 && (int)blockIdx.x == p.work_range[w.layer].x) {
-        T.sel[0].bin_a = s_res[0];
-        T.sel[0].need_a = need - s_res[1];
+    if ((int)blockIdx.x == p.work_range[w.layer].x) {
+        static_assert(kHistBins == 4 * kRefThreads, "a 128-bit store a thread");
+        reinterpret_cast<uint4*>(p.hist + (size_t)w.layer * kHistBins)[tid] = make_uint4(0u, 0u, 0u, 0u);   // for the next call
+        if (tid == 0) {
+            T.sel[0].bin_a = s_res[0];
+            T.sel[0].need_a = need - s_res[1];
+        }
     }
     for_each_candidate(p, cand_base, w.t0, w.t1, [&](uint32_t pat) {
         if ((pat >> 9) == prefix) atomicAdd(&s_cnt[pat & (kBinsB - 1)], 1u);
@@ -1369,7 +1348,7 @@ __global__ __launch_bounds__(kRefThreads) void topk_refine_b_kernel(RefineParams
 constexpr int kSliceBatch = 4;
 
 // per (tile, wavefront): entries above the threshold, entries equal to it (from its candidates)
-// KNOWN: the layer records say which layers take part and which selection record holds the threshold.
+// ks: the k asked for; KNOWN: the layer records say which layers take part and which selection record counts.
 // The exact threshold and the number of entries equal to it that are kept come from the layer's counts inside the
 // boundary sub-bin: wavefront q of every workgroup finds them for the batch's tile q, and the one with a layer's first
 // tile leaves them in its record.  (A kernel of its own in front of this one, a workgroup per layer, took 4-5 us and
@@ -1378,7 +1357,8 @@ static_assert(kSliceBatch == kThreads / 64, "a wavefront per tile of a batch");
 template <bool KNOWN>
 __global__ __launch_bounds__(kThreads) void topk_count_kernel(const Tile* __restrict__ tiles, int n_tiles,
                                                                const DevLayer* __restrict__ layers,
-                                                               TopkLayer* tl, const uint32_t* __restrict__ cnt_b,
+                                                               const uint32_t* __restrict__ ks, TopkLayer* tl,
+                                                               const uint32_t* __restrict__ cnt_b,
                                                                const TopkTileInfo* __restrict__ tinfo,
                                                                const uint32_t* __restrict__ cand,
                                                                uint2* __restrict__ wavecnt) {
@@ -1418,7 +1398,7 @@ __global__ __launch_bounds__(kThreads) void topk_count_kernel(const Tile* __rest
 #pragma unroll
     for (int q = 0; q < kSliceBatch; ++q) {
         const TopkLayer& T = tl[layer[q]];
-        if (!KNOWN) k[q] = T.sel[0].k;
+        if (!KNOWN) k[q] = ks[(size_t)layer[q] * kMaxTopk];
         base[q] = T.cand_base;
     }
     {
@@ -1431,7 +1411,7 @@ __global__ __launch_bounds__(kThreads) void topk_count_kernel(const Tile* __rest
         }
         TopkSel& S = tl[own.layer].sel[own_slot];
         const uint32_t need_a = S.need_a, prefix = (S.tbin << 10) | S.bin_a;
-        if (!KNOWN) own_on = own_on && S.k != 0;
+        if (!KNOWN) own_on = own_on && ks[(size_t)own.layer * kMaxTopk] != 0;
         static_assert(kBinsB == 64 * 8, "8 cells a lane");
         const uint32_t c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
         uint32_t bin, higher;
@@ -1450,7 +1430,7 @@ __global__ __launch_bounds__(kThreads) void topk_count_kernel(const Tile* __rest
     for (int q = 0; q < kSliceBatch; ++q) thr[q] = s_thr[q];
 #pragma unroll
     for (int q = 0; q < kSliceBatch; ++q) {
-        // a layer that is not compressed with Top-K has k = 0 in its record (and no candidates)
+        // a layer that is not compressed with Top-K has k = 0 (and neither candidates nor a record)
         active[q] = first + q < n_tiles && k[q] != 0;
         n[q] = active[q] ? n[q] : 0u;
         items[q] = active[q] ? cand + base[q] + pos[q] + start[q] : cand;
@@ -1687,8 +1667,8 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
     t->max_layers = max_layers;
     t->max_tiles = max_tiles;
     TK_CHECK(hipMalloc(&t->d_hist, sizeof(uint32_t) * (size_t)max_layers * kHistBins));
-    // Between calls the exact histogram is all zero: cleared here once, and by the last scan of every
-    // call for the layers that call counted.  hist_clean is false only after a call that failed midway.
+    // Between calls the exact histogram is all zero: cleared here once, and by the last kernel that
+    // follows the search of every call for the layers that call counted.  hist_clean is false only after a call that failed midway.
     TK_CHECK(hipMemset(t->d_hist, 0, sizeof(uint32_t) * (size_t)max_layers * kHistBins));
     t->hist_clean = true;
     TK_CHECK(hipMalloc(&t->d_tl, sizeof(TopkLayer) * (size_t)max_layers));
@@ -1945,40 +1925,6 @@ hipError_t topk_collect(TopkScratch* t, const float* g, const float* e, float* e
     return hipGetLastError();
 }
 
-// exact threshold bins; layers whose predicted bound was too high are collected again
-hipError_t topk_select(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers, int L,
-                       int ntk, Timing* tm, hipStream_t s, const QuantReduce* quant) {
-    {
-        Section sec(tm, "topk_scan");
-        ScanReduce red{};
-        if (quant) {
-            red.partials = quant->partials;
-            red.errors = quant->errors;
-            red.layers = d_layers;
-            red.stride = quant->stride;
-            red.cols.n = std::min(quant->ncols, (int)kMaxQuant);
-            for (int i = 0; i < red.cols.n; ++i) red.cols.col[i] = quant->cols[i];
-        }
-        if (t->nk_many)
-            hipLaunchKernelGGL(topk_scan_many_kernel, dim3(quant ? 2 * L : L), dim3(256), 0, s, t->d_hist,
-                               (const uint32_t*)t->d_many_in + t->nk_many, t->nk_many, t->d_lo, (TopkMany*)t->d_many, L, red);
-        else
-            hipLaunchKernelGGL(topk_scan_kernel, dim3(quant ? 2 * L : L), dim3(256), 0, s, t->d_hist,
-                               (const uint32_t*)t->d_k, ntk, (const int64_t*)t->d_cand_base, t->d_lo, (TopkLayer*)t->d_tl,
-                               L, red);
-        TK_CHECK(hipGetLastError());
-        t->hist_clean = true;
-    }
-    // Layers whose predicted bound was too high (flagged by the scan; none in the usual call) are
-    // collected a second time with the exact bound, by the first refinement kernel's workgroups,
-    // each for its own tiles: what that collection reads and writes is noted here.  It reads
-    // x = g + e again; in compress e already holds x, so g is not added.
-    t->rc_g = ef_out ? ef_out : g;
-    t->rc_e = ef_out ? nullptr : e;
-    t->rc_ef_out = ef_out;
-    return hipSuccess;
-}
-
 // The counts of a compression are all zero, for it to add to; the emit kernel's launch makes them so again.
 static hipError_t take_counts(TopkScratch* t, hipStream_t s) {
     if (!t->counts_clean) {
@@ -1991,10 +1937,29 @@ static hipError_t take_counts(TopkScratch* t, hipStream_t s) {
     return hipSuccess;
 }
 
-// d_errors null: the compression's refinement, one density
-hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d_tiles, int L, int ntk,
-                         const int* col, double* d_errors, int stride, Timing* tm, hipStream_t s) {
-    if (t->n_work <= 0) return hipSuccess;
+hipError_t topk_resolve(TopkScratch* t, const float* g, const float* e, float* ef_out, const DevLayer* d_layers,
+                        const Tile* d_tiles, int L, int ntk, const int* col, double* d_errors, int stride, Timing* tm,
+                        hipStream_t s, const QuantReduce* quant) {
+    if (t->n_work <= 0) {
+        t->hist_clean = true;
+        return hipSuccess;
+    }
+    ScanReduce red{};
+    if (quant) {
+        red.partials = quant->partials;
+        red.errors = quant->errors;
+        red.layers = d_layers;
+        red.stride = quant->stride;
+        red.cols.n = std::min(quant->ncols, (int)kMaxQuant);
+        for (int i = 0; i < red.cols.n; ++i) red.cols.col[i] = quant->cols[i];
+    }
+    if (t->nk_many) {
+        Section sec(tm, "topk_scan");
+        hipLaunchKernelGGL(topk_scan_many_kernel, dim3(quant ? 2 * L : L), dim3(256), 0, s, t->d_hist,
+                           (const uint32_t*)t->d_many_in + t->nk_many, t->nk_many, t->d_lo, (TopkMany*)t->d_many, L, red);
+        TK_CHECK(hipGetLastError());
+        t->hist_clean = true;
+    }
     // the pick kernel's workgroups: small ones, so that all of them run at once, unless a layer has
     // so many partial histograms to sum that its workgroup alone would outlast the rest
     const bool wide_pick = t->max_items > 64;
@@ -2006,6 +1971,10 @@ hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d
     p.cand = t->d_cand;
     p.work = (const RefWork*)t->d_work;
     p.work_range = (const int2*)t->d_work_range;
+    p.n_work = t->n_work;
+    p.hist = t->d_hist;
+    p.red = red;
+    p.cand_base = t->d_cand_base;
     p.base_part = t->d_base_part;
     p.below_part = t->d_below_part;
     p.cell_a = reinterpret_cast<unsigned long long*>(t->d_ref);
@@ -2015,13 +1984,15 @@ hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d
     p.stride = stride;
     p.ntk = ntk;
     for (int j = 0; j < ntk; ++j) p.col[j] = col ? col[j] : 0;
-    p.rc = collect_params(t, t->rc_g, t->rc_e, d_layers, d_tiles);
-    p.rc.ef_out = t->rc_ef_out;
-    p.rc.record_idx = (!t->rc_ef_out && t->cand_has_idx) ? 1 : 0;
+    // Layers whose predicted bound was too high (none in the usual call) are collected a second time with the exact
+    // bound, by the first refinement kernel's workgroups, each for its own tiles.  That reads x = g + e again; in
+    // a compression e already holds x, so g is not added.
+    p.rc = collect_params(t, ef_out ? ef_out : g, ef_out ? nullptr : e, d_layers, d_tiles);
+    p.rc.ef_out = ef_out;
+    p.rc.record_idx = (!ef_out && t->cand_has_idx) ? 1 : 0;
     Section sec(tm, "topk_refine");
     if (t->nk_many) {
         p.many = (const TopkMany*)t->d_many;
-        p.cand_base = t->d_cand_base;
         p.cols = (const int32_t*)t->d_many_in;
         p.room = (int)std::min<size_t>((size_t)t->nk_many, many_capacity(t) / t->n_work);
         p.cell_many = reinterpret_cast<unsigned long long*>(t->d_ref);
@@ -2044,16 +2015,17 @@ hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d
         return hipSuccess;
     }
     if (d_errors) {       // profile: level A gives the dropped energy, no exact threshold is needed
-        const size_t lds = refine_a_lds(ntk, true);
+        const size_t lds = std::max(refine_a_lds(ntk, true), quant ? sizeof(double) * kMaxQuant * 256 : 0);
         static bool configured[kMaxTopk + 1] = {};   // the dynamic LDS limit is raised once per variant
 #define LG_REFINE_A(N)                                                                                   \
     case N:                                                                                              \
         if (!configured[N]) {                                                                            \
             TK_CHECK(hipFuncSetAttribute((const void*)topk_refine_a_kernel<N>,                           \
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));         \
+                                         hipFuncAttributeMaxDynamicSharedMemorySize,                      \
+                                         (int)refine_a_lds(kMaxTopk, true)));                            \
             configured[N] = true;                                                                        \
         }                                                                                                \
-        hipLaunchKernelGGL(topk_refine_a_kernel<N>, dim3(t->n_work), dim3(kRefThreads), lds, s, p);      \
+        hipLaunchKernelGGL(topk_refine_a_kernel<N>, dim3(t->n_work + (quant ? L : 0)), dim3(kRefThreads), lds, s, p); \
         break;
         switch (ntk) {
             LG_REFINE_A(1) LG_REFINE_A(2) LG_REFINE_A(3) LG_REFINE_A(4)
@@ -2064,13 +2036,17 @@ hipError_t topk_finalize(TopkScratch* t, const DevLayer* d_layers, const Tile* d
         TK_CHECK(hipGetLastError());
         if (wide_pick) hipLaunchKernelGGL((topk_pick_a_kernel<512>), dim3(L * ntk), dim3(512), 0, s, p);
         else hipLaunchKernelGGL((topk_pick_a_kernel<256>), dim3(L * ntk), dim3(256), 0, s, p);
-        return hipGetLastError();
+        TK_CHECK(hipGetLastError());
+        t->hist_clean = true;
+        return hipSuccess;
     }
     if (ntk != 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(topk_refine_a_kernel<0>, dim3(t->n_work), dim3(kRefThreads), refine_a_lds(ntk, false), s, p);
     TK_CHECK(hipGetLastError());
     hipLaunchKernelGGL(topk_refine_b_kernel, dim3(t->n_work), dim3(kRefThreads), 0, s, p);
-    return hipGetLastError();
+    TK_CHECK(hipGetLastError());
+    t->hist_clean = true;
+    return hipSuccess;
 }
 
 // Sums over runs of tiles for the emission, where some layer has so many tiles that every workgroup's own sum costs
@@ -2099,13 +2075,12 @@ hipError_t topk_compress(TopkScratch* t, const float* g, float* e, const DevLaye
         Section sec(tm, "topk_collect", true);
         TK_CHECK(topk_collect(t, g, e_in, e, d_layers, d_tiles, n_tiles, s, &sec));
     }
-    TK_CHECK(topk_select(t, g, e_in, e, d_layers, L, 1, tm, s, nullptr));
     TK_CHECK(take_counts(t, s));
-    TK_CHECK(topk_finalize(t, d_layers, d_tiles, L, 1, nullptr, nullptr, 0, tm, s));
+    TK_CHECK(topk_resolve(t, g, e_in, e, d_layers, d_tiles, L, 1, nullptr, nullptr, 0, tm, s, nullptr));
     {
         Section sec(tm, "topk_count");
         hipLaunchKernelGGL(topk_count_kernel<false>, dim3((n_tiles + kSliceBatch - 1) / kSliceBatch), dim3(kThreads), 0,
-                           s, d_tiles, n_tiles, d_layers, (TopkLayer*)t->d_tl, (const uint32_t*)t->d_cnt_b,
+                           s, d_tiles, n_tiles, d_layers, (const uint32_t*)t->d_k, (TopkLayer*)t->d_tl, (const uint32_t*)t->d_cnt_b,
                            (const TopkTileInfo*)t->d_tinfo, (const uint32_t*)t->d_cand, (uint2*)t->d_tilecnt);
         TK_CHECK(hipGetLastError());
     }
@@ -2185,7 +2160,8 @@ hipError_t topk_compress_known(TopkScratch* t, const float* g, float* e, const D
     {
         Section sec(tm, "topk_count");
         hipLaunchKernelGGL(topk_count_kernel<true>, dim3((n_tiles + kSliceBatch - 1) / kSliceBatch), dim3(kThreads), 0,
-                           s, d_tiles, n_tiles, d_layers, (TopkLayer*)t->d_tl, (const uint32_t*)t->d_cnt_b, tinfo, cand,
+                           s, d_tiles, n_tiles, d_layers, (const uint32_t*)nullptr, (TopkLayer*)t->d_tl, (const uint32_t*)t->d_cnt_b,
+                           tinfo, cand,
                            (uint2*)t->d_tilecnt);
         TK_CHECK(hipGetLastError());
     }
