@@ -274,7 +274,7 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(const double* __re
                                                                int stride, ReduceCols cols,
                                                                const DevLayer* __restrict__ layers,
                                                                double* __restrict__ errors) {
-    __shared__ double s[kMaxQuant][256];
+    __shared__ double s[kMaxQuant][4];
     reduce_partials_block(partials, stride, cols, layers, errors, (int)blockIdx.x, s);
 }
 

@@ -12,13 +12,13 @@ struct ReduceCols {
     int32_t col[kMaxQuant];
 };
 
-// errors[l][c] = sum of the layer's tile partials in tile order (fixed tree -> reproducible); one
-// 256-thread workgroup per layer; all columns together: per thread the same strided sums, then the
-// same tree per column.
+// errors[l][c] = sum of the layer's tile partials (fixed order -> reproducible); one 256-thread workgroup per layer, all
+// columns together: per thread the same strided sums, then a tree inside the wavefront and the four wavefronts' (one barrier; with
+// a tree over the workgroup in LDS, eight of them: 5.9 us instead of 3.8 on 16 layers of 7 columns, 6 instead of 4.5 on 62).
 __device__ __forceinline__ void reduce_partials_block(const double* __restrict__ partials, int stride,
                                                       const ReduceCols& cols, const DevLayer* __restrict__ layers,
                                                       double* __restrict__ errors, int layer,
-                                                      double (*s)[256]) {
+                                                      double (*s)[4]) {
     const DevLayer L = layers[layer];
     double a[kMaxQuant];
 #pragma unroll
@@ -29,17 +29,15 @@ __device__ __forceinline__ void reduce_partials_block(const double* __restrict__
             if (ci < cols.n) a[ci] += partials[(size_t)t * stride + cols.col[ci]];
     }
 #pragma unroll
-    for (int ci = 0; ci < kMaxQuant; ++ci) s[ci][threadIdx.x] = a[ci];
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-#pragma unroll
-            for (int ci = 0; ci < kMaxQuant; ++ci)
-                if (ci < cols.n) s[ci][threadIdx.x] += s[ci][threadIdx.x + o];
+    for (int ci = 0; ci < kMaxQuant; ++ci) {
+        if (ci < cols.n) {
+            const double w = wave_sum(a[ci]);
+            if ((threadIdx.x & 63) == 0) s[ci][threadIdx.x >> 6] = w;
         }
-        __syncthreads();
     }
-    if ((int)threadIdx.x < cols.n) errors[(size_t)layer * stride + cols.col[threadIdx.x]] = s[threadIdx.x][0];
+    __syncthreads();
+    const int ci = threadIdx.x;
+    if (ci < cols.n) errors[(size_t)layer * stride + cols.col[ci]] = (s[ci][0] + s[ci][1]) + (s[ci][2] + s[ci][3]);
 }
 
 }  // namespace lgreco

@@ -65,7 +65,7 @@ constexpr int kRefThreads = 1024;
 constexpr int kRefSlots = 512;      // refinement workgroups the chip runs at a time (256 CUs x 2)
 constexpr int kRefEnergySlots = 256;    // work items aimed at where partial histograms hold energies too (see topk_begin)
 constexpr int kBinsA = 1024, kBinsB = 512;
-constexpr int kSampleSegs = 512, kSampleSeg = 32;     // sample of a layer: segments, consecutive elements in each
+constexpr int kSampleSegs = 512;     // sample of a layer: segments of 16 or 32 consecutive elements (see topk_begin)
 constexpr int kSampleThreads = 1024;
 
 // ------------------------------------------------------------------------ block helpers
@@ -194,14 +194,15 @@ struct RefWork {                     // one workgroup of the refinement kernels:
 
 // Lower bound of every layer's lowest threshold bin, one workgroup per layer: coarse histogram of a
 // sample in LDS, and the bin that holds somewhat more of it than the largest k asks for.  The sample
-// is 512 segments of 32 consecutive elements (one 128-byte line each), spread evenly over the layer with a
+// is 512 segments of SEG consecutive elements, spread evenly over the layer with a
 // scrambled offset inside each stride, so that no row length of a matrix lines up with it; a layer
-// of at most 16384 elements is taken whole and its bound is exact.  Every thread issues its 16 loads
-// (32 with error feedback) before it uses the first: the kernel is a memory round trip, 64 KB per
-// layer, and two searches of the histogram.  (A sample of 1/16 of the data in three kernels took 33 us
+// of at most 512 SEG elements is taken whole and its bound is exact.  Every thread issues its SEG / 2 loads
+// (twice that with error feedback) before it uses the first: the kernel is a memory round trip, 32 or 64 KB per
+// layer, and a search of the histogram.  (A sample of 1/16 of the data in three kernels took 33 us
 // on a 26 M-element model, remembering the last call's thresholds instead nothing, but a step
 // whose gradient is larger or smaller than the one before then collects everything again, or up to
 // half of the elements.)
+template <int SEG>
 __global__ __launch_bounds__(kSampleThreads) void topk_bound_kernel(const float* __restrict__ g,
                                                                     const float* __restrict__ e,
                                                                     const uint32_t* __restrict__ ks, int ntk,
@@ -212,7 +213,7 @@ __global__ __launch_bounds__(kSampleThreads) void topk_bound_kernel(const float*
     static_assert(kBinsPer == 4, "a thread's bins are one 128-bit read");
     __shared__ __align__(16) uint32_t s_hist[kCopies][kPitch];
     __shared__ uint32_t s_tot[kSampleThreads / 64];
-    constexpr int kPer = kSampleSegs * kSampleSeg / kSampleThreads;
+    constexpr int kPer = kSampleSegs * SEG / kSampleThreads;
     const int l = blockIdx.x, tid = threadIdx.x;
     uint32_t kmax = 0;
     for (int j = 0; j < ntk; ++j) kmax = max(kmax, ks[(size_t)l * kMaxTopk + j]);
@@ -222,8 +223,8 @@ __global__ __launch_bounds__(kSampleThreads) void topk_bound_kernel(const float*
     }
     const DevLayer L = layers[l];
     const uint32_t n = (uint32_t)L.numel;
-    const bool whole = n <= (uint32_t)(kSampleSegs * kSampleSeg);
-    const uint32_t stride = n / kSampleSegs;             // at least kSampleSeg unless whole
+    const bool whole = n <= (uint32_t)(kSampleSegs * SEG);
+    const uint32_t stride = n / kSampleSegs;             // at least SEG unless whole
     float x[kPer], y[kPer];
     uint32_t at[kPer];
 #pragma unroll
@@ -231,9 +232,9 @@ __global__ __launch_bounds__(kSampleThreads) void topk_bound_kernel(const float*
         if (whole) {
             at[q] = (uint32_t)(q * kSampleThreads + tid);
         } else {
-            const uint32_t seg = (uint32_t)(q * (kSampleThreads / kSampleSeg) + tid / kSampleSeg);
-            const uint32_t room = stride - kSampleSeg + 1u;
-            at[q] = seg * stride + __umulhi(seg * 2654435761u, room) + (uint32_t)(tid % kSampleSeg);
+            const uint32_t seg = (uint32_t)(q * (kSampleThreads / SEG) + tid / SEG);
+            const uint32_t room = stride - SEG + 1u;
+            at[q] = seg * stride + __umulhi(seg * 2654435761u, room) + (uint32_t)(tid % SEG);
         }
     }
     const float* const gl = g + L.offset;
@@ -253,7 +254,7 @@ __global__ __launch_bounds__(kSampleThreads) void topk_bound_kernel(const float*
     __syncthreads();
     uint32_t want = kmax;
     if (!whole) {
-        const float ns = (float)(kSampleSegs * kSampleSeg);
+        const float ns = (float)(kSampleSegs * SEG);
         const float t = (float)kmax * (ns / (float)n);   // expected sample entries above the threshold
         const float w = 1.2f * t + 5.0f * sqrtf(t) + 16.0f;      // a margin: the sample only has to be roughly right
         if (w >= ns) {
@@ -625,7 +626,7 @@ __global__ __launch_bounds__(256) void topk_scan_many_kernel(uint32_t* __restric
     __shared__ __align__(16) unsigned char s_raw[sizeof(uint32_t) * kHistBins];
     if ((int)blockIdx.x >= n_layers) {
         reduce_partials_block(red.partials, red.stride, red.cols, red.layers, red.errors, (int)blockIdx.x - n_layers,
-                              reinterpret_cast<double(*)[256]>(s_raw));
+                              reinterpret_cast<double(*)[4]>(s_raw));
         return;
     }
     uint32_t* const s_hist = reinterpret_cast<uint32_t*>(s_raw);
@@ -825,7 +826,7 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_a_kernel(RefinePar
     if (ENERGY && (int)blockIdx.x >= p.n_work) {
         if (tid < 256)                   // (the other wavefronts end here: a barrier is for those that are left)
             reduce_partials_block(p.red.partials, p.red.stride, p.red.cols, p.red.layers, p.red.errors,
-                                  (int)blockIdx.x - p.n_work, reinterpret_cast<double(*)[256]>(refine_smem));
+                                  (int)blockIdx.x - p.n_work, reinterpret_cast<double(*)[4]>(refine_smem));
         return;
     }
     const RefWork w = p.work[blockIdx.x];
@@ -933,12 +934,11 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_a_kernel(RefinePar
     }
 }
 
-// A thread's share (of 256) of a layer's energy below the collection bound, in index order with four loads in flight.
-__device__ __forceinline__ double base_energy(const RefineParams& p, int l) {
-    const DevLayer& L = p.layers[l];
-    const int end = L.tile_end;
+// A thread's share (of 256) of a layer's energy below the collection bound, tiles tile, tile + 256, ... before `end`, in
+// that order with four loads in flight.
+__device__ __forceinline__ double base_energy(const RefineParams& p, int tile, int end) {
     double part = 0.0;
-    for (int tt = L.tile_begin + (int)(threadIdx.x & 255); tt < end; tt += 4 * 256) {
+    for (int tt = tile; tt < end; tt += 4 * 256) {
         double v[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] = tt + q * 256 < end ? p.base_part[tt + q * 256] : 0.0;
@@ -1025,23 +1025,26 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
     if (j == 0)                          // the next call's main pass starts from zero
         for (int b = tid; b < kHistBins / 4; b += kPickThreads)
             reinterpret_cast<uint4*>(p.hist + (size_t)l * kHistBins)[b] = make_uint4(0u, 0u, 0u, 0u);
-    for (int b = tid; b < kBinsA; b += kPickThreads) {
-        s_hist[b] = 0;
-        s_en[b] = 0;
-    }
+    if (kPickThreads > 256)
+        for (int b = tid; b < kBinsA; b += kPickThreads) {
+            s_hist[b] = 0;
+            s_en[b] = 0;
+        }
     if (tid == 0) {
         s_e = 0;
         s_exact[0] = 0;
     }
-    // energy below the collection bound (tile partials) and of the candidates below the threshold
-    // bin (workgroup partials): loaded first so that the histogram work hides the latency; both
-    // are summed in a fixed order (per thread, then a fixed tree)
-    double part = 0.0;
+    // energy below the collection bound (tile partials) and of the candidates below the threshold bin (workgroup
+    // partials), both summed in a fixed order (per thread, then a fixed tree): the first of them are asked for here, beside
+    // the partial histograms, and added up behind those
+    const int tile0 = p.layers[l].tile_begin + t, tile1 = p.layers[l].tile_end;
+    double part = 0.0, base[4] = {0.0, 0.0, 0.0, 0.0}, low = 0.0;
     if (tid < 256) {
-        part = base_energy(p, l);
-        for (int wg = wr.x + tid; wg < wr.y; wg += 256) part += p.below_part[(size_t)wg * kMaxTopk + j];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) base[q] = tile0 + q * 256 < tile1 ? p.base_part[tile0 + q * 256] : 0.0;
+        if (wr.x + tid < wr.y) low = p.below_part[(size_t)(wr.x + tid) * kMaxTopk + j];
     }
-    __syncthreads();
+    if (kPickThreads > 256) __syncthreads();
     // sum the layer's workgroup partials of this k's list: 4 bins per thread as 16-byte loads (two
     // pairs of packed cells), the workgroups dealt round-robin to the thread groups,
     // integer LDS atomics join them (order does not matter).  The loop is a chain of memory round
@@ -1066,9 +1069,21 @@ __global__ __launch_bounds__(kPickThreads) void topk_pick_a_kernel(RefineParams 
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int cell = (q >> 1) * 512 + 2 * t + (q & 1);
-            if (c[q]) atomicAdd(&s_hist[cell], c[q]);
-            if (e[q]) atomicAdd(&s_en[cell], e[q]);
+            if (kPickThreads == 256) {                       // a thread's own cells
+                s_hist[cell] = c[q];
+                s_en[cell] = e[q];
+            } else {
+                if (c[q]) atomicAdd(&s_hist[cell], c[q]);
+                if (e[q]) atomicAdd(&s_en[cell], e[q]);
+            }
         }
+    }
+    if (tid < 256) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) part += base[q];
+        if (tile0 + 4 * 256 < tile1) part += base_energy(p, tile0 + 4 * 256, tile1);
+        part += low;
+        for (int wg = wr.x + 256 + tid; wg < wr.y; wg += 256) part += p.below_part[(size_t)wg * kMaxTopk + j];
     }
     __syncthreads();
     block_kth_from_top<kBinsA / 256>(s_hist, S.need, s_tot, s_res);
@@ -1211,7 +1226,7 @@ __global__ __launch_bounds__(256) void topk_pick_many_kernel(RefineParams p) {
     const int end = min((int)T.nlists, p.list0 + p.room);
     if (p.list0 + (int)blockIdx.y >= end) return;
     const int2 wr = p.work_range[l];
-    const double base = base_energy(p, l);
+    const double base = base_energy(p, p.layers[l].tile_begin + (int)(threadIdx.x & 255), p.layers[l].tile_end);
     for (int li = p.list0 + (int)blockIdx.y; li < end; li += (int)gridDim.y) {
         const uint32_t tbin = T.bin[li], first = T.first[li], count = T.first[li + 1] - first;
         double part = base;
@@ -1883,8 +1898,14 @@ hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevL
         TK_CHECK(hipGetLastError());
     }
     t->hist_clean = false;
-    hipLaunchKernelGGL(topk_bound_kernel, dim3(L), dim3(kSampleThreads), 0, s, g, e, (const uint32_t*)t->d_k, ntk, d_layers,
-                       t->d_lo);
+    // A sample of half the size costs 2 to 3 us less (26 M elements in 161 layers 11.2 -> 9.1 us, 5 M in 28 10.0 -> 8.0), and
+    // its wider margin lets half a per cent more elements through as candidates of 10 %: of 355 M elements that costs 6 us more than it gives.
+    if (base >= (int64_t)1 << 26)
+        hipLaunchKernelGGL(topk_bound_kernel<32>, dim3(L), dim3(kSampleThreads), 0, s, g, e, (const uint32_t*)t->d_k, ntk,
+                           d_layers, t->d_lo);
+    else
+        hipLaunchKernelGGL(topk_bound_kernel<16>, dim3(L), dim3(kSampleThreads), 0, s, g, e, (const uint32_t*)t->d_k, ntk,
+                           d_layers, t->d_lo);
     return hipGetLastError();
 }
 
@@ -2015,7 +2036,7 @@ hipError_t topk_resolve(TopkScratch* t, const float* g, const float* e, float* e
         return hipSuccess;
     }
     if (d_errors) {       // profile: level A gives the dropped energy, no exact threshold is needed
-        const size_t lds = std::max(refine_a_lds(ntk, true), quant ? sizeof(double) * kMaxQuant * 256 : 0);
+        const size_t lds = refine_a_lds(ntk, true);
         static bool configured[kMaxTopk + 1] = {};   // the dynamic LDS limit is raised once per variant
 #define LG_REFINE_A(N)                                                                                   \
     case N:                                                                                              \
