@@ -459,3 +459,43 @@ def test_places_in_a_layer_of_more_tiles_than_a_workgroup_adds_up(one_call):
         assert torch.equal(got[:k].view(torch.float32), x[idx]), l
         assert torch.equal(e[offsets[l]:offsets[l] + numels[l]], torch.where(kept, torch.zeros_like(x), x)), l
     h.close()
+
+
+@pytest.mark.parametrize("case", ["tiny layers", "ties", "tile edges", "large sample"])
+def test_thresholds_found_where_they_are_used(case):
+    """Every workgroup finds the bins and thresholds of its layers itself: four layers in one batch of tiles, every entry
+    equal, layers at the edges of tiles and work items, and the sample of large calls.  The handle's counts have to be zero
+    again behind each call, whichever way it compressed."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    rng = np.random.default_rng(77)
+    densities = (0.001, 0.01, 0.1)
+    if case == "tiny layers":
+        arrays = [rng.standard_normal(n).astype(np.float32) for n in (1, 2, 3, 5, 64, 127, 511, 512, 513, 1000, 7, 33)]
+    elif case == "ties":
+        arrays = [np.full(n, v, np.float32) for n, v in ((40000, 0.5), (9, -1.0), (70001, 0.0))]
+        arrays.append(np.repeat(np.float32([1.0, -2.0, 3.0]), 11000))
+    elif case == "tile edges":
+        arrays = [rng.standard_normal(n).astype(np.float32) for n in (8191, 8192, 8193, 32768, 32769, 600001, 16384)]
+    else:
+        arrays = [rng.standard_normal((1 << 26) + 3).astype(np.float32), rng.standard_normal(16385).astype(np.float32)]
+        densities = (0.01,)
+    batch = _flat_batch(arrays)
+    _check(batch, densities)
+
+    cands = [(W.TOPK, float(d)) for d in densities]
+    layers, ctab = tables(batch, cands)
+    g, e, _ = to_device(batch)
+    L = len(arrays)
+    h = B.Handle(int(batch.grads.size), L, len(cands))
+    offsets = B.payload_layout(layers, ctab, np.full(L, len(cands) - 1, np.int32))
+    room = int(offsets[-1]) + 16
+    for _ in range(2):
+        one, e_one = torch.zeros(room, dtype=torch.uint8, device="cuda"), e.clone()
+        st, _, _, _, choice, _, _, off = h.profile_solve_compress(g, e_one, layers, ctab, len(cands) // 2, 200, one)
+        assert st == B.OK
+        sep, e_sep = torch.zeros_like(one), e.clone()
+        h.compress(g, e_sep, layers, ctab, choice, sep, off)
+        torch.cuda.synchronize()
+        assert torch.equal(one, sep) and torch.equal(e_one.view(torch.int32), e_sep.view(torch.int32))
+    h.close()
