@@ -558,7 +558,7 @@ __global__ __launch_bounds__(256, 4) void lr_apply_kernel(LrParams p) {
 
 // ------------------------------------------------------------------ Q partials = X^T Phat
 // One workgroup: 128 columns of X (rows of Q) over one range of its rows, X and Phat in chunks of 32 rows through LDS
-// (two buffers).  Bound by the fp32 matrix pipe (67 M elements: 89 us; the products alone take 70 at the 2.1 GHz the
+// (two buffers).  Bound by the fp32 matrix pipe (67 M elements: 89 to 100 us from box to box; the products alone take 70 at the 2.1 GHz the
 // chip holds in a burst this short).  Every load of a chunk is issued without a condition and used after the
 // products of the chunk before it; rows past the range and columns past the matrix are made zero as they go to LDS.
 // (With both operands loaded straight in the layout of the instruction, no LDS and no barriers, 102-121 us: 204 registers
