@@ -34,6 +34,7 @@
 #include "internal.h"
 #include "reduce_dev.h"
 #include "topk_dev.h"
+#include "work_items.h"
 
 namespace lgreco {
 
@@ -63,7 +64,7 @@ constexpr int kRefTiles = 16;       // largest tiles per refinement workgroup (f
                                     // smaller tiles a workgroup takes proportionally more of them)
 constexpr int kRefThreads = 1024;
 constexpr int kRefSlots = 512;      // refinement workgroups the chip runs at a time (256 CUs x 2)
-constexpr int kRefEnergySlots = 256;    // work items aimed at where partial histograms hold energies too (see topk_begin)
+constexpr int kRefEnergySlots = 256;    // work items aimed at where they hold the energies of several densities (see topk_begin)
 constexpr int kBinsA = 1024, kBinsB = 512;
 constexpr int kSampleSegs = 512;     // sample of a layer: segments of 16 or 32 consecutive elements (see topk_begin)
 constexpr int kSampleThreads = 1024;
@@ -1833,30 +1834,25 @@ hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevL
     (void)n_tiles;
     (void)d_tiles;
     // Tiles per work item of the refinement kernels: 2^19 elements, fewer when that would leave part of the chip
-    // without a work item, but no fewer than needed for all items to run at once: a work item's time has a fixed part
+    // without a work item (see work_items.h).  An item's time has a fixed part
     // (its chain of loads, the partial histograms it clears and writes), and items past the slots start when
     // the first ones end.  The compression's partial histograms are counts of one density, 4 KB, and its items fill
-    // the chip, two workgroups to a compute unit.  The profile's are 8 KB a density, 31 MB in 650 items of 6 densities,
+    // the chip, two workgroups to a compute unit, as do those of a profile of one density.  A profile's of several are 8 KB a
+    // density, 31 MB in 650 items of 6 densities,
     // which the pick reads again: one workgroup to a compute unit.  Refinement and pick, us, with items for 1024 slots, as many
     // as before (650 and 620), for 512, 256 and 128: profile of 26 M elements in 161 layers 51, 38, 32, 30, 44; of 5 M
     // in 28 34, 34, 26, 22, 21; compression of the 26 M (both levels) 27, 27, 23, 28, 41.
     int group = kRefTiles * (kTile / tile_elems);
     {
-        int64_t active = 0;
-        for (int l = 0; l < L; ++l)
-            if (ks[(size_t)l * kMaxTopk]) active += h_layers[l].tile_end - h_layers[l].tile_begin;
+        const auto tiles_of = [&](int l) { return ks[(size_t)l * kMaxTopk] ? h_layers[l].tile_end - h_layers[l].tile_begin : 0; };
         if (nk_many) {
             // (more than kMaxTopk densities: kManySplit workgroups share an item's lists; aiming at one round of items
             // takes 55 us instead of 44, a workgroup walks its candidates for several chunks of lists)
+            int64_t active = 0;
+            for (int l = 0; l < L; ++l) active += tiles_of(l);
             group = (int)std::max<int64_t>(1, std::min<int64_t>(group, active * kManySplit / kRefSlots));
         } else {
-            const int most = group, slots = ntk > 1 ? kRefEnergySlots : kRefSlots;
-            for (group = (int)std::max<int64_t>(1, std::min<int64_t>(most, active / slots)); group < most; ++group) {
-                int64_t items = 0;
-                for (int l = 0; l < L && items <= slots; ++l)
-                    if (ks[(size_t)l * kMaxTopk]) items += (h_layers[l].tile_end - h_layers[l].tile_begin + group - 1) / group;
-                if (items <= slots) break;
-            }
+            group = tiles_per_item(L, tiles_of, ntk > 1 ? kRefEnergySlots : kRefSlots, group);
         }
     }
     TK_CHECK(ctl_writable(t));

@@ -499,3 +499,12 @@ def test_thresholds_found_where_they_are_used(case):
         torch.cuda.synchronize()
         assert torch.equal(one, sep) and torch.equal(e_one.view(torch.int32), e_sep.view(torch.int32))
     h.close()
+
+
+def test_more_layers_than_work_items_aimed_at():
+    """600 small layers and a few of many tiles, more than one item each: every layer's thresholds, errors and image."""
+    rng = np.random.default_rng(31)
+    arrays = [rng.standard_normal(n).astype(np.float32) for n in rng.integers(1, 300, 600)]
+    for at, n in ((0, 200000), (301, 70001), (605, 300007)):
+        arrays.insert(at, rng.standard_normal(n).astype(np.float32))
+    _check(_flat_batch(arrays), (0.001, 0.01, 0.1))
