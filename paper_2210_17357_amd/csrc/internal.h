@@ -227,7 +227,7 @@ struct TopkScratch {
     uint32_t* d_cand_idx = nullptr;   // compress: index within the layer (+ sign bit) of every candidate; a profile that
                                       // records where its candidates are uses it for 16-bit entries (place in tile, sign)
     bool cand_has_idx = false;        // the current call's profile recorded d_cand_idx too
-    // compression from the profile's candidates: what is kept of them, in element order
+    // compression from the profile's candidates: what is kept of them, in element order (behind the partial histograms)
     uint32_t* d_kept = nullptr;
     uint32_t* d_kept_idx = nullptr;
     void* d_tinfo_kept = nullptr;
@@ -240,8 +240,8 @@ struct TopkScratch {
     void* d_tinfo = nullptr;          // per tile, per wavefront: candidates written and where
     double* d_base_part = nullptr;    // per tile energy below the collection bound
     double* d_below_part = nullptr;   // refinement partial sums
-    uint32_t* d_ref = nullptr;        // per-workgroup refinement histograms (counts, integer energies)
-    size_t ref_words = 0;
+    void* d_ref = nullptr;            // per-workgroup refinement histograms (counts, integer energies)
+    size_t ref_bytes = 0;             // with d_kept and d_kept_idx behind them
     // control block, one upload per call and none when it repeats the last one:
     // [k | cand_base | work_range | work], then [many], uploaded on its own; the pointers above and below are views into it
     // (two device copies: profile calls and compress calls alternate and each repeats itself)

@@ -1674,9 +1674,10 @@ __global__ __launch_bounds__(kThreads) void topk_emit_kernel(float* __restrict__
     } while (0)
 
 // Partial histograms (and the energies beside them) of a call with more than kMaxTopk densities that the
-// refinement's buffer holds, in (work item, list) pairs; at least 7 per work item.
+// refinement's buffer holds, in (work item, list) pairs; at least 7 per work item.  The buffers behind it (what is kept
+// of a profile's candidates, x = g + e of the low-rank layers) are written after the refinement that reads these, if at all.
 constexpr size_t kManyBytes = sizeof(unsigned long long) * kBinsA + sizeof(double);
-static size_t many_capacity(const TopkScratch* t) { return t->ref_words * sizeof(uint32_t) / kManyBytes; }
+static size_t many_capacity(const TopkScratch* t) { return t->ref_bytes / kManyBytes; }
 
 hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers, int max_tiles, int max_cands) {
     t->max_elems = max_elems;
@@ -1696,8 +1697,6 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
     t->counts_clean = true;
     TK_CHECK(hipMalloc(&t->d_cand, sizeof(uint32_t) * (size_t)max_elems));
     TK_CHECK(hipMalloc(&t->d_cand_idx, sizeof(uint32_t) * (size_t)max_elems));
-    TK_CHECK(hipMalloc(&t->d_kept, sizeof(uint32_t) * (size_t)max_elems));
-    TK_CHECK(hipMalloc(&t->d_kept_idx, sizeof(uint32_t) * (size_t)max_elems));
     TK_CHECK(hipMalloc(&t->d_tinfo_kept, sizeof(TopkTileInfo) * (size_t)max_tiles));
     TK_CHECK(hipMalloc(&t->d_lo, sizeof(uint32_t) * (size_t)max_layers));
     TK_CHECK(hipMalloc(&t->d_tilecnt, sizeof(uint2) * (size_t)max_tiles * (kThreads / 64)));
@@ -1706,15 +1705,20 @@ hipError_t topk_scratch_create(TopkScratch* t, int64_t max_elems, int max_layers
     TK_CHECK(hipMalloc(&t->d_base_part, sizeof(double) * (size_t)max_tiles));
     t->max_work = (int)(max_elems / ((int64_t)kRefTiles * kTile)) + 2 * max_layers + 2 + 2 * kRefSlots;   // see topk_begin
     TK_CHECK(hipMalloc(&t->d_below_part, sizeof(double) * (size_t)t->max_work * kMaxTopk));
-    t->ref_words = (size_t)t->max_work * kMaxTopk * 2 * kBinsA;
+    // The refinement's partial histograms, then what is kept of a profile's candidates.  A handle that may be asked for
+    // more densities than kMaxTopk uses both for a list of each in every work item (see topk_begin for their number) where
+    // that fits with at most 112 KB a work item in the first part; what does not fit takes further passes.
+    const size_t kept = (sizeof(uint32_t) * (size_t)max_elems + 255) / 256 * 256, part = (size_t)t->max_work * kMaxTopk * kBinsA;
+    size_t ref = part * sizeof(unsigned long long);
     if (max_cands > (int)kMaxTopk) {
-        // more densities than that: room for a list of each in every work item (see topk_begin for their number), up to half
-        // a gigabyte; what does not fit takes further passes
         const size_t items = (size_t)std::max<int64_t>(2 * kRefSlots / kManySplit, max_elems / ((int64_t)kRefTiles * kTile)) + 2 * (size_t)max_layers + 2;
-        const size_t room = std::min<size_t>(items * (size_t)max_cands * kManyBytes, (size_t)512 << 20);
-        t->ref_words = std::max(t->ref_words, (room + sizeof(uint32_t) - 1) / sizeof(uint32_t));
+        const size_t want = items * (size_t)max_cands * kManyBytes, most = part * 14;
+        if (want > 2 * kept + ref) ref = std::min((want - 2 * kept + 255) / 256 * 256, most);
     }
-    TK_CHECK(hipMalloc(&t->d_ref, sizeof(uint32_t) * t->ref_words));
+    t->ref_bytes = ref + 2 * kept;
+    TK_CHECK(hipMalloc(&t->d_ref, t->ref_bytes));
+    t->d_kept = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(t->d_ref) + ref);
+    t->d_kept_idx = t->d_kept + kept / sizeof(uint32_t);
     if (max_cands > (int)kMaxTopk) TK_CHECK(hipMalloc(&t->d_many, sizeof(TopkMany) * (size_t)max_layers));
     // control block layout (every part a multiple of 16 bytes)
     const size_t o_k = 0;
@@ -1750,8 +1754,6 @@ void topk_scratch_destroy(TopkScratch* t) {
     (void)hipFree(t->d_cnt_a);
     (void)hipFree(t->d_cand);
     (void)hipFree(t->d_cand_idx);
-    (void)hipFree(t->d_kept);
-    (void)hipFree(t->d_kept_idx);
     (void)hipFree(t->d_tinfo_kept);
     (void)hipFree(t->d_lo);
     (void)hipFree(t->d_tilecnt);
@@ -2023,7 +2025,7 @@ hipError_t topk_resolve(TopkScratch* t, const float* g, const float* e, float* e
         }
         for (p.list0 = 0; p.list0 < t->nk_many; p.list0 += p.room) {
             // (a pass after the first finds nothing to do unless the layers have that many lists: small grids.  100
-            // densities of a 26 M-element model, about 25 lists in a buffer of 73: 3 of a run's 245 us)
+            // densities of a 26 M-element model, about 25 lists, when the buffer held 73: 3 of a run's 245 us)
             hipLaunchKernelGGL(topk_refine_many_kernel, dim3(t->n_work, p.list0 ? 1 : kManySplit), dim3(kRefThreads), lds, s, p);
             TK_CHECK(hipGetLastError());
             hipLaunchKernelGGL(topk_pick_many_kernel, dim3(L, p.list0 ? 4 : kManySlots), dim3(256), 0, s, p);

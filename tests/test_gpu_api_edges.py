@@ -99,3 +99,22 @@ def test_layer_of_more_than_2_pow_30_elements():
             assert float((ef.abs() > kept_min).sum()) == 0              # nothing larger was dropped
         del payload, ef, out
     h.close()
+
+
+@pytest.mark.parametrize("elems, layers, cands", [(1024, 163, 49), (1024, 163, 8), (25_600_000, 161, 100),
+                                                  (3_000_000, 292, 100)])
+def test_device_memory_of_a_handle_is_what_the_header_states(elems, layers, cands):
+    """16 bytes per element, and for the refinement's partial histograms 67 MB and 0.13 MB per layer up to 8 candidates, at
+    most 118 MB and 0.23 MB per layer above; a tenth of that and 24 MB left for the rest (tables per layer of 4096
+    and 10000 bins, tiles, allocation granularity)."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    B.Handle(1024, 1, 1).close()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    h = B.Handle(elems, layers, cands)
+    used = free - torch.cuda.mem_get_info()[0]
+    h.close()
+    mb = 16e-6 * elems + (118 + 0.23 * layers if cands > 8 else 67 + 0.13 * layers)
+    print("%.0f MB used, %.0f MB stated" % (used / 1e6, mb))
+    assert used < 1.1e6 * mb + 24e6
