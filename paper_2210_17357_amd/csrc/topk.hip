@@ -825,9 +825,8 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_a_kernel(RefinePar
     __shared__ uint32_t s_tot[kRefThreads / 64], s_bin[kMaxTopk], s_higher[kMaxTopk];
     const int tid = threadIdx.x;
     if (ENERGY && (int)blockIdx.x >= p.n_work) {
-        if (tid < 256)                   // (the other wavefronts end here: a barrier is for those that are left)
-            reduce_partials_block(p.red.partials, p.red.stride, p.red.cols, p.red.layers, p.red.errors,
-                                  (int)blockIdx.x - p.n_work, reinterpret_cast<double(*)[4]>(refine_smem));
+        reduce_partials_block(p.red.partials, p.red.stride, p.red.cols, p.red.layers, p.red.errors,
+                              (int)blockIdx.x - p.n_work, reinterpret_cast<double(*)[4]>(refine_smem));
         return;
     }
     const RefWork w = p.work[blockIdx.x];

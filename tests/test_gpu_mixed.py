@@ -243,3 +243,32 @@ def test_full_size_gpt2_medium_sampled_layers():
             ch = err2[np.arange(L), choice2]
             assert (np.abs(left - ch) <= 1e-4 * ch + 1e-60).all(), step
     h2.close()
+
+
+@pytest.mark.parametrize("start", [0, 1])
+def test_quantization_errors_are_summed_alike_in_every_launch(start):
+    """The tile partials are added up by a kernel of their own, by workgroups of 1024 threads beside one to eight
+    densities, and by workgroups of the scan beside more: in one order, so bit for bit the same.  Layers of one tile, of about as many
+    as the threads that add them up, and of several times that."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    rng = np.random.default_rng(17)
+    sizes = [start + 4, 100, 255 * 8192, 256 * 8192 + 1, 257 * 8192 - 3, 700 * 8192 + 77, 5 * 128 + 1]
+    total, offs = sum(sizes), np.concatenate([[0], np.cumsum(sizes)[:-1]])
+    x = (rng.standard_normal(total) * 1e-3).astype(np.float32)
+    g = torch.from_numpy(x).cuda()
+    quant = [(W.QUANT, float(b)) for b in range(1, 9)]
+    layers = B.layer_table(offs, sizes, [0] * len(sizes), [0] * len(sizes))
+    tables_ = []
+    for n_topk in (0, 1, 6, 8, 20):
+        cands = quant + [(W.TOPK, 0.001 * (c + 1)) for c in range(n_topk)]
+        h = B.Handle(total, len(sizes), len(cands))
+        errors, _ = h.profile(g, None, layers, B.cand_table(cands))
+        tables_.append(errors[:, :len(quant)].copy())
+        h.close()
+    for l in (0, 1, 3, 6):
+        ref = pipeline.profile(x, None, offs[l:l + 1], np.asarray(sizes[l:l + 1]), np.zeros(1, np.int32),
+                               np.zeros(1, np.int32), quant)
+        assert rel_err(tables_[0][l:l + 1], ref).max() < 1e-4, l
+    for t in tables_[1:]:
+        assert np.array_equal(t, tables_[0])
