@@ -311,18 +311,14 @@ struct CollectParams {
 // (nearly exactly the kept set qualifies), and the elements inside that boundary sub-bin are
 // counted by their last 9 pattern bits (s_hist: kBinsB cells) for the exact threshold.
 // TEAM (the second collection, made by the refinement kernel's workgroup for its own tiles): the
-// workgroup is several teams of kThreads threads, each with a tile of its own (or none: `active`
-// false; the teams still meet at the barrier) and its own s_red; the caller has checked that the
+// workgroup is several teams of kThreads threads, each with a tile of its own and its own s_red; a team without
+// a tile does not come here, so the barrier behind s_red and the sum of it are the caller's, who has checked that the
 // layer takes part and gives the bound, team_lo.
 template <bool HIST, bool EMIT, bool KNOWN = false, bool TEAM = false>
 __device__ __forceinline__ void collect_tile(const CollectParams& p, const int tile, uint32_t* s_hist, double* s_red,
-                                             const bool active = true, const uint32_t team_lo = 0) {
+                                             const uint32_t team_lo = 0) {
     static_assert(!(HIST && KNOWN), "the coarse histogram is not built when the thresholds are known");
     static_assert(!TEAM || (!HIST && !KNOWN), "teams collect, nothing else");
-    if (TEAM && !active) {             // (uniform over the team)
-        __syncthreads();
-        return;
-    }
     const Tile t = p.tiles[tile];
     const DevLayer L = p.layers[t.layer];
     uint32_t bound;
@@ -426,6 +422,7 @@ __device__ __forceinline__ void collect_tile(const CollectParams& p, const int t
         p.tinfo[tile].cnt[wave] = col.cur;
         p.tinfo[tile].start[wave] = start;
     }
+    if (TEAM) return;
     __syncthreads();
     if (tid == 0) p.base_part[tile] = (s_red[0] + s_red[1]) + (s_red[2] + s_red[3]);
     if (HIST) {
@@ -715,7 +712,12 @@ __device__ __forceinline__ void collect_again(const CollectParams& rc, int t0, i
     const int team = threadIdx.x / kThreads;
     for (int first = t0; first < t1; first += kTeams) {
         const int tile = first + team;
-        collect_tile<false, EMIT, false, true>(rc, min(tile, t1 - 1), nullptr, s_team_red[team], tile < t1, lo);
+        if (tile < t1) collect_tile<false, EMIT, false, true>(rc, tile, nullptr, s_team_red[team], lo);
+        __syncthreads();
+        if (tile < t1 && threadIdx.x % kThreads == 0) {
+            const double* const r = s_team_red[team];
+            rc.base_part[tile] = (r[0] + r[1]) + (r[2] + r[3]);
+        }
         __syncthreads();                                // s_team_red is reused; the tile's records are written
     }
 }
