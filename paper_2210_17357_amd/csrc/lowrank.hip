@@ -1019,13 +1019,12 @@ struct LrHost {
     // device copies
     LrLayer* d_layers = nullptr;
     LrTile* d_tiles = nullptr;      // the four tile tables back to back
-    size_t cap_layers = 0, cap_tiles = 0, cap_p = 0, cap_q = 0, cap_part = 0, cap_ppart = 0, cap_gram = 0, cap_T = 0,
+    size_t cap_layers = 0, cap_tiles = 0, cap_p = 0, cap_q = 0, cap_part = 0, cap_ppart = 0, cap_T = 0,
            cap_xn = 0, cap_qn = 0;
     float* P = nullptr;
     float* Q = nullptr;
-    float* part = nullptr;
+    float* part = nullptr;          // partials of Q, and before them of the Gram matrices: those are used up when Q is computed
     float* ppart = nullptr;
-    double* gram = nullptr;
     double* T = nullptr;
     double* xn = nullptr;
     double* qn = nullptr;
@@ -1062,7 +1061,6 @@ void lowrank_scratch_destroy(LowrankScratch* t) {
             (void)hipFree(H->Q);
             (void)hipFree(H->part);
             (void)hipFree(H->ppart);
-            (void)hipFree(H->gram);
             (void)hipFree(H->T);
             (void)hipFree(H->xn);
             (void)hipFree(H->qn);
@@ -1169,10 +1167,9 @@ static hipError_t lr_prepare(LowrankScratch* t, int slot, const DevLayer* hl, in
     if (tables_only) { p_off = q_off = part_off = ppart_off = 0; }
     LR_CHECK(grow((void**)&H->P, &H->cap_p, sizeof(float) * std::max<int64_t>(p_off, 1)));
     LR_CHECK(grow((void**)&H->Q, &H->cap_q, sizeof(float) * std::max<int64_t>(q_off, 1)));
-    LR_CHECK(grow((void**)&H->part, &H->cap_part, sizeof(float) * std::max<int64_t>(part_off, 1)));
+    const size_t gram = tables_only ? 0 : sizeof(double) * kLrCols * kLrCols * H->gram_tiles.size();
+    LR_CHECK(grow((void**)&H->part, &H->cap_part, std::max(sizeof(float) * std::max<int64_t>(part_off, 1), gram)));
     LR_CHECK(grow((void**)&H->ppart, &H->cap_ppart, sizeof(float) * std::max<int64_t>(ppart_off, 1)));
-    LR_CHECK(grow((void**)&H->gram, &H->cap_gram,
-                  sizeof(double) * kLrCols * kLrCols * (tables_only ? 1 : std::max<size_t>(H->gram_tiles.size(), 1))));
     LR_CHECK(grow((void**)&H->T, &H->cap_T,
                   sizeof(double) * kLrCols * kLrCols * (tables_only ? 1 : std::max<size_t>(nl, 1))));
     LR_CHECK(grow((void**)&H->xn, &H->cap_xn, sizeof(double) * std::max<size_t>(H->p_tiles.size(), 1)));
@@ -1204,7 +1201,7 @@ static void lr_fill_params(LrHost* H, LrParams* p) {
     p->Q = H->Q;
     p->part = H->part;
     p->ppart = H->ppart;
-    p->gram_part = H->gram;
+    p->gram_part = reinterpret_cast<double*>(H->part);
     p->T = H->T;
     p->xnorm_part = H->xn;
     p->qnorm_part = H->qn;
