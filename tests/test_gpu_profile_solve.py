@@ -110,21 +110,25 @@ def test_more_candidates_than_the_device_side_step_takes():
 
 
 @pytest.mark.parametrize("keep", [False, True])
-@pytest.mark.parametrize("kind", ["mixed", "topk", "quant", "lowrank"])
+@pytest.mark.parametrize("kind", ["mixed", "topk", "quant", "lowrank", "lowrank ragged rows"])
 def test_whole_path_as_one_call_equals_the_separate_calls(kind, keep):
     """lgreco_profile_solve_compress against lgreco_profile_solve + lgreco_payload_layout +
     lgreco_compress on the same inputs (which the other tests hold against the oracle): tables,
     assignment, layout, payload bytes, error feedback and the new Q bit for bit; twice in a row on
     one handle; with and without the profile leaving x in the error-feedback buffer for the
     compression (keep_ef_on_failure); a payload buffer that is too small is reported and leaves the
-    error feedback as the configuration says: untouched, or holding x = fl32(g + e)."""
+    error feedback as the configuration says: untouched, or holding x = fl32(g + e).  Ragged rows: layers whose rows are
+    whole lines, 128 of which a workgroup reconstructs at a time, with row counts that leave a wavefront rows
+    in part or none."""
     from paper_2210_17357_amd import binding as B
     torch = torch_cuda()
-    if kind == "lowrank":
+    if kind.startswith("lowrank"):
         base = W.workload("c3_transformer_lm_lowrank")
         shapes = tuple(s for s in W.transformer_lm_shapes(layers=1, d=256, d_ff=512, vocab=1024) if len(s) == 2)
-        w = W.Workload("psc_lowrank", shapes, base.candidates, base.default, 200, base.values, base.ef,
-                       base.scale_exp, only_2d=True, r_max=base.r_max)
+        if kind != "lowrank":
+            shapes = ((1000, 128), (129, 64), (31, 32), (257, 544), (96, 96), (65, 1056), (1, 32))
+        w = W.Workload("psc_lowrank", shapes, base.candidates, base.default, 200, base.values,
+                       base.ef if kind == "lowrank" else "normal0.1", base.scale_exp, only_2d=True, r_max=base.r_max)
     else:
         w = _workload(kind)
     batch = W.generate(w)
@@ -183,7 +187,7 @@ def test_whole_path_as_one_call_equals_the_separate_calls(kind, keep):
         h.profile_solve_compress(g, ef, layers, ctab, w.default, w.n_bins, small, q0.clone() if q0 is not None else None)
     assert err.value.status == B.ENOSPACE
     torch.cuda.synchronize()
-    left = e if (keep or kind == "lowrank") else g + e        # low-rank candidates: x is never written in place
+    left = e if (keep or kind.startswith("lowrank")) else g + e        # low-rank candidates: x is never written in place
     assert torch.equal(ef.view(torch.int32), left.view(torch.int32)) and int(small.count_nonzero()) == 0
     h.close()
 

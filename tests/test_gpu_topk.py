@@ -28,6 +28,31 @@ def _flat_batch(arrays, efs=None, pad=None):
                    np.zeros(len(n), np.int32), np.arange(len(n), dtype=np.int64))
 
 
+def _sampled(n, seg):
+    """Mask of the elements that the collection bound of a layer is predicted from: 512 segments of `seg` elements (16, in
+    calls of 2^26 elements and more 32), one at a scrambled place of every stride; all of a layer of up to 512 segments."""
+    if n <= 512 * seg:
+        return np.ones(n, bool)
+    i = np.arange(512, dtype=np.uint64)
+    stride = n // 512
+    first = i * stride + (((i * 2654435761) % (1 << 32)) * (stride - seg + 1) >> np.uint64(32))
+    mask = np.zeros(n, bool)
+    mask[(first[:, None] + np.arange(seg, dtype=np.uint64)).reshape(-1).astype(np.int64)] = True
+    return mask
+
+
+def _predicts_too_high(x, mask, density):
+    """Whether the bound predicted from the sample lies above the threshold's bin: the sample's entry of rank
+    1.2 t + 5 sqrt(t) + 16, t the k-th largest's expected rank in it, against the k-th largest."""
+    k, ns = topk.k_of(x.size, density), int(mask.sum())
+    t = k * ns / x.size
+    rank = int(1.2 * t + 5.0 * t ** 0.5 + 16.0)
+    if rank >= ns:
+        return False
+    bound, thr = (np.partition(np.abs(v), v.size - r)[v.size - r] for v, r in ((x[mask], rank), (x, k)))
+    return int(np.float32(bound).view(np.uint32)) >> 19 > int(np.float32(thr).view(np.uint32)) >> 19
+
+
 def _check(batch, densities, profile_ef=True, tol=1e-4):
     from paper_2210_17357_amd import binding as B
     torch = torch_cuda()
@@ -187,7 +212,7 @@ def test_range_rule_around_the_ten_percent_default():
 
 def test_unrepresentative_sample_is_corrected():
     # One 512-element chunk out of 16 holds large values and everything else small ones, or the other way round, or
-    # zeros: the sample's 32-element segments see them in whatever share they fall on, and results must not depend
+    # zeros: the sample's segments see them in whatever share they fall on, and results must not depend
     # on it.  (Layers laid out against the sample itself: test_bound_predicted_too_high_or_too_low.)
     rng = np.random.default_rng(7)
     n = 5 * 65536 + 3000
@@ -246,7 +271,7 @@ def test_results_do_not_depend_on_the_calls_before():
 
 def test_one_handle_serves_layer_tables_of_different_lengths():
     """One handle, calls whose layer tables differ in length and content, profile and compress
-    interleaved: the histograms a call leaves behind (cleared by its last scan, kept between
+    interleaved: the histograms a call leaves behind (cleared by the kernel behind the search, kept between
     calls) must never leak into a later call with more layers.  Every result is checked against the oracle."""
     from paper_2210_17357_amd import binding as B
     torch = torch_cuda()
@@ -327,23 +352,20 @@ def test_compress_calls_queued_back_to_back():
     h.close()
 
 
-@pytest.mark.parametrize("n", [16384, 16385, 300000, (1 << 20) + 3])
+@pytest.mark.parametrize("n", [8192, 8193, 16385, 300000, (1 << 20) + 3])
 def test_bound_predicted_too_high_or_too_low(n):
-    """Layers laid out against the sample (512 segments of 32 elements at scrambled places; a layer of
-    at most 16384 elements is taken whole): all large entries where it looks (the predicted
-    collection bound lies above the thresholds and the layer is collected again), or none of them
+    """Layers laid out against the sample: all large entries where it looks (the predicted
+    collection bound lies above the thresholds and the layer is collected again; of 8192 it looks at all, of 8193 at
+    all but one, and nothing fools it), or none of them
     (nearly everything is a candidate).  Profile and compression against the oracle."""
     rng = np.random.default_rng(n)
-    seg = np.arange(512, dtype=np.uint64)
-    stride = max(n // 512, 32)
-    first = seg * stride + (((seg * 2654435761) % (1 << 32)) * (stride - 31) >> np.uint64(32))
-    seen = (first[:, None] + np.arange(32, dtype=np.uint64)).reshape(-1).astype(np.int64)
-    sampled = np.zeros(n, bool)
-    sampled[seen[seen < n]] = True
+    sampled = _sampled(n, 16)
     big = rng.laplace(0, 1.0, n).astype(np.float32)
     small = rng.laplace(0, 1e-3, n).astype(np.float32)
     a = np.where(sampled, big, small).astype(np.float32)
     b = np.where(sampled, small, big).astype(np.float32)
+    assert sampled.sum() == 8192 and _predicts_too_high(a, sampled, 0.5) == (n > 8193)
+    assert not _predicts_too_high(b, sampled, 0.5)
     _check(_flat_batch([a, b]), (0.001, 0.01, 0.1, 0.5))
 
 
@@ -352,14 +374,13 @@ def test_more_densities_than_one_column_each(count):
     """Past 8 densities the profile resolves them per distinct threshold bin, in chunks of 8: from one bin for
     all (constant, zero) to one for each (values over 40 octaves), one entry to several work items,
     duplicates of a density, ties that need the exact route for several densities of one sub-bin, and a layer
-    whose sample misses its large entries."""
+    all of whose large entries are in its sample, which is collected again."""
     rng = np.random.default_rng(count)
     n = 300000
-    seg = np.arange(512, dtype=np.uint64)
-    first = seg * (n // 512) + (((seg * 2654435761) % (1 << 32)) * (n // 512 - 31) >> np.uint64(32))
-    seen = (first[:, None] + np.arange(32, dtype=np.uint64)).reshape(-1).astype(np.int64)
+    seen = _sampled(n, 16)
     fooled = rng.laplace(0, 1e-3, n).astype(np.float32)
-    fooled[seen] = rng.laplace(0, 1.0, seen.size)
+    fooled[seen] = rng.laplace(0, 1.0, int(seen.sum()))
+    assert _predicts_too_high(fooled, seen, 0.4)                   # (the largest density's bound)
     ties = rng.integers(-3, 4, 30000).astype(np.float32)
     near = np.where(rng.random(50000) < 0.3, np.float32(1.0) + np.float32(2.0 ** -23) * rng.integers(0, 400, 50000),
                     rng.laplace(0, 1e-2, 50000)).astype(np.float32)
@@ -464,7 +485,8 @@ def test_places_in_a_layer_of_more_tiles_than_a_workgroup_adds_up(one_call):
 @pytest.mark.parametrize("case", ["tiny layers", "ties", "tile edges", "large sample"])
 def test_thresholds_found_where_they_are_used(case):
     """Every workgroup finds the bins and thresholds of its layers itself: four layers in one batch of tiles, every entry
-    equal, layers at the edges of tiles and work items, and the sample of large calls.  The handle's counts have to be zero
+    equal, layers at the edges of tiles and work items, and the sample of large calls, with a layer that it predicts
+    wrongly and layers at the edge of being taken whole.  The handle's counts have to be zero
     again behind each call, whichever way it compressed."""
     from paper_2210_17357_amd import binding as B
     torch = torch_cuda()
@@ -478,7 +500,11 @@ def test_thresholds_found_where_they_are_used(case):
     elif case == "tile edges":
         arrays = [rng.standard_normal(n).astype(np.float32) for n in (8191, 8192, 8193, 32768, 32769, 600001, 16384)]
     else:
-        arrays = [rng.standard_normal((1 << 26) + 3).astype(np.float32), rng.standard_normal(16385).astype(np.float32)]
+        large = rng.standard_normal((1 << 26) + 3).astype(np.float32)
+        seen = _sampled(large.size, 32)
+        large[~seen] *= np.float32(1e-3)
+        assert seen.sum() == 16384 and _predicts_too_high(large, seen, 0.01)
+        arrays = [large, rng.standard_normal(16385).astype(np.float32), rng.standard_normal(16384).astype(np.float32)]
         densities = (0.01,)
     batch = _flat_batch(arrays)
     _check(batch, densities)
