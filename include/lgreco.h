@@ -36,7 +36,10 @@
  *     numerical results (never a fault).
  *   - Gradients of all layers live in one flat fp32 buffer; layer l is the range
  *     [offset, offset + numel).  Ranges must not overlap.  A layer may start at any
- *     element; starts at multiples of 4 elements are up to a tenth faster.
+ *     element; what helps is whole 128-byte lines.  Calls on 67 M elements whose layers all start at
+ *     multiples of 32 elements take 8 to 12 % less time (quantization, Top-K) than the same layers 1 or 4
+ *     elements further on, and low rank, where rows are multiples of 32 elements too, 19 to 21 %; a start
+ *     at a multiple of 4 alone gains nothing.
  */
 #ifndef LGRECO_H
 #define LGRECO_H
