@@ -108,7 +108,7 @@ __device__ __forceinline__ const float* matrix_of(const LrParams& p, const LrLay
 // wavefront touches; the 32 x 64 chunk of Q0, shared by the four, is staged behind a barrier (two buffers).
 // MFMA step (i, u) contracts the columns 8 i + u and 8 i + 4 + u of the chunk, so that a lane's four values of an i
 // are one 128-bit read of its row; rows are 36 words apart, 16 lanes of such a read on different banks.
-// 67 M elements of 66 matrices: 165 us, 4.9 TB/s of g, e and x (190 with a lane loading and storing 16 consecutive elements
+// 67 M elements of 66 matrices: 165 us, 4.9 TB/s of g, e and x (5.5 of the 913 MB that the counters see, with P and Q; 190 with a lane loading and storing 16 consecutive elements
 // of its own row, 64 pieces of lines an instruction).  Rows off 16-byte alignment take the same path: 73 M
 // elements of odd widths 1905 us a step, 811 with both contractions so (four scalar loads a lane before).
 // HAS_E: x = g + e is formed here and written to LrParams::x.
@@ -832,7 +832,7 @@ __device__ __forceinline__ void emit_known(const LrParams& p, int block) {
 // Bound by HBM: x once in, e' once out.  A workgroup takes 64 rows over a span of columns, 64 columns at a time, each
 // wavefront a 32 x 32 quadrant; where every row piece of 32 elements is a whole line (LrLayer::tall, sender only) 128 rows,
 // 32 columns at a time, the wavefronts below each other: half the reads of Q, as many bytes as x otherwise, for the
-// same lines of x (67 M elements: 131 -> 117 us behind a profile, 127 -> 123 in a compression; off the lines 64 columns
+// same lines of x (the caches served most of them: 405 -> 395 MB fetched from HBM, 268 of them x; 67 M elements: 131 -> 117 us behind a profile, 127 -> 123 in a compression; off the lines 64 columns
 // at a time cut fewer lines in two, 73 M elements of odd widths 781 us a step against 822, and the receiver has no x to
 // wait for, 147 us against 159).  Wavefronts on a SIMD: four behind a profile; three in a compression (four: 73 M elements 538
 // instead of 529 us, of odd widths 697 instead of 687).  Its rows of Phat are the same for the whole span and stay in registers; Q passes
