@@ -1175,8 +1175,11 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
         begin_call(h, s, LGRECO_CALL_COMPRESS);
         h->hl_uploaded.clear();
         ec->phase = h->tm->open_phase("phase_compress");
-        bool any_quant = false;
-        for (int c = 0; c < P; ++c) any_quant = any_quant || cands[c].family == LGRECO_QUANT;
+        bool any_quant = false, all_quant = true;
+        for (int c = 0; c < P; ++c) {
+            any_quant = any_quant || cands[c].family == LGRECO_QUANT;
+            all_quant = all_quant && cands[c].family == LGRECO_QUANT;
+        }
         // With both families the quantized layers' one kernel goes to the second stream: the Top-K
         // layers' part is one pass over the candidates and a handful of short kernels that leave
         // most of the chip idle, and the two parts write disjoint layers (error feedback and
@@ -1201,7 +1204,8 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
         if (any_quant) {
             Section sec(h->tm, "quant_compress", true);
             HIPCHK(launch_quant_compress(ec->x_in_e ? nullptr : d_grads, ec->d_ef, h->d_layers, h->d_tiles,
-                                         (int)h->ht.size(), ec->d_payload, h->cfg.stochastic != 0, h->cfg.seed,
+                                         (int)h->ht.size(), h->tile_elems, all_quant ? h->total_elems : 0, h->total_elems,
+                                         ec->d_payload, h->cfg.stochastic != 0, h->cfg.seed,
                                          beside ? h->side : s, &sec, beside ? 30 * 1024 : 0));
         }
         if (beside) {
@@ -1333,6 +1337,7 @@ static int compress_impl(lgreco_handle_t* h, const float* d_grads, float* d_ef, 
     int st = prepare_layers(h, layers, L);
     if (st != LGRECO_OK) return st;
     bool any[3] = {false, false, false};
+    int64_t elems[3] = {0, 0, 0};
     for (int l = 0; l < L; ++l) {
         if (choice[l] < 0 || choice[l] >= P) return LGRECO_EINVAL;
         const lgreco_cand_t& c = cands[choice[l]];
@@ -1344,6 +1349,7 @@ static int compress_impl(lgreco_handle_t* h, const float* d_grads, float* d_ef, 
         d.payload = offsets[l];
         d.iparam = (c.family == LGRECO_TOPK) ? (int32_t)topk_k(layers[l].numel, c.param) : (int32_t)c.param;
         any[c.family] = true;
+        elems[c.family] += layers[l].numel;
     }
     if (any[LGRECO_LOWRANK] && !d_q) return LGRECO_EINVAL;
     // the solver kernel wrote these very records into the device's table (same tables, same
@@ -1359,7 +1365,8 @@ static int compress_impl(lgreco_handle_t* h, const float* d_grads, float* d_ef, 
     if (x_in_e && any[LGRECO_LOWRANK]) return LGRECO_EINVAL;      // never set together (see the one-call entry point)
     if (any[LGRECO_QUANT] && !quant_done) {
         Section sec(h->tm, "quant_compress", true);
-        HIPCHK(launch_quant_compress(x_in_e ? nullptr : d_grads, d_ef, h->d_layers, h->d_tiles, n_tiles, d_payload,
+        HIPCHK(launch_quant_compress(x_in_e ? nullptr : d_grads, d_ef, h->d_layers, h->d_tiles, n_tiles, h->tile_elems,
+                                     elems[LGRECO_QUANT], h->total_elems, d_payload,
                                      h->cfg.stochastic != 0, h->cfg.seed, s, &sec));
     }
     if (any[LGRECO_TOPK] && !(quant_done && ec->topk_known)) {
@@ -1425,6 +1432,7 @@ int lgreco_decompress(lgreco_handle_t* h, const uint8_t* d_payload, const int64_
     int st = prepare_layers(h, layers, L);
     if (st != LGRECO_OK) return st;
     bool any[3] = {false, false, false};
+    int64_t elems[3] = {0, 0, 0};
     for (int l = 0; l < L; ++l) {
         if (choice[l] < 0 || choice[l] >= P) return LGRECO_EINVAL;
         const lgreco_cand_t& c = cands[choice[l]];
@@ -1436,11 +1444,12 @@ int lgreco_decompress(lgreco_handle_t* h, const uint8_t* d_payload, const int64_
         d.payload = offsets[l];
         d.iparam = (c.family == LGRECO_TOPK) ? (int32_t)topk_k(layers[l].numel, c.param) : (int32_t)c.param;
         any[c.family] = true;
+        elems[c.family] += layers[l].numel;
     }
     st = upload_layers(h, s, true);
     if (st != LGRECO_OK) return st;
-    HIPCHK(launch_decode(d_payload, h->d_layers, h->d_tiles, (int)h->ht.size(), d_out, accumulate != 0,
-                         any[LGRECO_QUANT], any[LGRECO_TOPK], h->tm, s));
+    HIPCHK(launch_decode(d_payload, h->d_layers, h->d_tiles, (int)h->ht.size(), h->tile_elems, elems[LGRECO_QUANT], h->total_elems, d_out,
+                         accumulate != 0, any[LGRECO_TOPK], h->tm, s));
     if (any[LGRECO_LOWRANK])
         HIPCHK(lowrank_decompress(&h->lowrank, h->hl.data(), L, h->cfg.r_max, d_payload, d_out, accumulate != 0,
                                   h->tm, s));

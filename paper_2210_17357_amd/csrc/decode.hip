@@ -19,20 +19,23 @@ struct DecodeParams {
     const Tile* tiles;
     float* out;
     int32_t accumulate;
+    int32_t part_shift;        // a tile's workgroups, as a power of two
+    int32_t part_elems;        // elements of a workgroup
 };
 
 // Bound by HBM, a stream of code words, one of the output's old values and one of its new ones.  A thread takes
 // 4 consecutive elements, so that a wavefront's accesses of the output are whole lines, and their 4 * bits
 // code bits from the one or two aligned words that hold them (a bucket starts on a word: 16 * bits bytes behind
-// payloads aligned to 16 and 8 bytes a bucket); kDepth of these are fetched before the first is used.
-// Ragged ends take an element per thread.  Adding 355 M elements of 4 bits to the
-// output: 580 us, 5.2 TB/s (690 when a thread took 8 elements, loaded their bits byte by byte and touched
-// half a line per instruction, one group at a time).
-constexpr int kDepth = 4;
+// payloads aligned to 16 and 8 bytes a bucket).  A workgroup is over after kDecodePart elements, two
+// rounds: short workgroups keep the chip's accesses in a narrow window of memory (see quant_compress_kernel).  Ragged ends
+// take an element per thread.  Adding 355 M elements of 4 bits to the output: 480 us, 6.3 TB/s (one round
+// 487, four 528, two with both rounds' loads ahead 492; 578 with tiles of 32768 and four rounds ahead).
+constexpr int kDecodePart = 2048;
 
 template <bool ACCUMULATE>
 __global__ __launch_bounds__(kThreads) void quant_decode_kernel(DecodeParams p) {
-    const Tile t = p.tiles[blockIdx.x];
+    const Tile t = p.tiles[blockIdx.x >> p.part_shift];
+    const int part = (int)(blockIdx.x & ((1u << p.part_shift) - 1u));
     const DevLayer L = p.layers[t.layer];
     if (L.family != LGRECO_QUANT) return;
     const int bits = L.iparam;
@@ -45,7 +48,7 @@ __global__ __launch_bounds__(kThreads) void quant_decode_kernel(DecodeParams p) 
 
     if (t.fast) {                                        // full buckets only
         const uint32_t* const words = reinterpret_cast<const uint32_t*>(codes);
-        const int nq = t.count / 4;
+        const int nq = min(t.count, (part + 1) * p.part_elems) / 4;
         const auto decode = [&](int q, uint32_t w0, uint32_t w1, float2 mu, float4 old) {
             const uint32_t v = __builtin_amdgcn_alignbit(w1, w0, (uint32_t)(4 * bits * q) & 31u);
             float4 x;
@@ -60,26 +63,11 @@ __global__ __launch_bounds__(kThreads) void quant_decode_kernel(DecodeParams p) 
         const auto word0 = [&](int q) { return words[(uint32_t)(4 * bits * q) >> 5]; };
         const auto word1 = [&](int q) { return words[(uint32_t)(4 * bits * (q + 1) - 1) >> 5]; };
         const float4 zero = make_float4(0.f, 0.f, 0.f, 0.f);
-        int q = tid;
-        for (; q + (kDepth - 1) * kThreads < nq; q += kDepth * kThreads) {
-            uint32_t w0[kDepth], w1[kDepth];
-            float2 mu[kDepth];
-            float4 old[kDepth];
-#pragma unroll
-            for (int u = 0; u < kDepth; ++u) {
-                const int qu = q + u * kThreads;
-                w0[u] = word0(qu);
-                w1[u] = word1(qu);
-                mu[u] = meta[qu / (kBucket / 4)];
-                old[u] = ACCUMULATE ? load_stream(out + 4 * qu) : zero;
-            }
-#pragma unroll
-            for (int u = 0; u < kDepth; ++u) decode(q + u * kThreads, w0[u], w1[u], mu[u], old[u]);
-        }
-        for (; q < nq; q += kThreads)
+        for (int q = part * p.part_elems / 4 + tid; q < nq; q += kThreads)
             decode(q, word0(q), word1(q), meta[q / (kBucket / 4)], ACCUMULATE ? load_stream(out + 4 * q) : zero);
         return;
     }
+    if (part) return;                                    // (less than a chunk)
     // a code lies in one byte or two; a short bucket's stream ends with the byte of its last code
     const auto low = [&](int i) { return (uint32_t)codes[(uint32_t)(bits * i) >> 3]; };
     const auto high = [&](int i) { return (uint32_t)codes[(uint32_t)(bits * i + bits - 1) >> 3]; };
@@ -88,23 +76,7 @@ __global__ __launch_bounds__(kThreads) void quant_decode_kernel(DecodeParams p) 
         const float x = __builtin_fmaf((float)code, mu.y, mu.x);
         out[i] = ACCUMULATE ? old + x : x;
     };
-    int i = tid;
-    for (; i + (kDepth - 1) * kThreads < t.count; i += kDepth * kThreads) {
-        uint32_t lo[kDepth], hi[kDepth];
-        float2 mu[kDepth];
-        float old[kDepth];
-#pragma unroll
-        for (int u = 0; u < kDepth; ++u) {
-            const int iu = i + u * kThreads;
-            lo[u] = low(iu);
-            hi[u] = high(iu);
-            mu[u] = meta[iu / kBucket];
-            old[u] = ACCUMULATE ? out[iu] : 0.0f;
-        }
-#pragma unroll
-        for (int u = 0; u < kDepth; ++u) decode(i + u * kThreads, lo[u], hi[u], mu[u], old[u]);
-    }
-    for (; i < t.count; i += kThreads) decode(i, low(i), high(i), meta[i / kBucket], ACCUMULATE ? out[i] : 0.0f);
+    for (int i = tid; i < t.count; i += kThreads) decode(i, low(i), high(i), meta[i / kBucket], ACCUMULATE ? out[i] : 0.0f);
 }
 
 // Top-K, first kernel (only when the image replaces the output): zero the layer.
@@ -139,7 +111,9 @@ __global__ __launch_bounds__(kThreads) void topk_decode_scatter_kernel(DecodePar
 }
 
 // Gradient accumulation between two runs of the algorithm (section "Implementation": per-layer
-// gradients are accumulated in auxiliary buffers in between runs).  acc = g or acc += g, fp32.
+// gradients are accumulated in auxiliary buffers in between runs).  acc = g or acc += g, fp32.  Bound by HBM; a
+// thread takes 4 elements and is done (see quant_compress_kernel), beyond 2^30 elements as often as it takes: 355 M
+// elements added 937 -> 673 us a call, copied 588 -> 449 (against 4096 workgroups that stride).
 __global__ __launch_bounds__(kThreads) void accumulate_kernel(float* __restrict__ acc, const float* __restrict__ g,
                                                               int64_t n, int reset) {
     const int64_t n4 = n / 4;
@@ -160,19 +134,25 @@ __global__ __launch_bounds__(kThreads) void accumulate_kernel(float* __restrict_
 
 hipError_t launch_accumulate(float* acc, const float* g, int64_t n, bool reset, hipStream_t s, Section* sec) {
     if (n <= 0) return hipSuccess;
-    const int64_t blocks = std::min<int64_t>((n / 4 + kThreads - 1) / kThreads + 1, 256 * 16);
+    const int64_t blocks = std::min<int64_t>((n / 4 + kThreads - 1) / kThreads + 1, 1 << 20);
     launch_timed(sec, true, true, accumulate_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s, acc, g, n, reset ? 1 : 0);
     return hipGetLastError();
 }
 
-hipError_t launch_decode(const uint8_t* payload, const DevLayer* layers, const Tile* tiles, int n_tiles,
-                         float* out, bool accumulate, bool any_quant, bool any_topk, Timing* tm, hipStream_t s) {
+hipError_t launch_decode(const uint8_t* payload, const DevLayer* layers, const Tile* tiles, int n_tiles, int tile_elems,
+                         int64_t quantized, int64_t total, float* out, bool accumulate, bool any_topk, Timing* tm, hipStream_t s) {
     if (n_tiles <= 0) return hipSuccess;
-    DecodeParams p{payload, layers, tiles, out, accumulate ? 1 : 0};
-    if (any_quant) {
+    DecodeParams p{payload, layers, tiles, out, accumulate ? 1 : 0, 0, 0};
+    if (quantized > 0) {
+        // longer ones where most of the workgroups would only find that their layer is another family's (see
+        // launch_quant_compress)
+        DecodeParams q = p;
+        q.part_elems = 4 * quantized >= 3 * total ? kDecodePart : 4 * kDecodePart;
+        while ((tile_elems >> q.part_shift) > q.part_elems) ++q.part_shift;
+        const dim3 grid((unsigned)n_tiles << q.part_shift);
         Section sec(tm, "quant_decode", true);
-        if (accumulate) launch_timed(&sec, true, true, quant_decode_kernel<true>, dim3(n_tiles), dim3(kThreads), 0, s, p);
-        else launch_timed(&sec, true, true, quant_decode_kernel<false>, dim3(n_tiles), dim3(kThreads), 0, s, p);
+        if (accumulate) launch_timed(&sec, true, true, quant_decode_kernel<true>, grid, dim3(kThreads), 0, s, q);
+        else launch_timed(&sec, true, true, quant_decode_kernel<false>, grid, dim3(kThreads), 0, s, q);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

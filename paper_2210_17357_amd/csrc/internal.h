@@ -123,9 +123,9 @@ inline void launch_timed(Section* sec, bool first, bool last, void (*kernel)(P..
 hipError_t launch_quant_profile(const QuantParams& p, int n_tiles, bool hist, hipStream_t s, Section* sec);
 hipError_t launch_reduce_partials(const double* partials, int stride, const int* cols, int ncols,
                                   const DevLayer* layers, int n_layers, double* errors, hipStream_t s);
-hipError_t launch_quant_compress(const float* g, float* e, const DevLayer* layers, const Tile* tiles,
-                                 int n_tiles, uint8_t* payload, bool stochastic, uint64_t seed,
-                                 hipStream_t s, Section* sec, size_t lds_pad = 0);   // lds_pad: LDS bytes requested and not used
+hipError_t launch_quant_compress(const float* g, float* e, const DevLayer* layers, const Tile* tiles, int n_tiles,
+                                 int tile_elems, int64_t quantized, int64_t total, uint8_t* payload, bool stochastic,
+                                 uint64_t seed, hipStream_t s, Section* sec, size_t lds_pad = 0);   // lds_pad: LDS bytes requested and not used
 
 // ---- dp.hip
 struct DpEntry {            // one usable candidate of a layer (equal bins merged by the host)
@@ -336,7 +336,8 @@ hipError_t lowrank_decompress(LowrankScratch* t, const DevLayer* h_layers, int L
 
 // ---- decode.hip: receiver side of quantization and Top-K, gradient accumulation
 hipError_t launch_accumulate(float* acc, const float* g, int64_t n, bool reset, hipStream_t s, Section* sec);
-hipError_t launch_decode(const uint8_t* payload, const DevLayer* layers, const Tile* tiles, int n_tiles,
-                         float* out, bool accumulate, bool any_quant, bool any_topk, Timing* tm, hipStream_t s);
+// quantized: elements of the quantized layers, of total
+hipError_t launch_decode(const uint8_t* payload, const DevLayer* layers, const Tile* tiles, int n_tiles, int tile_elems,
+                         int64_t quantized, int64_t total, float* out, bool accumulate, bool any_topk, Timing* tm, hipStream_t s);
 
 }  // namespace lgreco

@@ -286,13 +286,24 @@ struct QuantCompressParams {
     const Tile* tiles;
     uint8_t* payload;
     uint32_t seed_lo, seed_hi;
+    int32_t part_shift;        // a tile's workgroups, as a power of two
+    int32_t part_chunks;       // chunks of a workgroup
 };
 
-template <bool STOCH>
-__global__ __launch_bounds__(kThreads) void quant_compress_kernel(QuantCompressParams p) {
-    __shared__ uint32_t s_codes[kThreads / 64][4 * 16 * 8 / 4];   // 4 buckets x (16*8 bytes) per wave
+// Bound by HBM.  What it reaches there depends on how long a wavefront lives: short ones are started in the order of
+// the addresses, so that the whole chip works on a narrow window that moves through memory, while wavefronts that each
+// walk a stretch of their own drift apart over a hundred times as much.  The bare x = g + e on 355 M elements: 642 us
+// with 256 elements a wavefront, 671 with 512, 756 with 8192 (also where persistent workgroups walk the window
+// together: 740-800).  So a workgroup is one wavefront and one chunk of 512 elements: 4 bits a value, 355 M elements,
+// 852 -> 720 us, 6.2 TB/s (four wavefronts of a chunk each 750, of two 785, of four 805).  Two cases keep workgroups
+// of four wavefronts (see launch_quant_compress): the random numbers of stochastic rounding, and calls in which
+// most of the workgroups only find that their layer is not theirs.
+template <bool STOCH, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void quant_compress_kernel(QuantCompressParams p) {
+    __shared__ uint32_t s_codes[WAVES][4 * 16 * 8 / 4];   // 4 buckets x (16*8 bytes) per wave
 
-    const Tile t = p.tiles[blockIdx.x];
+    const Tile t = p.tiles[blockIdx.x >> p.part_shift];
+    const int part = (int)(blockIdx.x & ((1u << p.part_shift) - 1u));
     const DevLayer L = p.layers[t.layer];
     if (L.family != LGRECO_QUANT) return;
     const int bits = L.iparam;
@@ -311,9 +322,8 @@ __global__ __launch_bounds__(kThreads) void quant_compress_kernel(QuantCompressP
     if (t.fast) {
         const int j = lane & 15, row = lane >> 4;
         uint8_t* const sc = reinterpret_cast<uint8_t*>(s_codes[wave]);
-        int c_begin, c_end;
-        wave_range(t.count / kChunk, wave, &c_begin, &c_end);
-        for (int c = c_begin; c < c_end; ++c) {
+        const int c_end = min(t.count / kChunk, (part + 1) * p.part_chunks);
+        for (int c = part * p.part_chunks + wave; c < c_end; c += WAVES) {
             const int base = c * kChunk + row * kBucket + j * 4;
             float4 a = load_stream(e + base);
             float4 b = load_stream(e + base + 64);
@@ -380,11 +390,10 @@ __global__ __launch_bounds__(kThreads) void quant_compress_kernel(QuantCompressP
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
     } else {
+        if (part) return;                               // (less than a chunk)
         uint32_t* const sw = s_codes[wave];
         const int nb = (t.count + kBucket - 1) / kBucket;
-        int b_begin, b_end;
-        wave_range(nb, wave, &b_begin, &b_end);
-        for (int bk = b_begin; bk < b_end; ++bk) {
+        for (int bk = wave; bk < nb; bk += WAVES) {
             const int cnt = min(kBucket, t.count - bk * kBucket);
             for (int d = lane; d < 32; d += 64) sw[d] = 0;          // 128 elements x 8 bits max
             float x[2];
@@ -474,15 +483,27 @@ hipError_t launch_reduce_partials(const double* partials, int stride, const int*
     return hipGetLastError();
 }
 
-hipError_t launch_quant_compress(const float* g, float* e, const DevLayer* layers, const Tile* tiles,
-                                 int n_tiles, uint8_t* payload, bool stochastic, uint64_t seed,
-                                 hipStream_t s, Section* sec, size_t lds_pad) {
+// quantized: elements of the layers that take part, of total; where only the device knows, the least that may be.
+// A workgroup that finds its layer taken by another family costs about 0.2 ns: with a quarter of 355 M elements quantized
+// workgroups of 2048 elements (133 k of which do nothing) take 30 us of a step more than those of 8192, which lose 7 % on
+// what they do compress (one chunk each loses more).  So the short ones are for calls in which most of them have work.  Stochastic rounding
+// computes as long as it waits for memory (20 vector multiplications a word): 11.7 M elements 22 us with two
+// chunks a wavefront, 24 with one.
+hipError_t launch_quant_compress(const float* g, float* e, const DevLayer* layers, const Tile* tiles, int n_tiles,
+                                 int tile_elems, int64_t quantized, int64_t total, uint8_t* payload, bool stochastic,
+                                 uint64_t seed, hipStream_t s, Section* sec, size_t lds_pad) {
     if (n_tiles <= 0) return hipSuccess;
-    QuantCompressParams p{g, e, layers, tiles, payload, (uint32_t)seed, (uint32_t)(seed >> 32)};
+    QuantCompressParams p{g, e, layers, tiles, payload, (uint32_t)seed, (uint32_t)(seed >> 32), 0, 0};
+    const bool most = quantized >= total - total / 4;
+    p.part_chunks = !most ? 16 : stochastic ? 8 : 1;
+    while ((tile_elems >> p.part_shift) > p.part_chunks * kChunk) ++p.part_shift;
+    const dim3 grid((unsigned)n_tiles << p.part_shift);
     if (stochastic)
-        launch_timed(sec, true, true, quant_compress_kernel<true>, dim3(n_tiles), dim3(kThreads), lds_pad, s, p);
+        launch_timed(sec, true, true, quant_compress_kernel<true, 4>, grid, dim3(256), lds_pad, s, p);
+    else if (most)
+        launch_timed(sec, true, true, quant_compress_kernel<false, 1>, grid, dim3(64), lds_pad, s, p);
     else
-        launch_timed(sec, true, true, quant_compress_kernel<false>, dim3(n_tiles), dim3(kThreads), lds_pad, s, p);
+        launch_timed(sec, true, true, quant_compress_kernel<false, 4>, grid, dim3(256), lds_pad, s, p);
     return hipGetLastError();
 }
 
