@@ -13,8 +13,8 @@
 //                       every rank's error)
 //   compress: payload Phat[:, :r], Q[:, :r];  e' = X - Phat[:, :r] Q[:, :r]^T
 //
-// The two contractions and the reconstruction use v_mfma_f32_32x32x2f32 (fp32 in, fp32
-// accumulate).  Operand layout of that instruction, lane l of 64:
+// P = X Q0 and the reconstruction use v_mfma_f32_32x32x2f32 (fp32 in, fp32 accumulate), Q = X^T Phat the bf16
+// instruction on values cut in three (see split8).  Operand layout of the former, lane l of 64:
 //   A (32 x 2): A[i = l % 32][k = l / 32];   B (2 x 32): B[k = l / 32][j = l % 32]
 //   D (32 x 32): register v (0..15) holds D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32]
 #include <cstring>
@@ -95,6 +95,47 @@ struct LrParams {
     int32_t n_ef_tiles, n_row_tiles;     // KNOWN: workgroups behind the first n_ef_tiles fill payload and warm start
     const DevLayer* dev_layers;   // KNOWN kernels: the caller's layer records (family, rank, payload offset) on the device
 };
+
+// An address as a scalar base and a lane's byte offset, the form that costs no vector instructions.  Rows as wide as
+// kLrWide, whose offsets do not fit, take the paths of a matrix's edges.
+constexpr int kLrWide = 1 << 26;
+template <typename T>
+__device__ __forceinline__ T* at_bytes(T* base, uint32_t offset) {
+    typedef typename std::conditional<std::is_const<T>::value, const char, char>::type byte;
+    auto p = (__attribute__((address_space(1))) byte*)reinterpret_cast<byte*>(base);
+    asm("" : "+s"(p));                                       // (uniform; not to be folded into the lane's part)
+    return (T*)(p + offset);
+}
+
+// ------------------------------------------------------------------ fp32 products from bf16 pieces
+// An fp32 value is the sum of three bf16 values, exactly: its upper 16 bits (cut off, so that nothing overflows), the
+// rounded upper bits of the rest, and what is left (8 bits at most).  Of the nine products of two such sums the six that
+// reach 2^-24 of the whole are formed on v_mfma_f32_32x32x16_bf16 (products exact, fp32 accumulate).
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+struct Split8 { bf16x8 piece[3]; };                          // 8 values: largest pieces first
+__device__ __forceinline__ Split8 split8(const float* x) {
+    union { uint32_t w[4]; bf16x8 v; } h, m, l;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t u0 = __float_as_uint(x[2 * i]), u1 = __float_as_uint(x[2 * i + 1]);
+        h.w[i] = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+        const float r0 = x[2 * i] - __uint_as_float(u0 & 0xFFFF0000u), r1 = x[2 * i + 1] - __uint_as_float(u1 & 0xFFFF0000u);
+        typedef float f32x2 __attribute__((ext_vector_type(2)));
+        m.w[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{r0, r1}, bf16x2));
+        const float l0 = r0 - __uint_as_float(m.w[i] << 16), l1 = r1 - __uint_as_float(m.w[i] & 0xFFFF0000u);
+        l.w[i] = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
+    }
+    return Split8{{h.v, m.v, l.v}};
+}
+__device__ __forceinline__ f32x16 mfma_split(const Split8& a, const Split8& b, f32x16 c) {
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.piece[0], b.piece[2], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.piece[2], b.piece[0], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.piece[1], b.piece[1], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.piece[0], b.piece[1], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.piece[1], b.piece[0], c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.piece[0], b.piece[0], c, 0, 0, 0);
+}
 
 // The matrix as everything behind the first contraction reads it.
 __device__ __forceinline__ const float* matrix_of(const LrParams& p, const LrLayer& L) {
@@ -557,106 +598,81 @@ __global__ __launch_bounds__(256, 4) void lr_apply_kernel(LrParams p) {
 }
 
 // ------------------------------------------------------------------ Q partials = X^T Phat
-// One workgroup: 128 columns of X (rows of Q) over one range of its rows, X and Phat in chunks of 32 rows through LDS
-// (two buffers).  Bound by the fp32 matrix pipe (67 M elements: 89 to 100 us from box to box; the products alone take 70 at the 2.1 GHz the
-// chip holds in a burst this short).  Every load of a chunk is issued without a condition of its own and used after the
-// products of the chunk before it; rows past the range and columns past the matrix are made zero as they go to LDS.
-// Rows are clamped to the range in its last chunk only (in every chunk: 94 us instead of 89 without an error feedback).
-// (With both operands loaded straight in the layout of the instruction, no LDS and no barriers, 102-121 us: 204 registers
-// leave two wavefronts on a SIMD, too few to cover the loads.)
-__global__ __launch_bounds__(256) void lr_gemm2_kernel(LrParams p) {
-    __shared__ __align__(16) float Xs[2][kLrBK][kLrBM];
-    __shared__ __align__(16) float Ps[2][kLrBK][kLrCols];
+// One workgroup: 128 columns of X (rows of Q) over one range of its rows, 32 rows at a time; wavefront w owns columns
+// 32 w .. 32 w + 31, whose rows a lane loads straight in the layout of the instruction (two rows of 128 bytes an
+// instruction), a chunk ahead; the rows of Phat, shared by the four, go through LDS as pieces (two buffers, one barrier a chunk).
+// Products on the bf16 matrix pipe (see split8): 67 M elements 88 -> 70 us (94 -> 68 for the first passes after a pause),
+// where the fp32 products alone took 70 of the 88; now the reads of X (42 at HBM's rate), 21 us of products and 18 of vector
+// instructions (half of them splitting) overlap in part.  Its error against 64 bits is below that of the fp32 instructions (Q of
+// 8 shapes up to 32768 x 512, relative: 0.7e-7 to 4.1e-7 against 0.7e-7 to 4.8e-7, with heavy tails 1.4e-7 to 3.1e-7 against 2.1e-7 to 5.6e-7).  Splits of one
+// range are neighbours, so that workgroups that run together read whole rows.
+__global__ __launch_bounds__(256, 4) void lr_gemm2_kernel(LrParams p) {
+    __shared__ __align__(16) bf16x8 Ps[2][kLrBK / 8][3][kLrCols];       // [8 rows][piece][column]
     const LrTile tile = p.col_tiles[blockIdx.x];
     const LrLayer L = p.layers[tile.layer];
     const int m = L.rows, n = L.cols, col0 = tile.a0;
     const int kbeg = tile.split * L.ksplit, kend = min(m, kbeg + L.ksplit);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int half = lane >> 5, bj = lane & 31;
+    // columns past the matrix read its last one; their rows of Q are not written
     const float* __restrict__ X = matrix_of(p, L);
+    const int col = min(col0 + 32 * wave + bj, n - 1);
+    const uint32_t at_x = 4u * ((uint32_t)(8 * half) * (uint32_t)n + (uint32_t)col);
     const float* __restrict__ P = p.P + L.p_off;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    // this thread's columns of X: col .. col + 3, loaded `shift` columns further left where they would reach past the
-    // row's end (a matrix of fewer than 4 columns: element by element)
-    const int col = col0 + (tid & 31) * 4, from = max(min(col, n - 4), 0), shift = n >= 4 ? col - from : 0;
-    const bool cols_full = col0 + kLrBM <= n;
-    uint32_t at[4];                                          // (below 2^31, as the layer's size is)
-#pragma unroll
-    for (int s = 0; s < 4; ++s) at[s] = (uint32_t)((tid >> 5) + 8 * s) * (uint32_t)n;
 
-    float4 xr[4], pr[2];
+    float xr[16], pr[8];
     auto fetch = [&](int k0) __attribute__((always_inline)) {
-        const float* const x0 = X + (int64_t)k0 * n + from;
-        if (k0 + kLrBK <= kend && n >= 4) {                  // (uniform; nearly every chunk: nothing to work out)
+        if (k0 + kLrBK <= kend && n < kLrWide) {             // uniform: nearly every chunk
+            const float* const x0 = X + (int64_t)k0 * n;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) xr[s] = load4_any(x0 + at[s]);
+            for (int u = 0; u < 16; ++u) xr[u] = *at_bytes(x0 + (int64_t)((u & 7) + 2 * (u & 8)) * n, at_x);
+            const float* const p0 = P + (int64_t)(k0 + 8 * wave) * kLrCols;
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
-                pr[s] = *reinterpret_cast<const float4*>(P + (int64_t)(k0 + (tid >> 4) + 16 * s) * kLrCols + (tid & 15) * 4);
-            return;
-        }
-        const int last = kend - 1 - k0;                      // rows past the range read the last one
-        if (n >= 4) {                                        // (uniform)
+            for (int u = 0; u < 8; ++u) pr[u] = *at_bytes(p0 + u * kLrCols, 4u * (uint32_t)lane);
+        } else {                                             // rows past the range count as zero
 #pragma unroll
-            for (int s = 0; s < 4; ++s) xr[s] = load4_any(x0 + (uint32_t)min((tid >> 5) + 8 * s, last) * (uint32_t)n);
-        } else {
+            for (int u = 0; u < 16; ++u) {
+                const int k = k0 + 8 * half + (u & 7) + 2 * (u & 8);
+                xr[u] = X[(int64_t)min(k, kend - 1) * n + col];
+                if (k >= kend) xr[u] = 0.0f;
+            }
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const float* const row = x0 + min((tid >> 5) + 8 * s, last) * n;
-                xr[s] = make_float4(col < n ? row[col] : 0.f, col + 1 < n ? row[col + 1] : 0.f, col + 2 < n ? row[col + 2] : 0.f, 0.f);
+            for (int u = 0; u < 8; ++u) {
+                const int k = k0 + 8 * wave + u;
+                pr[u] = P[(int64_t)min(k, kend - 1) * kLrCols + lane];
+                if (k >= kend) pr[u] = 0.0f;
             }
         }
-#pragma unroll
-        for (int s = 0; s < 2; ++s)
-            pr[s] = *reinterpret_cast<const float4*>(P + (int64_t)(k0 + min((tid >> 4) + 16 * s, last)) * kLrCols + (tid & 15) * 4);
     };
-    auto stash = [&](int buf, int k0) __attribute__((always_inline)) {
-        if (!cols_full) {                                    // (uniform)
+    Split8 a[2];
+    auto take = [&](int buf) __attribute__((always_inline)) {
+        a[0] = split8(xr);
+        a[1] = split8(xr + 8);
+        const Split8 b = split8(pr);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                float4 v = xr[s];
-                v = shift == 0 ? v : shift == 1 ? make_float4(v.y, v.z, v.w, 0.f) : shift == 2 ? make_float4(v.z, v.w, 0.f, 0.f)
-                                 : shift == 3 ? make_float4(v.w, 0.f, 0.f, 0.f) : make_float4(0.f, 0.f, 0.f, 0.f);
-                xr[s] = v;
-            }
-        }
-        if (k0 + kLrBK > kend) {                             // (uniform)
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-                if (k0 + (tid >> 5) + 8 * s >= kend) xr[s] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-                if (k0 + (tid >> 4) + 16 * s >= kend) pr[s] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int f = tid + 256 * s;
-            *reinterpret_cast<float4*>(&Xs[buf][f >> 5][(f & 31) * 4]) = xr[s];
-        }
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int f = tid + 256 * s;
-            *reinterpret_cast<float4*>(&Ps[buf][f >> 4][(f & 15) * 4]) = pr[s];
-        }
+        for (int q = 0; q < 3; ++q) Ps[buf][wave][q][lane] = b.piece[q];
     };
 
     f32x16 acc0 = {0}, acc1 = {0};
     const int nchunks = (kend - kbeg + kLrBK - 1) / kLrBK;
     fetch(kbeg);
-    stash(0, kbeg);
-    __syncthreads();
-    const int ai = 32 * wave + (lane & 31), ak = lane >> 5, bj = lane & 31;
     for (int c = 0; c < nchunks; ++c) {
         const int buf = c & 1;
+        take(buf);
         if (c + 1 < nchunks) fetch(kbeg + (c + 1) * kLrBK);
+        __syncthreads();                                     // (the buffer's last readers were done before the barrier in between)
 #pragma unroll
-        for (int kk = 0; kk < kLrBK; kk += 2) {
-            const float a = Xs[buf][kk + ak][ai];
-            const float b0 = Ps[buf][kk + ak][bj];
-            const float b1 = Ps[buf][kk + ak][32 + bj];
-            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b0, acc0, 0, 0, 0);
-            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b1, acc1, 0, 0, 0);
+        for (int s = 0; s < 2; ++s) {
+            const bf16x8* const row = &Ps[buf][2 * s + half][0][bj];
+            Split8 b0, b1;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                b0.piece[q] = row[q * kLrCols];
+                b1.piece[q] = row[q * kLrCols + 32];
+            }
+            acc0 = mfma_split(a[s], b0, acc0);
+            acc1 = mfma_split(a[s], b1, acc1);
         }
-        if (c + 1 < nchunks) stash(buf ^ 1, kbeg + (c + 1) * kLrBK);
-        __syncthreads();
     }
     float* __restrict__ out = p.part + L.part_off + (int64_t)tile.split * n * kLrCols;
 #pragma unroll
@@ -1153,8 +1169,8 @@ static hipError_t lr_prepare(LowrankScratch* t, int slot, const DevLayer* hl, in
         a.tall = slot != kLrSlotDecode && a.offset % 32 == 0 && a.cols % 32 == 0 ? 1 : 0;
         for (int r0 = 0; r0 < a.rows; r0 += a.tall ? 128 : 64)
             for (int c0 = 0; c0 < a.cols; c0 += kLrEfSpan) H->ef_tiles.push_back(LrTile{li, r0, c0, 0});
-        for (int c0 = 0; c0 < a.cols; c0 += kLrBM)
-            for (int sp = 0; sp < a.splits; ++sp) H->col_tiles.push_back(LrTile{li, c0, sp, 0});
+        for (int sp = 0; sp < a.splits; ++sp)
+            for (int c0 = 0; c0 < a.cols; c0 += kLrBM) H->col_tiles.push_back(LrTile{li, c0, sp, 0});
         a.gram_begin = (int)H->gram_tiles.size();
         for (int r0 = 0; r0 < a.rows; r0 += kLrGramSpan) H->gram_tiles.push_back(LrTile{li, r0, 0, 0});
         a.gram_end = (int)H->gram_tiles.size();
@@ -1217,6 +1233,7 @@ static void lr_fill_params(LrHost* H, LrParams* p) {
     p->T = H->T;
     p->xnorm_part = H->xn;
     p->qnorm_part = H->qn;
+    p->n_ef_tiles = (int)H->ef_tiles.size();
 }
 
 // `iters` power-iteration steps: P = X Q, Phat = orth(P), Q = X^T Phat, Q feeding the next step.
@@ -1339,7 +1356,6 @@ hipError_t lowrank_compress_known(LowrankScratch* t, const float* g, float* e, c
     p.r_max = r_max;
     p.payload = payload;
     p.dev_layers = d_layers;
-    p.n_ef_tiles = (int)H->ef_tiles.size();
     p.n_row_tiles = (int)H->row_tiles.size();
     Section sec(tm, "lowrank_ef", true);
     launch_timed(&sec, true, true, lr_ef_kernel<false, true>,
