@@ -32,7 +32,6 @@ constexpr int kLrBK = 32;         // contraction chunk staged in LDS
 constexpr int kLrGramSpan = 128;  // rows per Gram partial (one workgroup)
 constexpr int kLrQChunk = 64;     // Q rows per workgroup in the split-K reduction
 constexpr int kLrPSplit = 512;    // columns contracted per workgroup in P = X Q0
-constexpr int kLrEfSpan = 512;    // columns reconstructed per workgroup
 
 struct LrLayer {
     int64_t offset;     // into g / e
@@ -51,7 +50,7 @@ struct LrLayer {
     int32_t rt_begin, rt_end;       // row-tile range (||X||^2 partials)
     int32_t qc_begin, qc_end;       // Q-chunk range (column-norm partials)
     int32_t index;      // index in the caller's layer table
-    int32_t tall;       // reconstruction: 128 rows x 32 columns at a time instead of 64 x 64 (see lr_ef_kernel)
+    int32_t lines;      // every row piece of 32 elements is a whole line (see lr_ef_kernel)
 };
 struct LrTile {
     int32_t layer, a0, split, pad;
@@ -71,7 +70,7 @@ struct LrParams {
     const LrLayer* layers;
     const LrTile* row_tiles;   // 128-row tiles (orthogonalisation)
     const LrTile* p_tiles;     // (128-row tile, column split) of P = X Q0
-    const LrTile* ef_tiles;    // (64-row tile, 512-column span) of the reconstruction
+    const LrTile* ef_tiles;    // (32 rows, 128 columns) of the reconstruction
     const LrTile* col_tiles;
     const LrTile* gram_tiles;
     const LrTile* q_chunks;
@@ -845,29 +844,27 @@ __device__ __forceinline__ void emit_known(const LrParams& p, int block) {
 // of the profile's rank-64 run, still in its scratch; whether the layer takes part and its rank
 // come from the layer records the solver kernel wrote.
 //
-// Bound by HBM: x once in, e' once out.  A workgroup takes 64 rows over a span of columns, 64 columns at a time, each
-// wavefront a 32 x 32 quadrant; where every row piece of 32 elements is a whole line (LrLayer::tall, sender only) 128 rows,
-// 32 columns at a time, the wavefronts below each other: half the reads of Q, as many bytes as x otherwise, for the
-// same lines of x (the caches served most of them: 405 -> 395 MB fetched from HBM, 268 of them x; 67 M elements: 131 -> 117 us behind a profile, 127 -> 123 in a compression; off the lines 64 columns
-// at a time cut fewer lines in two, 73 M elements of odd widths 781 us a step against 822, and the receiver has no x to
-// wait for, 147 us against 159).  Wavefronts on a SIMD: four behind a profile; three in a compression (four: 73 M elements 538
-// instead of 529 us, of odd widths 697 instead of 687).  Its rows of Phat are the same for the whole span and stay in registers; Q passes
-// through LDS (two buffers, one barrier per 64 columns); the product never does: an accumulator of the 32x32x2
-// instruction holds two rows of 32 consecutive columns, so x is loaded and e' stored in that layout, two
-// whole lines per instruction, whatever the layer's alignment.  x is fetched two tiles ahead, Q one.
-// Operands in LDS: row c of Q as its even columns, then its odd ones (lane half h of step i contracts column
-// 2 i + h, so four steps are one 128-bit read), 68 words apart (16 lanes of such a read on different banks).
-// On 67 M elements of 97 layers: image at the receiver 112 -> 74 us, a whole compression 516 -> 495, a one-call
-// step 570 -> 554, against factors and product staged through LDS with two barriers a tile and 16-byte accesses.
-constexpr int kLrEfPitch = kLrCols + 4;
+// Bound by HBM: x once in, e' once out.  A wavefront makes one tile of 32 x 32 and is over, a workgroup four of them
+// side by side, 512 bytes of 32 rows: short wavefronts in the order of the addresses keep the chip in a narrow window of
+// memory (a bare read and write of 67 M elements in this shape 84 us; 100 with workgroups that walk 512 columns of
+// 128 rows, 32 at a time, as here before; 105 with 128 rows of 32 columns).  The factors come from the caches straight in the layout of the
+// instruction; 16 consecutive workgroups run on one XCD and share their rows of them in its L2.  x is loaded and e' stored in the accumulator's
+// layout (two rows of 128 bytes an instruction), past the caches where those are whole lines: e' left in them as it is written out
+// costs the next call's first pass 30 us.  Four wavefronts on a SIMD or more (at three as many bytes are in flight as the latency covers, at six registers spill).
+// 67 M elements of 97 layers: compression 125 -> 98 us, behind a profile 120 -> 113, receiver 124 -> 103 a call (adding; 79 -> 62
+// replacing); 73 M elements of odd widths: a step 818 -> 700 with lr_gemm2_kernel's part (47), receiver 178 -> 133.
+constexpr int kLrEfRows = 32, kLrEfCols = 128;
+enum { kLrEfEdge, kLrEfPieces, kLrEfLines };
 template <bool DECODE, bool KNOWN = false>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KNOWN ? 4 : 3, KNOWN ? 4 : 3))) void lr_ef_kernel(LrParams p) {
-    __shared__ __align__(16) float Qs[2][kLrCols][kLrEfPitch];
+__global__ __launch_bounds__(256, 4) void lr_ef_kernel(LrParams p) {
     if (KNOWN && (int)blockIdx.x >= p.n_ef_tiles) {
         emit_known(p, (int)blockIdx.x - p.n_ef_tiles);
         return;
     }
-    const LrTile tile = p.ef_tiles[blockIdx.x];
+    // (workgroups are dealt to the eight XCDs in turn)
+    int which = (int)blockIdx.x;
+    if (which < p.n_ef_tiles / 128 * 128) which = which / 128 * 128 + which % 8 * 16 + which % 128 / 8;
+    const LrTile tile = p.ef_tiles[which];
     const LrLayer L = p.layers[tile.layer];
     int r = L.rank;
     if (KNOWN) {
@@ -876,155 +873,125 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KNOWN ? 4 :
         r = dl.iparam;
     }
     const int m = L.rows, n = L.cols;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int half = lane >> 5, bj = lane & 31;
+    const int row0 = tile.a0, c0 = tile.split + 32 * wave;
+    if (c0 >= n) return;
     // (the buffer written may be the one read: every element is read, then written, by the same lane)
     const float* const g = DECODE ? (p.accumulate ? p.e_out + L.offset : nullptr) : matrix_of(p, L);
     float* const e = p.e_out + L.offset;
     const float* __restrict__ P =
         DECODE ? reinterpret_cast<const float*>(p.payload + L.payload) : p.P + L.p_off;
     const float* __restrict__ Q = DECODE ? P + (int64_t)m * r : p.Q + L.qs_off;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // whole lines (every row piece of 32 elements is one): the wavefronts lie below each other, else in a square
-    const bool tall = !DECODE && L.tall;
-    const int wr = tall ? wave : wave >> 1, wc = tall ? 0 : wave & 1;
-    const int half = lane >> 5, bj = 32 * wc + (lane & 31);
-    const int row0 = tile.a0, cbeg = tile.split, cend = min(n, cbeg + kLrEfSpan);
+    const int stride = DECODE ? r : kLrCols;
 
-    // A operand: step i holds column 2 i + half of this lane's row of Phat (zero from the rank on)
-    float a[kLrCols / 2];
-    {
-        const int row = row0 + 32 * wr + (lane & 31);
-        if (DECODE) {                                    // payload: r columns per row
-            const float* const src = P + (int64_t)min(row, m - 1) * r;
+    // Operands: step (i, u) contracts the columns 8 i + u and 8 i + 4 + u of the factors, so that a lane's values of an
+    // i are one 128-bit load (in a payload moved back to the row's end), zero from the rank on.
+    const float* const pa = P + (int64_t)row0 * stride;
+    const float* const pb = Q + (int64_t)c0 * stride;
+    const int at_a = min(bj, m - 1 - row0) * stride, at_b = min(bj, n - 1 - c0) * stride;
+    f32x16 acc = {0};
+    const auto fetch = [&](auto& a, auto& b, int first) __attribute__((always_inline)) {
+        constexpr int N = sizeof(a) / sizeof(a[0]);
 #pragma unroll
-            for (int i = 0; i < kLrCols / 2; ++i) a[i] = row < m && 2 * i + half < r ? src[2 * i + half] : 0.0f;
-        } else {                                         // scratch: 64 columns per row
-            const float4* const src = reinterpret_cast<const float4*>(P + (int64_t)min(row, m - 1) * kLrCols);
-#pragma unroll
-            for (int j = 0; j < kLrCols / 4; ++j) {
-                const float4 v = src[j];
-                a[2 * j] = row < m && 4 * j + half < r ? (half ? v.y : v.x) : 0.0f;
-                a[2 * j + 1] = row < m && 4 * j + 2 + half < r ? (half ? v.w : v.z) : 0.0f;
+        for (int i = 0; i < N; ++i) {
+            const int k = 8 * (first + i) + 4 * half;
+            if (DECODE && r < 4) {                           // (uniform) rows shorter than a load
+                const float* const ra = pa + at_a;
+                const float* const rb = pb + at_b;
+                a[i] = make_float4(ra[0], r > 1 ? ra[1] : 0.f, r > 2 ? ra[2] : 0.f, 0.f);
+                b[i] = make_float4(rb[0], r > 1 ? rb[1] : 0.f, r > 2 ? rb[2] : 0.f, 0.f);
+                continue;
             }
-        }
-    }
-    // element v of an accumulator: row 8 (v / 4) + 4 half + v % 4 of the quadrant, column bj
-    // (scalar row starts and one 32-bit offset per lane: below 2^31, where it is used, as the layer's size is)
-    const int row_v = row0 + 32 * wr + 4 * half;
-    const uint32_t at_v = 4u * (uint32_t)half * (uint32_t)n + (uint32_t)bj;
-    const auto row_of = [](int v) { return 8 * (v >> 2) + (v & 3); };
-    const auto start_of = [&](int v, int c0) { return (int64_t)(row0 + 32 * wr + row_of(v)) * n + c0; };
-    const bool rows_in = row0 + 32 * wr + 32 <= m;
-    // Whole lines pass by the caches; pieces of lines don't, since their other half comes with the next tile (a
-    // compression of 9 layers of 211 x 1899: 284 us; 294 with the hint on everything).
-    // (Two copies of the loop: of a choice at each access the compiler makes one, without the hint.)
-    const auto span = [&](auto whole_lines) __attribute__((always_inline)) {
-        constexpr bool lines = decltype(whole_lines)::value;
-        constexpr int kCols = lines && !DECODE ? 32 : kLrCols;     // columns at a time
-
-        auto fetch_x = [&](float (&x)[16], int c0) __attribute__((always_inline)) {
-            if (DECODE && g == nullptr) {
-    #pragma unroll
-                for (int v = 0; v < 16; ++v) x[v] = 0.0f;
-            } else if (rows_in && c0 + kCols <= n) {
-    #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float* const src = g + start_of(v, c0) + at_v;
-                    if constexpr (lines) x[v] = __builtin_nontemporal_load(src);
-                    else x[v] = *src;
-                }
-            } else {
-    #pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    x[v] = row_v + row_of(v) < m && c0 + bj < n ? (g + start_of(v, c0))[at_v] : 0.0f;
-            }
-        };
-        float q[16];
-        auto fetch_q = [&](int c0) __attribute__((always_inline)) {
-            if (DECODE) {
-    #pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const int c = c0 + wave + 4 * u;
-                    q[u] = c < n && lane < r ? (Q + (int64_t)c * r)[lane] : 0.0f;
-                }
-            } else {
-    #pragma unroll
-                for (int u = 0; u < kCols / 16; ++u) {
-                    const int f = tid + 256 * u;
-                    const float4 w = c0 + kCols <= n || c0 + (f >> 4) < n
-                                         ? *reinterpret_cast<const float4*>(Q + (int64_t)c0 * kLrCols + 1024 * u + 4 * tid)
-                                         : make_float4(0.f, 0.f, 0.f, 0.f);
-                    q[4 * u] = w.x; q[4 * u + 1] = w.y; q[4 * u + 2] = w.z; q[4 * u + 3] = w.w;
-                }
-            }
-        };
-        auto store_q = [&](int buf) __attribute__((always_inline)) {
-            if (DECODE) {
-    #pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    Qs[buf][wave + 4 * u][(kLrCols / 2) * (lane & 1) + (lane >> 1)] = q[u];
-                }
-            } else {
-    #pragma unroll
-                for (int u = 0; u < kCols / 16; ++u) {
-                    const int f = tid + 256 * u, cc = f >> 4, k = (f & 15) * 4;
-                    *reinterpret_cast<float2*>(&Qs[buf][cc][k >> 1]) =
-                        make_float2(k < r ? q[4 * u] : 0.0f, k + 2 < r ? q[4 * u + 2] : 0.0f);
-                    *reinterpret_cast<float2*>(&Qs[buf][cc][kLrCols / 2 + (k >> 1)]) =
-                        make_float2(k + 1 < r ? q[4 * u + 1] : 0.0f, k + 3 < r ? q[4 * u + 3] : 0.0f);
-                }
-            }
-        };
-        // one tile; its x is replaced by that of the tile two further on
-        auto step = [&](float (&x)[16], int buf, int c0) __attribute__((always_inline)) {
-            store_q(buf);
-            __syncthreads();                                 // (the buffer's last readers were done before the barrier in between)
-            if (c0 + kCols < cend) fetch_q(c0 + kCols);
-            f32x16 acc = {0};
-            const float* const row = &Qs[buf][bj][(kLrCols / 2) * half];
-    #pragma unroll
-            for (int i = 0; i < kLrCols / 2; i += 4) {
-                if (2 * i < r) {
-                    const float4 b = *reinterpret_cast<const float4*>(row + i);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b.x, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i + 1], b.y, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i + 2], b.z, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i + 3], b.w, acc, 0, 0, 0);
-                }
-            }
-            float o[16];
-    #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                // zeros that are not read are still added (a gradient of -0 becomes the +0 the sum with
-                // a stored zero gives: every bit as without the promise)
-                const float xv = !DECODE && p.e_is_zero ? x[v] + 0.0f : x[v];
-                o[v] = DECODE ? xv + acc[v] : xv - acc[v];
-            }
-            if (rows_in && c0 + kCols <= n) {
-    #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    float* const dst = e + start_of(v, c0) + at_v;
-                    if constexpr (lines) __builtin_nontemporal_store(o[v], dst);
-                    else *dst = o[v];
-                }
-            } else {
-    #pragma unroll
-                for (int v = 0; v < 16; ++v)
-                    if (row_v + row_of(v) < m && c0 + bj < n) (e + start_of(v, c0))[at_v] = o[v];
-            }
-            if (c0 + 2 * kCols < cend) fetch_x(x, c0 + 2 * kCols);
-        };
-        float x0[16], x1[16];
-        fetch_q(cbeg);
-        fetch_x(x0, cbeg);
-        if (cbeg + kCols < cend) fetch_x(x1, cbeg + kCols);
-        for (int c0 = cbeg; c0 < cend; c0 += 2 * kCols) {
-            step(x0, 0, c0);
-            if (c0 + kCols < cend) step(x1, 1, c0 + kCols);
+            const int from = DECODE ? min(k, r - 4) : k;     // (not negative)
+            a[i] = load4_any(at_bytes(pa, 4u * (uint32_t)(at_a + from)));
+            b[i] = load4_any(at_bytes(pb, 4u * (uint32_t)(at_b + from)));
         }
     };
-    if (DECODE ? L.offset % 32 == 0 && n % 32 == 0 : tall) span(std::true_type());
-    else span(std::false_type());
+    const auto mask = [&](auto& a, auto& b, int first) __attribute__((always_inline)) {
+        constexpr int N = sizeof(a) / sizeof(a[0]);
+        if (8 * (first + N) <= r) return;                    // (uniform)
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int k = 8 * (first + i) + 4 * half, shift = DECODE && r >= 4 ? max(k - (r - 4), 0) : 0;
+            const auto behind = [&](float4 v) {
+                if (DECODE)
+                    v = shift == 0 ? v : shift == 1 ? make_float4(v.y, v.z, v.w, 0.f) : shift == 2 ? make_float4(v.z, v.w, 0.f, 0.f)
+                                                  : make_float4(v.w, 0.f, 0.f, 0.f);
+                return make_float4(k < r ? v.x : 0.f, k + 1 < r ? v.y : 0.f, k + 2 < r ? v.z : 0.f, k + 3 < r ? v.w : 0.f);
+            };
+            a[i] = behind(a[i]);
+            b[i] = behind(b[i]);
+        }
+    };
+    const auto multiply = [&](const auto& a, const auto& b) __attribute__((always_inline)) {
+        constexpr int N = sizeof(a) / sizeof(a[0]);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].x, b[i].x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].y, b[i].y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].z, b[i].z, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].w, b[i].w, acc, 0, 0, 0);
+        }
+    };
+    // element v of the accumulator: row 8 (v / 4) + 4 half + v % 4 of the tile, column bj
+    const auto row_of = [](int v) { return 8 * (v >> 2) + (v & 3); };
+    const auto finish = [&](auto groups, auto where, int first) __attribute__((always_inline)) {
+        constexpr bool full = decltype(where)::value != kLrEfEdge, lines = decltype(where)::value == kLrEfLines;
+        float4 a[decltype(groups)::value], b[decltype(groups)::value];
+        fetch(a, b, first);
+        asm volatile("" ::: "memory");                       // (the order of the loads)
+        // scalar row starts and one 32-bit offset per lane; at an edge the last row and column in place of what lies past
+        // them
+        const uint32_t at_v = 16u * (uint32_t)half * (uint32_t)n + 4u * (uint32_t)bj;
+        const auto at = [&](auto* base, int v) __attribute__((always_inline)) {
+            if constexpr (full) return at_bytes(base + (int64_t)(row0 + row_of(v)) * n + c0, at_v);
+            else return base + (int64_t)min(row0 + row_of(v) + 4 * half, m - 1) * n + min(c0 + bj, n - 1);
+        };
+        float x[16];
+        if (DECODE && g == nullptr) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) x[v] = 0.0f;
+        } else {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                if constexpr (lines) x[v] = __builtin_nontemporal_load(at(g, v));
+                else x[v] = *at(g, v);
+            }
+        }
+        asm volatile("" ::: "memory");
+        mask(a, b, first);
+        multiply(a, b);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            // zeros that are not read are still added (a gradient of -0 becomes the +0 the sum with
+            // a stored zero gives: every bit as without the promise)
+            const float xv = !DECODE && p.e_is_zero ? x[v] + 0.0f : x[v];
+            const float o = DECODE ? xv + acc[v] : xv - acc[v];
+            if constexpr (lines) __builtin_nontemporal_store(o, at(e, v));
+            else if (full || (row0 + row_of(v) + 4 * half < m && c0 + bj < n)) *at(e, v) = o;
+        }
+    };
+    const auto run = [&](auto where) __attribute__((always_inline)) {
+        if (r > 32) {
+            {
+                float4 a[4], b[4];
+                fetch(a, b, 0);
+                multiply(a, b);
+            }
+            finish(std::integral_constant<int, 4>(), where, 4);
+        } else if (r > 16) {
+            finish(std::integral_constant<int, 4>(), where, 0);
+        } else if (r > 8) {
+            finish(std::integral_constant<int, 2>(), where, 0);
+        } else {
+            finish(std::integral_constant<int, 1>(), where, 0);
+        }
+    };
+    // Whole lines pass by the caches; pieces of lines don't, since their other half is the next wavefront's.
+    if (row0 + 32 > m || c0 + 32 > n || n >= kLrWide) run(std::integral_constant<int, kLrEfEdge>());
+    else if (L.lines) run(std::integral_constant<int, kLrEfLines>());
+    else run(std::integral_constant<int, kLrEfPieces>());
 }
 
 // ------------------------------------------------------------------------ host side
@@ -1166,9 +1133,9 @@ static hipError_t lr_prepare(LowrankScratch* t, int slot, const DevLayer* hl, in
             for (int sp = 0; sp < a.psplits; ++sp) H->p_tiles.push_back(LrTile{li, r0, sp, 0});
         }
         a.rt_end = (int)H->p_tiles.size();
-        a.tall = slot != kLrSlotDecode && a.offset % 32 == 0 && a.cols % 32 == 0 ? 1 : 0;
-        for (int r0 = 0; r0 < a.rows; r0 += a.tall ? 128 : 64)
-            for (int c0 = 0; c0 < a.cols; c0 += kLrEfSpan) H->ef_tiles.push_back(LrTile{li, r0, c0, 0});
+        a.lines = a.offset % 32 == 0 && a.cols % 32 == 0 ? 1 : 0;
+        for (int r0 = 0; r0 < a.rows; r0 += kLrEfRows)
+            for (int c0 = 0; c0 < a.cols; c0 += kLrEfCols) H->ef_tiles.push_back(LrTile{li, r0, c0, 0});
         for (int sp = 0; sp < a.splits; ++sp)
             for (int c0 = 0; c0 < a.cols; c0 += kLrBM) H->col_tiles.push_back(LrTile{li, c0, sp, 0});
         a.gram_begin = (int)H->gram_tiles.size();
