@@ -13,7 +13,7 @@
 //                       every rank's error)
 //   compress: payload Phat[:, :r], Q[:, :r];  e' = X - Phat[:, :r] Q[:, :r]^T
 //
-// P = X Q0 and the reconstruction use v_mfma_f32_32x32x2f32 (fp32 in, fp32 accumulate), Q = X^T Phat the bf16
+// The reconstruction uses v_mfma_f32_32x32x2f32 (fp32 in, fp32 accumulate), the two contractions the bf16
 // instruction on values cut in three (see split8).  Operand layout of the former, lane l of 64:
 //   A (32 x 2): A[i = l % 32][k = l / 32];   B (2 x 32): B[k = l / 32][j = l % 32]
 //   D (32 x 32): register v (0..15) holds D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32]
@@ -143,20 +143,20 @@ __device__ __forceinline__ const float* matrix_of(const LrParams& p, const LrLay
 
 // ------------------------------------------------------------------ P = X Q0 (and ||X||^2)
 // One workgroup: 128 rows x 64 columns of P over one column range of X, 32 columns at a time; wavefront w owns rows
-// 32w .. 32w+31.  Bound by HBM (g and e in, x out).  A wavefront's loads take 8 rows of 128 bytes each, x leaves the
-// same way, and the operand (a lane holds a row) is formed through the wavefront's own LDS rows, which no other
-// wavefront touches; the 32 x 64 chunk of Q0, shared by the four, is staged behind a barrier (two buffers).
-// MFMA step (i, u) contracts the columns 8 i + u and 8 i + 4 + u of the chunk, so that a lane's four values of an i
-// are one 128-bit read of its row; rows are 36 words apart, 16 lanes of such a read on different banks.
-// 67 M elements of 66 matrices: 165 us, 4.9 TB/s of g, e and x (5.5 of the 913 MB that the counters see, with P and Q; 190 with a lane loading and storing 16 consecutive elements
-// of its own row, 64 pieces of lines an instruction).  Rows off 16-byte alignment take the same path: 73 M
-// elements of odd widths 1905 us a step, 811 with both contractions so (four scalar loads a lane before).
-// HAS_E: x = g + e is formed here and written to LrParams::x.
+// 32w .. 32w+31.  Bound by HBM where there is an e (g and e in, x out).  A wavefront's loads take 8 rows of 128 bytes each (past the caches
+// where those are whole lines), x leaves the same way, and the operand (a lane holds a row) is formed through the wavefront's own LDS rows, which no other
+// wavefront touches; the 32 x 64 chunk of Q0, shared by the four, is staged as pieces between two barriers.
+// Rows are 36 words apart, 16 lanes of a 128-bit read on different banks.  Products on the bf16 matrix pipe (see split8).
+// 67 M elements of 66 matrices: 167 -> 160 us, 5.0 TB/s of g, e and x (a bare read and write in this shape 148); without e 98 -> 79,
+// where the fp32 products alone took 70; 73 M elements of odd widths: a step 698 -> 678.  Three wavefronts on a SIMD with e: at four
+// registers spill (167 us).  A lane loading and storing 16 consecutive elements of its own row, 64 pieces of lines an instruction: 190;
+// 16 rows of 64 bytes an instruction, the operand's own layout: 175 to 250 for the bare read and write.
+// HAS_E: x = g + e is formed here and written to LrParams::x, for the caches: the passes behind read it.
 constexpr int kLrXPitch = kLrBK + 4;
 template <bool HAS_E>
-__global__ __launch_bounds__(256, 4) void lr_gemm1_kernel(LrParams p) {
+__global__ __launch_bounds__(256, HAS_E ? 3 : 4) void lr_gemm1_kernel(LrParams p) {
     __shared__ __align__(16) float Xs[4][32][kLrXPitch];
-    __shared__ __align__(16) float Qs[2][kLrBK][kLrCols];
+    __shared__ __align__(16) bf16x8 Qs[kLrBK / 8][3][kLrCols];       // [8 rows][piece][column]
     __shared__ double s_red[4];
     const LrTile tile = p.p_tiles[blockIdx.x];
     const LrLayer L = p.layers[tile.layer];
@@ -172,7 +172,6 @@ __global__ __launch_bounds__(256, 4) void lr_gemm1_kernel(LrParams p) {
     const float* __restrict__ q = qscr ? p.Q + L.qs_off : p.q0 + L.q_off;
     const int qstride = qscr ? kLrCols : p.r_max;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const bool qvec = (qstride == kLrCols) && (qscr || L.q_off % 4 == 0);
     const int half = lane >> 5, bj = lane & 31;
     // this lane's share of a chunk: rows 8 s + lane / 8 of the wavefront's, columns lc .. lc + 3.  Rows past the end
     // read the last one; nothing of theirs is written, summed or stored.
@@ -185,113 +184,101 @@ __global__ __launch_bounds__(256, 4) void lr_gemm1_kernel(LrParams p) {
         row_ok[s] = row0 + r < m;
         at[s] = (uint32_t)min(r, m - 1 - row0) * (uint32_t)n + (uint32_t)lc;
     }
-
-    float4 xg[4], xe[HAS_E ? 4 : 1], qr[2];
-    // issue the loads of one chunk (their values are first used after the MFMAs of the chunk
-    // that is being multiplied)
-    auto fetch = [&](int k0) __attribute__((always_inline)) {
-        const float* const gk = g + k0;
-        const float* const ek = HAS_E ? e + k0 : nullptr;
-        if (k0 + kLrBK <= kend) {                            // uniform
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                xg[s] = load4_any(gk + at[s]);
-                if (HAS_E) xe[s] = load4_any(ek + at[s]);
-            }
-        } else {
-            const int left = kend - k0 - lc;
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const float* const gs = gk + at[s];
-                xg[s] = make_float4(left > 0 ? gs[0] : 0.f, left > 1 ? gs[1] : 0.f, left > 2 ? gs[2] : 0.f, left > 3 ? gs[3] : 0.f);
-                if (HAS_E) {
-                    const float* const es = ek + at[s];
-                    xe[s] = make_float4(left > 0 ? es[0] : 0.f, left > 1 ? es[1] : 0.f, left > 2 ? es[2] : 0.f, left > 3 ? es[3] : 0.f);
-                }
-            }
-        }
-        if (qvec && k0 + kLrBK <= kend) {
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const int f = tid + 256 * s;
-                qr[s] = *reinterpret_cast<const float4*>(q + (int64_t)(k0 + (f >> 4)) * kLrCols + (f & 15) * 4);
-            }
-        } else {
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                const int f = tid + 256 * s;
-                const int k = k0 + (f >> 4), c = (f & 15) * 4;
-                float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (k < kend) {
-                    const float* src = q + (int64_t)k * qstride + c;
-                    if (c < qstride) v.x = src[0];
-                    if (c + 1 < qstride) v.y = src[1];
-                    if (c + 2 < qstride) v.z = src[2];
-                    if (c + 3 < qstride) v.w = src[3];
-                }
-                qr[s] = v;
-            }
-        }
-    };
-    float xsq = 0.0f;
-    // take the fetched chunk into use: x = g + e, ||x||^2, x to memory and LDS, Q0 rows to LDS
-    auto commit = [&](int buf, int k0) __attribute__((always_inline)) {
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            float4 v = xg[s];
-            if (HAS_E) { v.x += xe[s].x; v.y += xe[s].y; v.z += xe[s].z; v.w += xe[s].w; }
-            if (HAS_E && row_ok[s]) {
-                float* const xs = xo + k0 + at[s];
-                const int left = kend - k0 - lc;
-                if (k0 + kLrBK <= kend) {                    // uniform
-                    store4_any(xs, v);
-                } else {
-                    if (left > 0) xs[0] = v.x;
-                    if (left > 1) xs[1] = v.y;
-                    if (left > 2) xs[2] = v.z;
-                    if (left > 3) xs[3] = v.w;
-                }
-            }
-            *reinterpret_cast<float4*>(&Xs[wave][8 * s + (lane >> 3)][lc]) = v;
-            if (row_ok[s]) {
-                xsq = __builtin_fmaf(v.x, v.x, xsq);
-                xsq = __builtin_fmaf(v.y, v.y, xsq);
-                xsq = __builtin_fmaf(v.z, v.z, xsq);
-                xsq = __builtin_fmaf(v.w, v.w, xsq);
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const int f = tid + 256 * s;
-            *reinterpret_cast<float4*>(&Qs[buf][f >> 4][(f & 15) * 4]) = qr[s];
-        }
-    };
-
-    f32x16 acc0 = {0}, acc1 = {0};
     const int nchunks = (kend - kbeg + kLrBK - 1) / kLrBK;
-    fetch(kbeg);
-    commit(0, kbeg);
-    __syncthreads();
-    for (int c = 0; c < nchunks; ++c) {
-        const int buf = c & 1;
-        if (c + 1 < nchunks) fetch(kbeg + (c + 1) * kLrBK);
-        float4 a[4];
+    f32x16 acc0 = {0}, acc1 = {0};
+    float xsq = 0.0f;
+    // (two copies of the loop: of a choice at each access the compiler makes one, without the hint)
+    const auto span = [&](auto whole_lines) __attribute__((always_inline)) {
+        constexpr bool lines = decltype(whole_lines)::value;
+        float4 xg[4], xe[HAS_E ? 4 : 1];
+        float qr[8];
+        // issue the loads of one chunk (their values are first used after the MFMAs of the chunk
+        // that is being multiplied)
+        auto fetch = [&](int k0) __attribute__((always_inline)) {
+            const float* const gk = g + k0;
+            const float* const ek = HAS_E ? e + k0 : nullptr;
+            if (k0 + kLrBK <= kend) {                        // uniform
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = *reinterpret_cast<const float4*>(&Xs[wave][bj][8 * i + 4 * half]);
+                for (int s = 0; s < 4; ++s) {
+                    xg[s] = HAS_E && lines ? load_stream(gk + at[s]) : load4_any(gk + at[s]);
+                    if (HAS_E) xe[s] = lines ? load_stream(ek + at[s]) : load4_any(ek + at[s]);
+                }
+            } else {
+                const int left = kend - k0 - lc;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const float av = u == 0 ? a[i].x : u == 1 ? a[i].y : u == 2 ? a[i].z : a[i].w;
-                const float b0 = Qs[buf][8 * i + 4 * half + u][bj];
-                const float b1 = Qs[buf][8 * i + 4 * half + u][32 + bj];
-                acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(av, b0, acc0, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(av, b1, acc1, 0, 0, 0);
+                for (int s = 0; s < 4; ++s) {
+                    const float* const gs = gk + at[s];
+                    xg[s] = make_float4(left > 0 ? gs[0] : 0.f, left > 1 ? gs[1] : 0.f, left > 2 ? gs[2] : 0.f, left > 3 ? gs[3] : 0.f);
+                    if (HAS_E) {
+                        const float* const es = ek + at[s];
+                        xe[s] = make_float4(left > 0 ? es[0] : 0.f, left > 1 ? es[1] : 0.f, left > 2 ? es[2] : 0.f, left > 3 ? es[3] : 0.f);
+                    }
+                }
             }
+            // Q0: this wavefront's 8 rows of the chunk, a column a lane; zero past the range and the columns there are
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int k = k0 + 8 * wave + u;
+                qr[u] = k < kend && lane < qstride ? q[(int64_t)k * qstride + lane] : 0.0f;
+            }
+        };
+        // take the fetched chunk into use: x = g + e, ||x||^2, x to memory and LDS, Q0 rows to LDS
+        auto commit = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                float4 v = xg[s];
+                if (HAS_E) { v.x += xe[s].x; v.y += xe[s].y; v.z += xe[s].z; v.w += xe[s].w; }
+                if (HAS_E && row_ok[s]) {
+                    float* const xs = xo + k0 + at[s];
+                    const int left = kend - k0 - lc;
+                    if (k0 + kLrBK <= kend) {                // uniform
+                        store4_any(xs, v);
+                    } else {
+                        if (left > 0) xs[0] = v.x;
+                        if (left > 1) xs[1] = v.y;
+                        if (left > 2) xs[2] = v.z;
+                        if (left > 3) xs[3] = v.w;
+                    }
+                }
+                *reinterpret_cast<float4*>(&Xs[wave][8 * s + (lane >> 3)][lc]) = v;
+                if (row_ok[s]) {
+                    xsq = __builtin_fmaf(v.x, v.x, xsq);
+                    xsq = __builtin_fmaf(v.y, v.y, xsq);
+                    xsq = __builtin_fmaf(v.z, v.z, xsq);
+                    xsq = __builtin_fmaf(v.w, v.w, xsq);
+                }
+            }
+            const Split8 b = split8(qr);
+#pragma unroll
+            for (int t = 0; t < 3; ++t) Qs[wave][t][lane] = b.piece[t];
+        };
+        fetch(kbeg);
+        for (int c = 0; c < nchunks; ++c) {
+            const int k0 = kbeg + c * kLrBK;
+            commit(k0);
+            __syncthreads();
+            if (c + 1 < nchunks) fetch(k0 + kLrBK);
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const float4 lo = *reinterpret_cast<const float4*>(&Xs[wave][bj][16 * s + 8 * half]);
+                const float4 hi = *reinterpret_cast<const float4*>(&Xs[wave][bj][16 * s + 8 * half + 4]);
+                const float row[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                const Split8 a = split8(row);
+                const bf16x8* const col = &Qs[2 * s + half][0][bj];
+                Split8 b0, b1;
+#pragma unroll
+                for (int t = 0; t < 3; ++t) {
+                    b0.piece[t] = col[t * kLrCols];
+                    b1.piece[t] = col[t * kLrCols + 32];
+                }
+                acc0 = mfma_split(a, b0, acc0);
+                acc1 = mfma_split(a, b1, acc1);
+            }
+            __syncthreads();                                 // (the rows of Q0 are written again)
         }
-        if (c + 1 < nchunks) commit(buf ^ 1, kbeg + (c + 1) * kLrBK);
-        __syncthreads();
-    }
+    };
+    if (HAS_E && L.lines) span(std::true_type());
+    else span(std::false_type());
     float* __restrict__ P = L.psplits > 1 ? p.ppart + L.ppart_off + (int64_t)tile.split * m * kLrCols
                                           : p.P + L.p_off;
 #pragma unroll
