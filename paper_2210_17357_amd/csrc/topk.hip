@@ -190,8 +190,10 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
         p[i] = v;
 }
 
-struct RefWork {                     // one workgroup of the refinement kernels: tiles [t0, t1) of a layer
-    int32_t layer, t0, t1, pad;
+// One workgroup of the refinement kernels: tiles [t0, t1) of a layer.  Its results lie at `item`, which counts the
+// items in the order of the layers; the table itself is in the order in which they are to start (see topk_begin).
+struct RefWork {
+    int32_t layer, t0, t1, item;
 };
 
 // Lower bound of every layer's lowest threshold bin, one workgroup per layer: coarse histogram of a
@@ -843,7 +845,7 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_a_kernel(RefinePar
     for (int j = 0; j < kN; ++j) kk[j] = p.rc.ks[(size_t)l * kMaxTopk + j];
     const uint32_t used = p.rc.lo[l];
     const int64_t cand_base = p.cand_base[l];
-    const bool first_item = (int)blockIdx.x == p.work_range[l].x;
+    const bool first_item = w.item == p.work_range[l].x;
     unsigned long long* const s_cell = reinterpret_cast<unsigned long long*>(refine_smem);   // ENERGY
     uint32_t* const s_cnt = reinterpret_cast<uint32_t*>(refine_smem);                        // !ENERGY
     uint8_t* const s_tab = refine_smem + (size_t)kN * kBinsA * (ENERGY ? 8 : 4);
@@ -927,10 +929,10 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_a_kernel(RefinePar
     if (ENERGY && tid < kN) {
         double s = 0.0;
         for (int wv = 0; wv < kRefThreads / 64; ++wv) s += s_red[wv][tid];
-        p.below_part[(size_t)blockIdx.x * kMaxTopk + tid] = s;
+        p.below_part[(size_t)w.item * kMaxTopk + tid] = s;
     }
     if (ENERGY) {
-        unsigned long long* const gc = p.cell_a + (size_t)blockIdx.x * kMaxTopk * kBinsA;
+        unsigned long long* const gc = p.cell_a + (size_t)w.item * kMaxTopk * kBinsA;
         for (int i = tid; i < (int)nlists * kBinsA; i += kRefThreads) gc[i] = s_cell[i];
     } else {
         static_assert(kBinsA == kRefThreads, "a thread per cell");
@@ -1203,7 +1205,7 @@ __global__ __launch_bounds__(kRefThreads, 8) void topk_refine_many_kernel(Refine
             if ((tid & 63) == 0) s_red[tid >> 6][j] = s;
         }
         __syncthreads();
-        const size_t out = (size_t)blockIdx.x * p.room + (c0 - p.list0);
+        const size_t out = (size_t)w.item * p.room + (c0 - p.list0);
         if (tid < n) {
             double s = 0.0;
             for (int wv = 0; wv < kRefThreads / 64; ++wv) s += s_red[wv][tid];
@@ -1341,7 +1343,7 @@ __global__ __launch_bounds__(kRefThreads) void topk_refine_b_kernel(RefineParams
     }
     __syncthreads();
     const uint32_t prefix = (tbin << 10) | s_res[0];
-    if ((int)blockIdx.x == p.work_range[w.layer].x) {
+    if (w.item == p.work_range[w.layer].x) {
         static_assert(kHistBins == 4 * kRefThreads, "a 128-bit store a thread");
         reinterpret_cast<uint4*>(p.hist + (size_t)w.layer * kHistBins)[tid] = make_uint4(0u, 0u, 0u, 0u);   // for the next call
         if (tid == 0) {
@@ -1881,12 +1883,17 @@ hipError_t topk_begin(TopkScratch* t, const float* g, const float* e, const DevL
             base += h_layers[l].numel;
             for (int t0 = h_layers[l].tile_begin; t0 < h_layers[l].tile_end; t0 += group) {
                 if (nw >= t->max_work) return hipErrorInvalidValue;      // cannot happen: see max_work
-                work[nw++] = RefWork{l, t0, std::min(h_layers[l].tile_end, t0 + group), 0};
+                work[nw] = RefWork{l, t0, std::min(h_layers[l].tile_end, t0 + group), nw};
+                ++nw;
             }
         }
         wrange[l].y = nw;
         max_items = std::max(max_items, wrange[l].y - wrange[l].x);
     }
+    // Items past those that start at once: the largest first, so that what is left when the first ones end is small and
+    // the launch does not end with a few full ones (355 M elements in 292 layers, 1163 items: 89 -> 78 us).
+    if (nw > kRefSlots)
+        std::stable_sort(work, work + nw, [](const RefWork& a, const RefWork& b) { return a.t1 - a.t0 > b.t1 - b.t0; });
     t->n_work = nw;
     t->max_items = max_items;
     t->cand_has_idx = false;

@@ -1,0 +1,43 @@
+"""GPU parity of Top-K where the refinement has more work items than start at once: they run in another order than
+that of the layers."""
+import numpy as np
+import pytest
+
+from oracle import pipeline
+from paper_2210_17357_amd import workloads as W
+
+from gpu_util import rel_err, tables, to_device, torch_cuda
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("densities", ((0.01,), (0.001, 0.01, 0.1), tuple(i / 100 for i in range(1, 13))))
+@pytest.mark.parametrize("n_layers", (511, 513, 700))
+def test_more_items_than_slots(n_layers, densities):
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    rng = np.random.default_rng(n_layers)
+    sizes = rng.integers(1, 3000, n_layers)
+    sizes[::97] = rng.integers(8000, 40000, sizes[::97].size)       # several tiles, among layers of one
+    w = W.Workload("items", tuple((int(n),) for n in sizes), tuple((W.TOPK, d) for d in densities), 0, 100, "laplace",
+                   "normal0.1", (-4.0, -2.0))
+    batch = W.generate(w)
+    cands = list(w.candidates)
+    layers, ctab = tables(batch, cands)
+    g, e, _ = to_device(batch)
+    h = B.Handle(int(batch.grads.size), n_layers, len(cands))
+    errors, _ = h.profile(g, e, layers, ctab)
+    ref = pipeline.profile(batch.grads, batch.ef, batch.offsets, batch.numels, batch.rows, batch.cols, cands)
+    assert ((rel_err(errors, ref) < 1e-4) | (np.abs(errors - ref) < 1e-30)).all()
+    again, _ = h.profile(g, e, layers, ctab)
+    assert np.array_equal(errors, again)
+    choice = np.full(n_layers, len(cands) - 1, np.int32)
+    offsets = B.payload_layout(layers, ctab, choice)
+    payload = torch.zeros(int(offsets[-1]) + 16, dtype=torch.uint8, device="cuda")
+    h.compress(g, e, layers, ctab, choice, payload, offsets)
+    pay = payload.cpu().numpy()
+    for l in range(0, n_layers, 7):
+        p_ref, _, _ = pipeline.compress_layer(batch.grads, batch.ef, int(batch.offsets[l]), int(batch.numels[l]), 0, 0,
+                                              cands[choice[l]], l)
+        assert np.array_equal(pay[offsets[l]:offsets[l] + p_ref.size], p_ref), l
+    h.close()
