@@ -246,9 +246,21 @@ int check_layers(const lgreco_layer_t* layers, int32_t L) {
     return LGRECO_OK;
 }
 
-// Rebuild the tile table if the caller's layer table differs from the cached one.
-int prepare_layers(lgreco_handle* h, const lgreco_layer_t* layers, int32_t L) {
-    if ((int)h->cached.size() == L && std::memcmp(h->cached.data(), layers, sizeof(lgreco_layer_t) * L) == 0)
+// Tile size of a table of `total` elements (see kTilesFill).
+int tile_size(int64_t total, bool topk) {
+    int tile = kTile;
+    while (tile > kTileMin && total / tile < (topk && tile < kTile ? kTilesFill / 2 : kTilesFill)) tile /= 2;
+    return tile;
+}
+
+// Rebuild the tile table if the caller's layer table differs from the cached one.  A profile's sums follow the tiles
+// (what it rounds), so it also does where the cached one was cut for another kind of list; the other calls, whose results
+// do not depend on the tiles, take what is there.
+enum class Tiles { any, topk, profile, profile_topk };
+int prepare_layers(lgreco_handle* h, const lgreco_layer_t* layers, int32_t L, Tiles want) {
+    const bool topk = want == Tiles::topk || want == Tiles::profile_topk;
+    if ((int)h->cached.size() == L && std::memcmp(h->cached.data(), layers, sizeof(lgreco_layer_t) * L) == 0 &&
+        (want == Tiles::any || want == Tiles::topk || tile_size(h->total_elems, topk) == h->tile_elems))
         return LGRECO_OK;
     int st = check_layers(layers, L);
     if (st != LGRECO_OK) return st;
@@ -257,9 +269,7 @@ int prepare_layers(lgreco_handle* h, const lgreco_layer_t* layers, int32_t L) {
     for (int l = 0; l < L; ++l) total += layers[l].numel;
     if (total > h->max_elems) return LGRECO_ENOSPACE;
 
-    // tile size: see kTilesFill
-    int tile = kTile;
-    while (tile > kTileMin && total / tile < kTilesFill) tile /= 2;
+    const int tile = tile_size(total, topk);
     h->tile_elems = tile;
     h->layer_tiles = 0;
     h->hl.assign(L, DevLayer{});
@@ -739,7 +749,9 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
     if (!h || !d_grads || !layers || !cands || L <= 0 || P <= 0) return LGRECO_EINVAL;
     if (P > h->max_cands) return LGRECO_ENOSPACE;
     begin_call(h, s, LGRECO_CALL_PROFILE);
-    int st = prepare_layers(h, layers, L);
+    bool any_topk = false;
+    for (int c = 0; c < P; ++c) any_topk = any_topk || cands[c].family == LGRECO_TOPK;
+    int st = prepare_layers(h, layers, L, any_topk ? Tiles::profile_topk : Tiles::profile);
     if (st != LGRECO_OK) return st;
     // everything the profile queues, chains between the kernels included
     struct Phase {
@@ -1334,7 +1346,10 @@ static int compress_impl(lgreco_handle_t* h, const float* d_grads, float* d_ef, 
     } else {
         begin_call(h, s, LGRECO_CALL_COMPRESS);
     }
-    int st = prepare_layers(h, layers, L);
+    bool some_topk = false;
+    for (int l = 0; l < L && !some_topk; ++l)
+        some_topk = choice[l] >= 0 && choice[l] < P && cands[choice[l]].family == LGRECO_TOPK;
+    int st = prepare_layers(h, layers, L, some_topk ? Tiles::topk : Tiles::any);
     if (st != LGRECO_OK) return st;
     bool any[3] = {false, false, false};
     int64_t elems[3] = {0, 0, 0};
@@ -1429,7 +1444,7 @@ int lgreco_decompress(lgreco_handle_t* h, const uint8_t* d_payload, const int64_
     if ((uintptr_t)d_out % 16 || (uintptr_t)d_payload % 16) return LGRECO_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     begin_call(h, s, LGRECO_CALL_RECEIVE);
-    int st = prepare_layers(h, layers, L);
+    int st = prepare_layers(h, layers, L, Tiles::any);
     if (st != LGRECO_OK) return st;
     bool any[3] = {false, false, false};
     int64_t elems[3] = {0, 0, 0};

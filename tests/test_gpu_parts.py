@@ -78,3 +78,37 @@ def test_largest_tiles_give_what_the_smallest_do():
         hi = min(lo + 4_000_000 // 128 * 128, n)
         ef_part, out_part = run(lo, hi)
         assert torch.equal(ef[lo:hi], ef_part) and torch.equal(out[lo:hi], out_part), lo
+
+
+@pytest.mark.parametrize("stochastic", (False, True))
+@pytest.mark.parametrize("n", ((1 << 26) + 4096 + 512 + 77, (1 << 24) + 8192 + 4096 - 512, (1 << 24) + (1 << 20) + 3))
+def test_profile_of_parts_adds_up(n, stochastic):
+    """Tiles of 32768 and 16384 elements are profiled in parts; pieces of the same data in a handle of their own have
+    tiles of 8192.  Buckets are the same, so with deterministic rounding the errors add up to the whole's; the numbers
+    of stochastic rounding depend on the place in the layer, so there the first piece alone is compared, cut short."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    g = torch.empty(n, device="cuda").normal_(generator=gen)
+    cands = [(W.QUANT, 2.0), (W.QUANT, 4.0), (W.QUANT, 7.0)]
+    ctab = B.cand_table(cands)
+
+    def profile(x, lengths):
+        offs = np.concatenate([[0], np.cumsum(lengths)[:-1]])
+        layers = B.layer_table(offs, lengths, [0] * len(lengths), [0] * len(lengths))
+        h = B.Handle(int(x.numel()), len(lengths), 3, stochastic=stochastic, seed=11)
+        errors, _ = h.profile(x, None, layers, ctab)
+        h.close()
+        return errors
+
+    whole = profile(g, [n])
+    step = 1 << 22
+    if stochastic:
+        # layers of one handle: the first holds the same elements at the same places
+        split = profile(g, [step, n - step])
+        alone = profile(g[:step].clone(), [step])
+        assert np.allclose(split[0], alone[0], rtol=1e-6) and (whole[0] > split[0]).all()
+        return
+    parts = sum(profile(g[lo:min(lo + step, n)].clone(), [min(step, n - lo)])[0] for lo in range(0, n, step))
+    # fp32 sums of at most 64 squares a lane, then fp64
+    assert np.allclose(whole[0], parts, rtol=64 * 2.0 ** -24), (whole, parts)

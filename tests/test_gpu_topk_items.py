@@ -41,3 +41,36 @@ def test_more_items_than_slots(n_layers, densities):
                                               cands[choice[l]], l)
         assert np.array_equal(pay[offsets[l]:offsets[l] + p_ref.size], p_ref), l
     h.close()
+
+
+def test_lists_of_both_kinds_take_turns_on_one_handle():
+    """At 18 M elements a profile with densities cuts the layers into tiles of 16384, one without into tiles of 8192: on
+    one handle in turn, with compressions in between, each gives what a handle of its own gives, bit for bit."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    sizes = [9_000_000, 5_000_001, 77, 4_000_000 - 512, 16384, 8193]
+    offs = np.concatenate([[0], np.cumsum(sizes)[:-1]])
+    total = sum(sizes)
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    g = torch.empty(total, device="cuda").normal_(generator=gen)
+    e = torch.empty(total, device="cuda").normal_(generator=gen)
+    layers = B.layer_table(offs, sizes, [0] * len(sizes), [0] * len(sizes))
+    quant, topk = [(W.QUANT, 3.0), (W.QUANT, 6.0)], [(W.TOPK, 0.01), (W.TOPK, 0.1)]
+    lists = [quant, quant + topk, topk]
+    choice = np.array([i % 2 for i in range(len(sizes))], np.int32)
+
+    def calls(h, cands):
+        ctab = B.cand_table(cands)
+        errors, _ = h.profile(g, e, layers, ctab)
+        offsets = B.payload_layout(layers, ctab, choice)
+        payload, ef = torch.zeros(int(offsets[-1]) + 16, dtype=torch.uint8, device="cuda"), e.clone()
+        h.compress(g, ef, layers, ctab, choice, payload, offsets)
+        return errors, payload, ef
+
+    shared = B.Handle(total, len(sizes), 4)
+    for cands in lists + lists[::-1] + lists:
+        own = B.Handle(total, len(sizes), 4)
+        want, got = calls(own, cands), calls(shared, cands)
+        assert np.array_equal(want[0], got[0]) and torch.equal(want[1], got[1]) and torch.equal(want[2], got[2])
+        own.close()
+    shared.close()
