@@ -27,7 +27,7 @@ namespace lgreco {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kLrCols = 64;       // columns computed per layer (r_max <= 64)
-constexpr int kLrBM = 128;        // rows (GEMM1, reconstruction) / columns (GEMM2) per workgroup
+constexpr int kLrBM = 128;        // rows (GEMM1) / columns (GEMM2) per workgroup
 constexpr int kLrBK = 32;         // contraction chunk staged in LDS
 constexpr int kLrGramSpan = 128;  // rows per Gram partial (one workgroup)
 constexpr int kLrQChunk = 64;     // Q rows per workgroup in the split-K reduction
