@@ -108,8 +108,9 @@ __device__ __forceinline__ T* at_bytes(T* base, uint32_t offset) {
 
 // ------------------------------------------------------------------ fp32 products from bf16 pieces
 // An fp32 value is the sum of three bf16 values, exactly: its upper 16 bits (cut off, so that nothing overflows), the
-// rounded upper bits of the rest, and what is left (8 bits at most).  Of the nine products of two such sums the six that
-// reach 2^-24 of the whole are formed on v_mfma_f32_32x32x16_bf16 (products exact, fp32 accumulate).
+// rounded upper bits of the rest, and what is left (8 bits at most).  The second reaches 2^-7 of the value's leading power
+// of two and the third 2^-16.  Of the nine products of two such sums all but that of the two third pieces, 2^-32 of the
+// whole at most, are formed on v_mfma_f32_32x32x16_bf16 (products exact, fp32 accumulate).
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 struct Split8 { bf16x8 piece[3]; };                          // 8 values: largest pieces first
@@ -127,13 +128,29 @@ __device__ __forceinline__ Split8 split8(const float* x) {
     }
     return Split8{{h.v, m.v, l.v}};
 }
-__device__ __forceinline__ f32x16 mfma_split(const Split8& a, const Split8& b, f32x16 c) {
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.piece[0], b.piece[2], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.piece[2], b.piece[0], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.piece[1], b.piece[1], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.piece[0], b.piece[1], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.piece[1], b.piece[0], c, 0, 0, 0);
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.piece[0], b.piece[0], c, 0, 0, 0);
+// c + a b over a chunk of 32: two operands of 16 each a side; b(s, piece) is the second's.  The products of the first
+// pieces go to c itself, the others are added up from zero and then to c by a vector addition: the instruction rounds
+// to nearest where c is the larger part and cuts c off where the products are, by up to an ulp of what it gives.
+// So a product alone is as good as one rounded to fp32 (262144 of them: 1.0 x 2^-24 at most, 0.43 in the mean square, as with the
+// fp32 instruction; without the products of second with third pieces and with everything added to c 4.5 and 0.70), and a sum, with five roundings
+// a chunk where the fp32 instruction has 32, better: of 16 to 512 normal terms 0.15 to 0.27 x 2^-24 of the sum of magnitudes in
+// the mean square against 0.42 to 0.54, of 512 terms of one sign 2.1 to 2.4 against 5.0 to 5.7.
+template <typename B>
+__device__ __forceinline__ f32x16 mfma_split(const Split8 (&a)[2], B b, f32x16 c) {
+    f32x16 t = {0};
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const bf16x8 h = b(s, 0), m = b(s, 1), l = b(s, 2);
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s].piece[1], l, t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s].piece[2], m, t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s].piece[0], l, t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s].piece[2], h, t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s].piece[1], m, t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s].piece[0], m, t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s].piece[1], h, t, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s].piece[0], h, c, 0, 0, 0);
+    }
+    return c + t;
 }
 
 // The matrix as everything behind the first contraction reads it.
@@ -258,22 +275,16 @@ __global__ __launch_bounds__(256, HAS_E ? 3 : 4) void lr_gemm1_kernel(LrParams p
             commit(k0);
             __syncthreads();
             if (c + 1 < nchunks) fetch(k0 + kLrBK);
+            Split8 a[2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 const float4 lo = *reinterpret_cast<const float4*>(&Xs[wave][bj][16 * s + 8 * half]);
                 const float4 hi = *reinterpret_cast<const float4*>(&Xs[wave][bj][16 * s + 8 * half + 4]);
                 const float row[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-                const Split8 a = split8(row);
-                const bf16x8* const col = &Qs[2 * s + half][0][bj];
-                Split8 b0, b1;
-#pragma unroll
-                for (int t = 0; t < 3; ++t) {
-                    b0.piece[t] = col[t * kLrCols];
-                    b1.piece[t] = col[t * kLrCols + 32];
-                }
-                acc0 = mfma_split(a, b0, acc0);
-                acc1 = mfma_split(a, b1, acc1);
+                a[s] = split8(row);
             }
+            acc0 = mfma_split(a, [&](int s, int t) { return Qs[2 * s + half][t][bj]; }, acc0);
+            acc1 = mfma_split(a, [&](int s, int t) { return Qs[2 * s + half][t][32 + bj]; }, acc1);
             __syncthreads();                                 // (the rows of Q0 are written again)
         }
     };
@@ -587,10 +598,9 @@ __global__ __launch_bounds__(256, 4) void lr_apply_kernel(LrParams p) {
 // One workgroup: 128 columns of X (rows of Q) over one range of its rows, 32 rows at a time; wavefront w owns columns
 // 32 w .. 32 w + 31, whose rows a lane loads straight in the layout of the instruction (two rows of 128 bytes an
 // instruction), a chunk ahead; the rows of Phat, shared by the four, go through LDS as pieces (two buffers, one barrier a chunk).
-// Products on the bf16 matrix pipe (see split8): 67 M elements 88 -> 70 us (94 -> 68 for the first passes after a pause),
-// where the fp32 products alone took 70 of the 88; now the reads of X (42 at HBM's rate), 21 us of products and 18 of vector
-// instructions (half of them splitting) overlap in part.  Its error against 64 bits is below that of the fp32 instructions (Q of
-// 8 shapes up to 32768 x 512, relative: 0.7e-7 to 4.1e-7 against 0.7e-7 to 4.8e-7, with heavy tails 1.4e-7 to 3.1e-7 against 2.1e-7 to 5.6e-7).  Splits of one
+// Products on the bf16 matrix pipe (see split8 and mfma_split): 67 M elements 83 us in a step (with six products, all added
+// to the accumulator, 76); the reads of X are 42 of it at HBM's rate, the products 28, and vector instructions overlap both in part.
+// Its error against 64 bits is below that of the fp32 instructions at every length (see mfma_split).  Splits of one
 // range are neighbours, so that workgroups that run together read whole rows.
 __global__ __launch_bounds__(256, 4) void lr_gemm2_kernel(LrParams p) {
     __shared__ __align__(16) bf16x8 Ps[2][kLrBK / 8][3][kLrCols];       // [8 rows][piece][column]
@@ -647,18 +657,8 @@ __global__ __launch_bounds__(256, 4) void lr_gemm2_kernel(LrParams p) {
         take(buf);
         if (c + 1 < nchunks) fetch(kbeg + (c + 1) * kLrBK);
         __syncthreads();                                     // (the buffer's last readers were done before the barrier in between)
-#pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            const bf16x8* const row = &Ps[buf][2 * s + half][0][bj];
-            Split8 b0, b1;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                b0.piece[q] = row[q * kLrCols];
-                b1.piece[q] = row[q * kLrCols + 32];
-            }
-            acc0 = mfma_split(a[s], b0, acc0);
-            acc1 = mfma_split(a[s], b1, acc1);
-        }
+        acc0 = mfma_split(a, [&](int s, int t) { return Ps[buf][2 * s + half][t][bj]; }, acc0);
+        acc1 = mfma_split(a, [&](int s, int t) { return Ps[buf][2 * s + half][t][32 + bj]; }, acc1);
     }
     float* __restrict__ out = p.part + L.part_off + (int64_t)tile.split * n * kLrCols;
 #pragma unroll

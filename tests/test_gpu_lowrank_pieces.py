@@ -1,4 +1,4 @@
-"""GPU parity of Q = X^T Phat, whose operands are cut into bf16 pieces: as good as fp32 products."""
+"""GPU parity of P = X Q0 and Q = X^T Phat, whose operands are cut into bf16 pieces: as good as fp32 products."""
 import numpy as np
 import pytest
 
@@ -32,7 +32,7 @@ def test_second_contraction_is_an_fp32_product(rows, scale):
     h.compress(g, e, layers, ctab, choice, payload, offsets, q)
     pay = payload.cpu().numpy()
     h.close()
-    # the sum's roundings are at most one a row, the products left out and the pieces' rounding 3 * 2^-24 of a product
+    # the sum's roundings are at most one a row, eight for the products of a row's pieces
     tol = (rows + 8) * 2.0 ** -24
     for l, (m, n) in enumerate(shapes):
         o = int(batch.offsets[l])
@@ -40,6 +40,72 @@ def test_second_contraction_is_an_fp32_product(rows, scale):
         p, got = f[:m * rank].reshape(m, rank), f[m * rank:].reshape(n, rank)
         x = batch.grads[o:o + m * n].reshape(m, n).astype(np.float64)
         assert (np.abs(got - x.T @ p) <= tol * (np.abs(x).T @ np.abs(p)) + 1e-300).all(), shapes[l]
+
+
+# One product, formed as eight on the matrix unit: the largest, exact, and seven whose sum is at most 2^-6 of it, each
+# addition of which is within 2^-23 of what it gives; their sum is rounded once more.
+PRODUCT = 2.0 ** -24 + 7 * 2.0 ** -6 * 2.0 ** -23 + 2.0 ** -32
+
+
+def _factors(x, q0, rank):
+    """Phat and Q of one matrix, compressed from a zero error feedback."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    m, n = x.shape
+    layers, ctab = B.layer_table([0], [m * n], [m], [n]), B.cand_table([(W.LOWRANK, float(rank))])
+    choice = np.zeros(1, np.int32)
+    g = torch.from_numpy(np.ascontiguousarray(x, np.float32).ravel()).cuda()
+    q = torch.from_numpy(np.ascontiguousarray(q0, np.float32).ravel()).cuda()
+    h = B.Handle(m * n, 1, 1, r_max=q0.shape[1])
+    offsets = B.payload_layout(layers, ctab, choice)
+    payload = torch.zeros(int(offsets[-1]) + 16, dtype=torch.uint8, device="cuda")
+    h.compress(g, torch.zeros_like(g), layers, ctab, choice, payload, offsets, q)
+    f = payload.cpu().numpy()[:4 * (m + n) * rank].view(np.float32).astype(np.float64)
+    h.close()
+    return f[:m * rank].reshape(m, rank), f[m * rank:].reshape(n, rank)
+
+
+def _values(kind, rng, n):
+    if kind == "random":
+        return rng.standard_normal(n).astype(np.float32)
+    # the second piece as large as it can be and the third half a step of it, with one sign in every product
+    v = np.array([0x3F80FF80], np.uint32).view(np.float32)[0]
+    return (v * 2.0 ** rng.integers(-3, 4, n)).astype(np.float32)
+
+
+@pytest.mark.parametrize("kind", ("random", "worst"))
+def test_single_products_of_the_first_contraction(kind):
+    """Rows with one value: each row of P is one product.  Phat is P times a factor that rows whose product is exact tell."""
+    rng = np.random.default_rng(5)
+    m, n, exact = 65536, 64, 4096
+    col = rng.integers(1, n, m)
+    col[:exact] = 0
+    value = _values(kind, rng, m)
+    value[:exact] = rng.standard_normal(exact)
+    x, q0 = np.zeros((m, n), np.float32), _values(kind, rng, n)[:, None]
+    x[np.arange(m), col] = value
+    q0[0] = 1.0
+    phat = _factors(x, q0, 1)[0][:, 0]
+    want = value.astype(np.float64) * q0[col, 0]
+    half = np.spacing(np.abs(phat).astype(np.float32)).astype(np.float64) / 2
+    low = ((np.abs(phat) - half) / np.abs(want))[:exact].max()
+    high = ((np.abs(phat) + half) / np.abs(want))[:exact].min()
+    assert low <= high * (1 + 1e-12) and high / low - 1 < 2.0 ** -30
+    assert (np.abs(phat / (want * (low + high) / 2) - 1) <= PRODUCT + 2.0 ** -24 + 2.0 ** -30).all()
+
+
+@pytest.mark.parametrize("kind", ("random", "worst"))
+def test_single_products_of_the_second_contraction(kind):
+    """Columns with one value: each row of Q is one product of it with a row of Phat."""
+    rng = np.random.default_rng(6)
+    m, n = 64, 32768
+    row = rng.integers(0, m, n)
+    value = _values(kind, rng, n)
+    x = np.zeros((m, n), np.float32)
+    x[row, np.arange(n)] = value
+    phat, q = _factors(x, rng.standard_normal((n, 64)), 8)
+    want = value.astype(np.float64)[:, None] * phat[row]
+    assert (np.abs(q - want) <= PRODUCT * np.abs(want)).all()
 
 
 @pytest.mark.parametrize("rank", (2, 3, 4, 5, 15, 16, 17, 24, 32, 34))
