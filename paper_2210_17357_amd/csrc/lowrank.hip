@@ -153,6 +153,32 @@ __device__ __forceinline__ f32x16 mfma_split(const Split8 (&a)[2], B b, f32x16 c
     return c + t;
 }
 
+// Values below 2^-110 lose bits: what they leave for the third piece falls below bf16's subnormals.  That is less than 2^-133,
+// nothing beside values of the same sum some 2^30 times as large, but all that counts where there are none.  So a
+// wavefront that has met no value as large as below and whose sums are not all zero forms them once more, from the fp32
+// values on the fp32 instruction, two rows of the contraction a step.
+constexpr float kLrHeldSquare = 0x1p-120f;      // a lane's part of ||X||^2: one of its 256 values is 2^-64 or more
+constexpr float kLrHeldQ0 = 0x1p-100f;          // Q0
+constexpr float kLrHeldSum = 0x1p-90f;          // Q = X^T Phat: K values of X lose at most 2^-133 sqrt(K) of it, 2^-30 of this where K < 2^26
+__device__ __forceinline__ float largest(f32x16 a, f32x16 b) {
+    float v = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v = fmaxf(fmaxf(fabsf(a[i]), fabsf(b[i])), v);
+    return v;
+}
+// left(k), right(k, 0) and right(k, 1): this lane's values of the operands at k
+template <typename Left, typename Right>
+__device__ __forceinline__ void mfma_plain(int kbeg, int kend, int half, Left left, Right right, f32x16& c0, f32x16& c1) {
+    c0 = f32x16{0};
+    c1 = f32x16{0};
+    for (int k = kbeg; k < kend; k += 2) {
+        const int kk = min(k + half, kend - 1);
+        const float a = k + half < kend ? left(kk) : 0.0f;
+        c0 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, right(kk, 0), c0, 0, 0, 0);
+        c1 = __builtin_amdgcn_mfma_f32_32x32x2f32(a, right(kk, 1), c1, 0, 0, 0);
+    }
+}
+
 // The matrix as everything behind the first contraction reads it.
 __device__ __forceinline__ const float* matrix_of(const LrParams& p, const LrLayer& L) {
     return p.from_x ? p.x + L.x_off : p.g + L.offset;
@@ -175,6 +201,7 @@ __global__ __launch_bounds__(256, HAS_E ? 3 : 4) void lr_gemm1_kernel(LrParams p
     __shared__ __align__(16) float Xs[4][32][kLrXPitch];
     __shared__ __align__(16) bf16x8 Qs[kLrBK / 8][3][kLrCols];       // [8 rows][piece][column]
     __shared__ double s_red[4];
+    __shared__ bool s_held[4];
     const LrTile tile = p.p_tiles[blockIdx.x];
     const LrLayer L = p.layers[tile.layer];
     const int m = L.rows, n = L.cols, row0 = tile.a0;
@@ -203,7 +230,7 @@ __global__ __launch_bounds__(256, HAS_E ? 3 : 4) void lr_gemm1_kernel(LrParams p
     }
     const int nchunks = (kend - kbeg + kLrBK - 1) / kLrBK;
     f32x16 acc0 = {0}, acc1 = {0};
-    float xsq = 0.0f;
+    float xsq = 0.0f, qmax = 0.0f;
     // (two copies of the loop: of a choice at each access the compiler makes one, without the hint)
     const auto span = [&](auto whole_lines) __attribute__((always_inline)) {
         constexpr bool lines = decltype(whole_lines)::value;
@@ -265,6 +292,8 @@ __global__ __launch_bounds__(256, HAS_E ? 3 : 4) void lr_gemm1_kernel(LrParams p
                     xsq = __builtin_fmaf(v.w, v.w, xsq);
                 }
             }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) qmax = fmaxf(qmax, fabsf(qr[u]));
             const Split8 b = split8(qr);
 #pragma unroll
             for (int t = 0; t < 3; ++t) Qs[wave][t][lane] = b.piece[t];
@@ -290,6 +319,20 @@ __global__ __launch_bounds__(256, HAS_E ? 3 : 4) void lr_gemm1_kernel(LrParams p
     };
     if (HAS_E && L.lines) span(std::true_type());
     else span(std::false_type());
+    const double s = wave_sum((double)xsq);
+    const bool q_held = __any(qmax >= kLrHeldQ0);
+    if (lane == 0) {
+        s_red[wave] = s;
+        s_held[wave] = q_held;
+    }
+    __syncthreads();                                         // (also: what the wavefront has written to xo, for its other lanes)
+    if (tid == 0) p.xnorm_part[blockIdx.x] = s_red[0] + s_red[1] + s_red[2] + s_red[3];
+    const bool held = __any(xsq >= kLrHeldSquare) && (s_held[0] || s_held[1] || s_held[2] || s_held[3]);
+    if (!held && row0 + 32 * wave < m && __any(largest(acc0, acc1) > 0.0f)) {       // (uniform)
+        const float* const row = (HAS_E ? xo : g) + (int64_t)min(32 * wave + bj, m - 1 - row0) * n;
+        mfma_plain(kbeg, kend, half, [&](int k) { return row[k]; },
+                   [&](int k, int c) { return 32 * c + bj < qstride ? q[(int64_t)k * qstride + 32 * c + bj] : 0.0f; }, acc0, acc1);
+    }
     float* __restrict__ P = L.psplits > 1 ? p.ppart + L.ppart_off + (int64_t)tile.split * m * kLrCols
                                           : p.P + L.p_off;
 #pragma unroll
@@ -300,10 +343,6 @@ __global__ __launch_bounds__(256, HAS_E ? 3 : 4) void lr_gemm1_kernel(LrParams p
             P[(int64_t)orow * kLrCols + 32 + bj] = acc1[v];
         }
     }
-    const double s = wave_sum((double)xsq);
-    if (lane == 0) s_red[wave] = s;
-    __syncthreads();
-    if (tid == 0) p.xnorm_part[blockIdx.x] = s_red[0] + s_red[1] + s_red[2] + s_red[3];
 }
 
 // ------------------------------------------------------------------ partial Gram matrices
@@ -660,6 +699,10 @@ __global__ __launch_bounds__(256, 4) void lr_gemm2_kernel(LrParams p) {
         acc0 = mfma_split(a, [&](int s, int t) { return Ps[buf][2 * s + half][t][bj]; }, acc0);
         acc1 = mfma_split(a, [&](int s, int t) { return Ps[buf][2 * s + half][t][32 + bj]; }, acc1);
     }
+    const float most = largest(acc0, acc1);
+    if (!__any(most >= kLrHeldSum) && __any(most > 0.0f))    // (uniform)
+        mfma_plain(kbeg, kend, half, [&](int k) { return X[(int64_t)k * n + col]; },
+                   [&](int k, int c) { return P[(int64_t)k * kLrCols + 32 * c + bj]; }, acc0, acc1);
     float* __restrict__ out = p.part + L.part_off + (int64_t)tile.split * n * kLrCols;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {

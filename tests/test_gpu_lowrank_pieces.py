@@ -67,24 +67,30 @@ def _factors(x, q0, rank):
 
 def _values(kind, rng, n):
     if kind == "random":
-        return rng.standard_normal(n).astype(np.float32)
+        return (rng.uniform(1, 2, n) * rng.choice((-1, 1), n)).astype(np.float32)
     # the second piece as large as it can be and the third half a step of it, with one sign in every product
     v = np.array([0x3F80FF80], np.uint32).view(np.float32)[0]
     return (v * 2.0 ** rng.integers(-3, 4, n)).astype(np.float32)
 
 
+# X and Q0 so small that their third pieces are below what bf16 holds (from 2^-110 down), or not
+SCALES = ((1.0, 1.0), (2.0 ** -116, 1.0), (1.0, 2.0 ** -116), (2.0 ** -109, 1.0), (2.0 ** -64, 2.0 ** -52))
+
+
+@pytest.mark.parametrize("scale_x,scale_q", SCALES)
 @pytest.mark.parametrize("kind", ("random", "worst"))
-def test_single_products_of_the_first_contraction(kind):
+def test_single_products_of_the_first_contraction(kind, scale_x, scale_q):
     """Rows with one value: each row of P is one product.  Phat is P times a factor that rows whose product is exact tell."""
     rng = np.random.default_rng(5)
-    m, n, exact = 65536, 64, 4096
+    m, n, exact = 65500, 600, 4096                          # a last tile of few rows, two ranges of columns
     col = rng.integers(1, n, m)
     col[:exact] = 0
     value = _values(kind, rng, m)
-    value[:exact] = rng.standard_normal(exact)
-    x, q0 = np.zeros((m, n), np.float32), _values(kind, rng, n)[:, None]
+    value[:exact] = rng.uniform(1, 2, exact)
+    value *= np.float32(scale_x)
+    x, q0 = np.zeros((m, n), np.float32), _values(kind, rng, n)[:, None] * np.float32(scale_q)
     x[np.arange(m), col] = value
-    q0[0] = 1.0
+    q0[0] = scale_q
     phat = _factors(x, q0, 1)[0][:, 0]
     want = value.astype(np.float64) * q0[col, 0]
     half = np.spacing(np.abs(phat).astype(np.float32)).astype(np.float64) / 2
@@ -94,18 +100,46 @@ def test_single_products_of_the_first_contraction(kind):
     assert (np.abs(phat / (want * (low + high) / 2) - 1) <= PRODUCT + 2.0 ** -24 + 2.0 ** -30).all()
 
 
+@pytest.mark.parametrize("scale", (1.0, 2.0 ** -116, 2.0 ** -109))
 @pytest.mark.parametrize("kind", ("random", "worst"))
-def test_single_products_of_the_second_contraction(kind):
+def test_single_products_of_the_second_contraction(kind, scale):
     """Columns with one value: each row of Q is one product of it with a row of Phat."""
     rng = np.random.default_rng(6)
-    m, n = 64, 32768
+    m, n = 67, 32700
     row = rng.integers(0, m, n)
-    value = _values(kind, rng, n)
+    value = _values(kind, rng, n) * np.float32(scale)
     x = np.zeros((m, n), np.float32)
     x[row, np.arange(n)] = value
     phat, q = _factors(x, rng.standard_normal((n, 64)), 8)
     want = value.astype(np.float64)[:, None] * phat[row]
-    assert (np.abs(q - want) <= PRODUCT * np.abs(want)).all()
+    assert (np.abs(q - want) <= PRODUCT * np.abs(want) + 2.0 ** -149).all()
+
+
+@pytest.mark.parametrize("scale", (2.0 ** -100, 2.0 ** -116, 2.0 ** -122))
+def test_small_matrices_in_the_one_call(scale):
+    """Without an error feedback the first contraction is another kernel."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    rng = np.random.default_rng(7)
+    m, n, rank = 150, 700, 4
+    x = (rng.standard_normal((m, n)) * scale).astype(np.float32)
+    q0 = rng.standard_normal((n, 64)).astype(np.float32)
+    layers, ctab = B.layer_table([0], [m * n], [m], [n]), B.cand_table([(W.LOWRANK, float(rank))])
+    h = B.Handle(m * n, 1, 1, r_max=64)
+    h.set_ef_zero_on_entry(True)
+    payload = torch.zeros(4 * (m + n) * rank + 32, dtype=torch.uint8, device="cuda")
+    g, q = torch.from_numpy(x.ravel()).cuda(), torch.from_numpy(q0.ravel()).cuda()
+    h.profile_solve_compress(g, torch.zeros_like(g), layers, ctab, 0, 10, payload, q)
+    f = payload.cpu().numpy()[:4 * (m + n) * rank].view(np.float32).astype(np.float64)
+    h.close()
+    x64 = x.astype(np.float64) / scale
+    ortho, r = np.linalg.qr(x64 @ q0.astype(np.float64))
+    phat = (ortho * np.sign(np.diag(r)))[:, :rank]
+    got = f[:m * rank].reshape(m, rank)
+    # sums of 700 fp32 products, and a condition number below 4 of the leading columns
+    assert np.linalg.norm(got - phat) <= 4 * 30 * 2.0 ** -24 * np.linalg.norm(phat)
+    want = x64.T @ got
+    assert np.linalg.norm(f[m * rank:].reshape(n, rank) / scale - want) <= 150 * 2.0 ** -24 * np.linalg.norm(want) + 2.0 ** -149 / scale * n
 
 
 @pytest.mark.parametrize("rank", (2, 3, 4, 5, 15, 16, 17, 24, 32, 34))
