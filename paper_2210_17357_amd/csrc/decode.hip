@@ -10,6 +10,7 @@
 #include <algorithm>
 
 #include "internal.h"
+#include "parts.h"
 
 namespace lgreco {
 
@@ -147,8 +148,8 @@ hipError_t launch_decode(const uint8_t* payload, const DevLayer* layers, const T
         // longer ones where most of the workgroups would only find that their layer is another family's (see
         // launch_quant_compress)
         DecodeParams q = p;
-        q.part_elems = 4 * quantized >= 3 * total ? kDecodePart : 4 * kDecodePart;
-        while ((tile_elems >> q.part_shift) > q.part_elems) ++q.part_shift;
+        q.part_shift = part_shift(n_tiles, total, tile_elems, 4 * quantized >= 3 * total ? kDecodePart : 4 * kDecodePart);
+        q.part_elems = tile_elems >> q.part_shift;
         const dim3 grid((unsigned)n_tiles << q.part_shift);
         Section sec(tm, "quant_decode", true);
         if (accumulate) launch_timed(&sec, true, true, quant_decode_kernel<true>, grid, dim3(kThreads), 0, s, q);

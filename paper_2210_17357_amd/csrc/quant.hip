@@ -16,6 +16,7 @@
 // spread over the row's 16 lanes (lane c: unit of candidate c, lane 8+c: inv of candidate c)
 // and broadcast back with row_newbcast.
 #include "internal.h"
+#include "parts.h"
 #include "reduce_dev.h"
 #include "topk_dev.h"
 
@@ -495,12 +496,17 @@ hipError_t launch_quant_compress(const float* g, float* e, const DevLayer* layer
     if (n_tiles <= 0) return hipSuccess;
     QuantCompressParams p{g, e, layers, tiles, payload, (uint32_t)seed, (uint32_t)(seed >> 32), 0, 0};
     const bool most = quantized >= total - total / 4;
-    p.part_chunks = !most ? 16 : stochastic ? 8 : 1;
-    while ((tile_elems >> p.part_shift) > p.part_chunks * kChunk) ++p.part_shift;
+    const auto cut = [&](int chunks) {
+        p.part_shift = part_shift(n_tiles, total, tile_elems, chunks * kChunk);
+        p.part_chunks = (tile_elems >> p.part_shift) / kChunk;
+    };
+    cut(!most ? 16 : stochastic ? 8 : 1);
+    const bool single = most && !stochastic && p.part_chunks == 1;
+    if (most && !stochastic && !single) cut(4);              // (many tiles that are not full: a chunk for each of four wavefronts)
     const dim3 grid((unsigned)n_tiles << p.part_shift);
     if (stochastic)
         launch_timed(sec, true, true, quant_compress_kernel<true, 4>, grid, dim3(256), lds_pad, s, p);
-    else if (most)
+    else if (single)
         launch_timed(sec, true, true, quant_compress_kernel<false, 1>, grid, dim3(64), lds_pad, s, p);
     else
         launch_timed(sec, true, true, quant_compress_kernel<false, 4>, grid, dim3(256), lds_pad, s, p);
