@@ -156,10 +156,11 @@ __device__ __forceinline__ f32x16 mfma_split(const Split8 (&a)[2], B b, f32x16 c
 // Values below 2^-110 lose bits: what they leave for the third piece falls below bf16's subnormals.  That is less than 2^-133,
 // nothing beside values of the same sum some 2^30 times as large, but all that counts where there are none.  So a
 // wavefront that has met no value as large as below and whose sums are not all zero forms them once more, from the fp32
-// values on the fp32 instruction, two rows of the contraction a step.
-constexpr float kLrHeldSquare = 0x1p-120f;      // a lane's part of ||X||^2: one of its 256 values is 2^-64 or more
+// values on the fp32 instruction, two rows of the contraction a step (a compression of 67 M elements around 1e-33: 962 us instead
+// of 437, from 1e-25 up 437).
 constexpr float kLrHeldQ0 = 0x1p-100f;          // Q0
-constexpr float kLrHeldSum = 0x1p-90f;          // Q = X^T Phat: K values of X lose at most 2^-133 sqrt(K) of it, 2^-30 of this where K < 2^26
+constexpr float kLrHeldP = 0x1p-91f;            // P = X Q0 over the largest of Q0: 512 values of X lose at most 2^-124 of it, 2^-33 of this
+constexpr float kLrHeldQ = 0x1p-90f;            // Q = X^T Phat: K values of X lose at most 2^-133 sqrt(K), 2^-30 of this where K < 2^26
 __device__ __forceinline__ float largest(f32x16 a, f32x16 b) {
     float v = 0.0f;
 #pragma unroll
@@ -201,7 +202,7 @@ __global__ __launch_bounds__(256, HAS_E ? 3 : 4) void lr_gemm1_kernel(LrParams p
     __shared__ __align__(16) float Xs[4][32][kLrXPitch];
     __shared__ __align__(16) bf16x8 Qs[kLrBK / 8][3][kLrCols];       // [8 rows][piece][column]
     __shared__ double s_red[4];
-    __shared__ bool s_held[4];
+    __shared__ float s_qmax[4];
     const LrTile tile = p.p_tiles[blockIdx.x];
     const LrLayer L = p.layers[tile.layer];
     const int m = L.rows, n = L.cols, row0 = tile.a0;
@@ -320,15 +321,17 @@ __global__ __launch_bounds__(256, HAS_E ? 3 : 4) void lr_gemm1_kernel(LrParams p
     if (HAS_E && L.lines) span(std::true_type());
     else span(std::false_type());
     const double s = wave_sum((double)xsq);
-    const bool q_held = __any(qmax >= kLrHeldQ0);
+    for (int o = 32; o > 0; o >>= 1) qmax = fmaxf(qmax, __shfl_xor(qmax, o, 64));
     if (lane == 0) {
         s_red[wave] = s;
-        s_held[wave] = q_held;
+        s_qmax[wave] = qmax;
     }
     __syncthreads();                                         // (also: what the wavefront has written to xo, for its other lanes)
     if (tid == 0) p.xnorm_part[blockIdx.x] = s_red[0] + s_red[1] + s_red[2] + s_red[3];
-    const bool held = __any(xsq >= kLrHeldSquare) && (s_held[0] || s_held[1] || s_held[2] || s_held[3]);
-    if (!held && row0 + 32 * wave < m && __any(largest(acc0, acc1) > 0.0f)) {       // (uniform)
+    qmax = fmaxf(fmaxf(s_qmax[0], s_qmax[1]), fmaxf(s_qmax[2], s_qmax[3]));
+    const float most = largest(acc0, acc1);
+    const bool held = qmax >= kLrHeldQ0 && __any(most >= kLrHeldP * qmax);
+    if (!held && row0 + 32 * wave < m && __any(most > 0.0f)) {       // (uniform)
         const float* const row = (HAS_E ? xo : g) + (int64_t)min(32 * wave + bj, m - 1 - row0) * n;
         mfma_plain(kbeg, kend, half, [&](int k) { return row[k]; },
                    [&](int k, int c) { return 32 * c + bj < qstride ? q[(int64_t)k * qstride + 32 * c + bj] : 0.0f; }, acc0, acc1);
@@ -700,7 +703,7 @@ __global__ __launch_bounds__(256, 4) void lr_gemm2_kernel(LrParams p) {
         acc1 = mfma_split(a, [&](int s, int t) { return Ps[buf][2 * s + half][t][32 + bj]; }, acc1);
     }
     const float most = largest(acc0, acc1);
-    if (!__any(most >= kLrHeldSum) && __any(most > 0.0f))    // (uniform)
+    if (!__any(most >= kLrHeldQ) && __any(most > 0.0f))    // (uniform)
         mfma_plain(kbeg, kend, half, [&](int k) { return X[(int64_t)k * n + col]; },
                    [&](int k, int c) { return P[(int64_t)k * kLrCols + 32 * c + bj]; }, acc0, acc1);
     float* __restrict__ out = p.part + L.part_off + (int64_t)tile.split * n * kLrCols;
