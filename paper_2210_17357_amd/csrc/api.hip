@@ -23,20 +23,26 @@ struct lgreco_handle {
 
     // layer table cache (rebuilt only when the caller's table changes)
     std::vector<lgreco_layer_t> cached;
-    std::vector<DevLayer> hl;
-    std::vector<Tile> ht;
     int64_t total_elems = 0;
-    bool layers_dirty = true;       // device copy of hl is stale
+    // the table as it is cut into tiles: [1] by calls with Top-K layers where those take larger tiles than others (see
+    // kTilesFill), [0] by all other calls.  Each keeps its device copy, so that calls of both kinds in turn upload nothing.
+    struct Cut {
+        int32_t tile_elems = 0;         // tile size (0: not cut since the layer table changed)
+        int32_t layer_tiles = 0;        // tiles of its largest layer
+        std::vector<DevLayer> hl;
+        std::vector<Tile> ht;
+        bool dirty = true;              // device copy of ht and hl is stale
+        std::vector<DevLayer> hl_uploaded;   // what d_layers holds
+        DevLayer* d_layers = nullptr;
+        Tile* d_tiles = nullptr;
+    } cuts[2];
+    Cut* cut = &cuts[0];            // that of the call in progress / the last call
     // second stream of the one-call path: the quantized layers' compression runs there beside the
     // Top-K layers' chain of short kernels (default priority, joined before the call goes on)
     hipStream_t side = nullptr;
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
 
-    DevLayer* d_layers = nullptr;
-    Tile* d_tiles = nullptr;
     int32_t max_tiles = 0;
-    int32_t tile_elems = kTile;     // tile size of the current layer table
-    int32_t layer_tiles = 0;        // tiles of its largest layer
     double* d_partials = nullptr;   // [max_tiles x max_cands]
     double* h_errors = nullptr;     // [max_layers x max_cands], pinned host memory
     double* d_errors = nullptr;     // the same memory as the kernels address it
@@ -90,7 +96,6 @@ struct lgreco_handle {
     int32_t* h_apply = nullptr;          // pinned [max_layers x max_cands | max_cands | max_cands] iparam | family | Top-K slot
     int32_t* d_apply = nullptr;
     size_t apply_count = 0;              // int32 entries of h_apply / d_apply in use
-    std::vector<DevLayer> hl_uploaded;   // what d_layers holds
     // Top-K candidates of the last profile call: how many, and the candidate column of each of the
     // selection records it left on the device (valid while they number at most one group)
     int last_ntk = 0;
@@ -253,41 +258,60 @@ int tile_size(int64_t total, bool topk) {
     return tile;
 }
 
-// Rebuild the tile table if the caller's layer table differs from the cached one.  A profile's sums follow the tiles
-// (what it rounds), so it also does where the cached one was cut for another kind of list; the other calls, whose results
-// do not depend on the tiles, take what is there.
-enum class Tiles { any, topk, profile, profile_topk };
-int prepare_layers(lgreco_handle* h, const lgreco_layer_t* layers, int32_t L, Tiles want) {
-    const bool topk = want == Tiles::topk || want == Tiles::profile_topk;
-    if ((int)h->cached.size() == L && std::memcmp(h->cached.data(), layers, sizeof(lgreco_layer_t) * L) == 0 &&
-        (want == Tiles::any || want == Tiles::topk || tile_size(h->total_elems, topk) == h->tile_elems))
-        return LGRECO_OK;
-    int st = check_layers(layers, L);
-    if (st != LGRECO_OK) return st;
-    if (L > h->max_layers) return LGRECO_ENOSPACE;
-    int64_t total = 0;
-    for (int l = 0; l < L; ++l) total += layers[l].numel;
-    if (total > h->max_elems) return LGRECO_ENOSPACE;
+bool some_topk(const lgreco_cand_t* cands, int32_t P) {
+    return std::any_of(cands, cands + P, [](const lgreco_cand_t& c) { return c.family == LGRECO_TOPK; });
+}
+bool chosen_topk(const lgreco_cand_t* cands, int32_t P, const int32_t* choice, int32_t L) {
+    return some_topk(cands, P) && std::any_of(choice, choice + L, [&](int32_t c) {
+        return c >= 0 && c < P && cands[c].family == LGRECO_TOPK;
+    });
+}
 
-    const int tile = tile_size(total, topk);
-    h->tile_elems = tile;
-    h->layer_tiles = 0;
-    h->hl.assign(L, DevLayer{});
-    h->ht.clear();
+// Whether a handle of this size may meet tables that calls with Top-K layers cut otherwise.
+bool two_cuts(int64_t max_elems) { return max_elems >= (int64_t)(kTilesFill / 2) * (kTile / 2); }
+
+// Makes h->cut the cut of the caller's layer table that this call takes, whatever the calls before it were (a profile's sums
+// follow the tiles); cuts the table, and checks it, where that is not there from an earlier call.
+//   any_topk: whether the call has Top-K layers, asked only where it matters
+template <typename F>
+int prepare_layers(lgreco_handle* h, const lgreco_layer_t* layers, int32_t L, F any_topk) {
+    const bool known =
+        (int)h->cached.size() == L && std::memcmp(h->cached.data(), layers, sizeof(lgreco_layer_t) * L) == 0;
+    int64_t total = h->total_elems;
+    if (!known) {
+        const int st = check_layers(layers, L);
+        if (st != LGRECO_OK) return st;
+        if (L > h->max_layers) return LGRECO_ENOSPACE;
+        total = 0;
+        for (int l = 0; l < L; ++l) total += layers[l].numel;
+        if (total > h->max_elems) return LGRECO_ENOSPACE;
+        h->cached.assign(layers, layers + L);
+        h->total_elems = total;
+        for (auto& c : h->cuts) c.tile_elems = 0;
+    }
+    const int plain = tile_size(total, false), larger = tile_size(total, true);
+    const bool second = larger != plain && any_topk();
+    const int tile = second ? larger : plain;
+    lgreco_handle::Cut* const cut = h->cut = &h->cuts[second];
+    if (cut->tile_elems) return LGRECO_OK;
+
+    cut->layer_tiles = 0;
+    cut->hl.assign(L, DevLayer{});
+    cut->ht.clear();
     int64_t qoff = 0;
     for (int l = 0; l < L; ++l) {
         const lgreco_layer_t& a = layers[l];
-        DevLayer& d = h->hl[l];
+        DevLayer& d = cut->hl[l];
         d.offset = a.offset;
         d.numel = a.numel;
         d.rows = a.rows;
         d.cols = a.cols;
         d.q_offset = qoff;
         qoff += (int64_t)a.cols * h->cfg.r_max;
-        d.tile_begin = (int32_t)h->ht.size();
+        d.tile_begin = (int32_t)cut->ht.size();
         int64_t pos = 0, n = a.numel;
         auto push = [&](int64_t cnt, int fast) {
-            h->ht.push_back(Tile{pos, l, (int32_t)cnt, fast, 0});
+            cut->ht.push_back(Tile{pos, l, (int32_t)cnt, fast, 0});
             pos += cnt;
         };
         // whole chunks take the vector path wherever the layer starts, the rest of a layer the scalar one (73 M elements
@@ -297,36 +321,34 @@ int prepare_layers(lgreco_handle* h, const lgreco_layer_t* layers, int32_t L, Ti
         const int64_t rem = n - pos, mid = rem / kChunk * kChunk;
         if (mid) push(mid, 1);
         if (rem - mid) push(rem - mid, 0);
-        d.tile_end = (int32_t)h->ht.size();
-        h->layer_tiles = std::max(h->layer_tiles, d.tile_end - d.tile_begin);
+        d.tile_end = (int32_t)cut->ht.size();
+        cut->layer_tiles = std::max(cut->layer_tiles, d.tile_end - d.tile_begin);
     }
-    if ((int64_t)h->ht.size() > h->max_tiles) return LGRECO_ENOSPACE;
-    h->cached.assign(layers, layers + L);
-    h->total_elems = total;
-    h->layers_dirty = true;
+    if ((int64_t)cut->ht.size() > h->max_tiles) return LGRECO_ENOSPACE;
+    cut->tile_elems = tile;
+    cut->dirty = true;
     return LGRECO_OK;
 }
 
-// The tile table travels only when it was rebuilt; the layer records also when the caller changed
+// A cut travels only when it was made anew; the layer records also when the caller changed
 // their per-call fields (family, parameter, payload offset).  The copies read the handle's host
 // vectors, which the next call may rewrite while this call's kernels are still queued
 // (lgreco_compress does not wait at its end): a call that uploads waits for its copies here.  In a
 // loop that repeats one table and one choice nothing is uploaded and nothing waits.
 int upload_layers(lgreco_handle* h, hipStream_t s, bool layers_changed) {
+    lgreco_handle::Cut& c = *h->cut;
     bool copied = false;
-    if (h->layers_dirty || (layers_changed && (h->hl_uploaded.size() != h->hl.size() ||
-                                               std::memcmp(h->hl_uploaded.data(), h->hl.data(),
-                                                           sizeof(DevLayer) * h->hl.size()) != 0))) {
-        HIPCHK(hipMemcpyAsync(h->d_layers, h->hl.data(), sizeof(DevLayer) * h->hl.size(), hipMemcpyHostToDevice,
-                              s));
-        h->hl_uploaded = h->hl;
+    if (c.dirty || (layers_changed && (c.hl_uploaded.size() != c.hl.size() ||
+                                       std::memcmp(c.hl_uploaded.data(), c.hl.data(), sizeof(DevLayer) * c.hl.size()) != 0))) {
+        HIPCHK(hipMemcpyAsync(c.d_layers, c.hl.data(), sizeof(DevLayer) * c.hl.size(), hipMemcpyHostToDevice, s));
+        c.hl_uploaded = c.hl;
         copied = true;
     }
-    if (h->layers_dirty) {
-        HIPCHK(hipMemcpyAsync(h->d_tiles, h->ht.data(), sizeof(Tile) * h->ht.size(), hipMemcpyHostToDevice, s));
+    if (c.dirty) {
+        HIPCHK(hipMemcpyAsync(c.d_tiles, c.ht.data(), sizeof(Tile) * c.ht.size(), hipMemcpyHostToDevice, s));
         copied = true;
     }
-    h->layers_dirty = false;
+    c.dirty = false;
     if (copied) HIPCHK(hipStreamSynchronize(s));
     return LGRECO_OK;
 }
@@ -513,8 +535,11 @@ int lgreco_create(lgreco_handle_t** out, const lgreco_config_t* cfg, int64_t max
     } while (0)
     HIPCHK_C(hipGetDevice(&h->device));
     h->max_tiles = (int32_t)std::min<int64_t>(max_elems / kTileMin + 2 * (int64_t)max_layers + 2, INT32_MAX);
-    HIPCHK_C(hipMalloc(&h->d_layers, sizeof(DevLayer) * max_layers));
-    HIPCHK_C(hipMalloc(&h->d_tiles, sizeof(Tile) * h->max_tiles));
+    for (auto& c : h->cuts) {
+        if (&c != h->cuts && !two_cuts(max_elems)) break;
+        HIPCHK_C(hipMalloc(&c.d_layers, sizeof(DevLayer) * max_layers));
+        HIPCHK_C(hipMalloc(&c.d_tiles, sizeof(Tile) * h->max_tiles));
+    }
     HIPCHK_C(hipMalloc(&h->d_partials, sizeof(double) * (size_t)h->max_tiles * max_cands));
     // Small results (the error table, the solver's output) are written by the kernels straight into
     // pinned host memory: no copy operation between the last kernel and the host's wait.
@@ -577,8 +602,10 @@ int lgreco_create(lgreco_handle_t** out, const lgreco_config_t* cfg, int64_t max
 
 int lgreco_destroy(lgreco_handle_t* h) {
     if (!h) return LGRECO_EINVAL;
-    (void)hipFree(h->d_layers);
-    (void)hipFree(h->d_tiles);
+    for (auto& c : h->cuts) {
+        (void)hipFree(c.d_layers);
+        (void)hipFree(c.d_tiles);
+    }
     (void)hipFree(h->d_partials);
     (void)hipHostFree(h->h_errors);
     (void)hipFree(h->d_dp_in);
@@ -749,9 +776,7 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
     if (!h || !d_grads || !layers || !cands || L <= 0 || P <= 0) return LGRECO_EINVAL;
     if (P > h->max_cands) return LGRECO_ENOSPACE;
     begin_call(h, s, LGRECO_CALL_PROFILE);
-    bool any_topk = false;
-    for (int c = 0; c < P; ++c) any_topk = any_topk || cands[c].family == LGRECO_TOPK;
-    int st = prepare_layers(h, layers, L, any_topk ? Tiles::profile_topk : Tiles::profile);
+    int st = prepare_layers(h, layers, L, [&] { return some_topk(cands, P); });
     if (st != LGRECO_OK) return st;
     // everything the profile queues, chains between the kernels included
     struct Phase {
@@ -789,7 +814,7 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
     if (st != LGRECO_OK) return st;
     phase.idx = h->tm->open_phase("phase_profile");
 
-    const int n_tiles = (int)h->ht.size();
+    const int n_tiles = (int)h->cut->ht.size();
     const bool ptr_aligned = ((uintptr_t)d_grads % 16 == 0) && (!d_ef || (uintptr_t)d_ef % 16 == 0);
     if (!ptr_aligned) return LGRECO_EINVAL;     // device allocations are always 256-byte aligned
 
@@ -819,14 +844,14 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
         return lgreco_sizes(layers, L, cands, P, h->cfg.bucket, sizes ? sizes : own_sizes.data());
     };
     if (ntk)
-        HIPCHK(topk_begin(&h->topk, d_grads, d_ef, h->d_layers, h->hl.data(), h->d_tiles, L, n_tiles,
-                          h->tile_elems, ks.data(), ntk, 0, h->tm, s, many ? ntk_all : 0));
+        HIPCHK(topk_begin(&h->topk, d_grads, d_ef, h->cut->d_layers, h->cut->hl.data(), h->cut->d_tiles, L, n_tiles,
+                          h->cut->tile_elems, ks.data(), ntk, 0, h->tm, s, many ? ntk_all : 0));
     if (qp.nq) {
         qp.g = d_grads;
         qp.e = d_ef;
         qp.x_out = x_out;
-        qp.layers = h->d_layers;
-        qp.tiles = h->d_tiles;
+        qp.layers = h->cut->d_layers;
+        qp.tiles = h->cut->d_tiles;
         qp.partials = h->d_partials;
         qp.stride = P;
         qp.stochastic = h->cfg.stochastic;
@@ -849,7 +874,7 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
         HIPCHK(launch_quant_profile(qp, n_tiles, ntk > 0, s, &sec));
     } else if (ntk) {
         Section sec(h->tm, "topk_collect", true);
-        HIPCHK(topk_collect(&h->topk, d_grads, d_ef, nullptr, h->d_layers, h->d_tiles, n_tiles, s, &sec, x_out));
+        HIPCHK(topk_collect(&h->topk, d_grads, d_ef, nullptr, h->cut->d_layers, h->cut->d_tiles, n_tiles, s, &sec, x_out));
     }
     if (many) {
         st = fill_sizes();
@@ -864,14 +889,14 @@ static int profile_enqueue(lgreco_handle_t* h, const float* d_grads, const float
     if (ntk) {
         // (the per-layer sums of the quantization errors ride on a launch of it)
         const QuantReduce qr{h->d_partials, d_err, P, qp.col, qp.nq};
-        HIPCHK(topk_resolve(&h->topk, g_after, e_after, nullptr, h->d_layers, h->d_tiles, L, ntk, tk_col, d_err, P, h->tm, s,
+        HIPCHK(topk_resolve(&h->topk, g_after, e_after, nullptr, h->cut->d_layers, h->cut->d_tiles, L, ntk, tk_col, d_err, P, h->tm, s,
                             qp.nq ? &qr : nullptr));
     } else if (qp.nq) {
         Section sec(h->tm, "reduce_partials");
-        HIPCHK(launch_reduce_partials(h->d_partials, P, qp.col, qp.nq, h->d_layers, L, d_err, s));
+        HIPCHK(launch_reduce_partials(h->d_partials, P, qp.col, qp.nq, h->cut->d_layers, L, d_err, s));
     }
     if (nlr) {
-        HIPCHK(lowrank_profile(&h->lowrank, d_grads, d_ef, h->d_layers, h->hl.data(), L, d_q0, h->cfg.r_max,
+        HIPCHK(lowrank_profile(&h->lowrank, d_grads, d_ef, h->cut->d_layers, h->cut->hl.data(), L, d_q0, h->cfg.r_max,
                                lr_rank, lr_col, nlr, d_err, P, lowrank_x(h), h->tm, s));
     }
     return many ? LGRECO_OK : fill_sizes();
@@ -1171,7 +1196,7 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
             HIPCHK(hipMemcpyAsync(h->d_apply, h->h_apply, sizeof(int32_t) * n_apply, hipMemcpyHostToDevice, s));
             HIPCHK(hipStreamSynchronize(s));      // h_apply may be rewritten by the next call
         }
-        sp.apply = SolveApply{h->d_layers, h->d_apply, h->d_apply + (size_t)L * P, h->d_apply + (size_t)L * P + P,
+        sp.apply = SolveApply{h->cut->d_layers, h->d_apply, h->d_apply + (size_t)L * P, h->d_apply + (size_t)L * P + P,
                               ec->capacity};
     }
     {
@@ -1185,7 +1210,7 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
         // layer table holds, until lgreco_compress has worked out the same records.
         Timing* const solve_tm = h->tm;
         begin_call(h, s, LGRECO_CALL_COMPRESS);
-        h->hl_uploaded.clear();
+        h->cut->hl_uploaded.clear();
         ec->phase = h->tm->open_phase("phase_compress");
         bool any_quant = false, all_quant = true;
         for (int c = 0; c < P; ++c) {
@@ -1209,14 +1234,14 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
         if (ec->topk_known) {
             // the Top-K layers' part, from the selection records the profile left for this very
             // data: the chosen density's record is picked on the device
-            HIPCHK(topk_compress_known(&h->topk, d_grads, ec->d_ef, h->d_layers, h->d_tiles, L, (int)h->ht.size(),
-                                       h->layer_tiles, ec->d_payload, h->tm, s, ec->x_in_e));
+            HIPCHK(topk_compress_known(&h->topk, d_grads, ec->d_ef, h->cut->d_layers, h->cut->d_tiles, L, (int)h->cut->ht.size(),
+                                       h->cut->layer_tiles, ec->d_payload, h->tm, s, ec->x_in_e));
         }
         if (beside) HIPCHK(hipStreamWaitEvent(h->side, h->ev_fork, 0));
         if (any_quant) {
             Section sec(h->tm, "quant_compress", true);
-            HIPCHK(launch_quant_compress(ec->x_in_e ? nullptr : d_grads, ec->d_ef, h->d_layers, h->d_tiles,
-                                         (int)h->ht.size(), h->tile_elems, all_quant ? h->total_elems : 0, h->total_elems,
+            HIPCHK(launch_quant_compress(ec->x_in_e ? nullptr : d_grads, ec->d_ef, h->cut->d_layers, h->cut->d_tiles,
+                                         (int)h->cut->ht.size(), h->cut->tile_elems, all_quant ? h->total_elems : 0, h->total_elems,
                                          ec->d_payload, h->cfg.stochastic != 0, h->cfg.seed,
                                          beside ? h->side : s, &sec, beside ? 30 * 1024 : 0));
         }
@@ -1229,7 +1254,7 @@ static int profile_solve_impl(lgreco_handle_t* h, const float* d_grads, const fl
         if (ec->lowrank_known) {
             // ... and the low-rank layers': the factors of every rank are the leading columns of
             // the rank-64 run the profile just made on this data
-            HIPCHK(lowrank_compress_known(&h->lowrank, d_grads, ec->d_ef, h->d_layers, ec->d_q, h->cfg.r_max,
+            HIPCHK(lowrank_compress_known(&h->lowrank, d_grads, ec->d_ef, h->cut->d_layers, ec->d_q, h->cfg.r_max,
                                           ec->d_payload, d_ef ? lowrank_x(h) : nullptr, h->tm, s, h->ef_zero_on_entry));
         }
         // the compress call stays open until lgreco_compress's part has queued the rest: nobody
@@ -1346,10 +1371,8 @@ static int compress_impl(lgreco_handle_t* h, const float* d_grads, float* d_ef, 
     } else {
         begin_call(h, s, LGRECO_CALL_COMPRESS);
     }
-    bool some_topk = false;
-    for (int l = 0; l < L && !some_topk; ++l)
-        some_topk = choice[l] >= 0 && choice[l] < P && cands[choice[l]].family == LGRECO_TOPK;
-    int st = prepare_layers(h, layers, L, some_topk ? Tiles::topk : Tiles::any);
+    // (behind a profile of the same call: the cut that the profile took)
+    int st = prepare_layers(h, layers, L, [&] { return ec ? some_topk(cands, P) : chosen_topk(cands, P, choice, L); });
     if (st != LGRECO_OK) return st;
     bool any[3] = {false, false, false};
     int64_t elems[3] = {0, 0, 0};
@@ -1359,7 +1382,7 @@ static int compress_impl(lgreco_handle_t* h, const float* d_grads, float* d_ef, 
         st = check_cand(c, &layers[l], h->cfg.r_max);
         if (st != LGRECO_OK) return st;
         if (offsets[l] < 0 || offsets[l] % 16) return LGRECO_EINVAL;
-        DevLayer& d = h->hl[l];
+        DevLayer& d = h->cut->hl[l];
         d.family = c.family;
         d.payload = offsets[l];
         d.iparam = (c.family == LGRECO_TOPK) ? (int32_t)topk_k(layers[l].numel, c.param) : (int32_t)c.param;
@@ -1369,27 +1392,27 @@ static int compress_impl(lgreco_handle_t* h, const float* d_grads, float* d_ef, 
     if (any[LGRECO_LOWRANK] && !d_q) return LGRECO_EINVAL;
     // the solver kernel wrote these very records into the device's table (same tables, same
     // arithmetic) and the quantization kernel has run on them: nothing to upload, nothing to repeat
-    const bool quant_done = early && ec->applied && !h->layers_dirty;
-    if (quant_done) h->hl_uploaded = h->hl;
+    const bool quant_done = early && ec->applied && !h->cut->dirty;
+    if (quant_done) h->cut->hl_uploaded = h->cut->hl;
     st = upload_layers(h, s, true);
     if (st != LGRECO_OK) return st;
-    const int n_tiles = (int)h->ht.size();
+    const int n_tiles = (int)h->cut->ht.size();
     const int phase = early ? ec->phase : h->tm->open_phase("phase_compress");
     // behind a profile of the same call that left x in the error-feedback buffer, x is read from there
     const bool x_in_e = ec && ec->x_in_e;                 // whether or not the early kernels were queued
     if (x_in_e && any[LGRECO_LOWRANK]) return LGRECO_EINVAL;      // never set together (see the one-call entry point)
     if (any[LGRECO_QUANT] && !quant_done) {
         Section sec(h->tm, "quant_compress", true);
-        HIPCHK(launch_quant_compress(x_in_e ? nullptr : d_grads, d_ef, h->d_layers, h->d_tiles, n_tiles, h->tile_elems,
+        HIPCHK(launch_quant_compress(x_in_e ? nullptr : d_grads, d_ef, h->cut->d_layers, h->cut->d_tiles, n_tiles, h->cut->tile_elems,
                                      elems[LGRECO_QUANT], h->total_elems, d_payload,
                                      h->cfg.stochastic != 0, h->cfg.seed, s, &sec));
     }
     if (any[LGRECO_TOPK] && !(quant_done && ec->topk_known)) {
-        HIPCHK(topk_compress(&h->topk, x_in_e ? d_ef : d_grads, d_ef, h->d_layers, h->hl.data(), h->d_tiles, L,
-                             n_tiles, h->tile_elems, h->layer_tiles, d_payload, h->tm, s, x_in_e));
+        HIPCHK(topk_compress(&h->topk, x_in_e ? d_ef : d_grads, d_ef, h->cut->d_layers, h->cut->hl.data(), h->cut->d_tiles, L,
+                             n_tiles, h->cut->tile_elems, h->cut->layer_tiles, d_payload, h->tm, s, x_in_e));
     }
     if (any[LGRECO_LOWRANK] && !(quant_done && ec->lowrank_known)) {
-        HIPCHK(lowrank_compress(&h->lowrank, d_grads, d_ef, h->d_layers, h->hl.data(), L, d_q, h->cfg.r_max,
+        HIPCHK(lowrank_compress(&h->lowrank, d_grads, d_ef, h->cut->d_layers, h->cut->hl.data(), L, d_q, h->cfg.r_max,
                                 d_payload, h->tm, s));
     }
     h->tm->close_phase(phase);
@@ -1444,7 +1467,7 @@ int lgreco_decompress(lgreco_handle_t* h, const uint8_t* d_payload, const int64_
     if ((uintptr_t)d_out % 16 || (uintptr_t)d_payload % 16) return LGRECO_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     begin_call(h, s, LGRECO_CALL_RECEIVE);
-    int st = prepare_layers(h, layers, L, Tiles::any);
+    int st = prepare_layers(h, layers, L, [&] { return chosen_topk(cands, P, choice, L); });
     if (st != LGRECO_OK) return st;
     bool any[3] = {false, false, false};
     int64_t elems[3] = {0, 0, 0};
@@ -1454,7 +1477,7 @@ int lgreco_decompress(lgreco_handle_t* h, const uint8_t* d_payload, const int64_
         st = check_cand(c, &layers[l], h->cfg.r_max);
         if (st != LGRECO_OK) return st;
         if (offsets[l] < 0 || offsets[l] % 16) return LGRECO_EINVAL;
-        DevLayer& d = h->hl[l];
+        DevLayer& d = h->cut->hl[l];
         d.family = c.family;
         d.payload = offsets[l];
         d.iparam = (c.family == LGRECO_TOPK) ? (int32_t)topk_k(layers[l].numel, c.param) : (int32_t)c.param;
@@ -1463,10 +1486,10 @@ int lgreco_decompress(lgreco_handle_t* h, const uint8_t* d_payload, const int64_
     }
     st = upload_layers(h, s, true);
     if (st != LGRECO_OK) return st;
-    HIPCHK(launch_decode(d_payload, h->d_layers, h->d_tiles, (int)h->ht.size(), h->tile_elems, elems[LGRECO_QUANT], h->total_elems, d_out,
+    HIPCHK(launch_decode(d_payload, h->cut->d_layers, h->cut->d_tiles, (int)h->cut->ht.size(), h->cut->tile_elems, elems[LGRECO_QUANT], h->total_elems, d_out,
                          accumulate != 0, any[LGRECO_TOPK], h->tm, s));
     if (any[LGRECO_LOWRANK])
-        HIPCHK(lowrank_decompress(&h->lowrank, h->hl.data(), L, h->cfg.r_max, d_payload, d_out, accumulate != 0,
+        HIPCHK(lowrank_decompress(&h->lowrank, h->cut->hl.data(), L, h->cfg.r_max, d_payload, d_out, accumulate != 0,
                                   h->tm, s));
     HIPCHK(hipStreamSynchronize(s));
     return LGRECO_OK;

@@ -74,3 +74,58 @@ def test_lists_of_both_kinds_take_turns_on_one_handle():
         assert np.array_equal(want[0], got[0]) and torch.equal(want[1], got[1]) and torch.equal(want[2], got[2])
         own.close()
     shared.close()
+
+
+def test_calls_of_both_kinds_leave_each_other_nothing_to_upload():
+    """Calls with Top-K layers and calls without keep a cut of the layers on the device each: whatever calls come between,
+    a compression that ran before queues kernels alone, so that it can be captured, and gives on every replay what a handle of
+    its own gives."""
+    from paper_2210_17357_amd import binding as B
+    torch = torch_cuda()
+    sizes = [9_000_000, 5_000_001, 77, 4_000_000 - 512, 16384, 8193]
+    offs = np.concatenate([[0], np.cumsum(sizes)[:-1]])
+    total, n = sum(sizes), len(sizes)
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    g = torch.empty(total, device="cuda").normal_(generator=gen)
+    e = torch.empty(total, device="cuda").normal_(generator=gen)
+    layers = B.layer_table(offs, sizes, [0] * n, [0] * n)
+    quant, both = B.cand_table([(W.QUANT, 3.0)]), B.cand_table([(W.QUANT, 3.0), (W.TOPK, 0.01), (W.TOPK, 0.1)])
+    choices = np.zeros(n, np.int32), np.array([0, 1, 2, 1, 0, 2], np.int32)
+    layouts = [B.payload_layout(layers, both, c) for c in choices]
+
+    def buffers():
+        return e.clone(), torch.zeros(int(layouts[0][-1]) + 16, dtype=torch.uint8, device="cuda")
+
+    h, own = B.Handle(total, n, 3), B.Handle(total, n, 3)
+    ef, payload = buffers()
+    stream = torch.cuda.Stream()
+
+    def profiles():
+        h.profile(g, e, layers, quant)
+        h.profile(g, e, layers, both)
+
+    for choice, offsets in zip(choices, layouts):
+        h.compress(g, ef, layers, both, choice, payload, offsets)
+        profiles()
+    graphs = []
+    for choice, offsets in zip(choices, layouts):
+        torch.cuda.synchronize()
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1], stream=stream):
+            h.compress(g, ef, layers, both, choice, payload, offsets, stream=stream.cuda_stream)
+        profiles()
+    ef.copy_(e)
+    want_ef, want_payload = buffers()
+    for _ in range(3):
+        for graph, choice, offsets in zip(graphs, choices, layouts):
+            payload.zero_()
+            want_payload.zero_()
+            torch.cuda.synchronize()
+            graph.replay()
+            own.compress(g, want_ef, layers, both, choice, want_payload, offsets)
+            torch.cuda.synchronize()
+            assert torch.equal(ef, want_ef) and torch.equal(payload, want_payload)
+            profiles()
+    del graphs
+    h.close()
+    own.close()
