@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "internal.h"
+#include "pack.h"
 
 namespace lgreco {
 
@@ -1122,16 +1123,11 @@ static hipError_t lr_prepare(LowrankScratch* t, int slot, const DevLayer* hl, in
     H->gram_tiles.clear();
     H->q_chunks.clear();
     H->many_partials = false;
-    // x: in the place of the error feedback when compressing; packed after a profile, aligned layers first, so that
-    // they stay aligned
+    // x: in the place of the error feedback when compressing; packed after a profile
     std::vector<int64_t> x_off((size_t)L, 0);
-    int64_t x_end = 0;
-    for (int pass = 0; pass < 2; ++pass) {
-        for (int l = 0; l < L; ++l) {
-            const bool aligned = hl[l].offset % 4 == 0 && hl[l].cols % 4 == 0;
-            if (rank[l] > 0 && aligned == (pass == 0)) { x_off[l] = x_end; x_end += (int64_t)hl[l].rows * hl[l].cols; }
-        }
-    }
+    pack_matrices(L, [&](int l) { return hl[l].offset; }, [&](int l) { return hl[l].cols; },
+                  [&](int l) { return rank[l] > 0 ? (int64_t)hl[l].rows * hl[l].cols : 0; },
+                  [&](int l, int64_t at) { x_off[l] = at; });
     int64_t p_off = 0, q_off = 0, part_off = 0, ppart_off = 0;
     for (int l = 0; l < L; ++l) {
         if (rank[l] <= 0) continue;
@@ -1166,7 +1162,7 @@ static hipError_t lr_prepare(LowrankScratch* t, int slot, const DevLayer* hl, in
             for (int sp = 0; sp < a.psplits; ++sp) H->p_tiles.push_back(LrTile{li, r0, sp, 0});
         }
         a.rt_end = (int)H->p_tiles.size();
-        a.lines = a.offset % 32 == 0 && a.cols % 32 == 0 ? 1 : 0;
+        a.lines = whole_lines(a.offset, a.cols) ? 1 : 0;         // (and x_off as well, see pack_matrices)
         for (int r0 = 0; r0 < a.rows; r0 += kLrEfRows)
             for (int c0 = 0; c0 < a.cols; c0 += kLrEfCols) H->ef_tiles.push_back(LrTile{li, r0, c0, 0});
         for (int sp = 0; sp < a.splits; ++sp)
