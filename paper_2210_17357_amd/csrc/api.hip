@@ -251,13 +251,6 @@ int check_layers(const lgreco_layer_t* layers, int32_t L) {
     return LGRECO_OK;
 }
 
-// Tile size of a table of `total` elements (see kTilesFill).
-int tile_size(int64_t total, bool topk) {
-    int tile = kTile;
-    while (tile > kTileMin && total / tile < (topk && tile < kTile ? kTilesFill / 2 : kTilesFill)) tile /= 2;
-    return tile;
-}
-
 bool some_topk(const lgreco_cand_t* cands, int32_t P) {
     return std::any_of(cands, cands + P, [](const lgreco_cand_t& c) { return c.family == LGRECO_TOPK; });
 }

@@ -5,23 +5,10 @@
 #include <stdint.h>
 
 #include "../../include/lgreco.h"
+#include "parts.h"
 
 namespace lgreco {
 
-constexpr int kTile = 32768;       // largest streaming tile in elements (256 buckets of 128); a position inside a
-                                   // tile fits 15 bits (the Top-K candidate records rely on it)
-constexpr int kTileMin = 8192;     // smallest: small problems get smaller tiles so that the launch still fills the chip
-// Tile size: halved from kTile while there would be fewer than kTilesFill tiles (small problems
-// still fill the chip); in calls with Top-K layers, from kTile / 2 to kTileMin while there would be fewer than half as
-// many.  A tile of Top-K work ends with a flush of its
-// histogram, whose adding up in memory (0.3 ns for every line of it and tile) the kernel waits for, and every
-// later kernel has a record and a chain of loads per tile; a tile without ends with a few numbers, and short workgroups suit it.  Measured on 355 M elements: 10.8 k tiles of 32768
-// took 4 % off the streaming kernels against 5.4 k of 65536; 21.7 k of 16384 cost the histogram
-// pass more than it gained.  Steps, us, with kTileMin / twice that: Top-K of 17 M elements 129 / 125, 22 M 143 / 136, 28 M
-// 172 / 162, 31 M 172 / 161, both families 157 / 154, 171 / 168, 200 / 191, 199 / 189, 100 densities of 26 M 181 / 170, quantization alone of 20 M
-// 110 / 116, 27 M 134 / 139; with kTile / 2 / kTile: Top-K of 54 M 237 / 237, 66 M 273 / 274, both families 273 / 277, 310 / 318.
-// Compressions of Top-K layers, 20 M elements 114 / 110, 26 M 95.5 / 96.4: as the profile in front of them, whose cut they share.
-constexpr int kTilesFill = 2048;
 constexpr int kBucket = 128;       // quantization bucket (elements)
 constexpr int kChunk = 512;        // elements one wavefront handles per step (4 buckets)
 constexpr int kThreads = 256;      // workgroup size of the streaming kernels (4 wavefronts)

@@ -10,7 +10,6 @@
 #include <algorithm>
 
 #include "internal.h"
-#include "parts.h"
 
 namespace lgreco {
 

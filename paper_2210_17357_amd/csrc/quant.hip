@@ -16,7 +16,6 @@
 // spread over the row's 16 lanes (lane c: unit of candidate c, lane 8+c: inv of candidate c)
 // and broadcast back with row_newbcast.
 #include "internal.h"
-#include "parts.h"
 #include "reduce_dev.h"
 #include "topk_dev.h"
 

@@ -26,3 +26,28 @@ def rel_err(a, b):
     a = np.asarray(a, np.float64)
     b = np.asarray(b, np.float64)
     return np.abs(a - b) / np.maximum(np.abs(b), 1e-300)
+
+
+def tile_size(total, topk):
+    """Tile size of a layer table of `total` elements in calls with and without Top-K layers (checked against the library's
+    rule by test_parts_rule)."""
+    tile = 32768
+    while tile > 8192 and total // tile < (1024 if topk and tile < 32768 else 2048):
+        tile //= 2
+    return tile
+
+
+def many_small(n_layers):
+    """Lengths of so many layers, most below 1500 elements, that parts of tiles are longer than asked for: 4096 elements of
+    tiles of 8192 for 1200 layers, whole tiles for 3000."""
+    rng = np.random.default_rng(n_layers)
+    lengths = rng.integers(1, 1500, n_layers)
+    lengths[::300] = rng.integers(8192, 40000, lengths[::300].size)
+    lengths[7:n_layers:400] = 8192 + 4096 + 512 + 3
+    return lengths
+
+
+def tile_count(lengths, tile):
+    n = np.asarray(lengths, np.int64)
+    rest = n % tile
+    return int((n // tile + (rest >= 512) + (rest % 512 > 0)).sum())

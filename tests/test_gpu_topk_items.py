@@ -6,7 +6,7 @@ import pytest
 from oracle import pipeline
 from paper_2210_17357_amd import workloads as W
 
-from gpu_util import rel_err, tables, to_device, torch_cuda
+from gpu_util import rel_err, tables, tile_size, to_device, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -44,35 +44,51 @@ def test_more_items_than_slots(n_layers, densities):
 
 
 def test_lists_of_both_kinds_take_turns_on_one_handle():
-    """At 18 M elements a profile with densities cuts the layers into tiles of 16384, one without into tiles of 8192: on
-    one handle in turn, with compressions in between, each gives what a handle of its own gives, bit for bit."""
+    """At 18 M elements a call with Top-K layers cuts them into tiles of 16384, one without into tiles of 8192: on one handle,
+    behind profiles of every kind of list, profiles and compressions give what a handle of their own gives, bit for
+    bit, and layers alone (tiles of 8192) the same payload as in the table."""
     from paper_2210_17357_amd import binding as B
     torch = torch_cuda()
     sizes = [9_000_000, 5_000_001, 77, 4_000_000 - 512, 16384, 8193]
     offs = np.concatenate([[0], np.cumsum(sizes)[:-1]])
-    total = sum(sizes)
+    total, n = sum(sizes), len(sizes)
+    assert tile_size(total, True) == 16384 and tile_size(total, False) == 8192
     gen = torch.Generator(device="cuda").manual_seed(8)
     g = torch.empty(total, device="cuda").normal_(generator=gen)
     e = torch.empty(total, device="cuda").normal_(generator=gen)
-    layers = B.layer_table(offs, sizes, [0] * len(sizes), [0] * len(sizes))
-    quant, topk = [(W.QUANT, 3.0), (W.QUANT, 6.0)], [(W.TOPK, 0.01), (W.TOPK, 0.1)]
-    lists = [quant, quant + topk, topk]
-    choice = np.array([i % 2 for i in range(len(sizes))], np.int32)
+    layers = B.layer_table(offs, sizes, [0] * n, [0] * n)
+    cands = [(W.QUANT, 3.0), (W.QUANT, 6.0), (W.TOPK, 0.01), (W.TOPK, 0.1)]
+    ctab = B.cand_table(cands)
+    lists = [B.cand_table(cands[:2]), ctab, B.cand_table(cands[2:])]
+    choices = [np.array(c, np.int32) for c in ((0, 1, 0, 1, 0, 1), (0, 2, 3, 1, 2, 0), (2, 3, 2, 2, 3, 3))]
 
-    def calls(h, cands):
-        ctab = B.cand_table(cands)
-        errors, _ = h.profile(g, e, layers, ctab)
-        offsets = B.payload_layout(layers, ctab, choice)
-        payload, ef = torch.zeros(int(offsets[-1]) + 16, dtype=torch.uint8, device="cuda"), e.clone()
-        h.compress(g, ef, layers, ctab, choice, payload, offsets)
-        return errors, payload, ef
+    def compress(h, table, choice, lo=0, hi=total):
+        offsets = B.payload_layout(table, ctab, choice)
+        payload, ef = torch.zeros(int(offsets[-1]) + 16, dtype=torch.uint8, device="cuda"), e[lo:hi].clone()
+        h.compress(g[lo:hi].clone(), ef, table, ctab, choice, payload, offsets)
+        out = torch.zeros(hi - lo, device="cuda")
+        h.decompress(payload, offsets, table, ctab, choice, out, accumulate=False)
+        return offsets, payload, ef, out
 
-    shared = B.Handle(total, len(sizes), 4)
-    for cands in lists + lists[::-1] + lists:
-        own = B.Handle(total, len(sizes), 4)
-        want, got = calls(own, cands), calls(shared, cands)
-        assert np.array_equal(want[0], got[0]) and torch.equal(want[1], got[1]) and torch.equal(want[2], got[2])
+    shared = B.Handle(total, n, 4)
+    for choice in choices:
+        own = B.Handle(total, n, 4)
+        offsets, *want = compress(own, layers, choice)
         own.close()
+        for profiled in lists:                              # of the compression's kind and of the others
+            own = B.Handle(total, n, 4)
+            assert np.array_equal(shared.profile(g, e, layers, profiled)[0], own.profile(g, e, layers, profiled)[0])
+            own.close()
+            _, *got = compress(shared, layers, choice)
+            assert all(torch.equal(a, b) for a, b in zip(want, got))
+        for l in (1, 2, 3, 5):
+            lo, hi = int(offs[l]), int(offs[l]) + sizes[l]
+            alone = B.Handle(sizes[l], 1, 4)
+            one = compress(alone, B.layer_table([0], [sizes[l]], [0], [0]), choice[l:l + 1], lo, hi)
+            alone.close()
+            size = int(B.sizes(layers, ctab)[l, choice[l]])
+            assert torch.equal(want[0][int(offsets[l]):int(offsets[l]) + size], one[1][:size]), l
+            assert torch.equal(want[1][lo:hi], one[2]) and torch.equal(want[2][lo:hi], one[3]), l
     shared.close()
 
 

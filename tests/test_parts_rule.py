@@ -1,5 +1,5 @@
-"""How many workgroups a tile is dealt to, compiled from the header on the CPU: as many as its size asks for where most tiles are
-full, and no more than one for 4096 elements (and 4096) that find nothing to do unless every tile has one."""
+"""Sizes of tiles and how many workgroups a tile is dealt to, compiled from the header on the CPU: as many as its size asks for where
+most tiles are full, and no more than one for 4096 elements (and 4096) that find nothing to do unless every tile has one."""
 import os
 import subprocess
 
@@ -8,15 +8,18 @@ import pytest
 
 from paper_2210_17357_amd import workloads as W
 
+from gpu_util import many_small, tile_count as _tiles, tile_size
+
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2210_17357_amd", "csrc")
 
 PROGRAM = r"""
 #include <cstdio>
 #include "parts.h"
 int main() {
+    // part 0: the size of the tiles, `tile` 1 in calls with Top-K layers
     long long n, total, tile, part;
     while (std::scanf("%lld %lld %lld %lld", &n, &total, &tile, &part) == 4)
-        std::printf("%d\n", lgreco::part_shift(n, total, tile, part));
+        std::printf("%d\n", part ? lgreco::part_shift(n, total, tile, part) : lgreco::tile_size(total, tile != 0));
 }
 """
 PARTS = (512, 2048, 4096, 8192)
@@ -33,12 +36,6 @@ def rule(tmp_path_factory):
         return [int(v) for v in subprocess.run([str(d / "main")], input=text, capture_output=True, text=True,
                                                check=True).stdout.split()]
     return call
-
-
-def _tiles(numels, tile):
-    n = np.asarray(numels, np.int64)
-    rest = n % tile
-    return int((n // tile + (rest >= 512) + (rest % 512 > 0)).sum())
 
 
 @pytest.mark.parametrize("name", ["resnet18", "resnet50", "gpt2_medium", "transformer_lm", "tiny"])
@@ -77,3 +74,19 @@ def test_tens_of_thousands_of_small_layers(rule):
     with_one_large = numels[:5000] + [1 << 26]
     n = _tiles(with_one_large, 32768)
     assert rule((n, sum(with_one_large), 32768, 512)) == [1]
+
+
+def test_sizes_of_tiles(rule):
+    """The GPU tests' copy of the rule, around every size at which a tile changes."""
+    edges = [t * 2 ** k + d for t in (1024, 2048) for k in range(12, 17) for d in (-1, 0, 1)]
+    totals = edges + [1, 511, 10 ** 6, 3 * 10 ** 8] + [e * 3 // 2 for e in edges]
+    for topk in (0, 1):
+        assert rule(*((0, t, topk, 0) for t in totals)) == [tile_size(t, bool(topk)) for t in totals]
+
+
+def test_lengths_that_the_gpu_tests_rely_on(rule):
+    for n_layers, shift in ((1200, 1), (3000, 0)):
+        lengths = many_small(n_layers)
+        total = int(lengths.sum())
+        assert tile_size(total, False) == 8192
+        assert rule(*((_tiles(lengths, 8192), total, 8192, p) for p in (512, 2048, 4096))) == [shift] * 3
