@@ -1,4 +1,4 @@
-// PowerSGD-style low rank: one power-iteration step per layer on fp32 MFMA, for gfx950.
+// PowerSGD-style low rank: one power-iteration step per layer on the matrix pipes, fp32 products and sums, for gfx950.
 //
 //   P = X Q0            X = g + e viewed as [m x n] row-major, Q0 [n x 64] warm start
 //   Phat = orth(P)      Gram-Schmidt on the columns, done in coefficient space: G = P^T P in
@@ -158,7 +158,8 @@ __device__ __forceinline__ f32x16 mfma_split(const Split8 (&a)[2], B b, f32x16 c
 // nothing beside values of the same sum some 2^30 times as large, but all that counts where there are none.  So a
 // wavefront that has met no value as large as below and whose sums are not all zero forms them once more, from the fp32
 // values on the fp32 instruction, two rows of the contraction a step (a compression of 67 M elements around 1e-33: 962 us instead
-// of 437, from 1e-25 up 437).
+// of 437, from 1e-25 up 437).  Rows of values below 2^-110 that share a wavefront with larger ones keep what is left of their
+// values above 2^-133.
 constexpr float kLrHeldQ0 = 0x1p-100f;          // Q0
 constexpr float kLrHeldP = 0x1p-91f;            // P = X Q0 over the largest of Q0: 512 values of X lose at most 2^-124 of it, 2^-33 of this
 constexpr float kLrHeldQ = 0x1p-90f;            // Q = X^T Phat: K values of X lose at most 2^-133 sqrt(K), 2^-30 of this where K < 2^26
@@ -188,12 +189,12 @@ __device__ __forceinline__ const float* matrix_of(const LrParams& p, const LrLay
 
 // ------------------------------------------------------------------ P = X Q0 (and ||X||^2)
 // One workgroup: 128 rows x 64 columns of P over one column range of X, 32 columns at a time; wavefront w owns rows
-// 32w .. 32w+31.  Bound by HBM where there is an e (g and e in, x out).  A wavefront's loads take 8 rows of 128 bytes each (past the caches
-// where those are whole lines), x leaves the same way, and the operand (a lane holds a row) is formed through the wavefront's own LDS rows, which no other
+// 32w .. 32w+31.  Bound by HBM where there is an e (g and e in, x out).  A wavefront's loads take 8 rows of 128 bytes each (g and e past the caches
+// where those are whole lines), x leaves in the same pieces, and the operand (a lane holds a row) is formed through the wavefront's own LDS rows, which no other
 // wavefront touches; the 32 x 64 chunk of Q0, shared by the four, is staged as pieces between two barriers.
 // Rows are 36 words apart, 16 lanes of a 128-bit read on different banks.  Products on the bf16 matrix pipe (see split8).
-// 67 M elements of 66 matrices: 167 -> 160 us, 5.0 TB/s of g, e and x (a bare read and write in this shape 148); without e 98 -> 79,
-// where the fp32 products alone took 70; 73 M elements of odd widths: a step 698 -> 678.  Three wavefronts on a SIMD with e: at four
+// 67 M elements of 66 matrices: 167 -> 160 us, 5.0 TB/s of g, e and x (a bare read and write in this shape 148); without e 98 -> 86
+// (79 with six products, all added to the accumulator), where the fp32 instruction's alone took 70; 73 M elements of odd widths: a step 698 -> 678.  Three wavefronts on a SIMD with e: at four
 // registers spill (167 us).  A lane loading and storing 16 consecutive elements of its own row, 64 pieces of lines an instruction: 190;
 // 16 rows of 64 bytes an instruction, the operand's own layout: 175 to 250 for the bare read and write.
 // HAS_E: x = g + e is formed here and written to LrParams::x, for the caches: the passes behind read it.

@@ -487,7 +487,7 @@ hipError_t launch_reduce_partials(const double* partials, int stride, const int*
 // A workgroup that finds its layer taken by another family costs about 0.2 ns: with a quarter of 355 M elements quantized
 // workgroups of 2048 elements (133 k of which do nothing) take 30 us of a step more than those of 8192, which lose 7 % on
 // what they do compress (one chunk each loses more).  So the short ones are for calls in which most of them have work.  Stochastic rounding
-// computes as long as it waits for memory (20 vector multiplications a word): 11.7 M elements 22 us with two
+// computes as long as it waits for memory (five multiplications of 32 by 32 bits a word): 11.7 M elements 22 us with two
 // chunks a wavefront, 24 with one.
 hipError_t launch_quant_compress(const float* g, float* e, const DevLayer* layers, const Tile* tiles, int n_tiles,
                                  int tile_elems, int64_t quantized, int64_t total, uint8_t* payload, bool stochastic,
