@@ -156,9 +156,10 @@ __device__ __forceinline__ f32x16 mfma_split(const Split8 (&a)[2], B b, f32x16 c
 
 // Values below 2^-110 lose bits: what they leave for the third piece falls below bf16's subnormals.  That is less than 2^-133,
 // nothing beside values of the same sum some 2^30 times as large, but all that counts where there are none.  So a
-// wavefront that has met no value as large as below and whose sums are not all zero forms them once more, from the fp32
+// wavefront that has met no value as large as below forms its sums once more (where all are zero, if its operands are not: below 2^-134
+// nothing is left for the first piece either), from the fp32
 // values on the fp32 instruction, two rows of the contraction a step (a compression of 67 M elements around 1e-33: 962 us instead
-// of 437, from 1e-25 up 437).  Rows of values below 2^-110 that share a wavefront with larger ones keep what is left of their
+// of 437, from 1e-25 up 437; of zeros, which are read once more to see that they are, 459).  Rows of values below 2^-110 that share a wavefront with larger ones keep what is left of their
 // values above 2^-133.
 constexpr float kLrHeldQ0 = 0x1p-100f;          // Q0
 constexpr float kLrHeldP = 0x1p-91f;            // P = X Q0 over the largest of Q0: 512 values of X lose at most 2^-124 of it, 2^-33 of this
@@ -168,6 +169,20 @@ __device__ __forceinline__ float largest(f32x16 a, f32x16 b) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) v = fmaxf(fmaxf(fabsf(a[i]), fabsf(b[i])), v);
     return v;
+}
+// Whether one of the wavefront's values is not zero; bits(i), i < count: this lane's, or several together.
+__device__ __forceinline__ uint32_t bits_of(float4 v) {
+    return __float_as_uint(v.x) | __float_as_uint(v.y) | __float_as_uint(v.z) | __float_as_uint(v.w);
+}
+template <typename Bits>
+__device__ __forceinline__ bool any_value(int count, Bits bits) {
+    for (int i = 0; i < count; i += 8) {
+        uint32_t all = 0;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) all |= bits(min(i + u, count - 1));
+        if (__any((all << 1) != 0)) return true;
+    }
+    return false;
 }
 // left(k), right(k, 0) and right(k, 1): this lane's values of the operands at k
 template <typename Left, typename Right>
@@ -333,8 +348,20 @@ __global__ __launch_bounds__(256, HAS_E ? 3 : 4) void lr_gemm1_kernel(LrParams p
     qmax = fmaxf(fmaxf(s_qmax[0], s_qmax[1]), fmaxf(s_qmax[2], s_qmax[3]));
     const float most = largest(acc0, acc1);
     const bool held = qmax >= kLrHeldQ0 && __any(most >= kLrHeldP * qmax);
-    if (!held && row0 + 32 * wave < m && __any(most > 0.0f)) {       // (uniform)
-        const float* const row = (HAS_E ? xo : g) + (int64_t)min(32 * wave + bj, m - 1 - row0) * n;
+    const float* const x = HAS_E ? xo : g;
+    const auto some = [&] {
+        if (kend - kbeg < 4)
+            return any_value(32, [&](int i) {
+                return __float_as_uint(x[(int64_t)min(32 * wave + i, m - 1 - row0) * n + min(kbeg + lane, kend - 1)]);
+            });
+        const int id = __lane_id();                          // (found anew: kept through the loop the register spills others)
+        return any_value(4 * ((kend - kbeg + 31) / 32), [&](int i) {         // 8 rows of 32 columns at a time
+            const int r = min(32 * wave + 8 * (i & 3) + (id >> 3), m - 1 - row0);
+            return bits_of(load4_any(x + (int64_t)r * n + min(kbeg + 32 * (i >> 2) + 4 * (id & 7), kend - 4)));
+        });
+    };
+    if (!held && row0 + 32 * wave < m && (__any(most > 0.0f) || (qmax > 0.0f && some()))) {      // (uniform)
+        const float* const row = x + (int64_t)min(32 * wave + bj, m - 1 - row0) * n;
         mfma_plain(kbeg, kend, half, [&](int k) { return row[k]; },
                    [&](int k, int c) { return 32 * c + bj < qstride ? q[(int64_t)k * qstride + 32 * c + bj] : 0.0f; }, acc0, acc1);
     }
@@ -705,7 +732,15 @@ __global__ __launch_bounds__(256, 4) void lr_gemm2_kernel(LrParams p) {
         acc1 = mfma_split(a, [&](int s, int t) { return Ps[buf][2 * s + half][t][32 + bj]; }, acc1);
     }
     const float most = largest(acc0, acc1);
-    if (!__any(most >= kLrHeldQ) && __any(most > 0.0f))    // (uniform)
+    const auto some = [&] {
+        return any_value((kend - kbeg + 3) / 4, [&](int i) {                 // 4 rows at a time
+                   return bits_of(load4_any(P + (int64_t)min(kbeg + 4 * i + (lane >> 4), kend - 1) * kLrCols + 4 * (lane & 15)));
+               }) &&
+               any_value((kend - kbeg + 1) / 2, [&](int i) {
+                   return __float_as_uint(X[(int64_t)min(kbeg + 2 * i + half, kend - 1) * n + col]);
+               });
+    };
+    if (!__any(most >= kLrHeldQ) && (__any(most > 0.0f) || some()))        // (uniform)
         mfma_plain(kbeg, kend, half, [&](int k) { return X[(int64_t)k * n + col]; },
                    [&](int k, int c) { return P[(int64_t)k * kLrCols + 32 * c + bj]; }, acc0, acc1);
     float* __restrict__ out = p.part + L.part_off + (int64_t)tile.split * n * kLrCols;

@@ -47,8 +47,9 @@ def test_second_contraction_is_an_fp32_product(rows, scale):
 PRODUCT = 2.0 ** -24 + 7 * 2.0 ** -6 * 2.0 ** -23 + 2.0 ** -32
 
 
-def _factors(x, q0, rank):
-    """Phat and Q of one matrix, compressed from a zero error feedback."""
+def _factors(x, q0, rank, one_call=False):
+    """Phat and Q of one matrix, compressed from a zero error feedback; one_call: without one, where the first contraction is
+    another kernel."""
     from paper_2210_17357_amd import binding as B
     torch = torch_cuda()
     m, n = x.shape
@@ -59,7 +60,11 @@ def _factors(x, q0, rank):
     h = B.Handle(m * n, 1, 1, r_max=q0.shape[1])
     offsets = B.payload_layout(layers, ctab, choice)
     payload = torch.zeros(int(offsets[-1]) + 16, dtype=torch.uint8, device="cuda")
-    h.compress(g, torch.zeros_like(g), layers, ctab, choice, payload, offsets, q)
+    if one_call:
+        h.set_ef_zero_on_entry(True)
+        h.profile_solve_compress(g, torch.zeros_like(g), layers, ctab, 0, 10, payload, q)
+    else:
+        h.compress(g, torch.zeros_like(g), layers, ctab, choice, payload, offsets, q)
     f = payload.cpu().numpy()[:4 * (m + n) * rank].view(np.float32).astype(np.float64)
     h.close()
     return f[:m * rank].reshape(m, rank), f[m * rank:].reshape(n, rank)
@@ -140,6 +145,30 @@ def test_small_matrices_in_the_one_call(scale):
     assert np.linalg.norm(got - phat) <= 4 * 30 * 2.0 ** -24 * np.linalg.norm(phat)
     want = x64.T @ got
     assert np.linalg.norm(f[m * rank:].reshape(n, rank) / scale - want) <= 150 * 2.0 ** -24 * np.linalg.norm(want) + 2.0 ** -149 / scale * n
+
+
+@pytest.mark.parametrize("one_call", (False, True))
+@pytest.mark.parametrize("small", ("x", "q0"))
+@pytest.mark.parametrize("m,n", ((3, 3), (33, 65), (97, 600), (700, 130)))
+def test_smallest_values_are_not_zero(m, n, small, one_call):
+    """X, or Q0, of whole multiples of the smallest fp32 value, all too small for any piece; products and sums of P are exact."""
+    rng = np.random.default_rng(8)
+    x = rng.integers(-1000, 1000, (m, n)) * (rng.random((m, n)) < 0.02)
+    x[m // 2, n // 2] = 999
+    q0 = rng.choice((-2, -1, 1, 2), (n, 1))
+    least = 2.0 ** -149
+    phat, q = _factors(x * least, q0, 1, one_call) if small == "x" else _factors(x, q0 * least, 1, one_call)
+    p = (x @ q0).astype(np.float64)
+    assert np.linalg.norm(phat - p / np.linalg.norm(p)) <= 2.0 ** -21
+    # each product of Q and each addition is rounded once, to the smallest value where X is
+    unit = least if small == "x" else 1.0
+    assert (np.abs(q / unit - x.T @ phat) <= 2 * m * (1.0 if small == "x" else 2.0 ** -23 * (np.abs(x).T @ np.abs(phat)))).all()
+
+
+def test_zero_matrices_stay_zero():
+    x, q0 = np.zeros((70, 300), np.float32), np.random.default_rng(9).standard_normal((300, 8))
+    for factor in _factors(x, q0, 4) + _factors(x + 1.0, np.zeros_like(q0), 4) + _factors(x, q0, 4, one_call=True):
+        assert not factor.any()
 
 
 @pytest.mark.parametrize("rank", (2, 3, 4, 5, 15, 16, 17, 24, 32, 34))
